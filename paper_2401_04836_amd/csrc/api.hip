@@ -648,10 +648,10 @@ conststn_status conststn_plan_options(const char *schedule, const int *fusion, i
     if (plan->family == FAM_TTMC3 && plan->use_rows) {
         char b[128];
         if (plan->use_stream)
-            // mfma = matrix instructions one execute issues: K-steps x (R2/16) x (R3/16) tiles
+            // mfma = matrix instructions one execute issues: K-steps x tiles of a row block
             snprintf(b, sizeof(b), " kernel=stream producers %d batches %lld ksteps %lld mfma=%lld", plan->stream_producers,
                      (long long)plan->n_stream_wg, (long long)plan->n_ksteps,
-                     (long long)(plan->n_ksteps * (plan->rank_of_level[1] / 16) * (plan->rank_of_level[2] / 16)));
+                     (long long)(plan->n_ksteps * ((plan->rank_of_level[1] + 15) / 16) * ((plan->rank_of_level[2] + 31) / 32 * 2)));
         else
             snprintf(b, sizeof(b), " kernel=rows");
         plan->description += b;

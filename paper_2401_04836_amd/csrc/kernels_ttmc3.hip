@@ -277,7 +277,18 @@ ttmc3_mfma_kernel(Ttmc3RowArgs a) {
 // Packets are double-buffered; one s_barrier per round (NP K-steps) orders the two sides.  A workgroup
 // takes a batch of whole items of about equal cost (plan table wg_kstep).  Empty rows of a partial
 // K-step repeat the step's last row with value 0 and a zero U2 operand, so every load is
-// unconditional.  (A ring of packets with ready flags instead of the barrier, letting the producers
+// unconditional.
+//
+// Ranks.  A row block is covered by PN = ceil(R2/16) x 2*NC = 2*ceil(R3/32) tiles whatever the ranks are.
+// Vector x of a lane's U2 operand is columns 32x + 2c, +1 of the factor row, and its T operand likewise, so
+// tile 2x + y takes the rows 32x + 2i + y (the last tile of an odd PN: rows 32x + i).  Ranks that do not fill
+// the tiles (kRaggedEven, kRaggedOdd): a lane beyond the end of a factor row reads the row's last two entries
+// instead -- the rows and columns of the row block that they feed are beyond the ranks and never stored, so
+// neither the gathers nor the matrix instructions need a test -- and only the stores are masked.  An odd rank
+// leaves one lane with half a pair; it moves the second entry it read into the first place.
+// Before, such ranks took the general kernel, which sums one leaf at a time per wavefront: 7.1 ms at
+// 12 007 x 9 001 x 28 999, 5 M nonzeros, ranks 50 x 50.
+// (A ring of packets with ready flags instead of the barrier, letting the producers
 // run sixteen K-steps ahead, measured slower: 20.2 against 18.2 ms on the 140 M-nonzero tensor.)
 struct Ttmc3StreamArgs {
     int R2, R3;
@@ -312,7 +323,10 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int PN, int NC, int NP>
+enum RankFit { kFullTiles = 0, kRaggedEven = 1, kRaggedOdd = 2 };
+typedef double v2f64_u __attribute__((ext_vector_type(2), aligned(8)));   // a pair at any element
+
+template <int PN, int NC, int NP, int FIT>
 __global__ void __launch_bounds__(64 * (NP + NC))
 ttmc3_stream_kernel(Ttmc3StreamArgs a) {
     constexpr int APV = (PN + 1) / 2;                 // 16-byte vectors of a lane's U2 operand
@@ -331,6 +345,15 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
 
     if (wave < NP) {
         // ------------------------------------------------------------------ producer
+        // first entry of a lane's vectors in the factor rows (a lane past the row's end: the row's last entries)
+        int u2_at[APV], u3_at[NC];
+#pragma unroll
+        for (int x = 0; x < APV; ++x) {
+            if (PN % 2 == 1 && x == APV - 1) u2_at[x] = FIT == kFullTiles ? 32 * x + c : min(32 * x + c, R2 - 1);
+            else u2_at[x] = FIT == kFullTiles ? 32 * x + 2 * c : min(32 * x + 2 * c, R2 - 2);
+        }
+#pragma unroll
+        for (int q = 0; q < NC; ++q) u3_at[q] = FIT == kFullTiles ? 32 * q + 2 * c : min(32 * q + 2 * c, R3 - 2);
         struct Rows { int64_t leaf; int cnt; int32_t j; bool live; };
         struct Feed { int32_t k; double v; int maxcnt; v2f64 av[APV]; };
         typedef int v4i32 __attribute__((ext_vector_type(4)));
@@ -358,12 +381,14 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
             const double v = a.vals[r.leaf + ci];
             const bool keep = (c < r.cnt) & r.live;     // no short circuit: a branch here draws the load under it
             f.v = keep ? v : 0.0;
-            const v2f64 *src = reinterpret_cast<const v2f64 *>(a.U2 + int64_t(r.j) * R2 + PN * c);
+            const double *src = a.U2 + int64_t(r.j) * R2;
 #pragma unroll
             for (int x = 0; x < APV; ++x) {
                 v2f64 u;
-                if (PN % 2 == 1 && x == APV - 1) u = v2f64{a.U2[int64_t(r.j) * R2 + PN * c + PN - 1], 0.0};
-                else u = src[x];
+                if (PN % 2 == 1 && x == APV - 1) u = v2f64{src[u2_at[x]], 0.0};
+                else if (FIT == kFullTiles) u = *reinterpret_cast<const v2f64 *>(src + u2_at[x]);
+                else u = *reinterpret_cast<const v2f64_u *>(src + u2_at[x]);
+                if (FIT == kRaggedOdd && 32 * x + 2 * c == R2 - 1 && !(PN % 2 == 1 && x == APV - 1)) u[0] = u[1];
                 f.av[x] = r.live ? u : v2f64{0.0, 0.0};
             }
             const int c0 = __builtin_amdgcn_readlane(r.cnt, 0), c1 = __builtin_amdgcn_readlane(r.cnt, 16),
@@ -385,7 +410,7 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
             dest_cur = d0.dest;
         }
         const char *u3 = reinterpret_cast<const char *>(a.U3);
-        const uint32_t row_bytes = uint32_t(R3) * 8u, lane_off = uint32_t(c) * 16u;
+        const uint32_t row_bytes = uint32_t(R3) * 8u;
         for (int r = 0; r < rounds; ++r) {
             // loads of the rounds ahead, issued before this round's gathers
             const Feed nxt = load_feed(r1);
@@ -412,9 +437,14 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
 #pragma unroll
                 for (int u = 0; u < N; ++u)
 #pragma unroll
-                    for (int q = 0; q < NC; ++q)
-                        uu[u][q] = *reinterpret_cast<const v2f64 *>(
-                            u3 + size_t(uint32_t(kk[u]) * row_bytes + lane_off) + q * 256);
+                    for (int q = 0; q < NC; ++q) {
+                        if (FIT == kFullTiles)
+                            uu[u][q] = *reinterpret_cast<const v2f64 *>(
+                                u3 + size_t(uint32_t(kk[u]) * row_bytes + uint32_t(u3_at[0]) * 8u) + q * 256);
+                        else
+                            uu[u][q] = *reinterpret_cast<const v2f64_u *>(
+                                u3 + size_t(uint32_t(kk[u]) * row_bytes + uint32_t(u3_at[q]) * 8u));
+                    }
 #pragma unroll
                 for (int u = 0; u < N; ++u)
 #pragma unroll
@@ -441,6 +471,10 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
                     chunk(std::integral_constant<int, 8>{}, maxcnt - 8);
                     if (maxcnt > 12) chunk(std::integral_constant<int, 12>{}, maxcnt - 12);
                 }
+            }
+            if (FIT == kRaggedOdd) {
+#pragma unroll
+                for (int q = 0; q < NC; ++q) t[q][0] = 32 * q + 2 * c == R3 - 1 ? t[q][1] : t[q][0];
             }
             v2f64 *dst = &pkt[r & 1][wave][0];
 #pragma unroll
@@ -483,14 +517,23 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
                     if (meta & 8) {
                         const int64_t dest = uniform64(pkt_dest[r & 1][w]);
                         double *base = dest >= 0 ? a.out + dest * RR : a.partial + (~dest) * RR;
-                        // tile (p,q): accumulator register v of a lane holds row PN*(slot + 4v) + p,
-                        // column part*32 + 2c + q; streaming stores, the block is never read here
+                        // accumulator register v of a lane: row i = slot + 4v of its tile, columns part*32 + 2c, +1.
+                        // Full tiles: streaming stores, the block is never read here; rows of other lengths
+                        // share cache lines with their neighbours and go through the L2.
+                        const int col = part * 32 + 2 * c;
 #pragma unroll
                         for (int p = 0; p < PN; ++p)
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
-                                double *o = base + int64_t(PN * (slot + 4 * v) + p) * R3 + part * 32 + 2 * c;
-                                __builtin_nontemporal_store(v2f64{acc[p][0][v], acc[p][1][v]}, reinterpret_cast<v2f64 *>(o));
+                                const int i = slot + 4 * v;
+                                const int row = (PN % 2 == 1 && p == PN - 1) ? 32 * (p / 2) + i : 32 * (p / 2) + 2 * i + p % 2;
+                                double *o = base + int64_t(row) * R3 + col;
+                                if (FIT == kFullTiles)
+                                    __builtin_nontemporal_store(v2f64{acc[p][0][v], acc[p][1][v]}, reinterpret_cast<v2f64 *>(o));
+                                else if (row < R2 && col + 1 < R3)
+                                    *reinterpret_cast<v2f64_u *>(o) = v2f64_u{acc[p][0][v], acc[p][1][v]};
+                                else if (FIT == kRaggedOdd && row < R2 && col < R3)
+                                    *o = acc[p][0][v];
                             }
 #pragma unroll
                         for (int p = 0; p < PN; ++p) acc[p][0] = acc[p][1] = v4f64{0.0, 0.0, 0.0, 0.0};
@@ -506,19 +549,26 @@ template <int PN, int NC>
 static conststn_status launch_stream_np(const conststn_plan_s *plan, const Ttmc3StreamArgs &a, hipStream_t stream) {
     ProfScope prof(plan, stream);
     const dim3 grid(unsigned(plan->n_stream_wg));
+    if (a.R2 != 16 * PN || a.R3 != 32 * NC) {
+        if (a.R2 % 2 == 0 && a.R3 % 2 == 0)
+            ttmc3_stream_kernel<PN, NC, 4, kRaggedEven><<<grid, dim3(64 * (4 + NC)), 0, stream>>>(a);
+        else
+            ttmc3_stream_kernel<PN, NC, 4, kRaggedOdd><<<grid, dim3(64 * (4 + NC)), 0, stream>>>(a);
+        return CONSTSTN_OK;
+    }
     switch (plan->stream_producers) {
-        case 2: ttmc3_stream_kernel<PN, NC, 2><<<grid, dim3(64 * (2 + NC)), 0, stream>>>(a); break;
-        case 3: ttmc3_stream_kernel<PN, NC, 3><<<grid, dim3(64 * (3 + NC)), 0, stream>>>(a); break;
-        case 6: ttmc3_stream_kernel<PN, NC, 6><<<grid, dim3(64 * (6 + NC)), 0, stream>>>(a); break;
-        case 8: ttmc3_stream_kernel<PN, NC, 8><<<grid, dim3(64 * (8 + NC)), 0, stream>>>(a); break;
-        default: ttmc3_stream_kernel<PN, NC, 4><<<grid, dim3(64 * (4 + NC)), 0, stream>>>(a); break;
+        case 2: ttmc3_stream_kernel<PN, NC, 2, kFullTiles><<<grid, dim3(64 * (2 + NC)), 0, stream>>>(a); break;
+        case 3: ttmc3_stream_kernel<PN, NC, 3, kFullTiles><<<grid, dim3(64 * (3 + NC)), 0, stream>>>(a); break;
+        case 6: ttmc3_stream_kernel<PN, NC, 6, kFullTiles><<<grid, dim3(64 * (6 + NC)), 0, stream>>>(a); break;
+        case 8: ttmc3_stream_kernel<PN, NC, 8, kFullTiles><<<grid, dim3(64 * (8 + NC)), 0, stream>>>(a); break;
+        default: ttmc3_stream_kernel<PN, NC, 4, kFullTiles><<<grid, dim3(64 * (4 + NC)), 0, stream>>>(a); break;
     }
     return CONSTSTN_OK;
 }
 
 static conststn_status launch_stream(const conststn_plan_s *plan, const Ttmc3StreamArgs &a, hipStream_t stream) {
-    const int pn = a.R2 / 16;
-    if (a.R3 == 64) {
+    const int pn = (a.R2 + 15) / 16;
+    if (a.R3 > 32) {
         switch (pn) {
             case 1: return launch_stream_np<1, 2>(plan, a, stream);
             case 2: return launch_stream_np<2, 2>(plan, a, stream);
@@ -566,8 +616,19 @@ ttmc_fixup_kernel(int64_t RR, const int32_t *__restrict__ split_slices,
     const int cnt = split_count[q];
     const int64_t row = compact ? s : int64_t(idx0[s]);
     for (int64_t e = int64_t(blockIdx.y) * blockDim.x + threadIdx.x; e < RR; e += int64_t(gridDim.y) * blockDim.x) {
+        // eight partial blocks in flight, added in order: one at a time the sum of a heavy slice (hundreds of
+        // blocks) is a chain of memory latencies
+        const double *src = partial + first * RR + e;
         double sum = 0.0;
-        for (int p = 0; p < cnt; ++p) sum += partial[(first + p) * RR + e];
+        int p = 0;
+        for (; p + 8 <= cnt; p += 8) {
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = src[(p + u) * RR];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += x[u];
+        }
+        for (; p < cnt; ++p) sum += src[p * RR];
         out[row * RR + e] = sum;
     }
 }
@@ -647,9 +708,10 @@ static conststn_status launch_ttmc3_with(const conststn_plan_s *plan, const doub
     if (!plan->compact && X->nodes[0] < plan->out_rows)
         CST_TRY(zero_fill(out, plan->out_rows * plan->row_elems, stream));
     if (a.n_items == 0) return CONSTSTN_OK;
-    if (plan->use_rows && plan->use_stream &&
-        (reinterpret_cast<uintptr_t>(a.U2) | reinterpret_cast<uintptr_t>(a.U3) | reinterpret_cast<uintptr_t>(out)) % 16 == 0 &&
-        int64_t(X->dims[X->mode_order[2]]) * a.R3 * 8 < (int64_t(1) << 32)) {
+    // full tiles are moved 16 bytes at a time and need that alignment; ragged ones take any
+    const bool whole = a.R2 % 16 == 0 && a.R3 % 32 == 0;
+    if (plan->use_stream && (!whole || (reinterpret_cast<uintptr_t>(a.U2) | reinterpret_cast<uintptr_t>(a.U3) |
+                                        reinterpret_cast<uintptr_t>(out)) % 16 == 0)) {
         Ttmc3StreamArgs sa{};
         sa.R2 = a.R2;
         sa.R3 = a.R3;

@@ -867,7 +867,6 @@ static conststn_status build_stream_tables(conststn_plan_s *plan) {
     if (n_items == 0) return CONSTSTN_OK;
     // an item costs its K-steps plus the store of its row block
     const int64_t item_cost = std::max<int64_t>(plan->opt("ttmc3_itemcost", 2), 0);
-    const int64_t target = std::max<int64_t>(plan->opt("ttmc3_batch", 2048), 1);
     DevBuf<int64_t> ksteps_of, cost_of, kstep_off, cost_off;
     CST_TRY(ksteps_of.alloc(n_items));
     CST_TRY(cost_of.alloc(n_items));
@@ -880,6 +879,11 @@ static conststn_status build_stream_tables(conststn_plan_s *plan) {
     int64_t total_cost = 0;
     CST_TRY(exscan(ksteps_of.p, kstep_off.p, n_items, &plan->n_ksteps));
     CST_TRY(exscan(cost_of.p, cost_off.p, n_items, &total_cost));
+    // long enough that a batch's prologue (six dependent loads) does not count, short enough that there are
+    // some for every CU: with 2048 units whatever the size, the 200 slices of a tensor of 8 000 nonzeros
+    // would be two batches
+    const int64_t even_share = std::max<int64_t>(total_cost / (int64_t(plan->n_cus) * 4), 8);
+    const int64_t target = std::max<int64_t>(plan->opt("ttmc3_batch", std::min<int64_t>(even_share, 2048)), 1);
     if (plan->n_ksteps >= (int64_t(1) << 31)) { set_error("more than 2^31 K-steps"); return CONSTSTN_EUNSUPPORTED; }
     CST_TRY(plan->ksteps.alloc(size_t(plan->n_ksteps)));
     fill_ksteps_kernel<<<dim3(unsigned(div_up(plan->n_ksteps, 256))), block>>>(
@@ -950,10 +954,15 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
     // order 3 splits by leaves, order 4 by level-1 fibers (each carries a whole sub-tree)
     const int64_t *unit_ptr = order == 3 ? plan->slice_leaf.p : X->ptr[0].p;
     int64_t split = order == 3 ? plan->opt("ttmc3_split", 4096) : plan->opt("ttmc4_split", 256);
-    // ranks that are multiples of 16 take the MFMA kernel, whose items are ranges of rows
-    plan->use_rows = order == 3 && plan->rank_of_level[1] % 16 == 0 && plan->rank_of_level[2] % 16 == 0 &&
-                     plan->rank_of_level[1] <= 64 && plan->rank_of_level[2] <= 64 &&
-                     plan->opt("ttmc3_mfma", 1) == 1;
+    // The matrix-core kernels of order 3 work on items that are ranges of rows.  The streaming form takes any
+    // ranks from 2 to 64 (see kernels_ttmc3.hip) whose leaf factor its 32-bit byte offsets reach; the form
+    // with one wavefront per item takes multiples of 16: 16 and 48 in the last rank, where the streaming
+    // form's pairs of column tiles would be half empty, and factors of 4 GiB and more.
+    const int R2 = plan->rank_of_level[1], R3 = plan->rank_of_level[2];
+    const bool rows16 = order == 3 && R2 % 16 == 0 && R3 % 16 == 0 && R2 <= 64 && R3 <= 64;
+    const bool stream = order == 3 && R2 >= 2 && R3 >= 2 && R2 <= 64 && R3 <= 64 && !(rows16 && R3 % 32 != 0) &&
+                        X->dims[X->mode_order[2]] * R3 * 8 < (int64_t(1) << 32) && plan->opt("ttmc3_stream", 1) == 1;
+    plan->use_rows = (rows16 || stream) && plan->opt("ttmc3_mfma", 1) == 1;
     if (plan->use_rows) {
         CST_TRY(build_rows(plan));
         unit_ptr = plan->slice_row.p;
@@ -981,10 +990,7 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
                              plan->split_first, plan->split_count, plan->partial));
     CST_HIP(hipDeviceSynchronize());
     if (X->order == 4 && plan->use_rows && plan->n_items > 1) CST_TRY(order_items_by_cost(plan));
-    // streaming form of the order-3 matrix-core path: R3 of 32 or 64 (two column tiles per multiplying
-    // wavefront), rows and output blocks reachable with the table's 32-bit fields
-    plan->use_stream = X->order == 3 && plan->use_rows && (plan->rank_of_level[2] == 32 || plan->rank_of_level[2] == 64) &&
-                       plan->opt("ttmc3_stream", 1) == 1;
+    plan->use_stream = stream && plan->use_rows;
     if (plan->use_stream) {
         int np = int(plan->opt("ttmc3_producers", 4));
         plan->stream_producers = np == 2 || np == 3 || np == 6 || np == 8 ? np : 4;

@@ -1,0 +1,41 @@
+"""Order-3 TTMc on the streaming matrix-core kernel at ranks that do not fill its 16 x 32 tiles: the smallest,
+one above and one below every tile edge, odd and even, against the CPU oracle.  A guard behind the result shows
+that the masked stores stay inside it, and a result that is not aligned to 16 bytes is written alike."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2401_04836_amd as cst
+from paper_2401_04836_amd import schedules as S
+
+pytestmark = pytest.mark.gpu
+
+RANKS = [(2, 2), (8, 8), (10, 7), (7, 10), (15, 33), (17, 31), (31, 3), (33, 64), (64, 33), (47, 49), (50, 50), (63, 63),
+         (48, 50), (64, 62)]
+
+
+@pytest.mark.parametrize("ranks", RANKS)
+@pytest.mark.parametrize("dims,nnz", [((7, 11, 13), 300), ((1, 5, 900), 2000), ((40, 3, 50), 3000)])
+def test_ranks_beside_the_tile_edges(ranks, dims, nnz):
+    R2, R3 = ranks
+    rng = np.random.default_rng(R2 * 100 + R3)
+    keys = rng.permutation(np.unique(rng.integers(0, np.prod(dims), nnz)))
+    c = [x.astype(np.int32) for x in np.unravel_index(keys, dims)]
+    v = rng.uniform(-1, 1, len(keys))
+    U2, U3 = rng.uniform(-1, 1, (dims[1], R2)), rng.uniform(-1, 1, (dims[2], R3))
+    print("[case] ranks %s dims %s nnz %d" % (ranks, dims, len(keys)), flush=True)
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2])
+    u2, u3 = torch.from_numpy(U2).cuda(), torch.from_numpy(U3).cuda()
+    pl = cst.plan(S.TTMC3, [("X", csf), ("U3", u3), ("U2", u2)], options=dict(ttmc3_rowsplit=64))
+    assert "kernel=stream" in pl.describe()
+    pl.check()
+    want, S_abs = oracle.ttmc3(c, v, dims, U2, U3, 0), oracle.ttmc3_abs(c, v, dims, U2, U3, 0)
+    n = want.size
+    for shift in (0, 1):
+        buf = torch.full((n + 16,), 7.0, dtype=torch.float64, device="cuda")
+        cst.execute(pl, [u3, u2], out=buf[shift:shift + n])
+        got = buf.cpu().numpy()
+        # sums of at most 3000 products of three factors in any order: 3002 roundings of 1.1e-16
+        assert oracle.rel_err(got[shift:shift + n].reshape(want.shape), want, S_abs) <= 3.4e-13
+        assert (got[:shift] == 7.0).all() and (got[shift + n:] == 7.0).all()
