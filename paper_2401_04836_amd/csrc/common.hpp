@@ -35,6 +35,19 @@ void clear_error();
         if (s__ != CONSTSTN_OK) return s__;          \
     } while (0)
 
+// ---- device memory (memory.cpp): hipMalloc / hipFree with a bounded cache of released blocks ------
+hipError_t device_alloc(void **p, size_t bytes);      // on the current device
+void device_free(void *p);                             // waits for the device
+
+// Held by every CSF and every plan, as the first member (so that it outlives the buffers beside it): while
+// one is alive, released blocks are kept for reuse.
+struct MemoryUser {
+    MemoryUser();
+    ~MemoryUser();
+    MemoryUser(const MemoryUser &) = delete;
+    MemoryUser &operator=(const MemoryUser &) = delete;
+};
+
 // ---- owned device buffer ---------------------------------------------------------------
 template <typename T>
 struct DevBuf {
@@ -45,17 +58,17 @@ struct DevBuf {
     DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf() { release(); }
     void release() {
-        if (p) (void)hipFree(p);
+        device_free(p);
         p = nullptr;
         n = 0;
     }
     conststn_status alloc(size_t count) {
         release();
         if (count == 0) count = 1;   // keep a valid pointer for empty arrays
-        hipError_t e = hipMalloc(reinterpret_cast<void **>(&p), count * sizeof(T));
+        hipError_t e = device_alloc(reinterpret_cast<void **>(&p), count * sizeof(T));
         if (e != hipSuccess) {
             p = nullptr;
-            set_error("hipMalloc of %zu bytes failed: %s", count * sizeof(T), hipGetErrorString(e));
+            set_error("device allocation of %zu bytes failed: %s", count * sizeof(T), hipGetErrorString(e));
             (void)hipGetLastError();
             return CONSTSTN_ENOMEM;
         }
@@ -76,6 +89,7 @@ static inline int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // The CSF handle.  Level l: idx[l] (nodes[l] entries), ptr[l] (nodes[l]+1 entries, l < order-1).
 struct conststn_csf_s {
+    cst::MemoryUser memory_user;
     int order = 0;
     int64_t dims[CONSTSTN_MAX_ORDER] = {0};
     int mode_order[CONSTSTN_MAX_ORDER] = {0};

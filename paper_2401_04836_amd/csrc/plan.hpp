@@ -152,6 +152,7 @@ struct MttkrpPart {
 }  // namespace cst
 
 struct conststn_plan_s {
+    cst::MemoryUser memory_user;
     cst::Schedule sched;
     cst::Family family = cst::FAM_NONE;
     unsigned flags = 0;
