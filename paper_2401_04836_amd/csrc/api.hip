@@ -87,11 +87,16 @@ static conststn_status match_chain(conststn_plan_s *plan) {
     const Stmt &last = s.stmts[m - 1];
     if (all_same && m > 1) {
         // MTTKRP: batch index r; output M[x0, r]
-        if (n != 3) { set_error("MTTKRP kernels exist for order-3 tensors only"); return CONSTSTN_EUNSUPPORTED; }
         if (last.out.idx.size() != 2 || last.out.idx[0] != x[0] || last.out.idx[1] != ranks[0]) return CONSTSTN_EUNSUPPORTED;
         for (int l = 2; l < n; ++l)
             if (plan->rank_of_level[l] != plan->rank_of_level[1]) { set_error("batch index with two extents"); return CONSTSTN_ESCHED; }
-        plan->family = FAM_MTTKRP3;
+        // order 4 belongs to the generic executor, which runs the whole chain as one kernel; where its options
+        // ask for nothing else, that kernel is the record stream's
+        plan->use_records = record_stream_fits(X.csf, plan->rank_of_level[1]) &&
+                            (n == 3 || (plan->opt("generic_fuse", 1) == 1 && !plan->options.count("generic_span")));
+        if (n == 4 && !plan->use_records) { set_error("MTTKRP kernels exist for order-3 tensors only"); return CONSTSTN_EUNSUPPORTED; }
+        plan->family = n == 3 ? FAM_MTTKRP3 : FAM_GENERIC;
+        plan->gen_rooted = n == 4;
         plan->row_elems = plan->rank_of_level[1];
     } else if (all_distinct) {
         // TTMc: output Y[x0, r(level 1), r(level 2), ...]
@@ -314,6 +319,7 @@ static conststn_status match_rerooted(conststn_plan_s *plan) {
     plan->factor_of_level[2] = facs[b].ordinal;
     plan->rank_of_level[2] = facs[b].extent;
     plan->family = mttkrp ? FAM_MTTKRP3 : FAM_TTMC3;
+    plan->use_records = mttkrp && record_stream_fits(plan->rerooted_x.get(), plan->rank_of_level[1]);
     plan->row_elems = mttkrp ? facs[a].extent : int64_t(facs[a].extent) * facs[b].extent;
     return CONSTSTN_OK;
 }
@@ -321,7 +327,7 @@ static conststn_status match_rerooted(conststn_plan_s *plan) {
 // rank extents the tuned kernels are built for
 static bool tuned_kernel_fits(const conststn_plan_s *plan) {
     switch (plan->family) {
-        case FAM_MTTKRP3: return plan->rank_of_level[1] <= 128;
+        case FAM_MTTKRP3: return plan->use_records;
         case FAM_TTMC3: return plan->rank_of_level[1] <= 64 && plan->rank_of_level[2] <= 64;
         case FAM_TTMC4: return plan->rank_of_level[1] <= 16 && plan->rank_of_level[2] <= 16 && plan->rank_of_level[3] <= 16;
         default: return true;
@@ -604,6 +610,7 @@ conststn_status conststn_plan_options(const char *schedule, const int *fusion, i
         plan->family = FAM_NONE;
         plan->rerooted_x.reset();
         plan->rerooted_level = -1;
+        plan->use_records = false;
         plan->X = nullptr;
         st = build_generic(plan);
         if (st == CONSTSTN_EUNSUPPORTED) {
@@ -620,6 +627,9 @@ conststn_status conststn_plan_options(const char *schedule, const int *fusion, i
     if (plan->family == FAM_GENERIC && !plan->gen_rooted) plan->out_rows = 1;    // fully contracted sparse modes
     switch (plan->family) {
         case FAM_MTTKRP3: CST_TRY(build_mttkrp3_tables(plan)); break;
+        case FAM_GENERIC:
+            if (plan->use_records) CST_TRY(build_record_stream(plan));
+            break;
         case FAM_TTMC3:
         case FAM_TTMC4: CST_TRY(build_ttmc_tables(plan)); break;
         case FAM_SPTN3: CST_TRY(build_sptn3_tables(plan)); break;
@@ -662,10 +672,15 @@ conststn_status conststn_plan_options(const char *schedule, const int *fusion, i
         plan->description += b;
     }
     if (plan->family == FAM_GENERIC) {
-        int fused = 0, pairs = 0;
+        int fused = 0, pairs = 0, stmts = int(plan->gen.size());
+        if (plan->use_records) {                     // one kernel, every producer inlined
+            stmts = int(plan->sched.stmts.size());
+            fused = stmts - 1;
+            pairs = plan->rank_of_level[1] % 2 == 0 ? 1 : 0;
+        }
         for (const GenStmt &g : plan->gen) { fused += g.skip; pairs += (g.fused && !g.skip && g.fused_pairs) ? 1 : 0; }
         char b[96];
-        snprintf(b, sizeof(b), " kernels=%d inlined_producers=%d", int(plan->gen.size()) - fused, fused);
+        snprintf(b, sizeof(b), " kernels=%d inlined_producers=%d", stmts - fused, fused);
         plan->description += b;
         snprintf(b, sizeof(b), " two_elements_per_lane=%d", pairs);
         plan->description += b;
@@ -779,13 +794,15 @@ conststn_status conststn_execute(const conststn_plan_t *plan, const double *cons
         if (!dense_factors[d]) { set_error("dense_factors[%d] is null", d); return CONSTSTN_EINVAL; }
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (plan->family) {
-        case FAM_MTTKRP3: return launch_mttkrp3(plan, dense_factors, out, st);
+        case FAM_MTTKRP3:
+            return plan->split ? launch_mttkrp3(plan, dense_factors, out, st) : launch_record_stream(plan, dense_factors, out, st);
         case FAM_TTMC3: return launch_ttmc3(plan, dense_factors, out, st);
         case FAM_TTMC4: return launch_ttmc4(plan, dense_factors, out, st);
         case FAM_SPTN3: return launch_sptn3(plan, dense_factors, out, st);
         case FAM_SPCHAIN3: return launch_spchain3(plan, out, st);
         case FAM_SPPAIR4: return launch_sppair4(plan, out, st);
-        case FAM_GENERIC: return launch_generic(plan, dense_factors, out, st);
+        case FAM_GENERIC:
+            return plan->use_records ? launch_record_stream(plan, dense_factors, out, st) : launch_generic(plan, dense_factors, out, st);
         default: set_error("plan has no kernel family"); return CONSTSTN_EINVAL;
     }
 }

@@ -72,13 +72,13 @@ check_level_kernel(CsfView v, int l, unsigned *flags) {
     if (bad) atomicOr(flags, bad);
 }
 
-// MTTKRP tables over a CSF given as raw arrays (the caller's tensor or one of the two sub-tensors)
+// MTTKRP tables of one of the two sub-tensors
 struct MttkrpView {
     int64_t slices, fibers, nnz, q, n_chunks, out_rows, dim1, dim2;
     const int64_t *ptr0, *ptr1, *slice_leaf, *chunk_fiber;
     const int32_t *chunk_slice, *row_of_slice, *idx1;
     const uint32_t *code;                      // re-encoded leaves, or nullptr
-    int n_hot, mode;                           // mode 1: every leaf hot, 2: every leaf cold, 0: marked per leaf
+    int n_hot, mode;                           // mode 1: every leaf hot, 2: every leaf cold
 };
 
 __global__ void __launch_bounds__(256)
@@ -99,7 +99,7 @@ check_mttkrp_kernel(MttkrpView m, unsigned *flags) {
     if (t < m.fibers && (m.idx1[t] < 0 || m.idx1[t] >= m.dim1)) bad |= kBadIndex;
     if (m.code && t < m.nnz) {
         const uint32_t cd = m.code[t];
-        const bool hot = m.mode == 1 || (m.mode == 0 && (cd & 0x80000000u));
+        const bool hot = m.mode == 1;
         const int64_t row = cd & 0x0fffffffu;
         if (hot ? row >= m.n_hot : row >= m.dim2) bad |= kBadCode;
         // the marks: this leaf ends its fiber / its slice exactly when the pointer arrays say so
@@ -342,6 +342,12 @@ extern "C" conststn_status conststn_plan_check(const conststn_plan_t *plan) {
     CST_TRY(flags.alloc(1));
     CST_HIP(hipMemset(flags.p, 0, sizeof(unsigned)));
     CST_TRY(run_csf_check(X, flags.p));                    // the tensor the kernels walk (the private copy, if one was made)
+    if (plan->use_records && !plan->split) {
+        CST_TRY(check_record_stream(plan, kBadCode, kBadChunk, flags.p));
+        unsigned hr = 0;
+        CST_HIP(hipMemcpy(&hr, flags.p, sizeof(hr), hipMemcpyDeviceToHost));
+        return report(hr, "plan tables");
+    }
     if (plan->family == FAM_GENERIC) {
         CST_TRY(check_generic_tables(plan, flags.p));
         unsigned hg = 0;
@@ -356,19 +362,11 @@ extern "C" conststn_status conststn_plan_check(const conststn_plan_t *plan) {
             CST_HIP(hipGetLastError());
             return CONSTSTN_OK;
         };
-        if (plan->split) {
-            for (int part = 0; part < 2; ++part) {
-                const MttkrpPart &P = plan->part[part];
-                if (P.nnz == 0) continue;
-                MttkrpView m{P.slices, P.fibers, P.nnz, P.chunk_q, P.n_chunks, plan->out_rows, dim1, dim2,
-                             P.ptr0.p, P.ptr1.p, P.slice_leaf.p, P.chunk_fiber.p, P.chunk_slice.p, P.row_of_slice.p,
-                             P.idx1.p, P.code.p, plan->n_hot, part == 0 ? 1 : 2};
-                CST_TRY(launch(m));
-            }
-        } else {
-            MttkrpView m{X->nodes[0], X->nodes[1], X->nnz, plan->chunk_q, plan->n_chunks, plan->out_rows, dim1, dim2,
-                         X->ptr[0].p, X->ptr[1].p, plan->slice_leaf.p, plan->chunk_fiber.p, plan->chunk_slice.p, nullptr,
-                         X->idx[1].p, plan->leaf_code.p, plan->n_hot, 0};
+        for (int part = 0; part < 2; ++part) {
+            const MttkrpPart &P = plan->part[part];
+            MttkrpView m{P.slices, P.fibers, P.nnz, P.chunk_q, P.n_chunks, plan->out_rows, dim1, dim2,
+                         P.ptr0.p, P.ptr1.p, P.slice_leaf.p, P.chunk_fiber.p, P.chunk_slice.p, P.row_of_slice.p,
+                         P.idx1.p, P.code.p, plan->n_hot, part == 0 ? 1 : 2};
             CST_TRY(launch(m));
         }
     }

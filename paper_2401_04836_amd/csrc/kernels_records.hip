@@ -1,0 +1,724 @@
+// MTTKRP of order 3 and 4 as a walk over one stream of records (Sec. 5.2, 5.3):
+//     M[i,r] = sum_{j,k} X[i,j,k] B[j,r] C[k,r]       and       M[i,r] = sum X[i,j,k,l] B[j,r] C[k,r] D[l,r]
+// fused on the whole sparse prefix, so that every intermediate is one length-R vector (Fig. 3b).
+//
+// The plan turns the tree into a flat stream in which every record reads exactly ONE factor row:
+//     leaf             t   += v * F_leaf[index]
+//     end of a fiber   acc += t * F_1[index], t = 0         (order 4: u += t * F_2[index], t = 0)
+//     end of a node    acc += u * F_1[index], u = 0         (order 4 only)
+// and the last record of a slice is marked.  The stream is cut into chunks of q records; LPR lanes own a chunk
+// and hold NV pairs of rank entries each.  The four (eight) lane groups of a wavefront walk their chunks in
+// lock step, one record per step: a step is NV gathers in which every group takes part, whatever its record is.
+// With the rows of ended fibers read beside the leaf rows, as a stream of leaves needs it, half the gathers serve
+// 1.4 of 4 groups.  The bound is the L1 pipeline, which takes 16 cycles for such a gather (64 bytes a cycle) and
+// more where it misses: 95 % busy by the counters at 76 M nonzeros, rank 32, 89 M records.  Neither fewer
+// instructions per record (groups of 4 or 8 lanes with 4 or 2 pairs each: 1.54, 1.28 against 1.23 ms), nor
+// selects in place of branches (1.25), nor twice the rows in flight (1.20), nor the most named rows in LDS (1.20)
+// change it by more than that.
+//   - a block of LPR records is read with one load per lane, two blocks ahead; each lane forms the address of
+//     its record's row and the group takes address and value round with row broadcasts;
+//   - which groups meet an end in a step is known per wavefront (a ballot per block), so the two kinds of step
+//     differ by lane masks made in scalar registers;
+//   - a slice that ends in the chunk it began in is stored; its parts in other chunks go to partial rows,
+//     two per chunk, which records_fixup_kernel adds in chunk order.  No atomics: the sums are reproducible.
+// Ranks that do not fill the lanes: a lane past the row's end takes the row's last two entries and stores
+// nothing; with an odd rank one lane repeats an entry of its neighbour.
+#include <algorithm>
+#include <utility>
+
+#include "plan.hpp"
+
+namespace cst {
+
+namespace {
+
+constexpr uint32_t kRecFiberEnd = 1u << 30, kRecNodeEnd = 2u << 30, kRecSliceEnd = 1u << 29, kRecIndex = (1u << 28) - 1;
+constexpr uint32_t kChunkInside = 1u << 31;           // the chunk begins inside its first slice
+
+typedef double v2f64_u __attribute__((ext_vector_type(2), aligned(8)));
+typedef double v2f64 __attribute__((ext_vector_type(2)));
+typedef int v2i32 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) const v2f64_u global_v2f64_u;     // an address put together from integers
+
+struct RecordArgs {
+    int64_t n_chunks;
+    int q, R;
+    int32_t slices;
+    const uint32_t *code;
+    const double *vals;
+    const uint32_t *chunk_slice;
+    const int32_t *open1, *open2;                      // rows of the fiber / node left open at a chunk's end, or -1
+    const int32_t *row_of_slice;
+    const double *f0, *f1, *f2;                        // factors of the leaves, of the fibers, of the nodes above them
+    double *out, *partial;
+};
+
+// entry T of every LPR lanes, to all of them
+template <int LPR, int T>
+__device__ __forceinline__ int group_bcast(int x) {
+    if (LPR == 16) return __builtin_amdgcn_mov_dpp(x, 0x150 + T, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, x, 0x150 + T, 0xf, 0x3, false);
+    return __builtin_amdgcn_update_dpp(lo, x, 0x150 + 8 + T % 8, 0xf, 0xc, false);
+}
+
+template <int... I, class F>
+__device__ __forceinline__ void each(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+template <int LPR, int NV, int LEVELS>
+__global__ void __launch_bounds__(256)
+records_kernel(RecordArgs a) {
+    constexpr int U = NV == 1 ? 8 : 4;                 // rows in flight per lane group
+    constexpr uint64_t kOne = LPR == 16 ? 0x0001000100010001ull : 0x0101010101010101ull;
+    const int gl = threadIdx.x % LPR;
+    int64_t c = int64_t(blockIdx.x) * (256 / LPR) + threadIdx.x / LPR;
+    const bool live = c < a.n_chunks;
+    if (!live) c = a.n_chunks - 1;                     // walks along and stores nothing
+    const int R = a.R;
+    int col[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) col[v] = min(2 * (LPR * v + gl), R - 2);
+    const uint32_t row_bytes = uint32_t(R) * 8u;
+    const uint32_t *code = a.code + c * a.q;
+    const double *vals = a.vals + c * a.q;
+    const uint32_t head = a.chunk_slice[c];
+    int32_t s = int32_t(head & ~kChunkInside);
+    bool whole = !(head & kChunkInside);               // the slice being summed began in this chunk
+    bool first = true;                                 // and is the chunk's first
+    int32_t row = a.row_of_slice[s];
+
+    double t[NV][2], u[NV][2], acc[NV][2];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) t[v][e] = u[v][e] = acc[v][e] = 0.0;
+
+    auto put = [&](double *dst) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int mine = 2 * (LPR * v + gl);
+            if (mine + 1 < R) *reinterpret_cast<v2f64_u *>(dst + mine) = v2f64_u{acc[v][0], acc[v][1]};
+            else if (mine < R) dst[mine] = acc[v][1];  // odd rank: this lane holds entries R-2 and R-1
+        }
+    };
+    auto emit = [&](bool ends) {
+        double *dst = (ends && whole) ? a.out + int64_t(row) * R : a.partial + (2 * c + (first ? 0 : 1)) * R;
+        if (live) put(dst);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v][0] = acc[v][1] = 0.0;
+        whole = true;
+        first = false;
+        ++s;
+        row = a.row_of_slice[min(s, a.slices - 1)];
+    };
+
+    const int blocks = a.q / LPR;
+    uint32_t code_cur = code[gl], code_nxt = code[(blocks > 1 ? LPR : 0) + gl];
+    double val_cur = vals[gl], val_nxt = vals[(blocks > 1 ? LPR : 0) + gl];
+    for (int b = 0; b < blocks; ++b) {
+        const int ahead = min(b + 2, blocks - 1) * LPR + gl;
+        const uint32_t code_n2 = code[ahead];
+        const double val_n2 = vals[ahead];
+        const uint32_t kind = code_cur >> 30;
+        const double *base = a.f0;
+        if (kind == 1) base = a.f1;
+        if (LEVELS == 3 && kind == 2) base = a.f2;
+        const uint64_t addr = reinterpret_cast<uint64_t>(base) + uint64_t(code_cur & kRecIndex) * row_bytes;
+        const int addr_lo = int(uint32_t(addr)), addr_hi = int(uint32_t(addr >> 32));
+        const int val_lo = __double2loint(val_cur), val_hi = __double2hiint(val_cur);
+        const uint64_t ends1 = __builtin_amdgcn_ballot_w64(kind == 1);
+        const uint64_t ends2 = LEVELS == 3 ? __builtin_amdgcn_ballot_w64(kind == 2) : 0;
+        const uint64_t last = __builtin_amdgcn_ballot_w64((code_cur & kRecSliceEnd) != 0);
+        // lanes of the groups whose step-T record is marked in m
+        auto groups = [&](uint64_t m, int T) -> uint64_t {
+            const uint64_t x = (m >> T) & kOne;
+            return (x << LPR) - x;
+        };
+        auto batch = [&](auto T0c) {
+            constexpr int T0 = decltype(T0c)::value * U;
+            v2f64 x[U][NV];
+            each(std::make_integer_sequence<int, U>{}, [&](auto Uc) {
+                constexpr int k = decltype(Uc)::value, T = T0 + k;
+                const v2i32 at{group_bcast<LPR, T>(addr_lo), group_bcast<LPR, T>(addr_hi)};
+                const uint64_t p = __builtin_bit_cast(uint64_t, at);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) x[k][v] = *reinterpret_cast<global_v2f64_u *>(p + uint64_t(uint32_t(col[v] * 8)));
+            });
+            each(std::make_integer_sequence<int, U>{}, [&](auto Uc) {
+                constexpr int k = decltype(Uc)::value, T = T0 + k;
+                const v2f64 *row_x = x[k];
+                const bool e1 = __builtin_amdgcn_inverse_ballot_w64(groups(ends1, T));
+                const double value = __hiloint2double(group_bcast<LPR, T>(val_hi), group_bcast<LPR, T>(val_lo));
+                if (e1) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            if (LEVELS == 3) u[v][e] = fma(t[v][e], row_x[v][e], u[v][e]);
+                            else acc[v][e] = fma(t[v][e], row_x[v][e], acc[v][e]);
+                            t[v][e] = 0.0;
+                        }
+                } else if (LEVELS == 2 || !__builtin_amdgcn_inverse_ballot_w64(groups(ends2, T))) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) t[v][e] = fma(value, row_x[v][e], t[v][e]);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            acc[v][e] = fma(u[v][e], row_x[v][e], acc[v][e]);
+                            u[v][e] = 0.0;
+                        }
+                }
+                if (last & (kOne << T)) {
+                    if (__builtin_amdgcn_inverse_ballot_w64(groups(last, T))) emit(true);
+                }
+            });
+        };
+        each(std::make_integer_sequence<int, LPR / U>{}, batch);
+        code_cur = code_nxt;
+        val_cur = val_nxt;
+        code_nxt = code_n2;
+        val_nxt = val_n2;
+    }
+    // the chunk may end inside a fiber, a node and a slice: their sums so far count with the rows still to come
+    const int32_t o1 = a.open1[c], o2 = LEVELS == 3 ? a.open2[c] : -1;
+    if (o1 >= 0) {
+        const double *r1 = a.f1 + int64_t(o1) * R;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                if (LEVELS == 3) u[v][e] = fma(t[v][e], r1[col[v] + e], u[v][e]);
+                else acc[v][e] = fma(t[v][e], r1[col[v] + e], acc[v][e]);
+            }
+    }
+    if (LEVELS == 3 && o2 >= 0) {
+        const double *r2 = a.f2 + int64_t(o2) * R;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) acc[v][e] = fma(u[v][e], r2[col[v] + e], acc[v][e]);
+    }
+    if (s < a.slices) emit(false);
+}
+
+// ---- rows of slices that several chunks share ---------------------------------------------------------
+//
+// One launch: first the slices of many chunks (kRecLight and more; a workgroup, or kRecSegments of them, per
+// slice), then those of a few (W threads each), then the rows of empty slices, which are zero.
+constexpr int kRecLight = 32, kRecOneBlock = 1024, kRecSegments = 32;
+
+struct RecordFixArgs {
+    int R, q, segments;
+    int64_t n_heavy, n_light, n_empty, heavy_blocks, light_blocks;
+    const int32_t *heavy, *light, *empty, *row_of_slice;
+    const int64_t *slice_rec;
+    const double *partial;
+    double *heavy_partial, *out;
+};
+
+// partial row of slice [lo, ...) in chunk c: the second one where the slice begins inside the chunk
+__device__ __forceinline__ int64_t partial_row(int64_t c, int64_t ca, int64_t lo, int q) {
+    return 2 * c + ((c == ca && lo != ca * q) ? 1 : 0);
+}
+
+template <int W, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+records_fixup_kernel(RecordFixArgs a) {
+    constexpr int G = THREADS / W;
+    __shared__ double red[THREADS];
+    const int g = threadIdx.x / W, col = threadIdx.x % W, R = a.R;
+    const bool mine = col < R;
+    int64_t b = blockIdx.x;
+    if (b < a.heavy_blocks) {
+        const int64_t h = b / a.segments, seg = b % a.segments;
+        const int64_t s = a.heavy[h], lo = a.slice_rec[s], hi = a.slice_rec[s + 1];
+        const int64_t ca = lo / a.q, cb = (hi - 1) / a.q, n = cb - ca + 1;
+        const int64_t c0 = ca + n * seg / a.segments, c1 = ca + n * (seg + 1) / a.segments;
+        double sum = 0.0;
+        if (mine) {
+            int64_t c = c0 + g;
+            for (; c + 7 * G < c1; c += 8 * G) {
+                double x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) x[k] = a.partial[partial_row(c + k * G, ca, lo, a.q) * R + col];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sum += x[k];
+            }
+            for (; c < c1; c += G) sum += a.partial[partial_row(c, ca, lo, a.q) * R + col];
+        }
+        red[threadIdx.x] = sum;
+        __syncthreads();
+        if (g == 0 && mine) {
+            for (int gg = 1; gg < G; ++gg) sum += red[gg * W + col];
+            if (a.segments == 1) a.out[int64_t(a.row_of_slice[s]) * R + col] = sum;
+            else a.heavy_partial[(h * a.segments + seg) * R + col] = sum;
+        }
+        return;
+    }
+    b -= a.heavy_blocks;
+    if (b < a.light_blocks) {
+        const int64_t k = b * G + g;
+        if (k >= a.n_light || !mine) return;
+        const int64_t s = a.light[k], lo = a.slice_rec[s], hi = a.slice_rec[s + 1];
+        const int64_t ca = lo / a.q, cb = (hi - 1) / a.q;
+        double sum = a.partial[partial_row(ca, ca, lo, a.q) * R + col];
+        int64_t c = ca + 1;
+        for (; c + 3 <= cb; c += 4) {
+            double x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = a.partial[2 * (c + e) * R + col];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum += x[e];
+        }
+        for (; c <= cb; ++c) sum += a.partial[2 * c * R + col];
+        a.out[int64_t(a.row_of_slice[s]) * R + col] = sum;
+        return;
+    }
+    b -= a.light_blocks;
+    const int64_t k = b * G + g;
+    if (k < a.n_empty && mine) a.out[int64_t(a.empty[k]) * R + col] = 0.0;
+}
+
+__global__ void __launch_bounds__(128)
+records_final_kernel(RecordFixArgs a) {
+    const int64_t h = blockIdx.x;
+    const int col = threadIdx.x;
+    if (col >= a.R) return;
+    double sum = 0.0;
+#pragma unroll 8
+    for (int seg = 0; seg < kRecSegments; ++seg) sum += a.heavy_partial[(h * kRecSegments + seg) * a.R + col];
+    a.out[int64_t(a.row_of_slice[a.heavy[h]]) * a.R + col] = sum;
+}
+
+// ---- the plan's side ------------------------------------------------------------------------------------
+
+// parent[e] = the node one level up that child e hangs below.  A workgroup takes 2048 children: it finds the
+// parent of the first by binary search and marks where the others begin.
+constexpr int kExpandTile = 2048;
+__global__ void __launch_bounds__(256)
+expand_parents_kernel(int64_t children, int64_t parents, const int64_t *__restrict__ ptr, int32_t *__restrict__ parent) {
+    __shared__ uint8_t begins[kExpandTile];
+    __shared__ int64_t p0_shared;
+    __shared__ int wtot[4];
+    const int64_t base = int64_t(blockIdx.x) * kExpandTile;
+    const int64_t end = base + kExpandTile < children ? base + kExpandTile : children;
+    reinterpret_cast<uint64_t *>(begins)[threadIdx.x] = 0;
+    if (threadIdx.x == 0) p0_shared = parent_of(ptr, parents, base);
+    __syncthreads();
+    const int64_t p0 = p0_shared;
+    for (int64_t p = p0 + 1 + threadIdx.x; p < parents; p += 256) {
+        const int64_t at = ptr[p];
+        if (at >= end) break;
+        begins[at - base] = 1;
+    }
+    __syncthreads();
+    const uint64_t mine = reinterpret_cast<const uint64_t *>(begins)[threadIdx.x];
+    const int cnt = __popcll(mine);                                  // bytes are 0 or 1
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    int inc = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += up;
+    }
+    if (lane == 63) wtot[wave] = inc;
+    __syncthreads();
+    int run = inc - cnt;
+    for (int w = 0; w < wave; ++w) run += wtot[w];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        run += int((mine >> (8 * k)) & 1u);
+        const int64_t e = base + threadIdx.x * 8 + k;
+        if (e < end) parent[e] = int32_t(p0 + run);
+    }
+}
+
+struct RecordFill {
+    int64_t leaves, fibers, nodes, slices, n_rec, total;             // nodes: order 4 only (0 otherwise)
+    const int64_t *ptr_slice, *ptr_node, *ptr_fiber;                  // slices -> level 1, nodes -> fibers, fibers -> leaves
+    const int32_t *idx_slice, *idx_node, *idx_fiber, *idx_leaf;
+    const double *vals;
+    const int32_t *fiber_of, *node_of;
+    uint32_t *code;
+    double *out_vals;
+    int64_t *slice_rec;
+};
+
+__global__ void __launch_bounds__(256)
+record_leaves_kernel(RecordFill a) {
+    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (e >= a.leaves) {
+        // records past the end name the last leaf's row with the value 0
+        const int64_t pad = a.n_rec + (e - a.leaves);
+        if (pad < a.total) { a.code[pad] = uint32_t(a.idx_leaf[a.leaves - 1]); a.out_vals[pad] = 0.0; }
+        return;
+    }
+    const int32_t f = a.fiber_of[e];
+    const int64_t at = e + f + (a.nodes ? a.node_of[f] : 0);
+    a.code[at] = uint32_t(a.idx_leaf[e]);
+    a.out_vals[at] = a.vals[e];
+}
+
+__device__ __forceinline__ int64_t fiber_end_record(const RecordFill &a, int64_t f) {
+    return a.ptr_fiber[f + 1] + f + (a.nodes ? a.node_of[f] : 0);
+}
+__device__ __forceinline__ int64_t node_end_record(const RecordFill &a, int64_t n) {
+    const int64_t f = a.ptr_node[n + 1];
+    return a.ptr_fiber[f] + f + n;
+}
+
+__global__ void __launch_bounds__(256)
+record_ends_kernel(RecordFill a) {
+    const int64_t x = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (x < a.fibers) {
+        const int64_t at = fiber_end_record(a, x);
+        a.code[at] = kRecFiberEnd | uint32_t(a.idx_fiber[x]);
+        a.out_vals[at] = 0.0;
+    }
+    if (x < a.nodes) {
+        const int64_t at = node_end_record(a, x);
+        a.code[at] = kRecNodeEnd | uint32_t(a.idx_node[x]);
+        a.out_vals[at] = 0.0;
+    }
+    if (x <= a.slices) {
+        int64_t f = x, n = 0;
+        if (a.nodes) { n = a.ptr_slice[x]; f = a.ptr_node[n]; }
+        else f = a.ptr_slice[x];
+        a.slice_rec[x] = a.ptr_fiber[f] + f + n;
+    }
+}
+
+__global__ void __launch_bounds__(256)
+record_slices_kernel(RecordFill a) {
+    const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (s < a.slices) a.code[a.slice_rec[s + 1] - 1] |= kRecSliceEnd;
+}
+
+// smallest x in [0, n) with end(x) >= at
+template <class F>
+__device__ __forceinline__ int64_t first_end(int64_t n, int64_t at, F &&end) {
+    int64_t lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (end(mid) >= at) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
+__global__ void __launch_bounds__(256)
+record_chunks_kernel(RecordFill a, int64_t n_chunks, int64_t q, uint32_t *chunk_slice, int32_t *open1, int32_t *open2) {
+    const int64_t c = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (c >= n_chunks) return;
+    const int64_t r0 = c * q, r1 = (c + 1) * q < a.n_rec ? (c + 1) * q : a.n_rec;
+    const int64_t s = parent_of(a.slice_rec, a.slices, r0);
+    chunk_slice[c] = uint32_t(s) | (a.slice_rec[s] == r0 ? 0u : kChunkInside);
+    const uint32_t kind = a.code[r1 - 1] >> 30;
+    int32_t o1 = -1, o2 = -1;
+    if (kind == 0) o1 = a.idx_fiber[first_end(a.fibers, r1, [&](int64_t f) { return fiber_end_record(a, f); })];
+    if (a.nodes && kind != 2) o2 = a.idx_node[first_end(a.nodes, r1, [&](int64_t n) { return node_end_record(a, n); })];
+    open1[c] = o1;
+    if (open2) open2[c] = o2;
+}
+
+// 0: inside one chunk; 1: shared by a few chunks; 2: by many
+__device__ __forceinline__ int share_of(const int64_t *slice_rec, int64_t s, int64_t q) {
+    const int64_t span = (slice_rec[s + 1] - 1) / q - slice_rec[s] / q;
+    return span == 0 ? 0 : (span < kRecLight ? 1 : 2);
+}
+__global__ void __launch_bounds__(256)
+record_shared_kernel(int64_t slices, const int64_t *__restrict__ slice_rec, int64_t q, int kind, int64_t *flag, int *widest) {
+    const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (s >= slices) return;
+    flag[s] = share_of(slice_rec, s, q) == kind;
+    if (kind == 2 && flag[s]) {
+        const int64_t span = (slice_rec[s + 1] - 1) / q - slice_rec[s] / q + 1;
+        atomicMax(widest, int(span < 0x7fffffff ? span : 0x7fffffff));
+    }
+}
+__global__ void __launch_bounds__(256)
+list_flagged_kernel(int64_t n, const int64_t *__restrict__ flag, const int64_t *__restrict__ pos, int32_t *list) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n && flag[i]) list[pos[i]] = int32_t(i);
+}
+__global__ void __launch_bounds__(256)
+empty_rows_kernel(int64_t rows, int64_t slices, const int32_t *__restrict__ idx0, int64_t *flag) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= rows) return;
+    int64_t lo = 0, hi = slices;                                      // root indices ascend
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (idx0[mid] < i) lo = mid + 1; else hi = mid;
+    }
+    flag[i] = lo == slices || idx0[lo] != i;
+}
+__global__ void __launch_bounds__(256)
+rows_of_slices_kernel(int64_t slices, const int32_t *__restrict__ idx0, int compact, int32_t *row) {
+    const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (s < slices) row[s] = compact ? int32_t(s) : idx0[s];
+}
+
+dim3 blocks_for(int64_t n) { return dim3(unsigned(div_up(std::max<int64_t>(n, 1), 256))); }
+
+conststn_status list_of_flags(DevBuf<int64_t> &flag, int64_t n, DevBuf<int32_t> &list, int64_t *count) {
+    DevBuf<int64_t> pos;
+    CST_TRY(pos.alloc(size_t(n)));
+    CST_TRY(exscan(flag.p, pos.p, n, count));
+    CST_TRY(list.alloc(size_t(*count)));
+    if (*count > 0) {
+        list_flagged_kernel<<<blocks_for(n), dim3(256)>>>(n, flag.p, pos.p, list.p);
+        CST_HIP(hipGetLastError());
+        CST_HIP(hipDeviceSynchronize());
+    }
+    return CONSTSTN_OK;
+}
+
+// Every record recomputed from the level arrays, every chunk and row table against what it indexes.
+__global__ void __launch_bounds__(256)
+check_records_kernel(RecordFill a, int64_t dims1, int64_t q, int64_t n_chunks, int64_t out_rows, const uint32_t *chunk_slice,
+                     const int32_t *open1, const int32_t *open2, const int32_t *row_of_slice, unsigned bad_code, unsigned bad_chunk,
+                     unsigned *flags) {
+    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    unsigned bad = 0;
+    if (t < a.n_rec) {
+        uint32_t want;
+        int64_t n = 0, n_end = -1;
+        if (a.nodes) {
+            n = first_end(a.nodes, t, [&](int64_t x) { return node_end_record(a, x); });
+            n_end = node_end_record(a, n);
+        }
+        if (t == n_end) want = kRecNodeEnd | uint32_t(a.idx_node[n]);
+        else {
+            // records before t that belong to fibers: t minus the node ends before it
+            auto end_of = [&](int64_t f) { return a.ptr_fiber[f + 1] + f + (a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0); };
+            const int64_t f = first_end(a.fibers, t, end_of);
+            const int64_t nf = a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0;
+            want = t == end_of(f) ? (kRecFiberEnd | uint32_t(a.idx_fiber[f])) : uint32_t(a.idx_leaf[t - f - nf]);
+        }
+        const int64_t s = parent_of(a.slice_rec, a.slices, t);
+        if (a.slice_rec[s + 1] == t + 1) want |= kRecSliceEnd;
+        if (a.code[t] != want) bad |= bad_code;
+    } else if (t < a.total && (a.code[t] >> 29 != 0 || a.out_vals[t] != 0.0)) bad |= bad_code;
+    if (t <= a.slices) {
+        if (t == a.slices ? a.slice_rec[t] != a.n_rec : (a.slice_rec[t] < 0 || a.slice_rec[t + 1] <= a.slice_rec[t])) bad |= bad_chunk;
+        if (t < a.slices && (row_of_slice[t] < 0 || row_of_slice[t] >= out_rows)) bad |= bad_chunk;
+    }
+    if (t < n_chunks) {
+        const int64_t s = chunk_slice[t] & ~kChunkInside;
+        if (s >= a.slices || a.slice_rec[s] > t * q || a.slice_rec[s + 1] <= t * q ||
+            (a.slice_rec[s] != t * q) != ((chunk_slice[t] & kChunkInside) != 0))
+            bad |= bad_chunk;
+        if (open1[t] >= dims1 || (open2 && open2[t] >= dims1)) bad |= bad_chunk;
+    }
+    if (bad) atomicOr(flags, bad);
+}
+
+RecordFill view_of_stream(const conststn_csf_s *X, const RecordStream &rs) {
+    const int n = X->order;
+    RecordFill a{};
+    a.leaves = X->nnz;
+    a.fibers = X->nodes[n - 2];
+    a.nodes = n == 4 ? X->nodes[1] : 0;
+    a.slices = X->nodes[0];
+    a.n_rec = a.leaves + a.fibers + a.nodes;
+    a.total = rs.n_chunks * rs.q;
+    a.ptr_slice = X->ptr[0].p;
+    a.ptr_node = n == 4 ? X->ptr[1].p : nullptr;
+    a.ptr_fiber = X->ptr[n - 2].p;
+    a.idx_slice = X->idx[0].p;
+    a.idx_node = n == 4 ? X->idx[1].p : nullptr;
+    a.idx_fiber = X->idx[n - 2].p;
+    a.idx_leaf = X->idx[n - 1].p;
+    a.vals = X->vals.p;
+    a.code = rs.code.p;
+    a.out_vals = rs.vals.p;
+    a.slice_rec = rs.slice_rec.p;
+    return a;
+}
+
+}  // namespace
+
+conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_code, unsigned bad_chunk, unsigned *flags) {
+    const conststn_csf_s *X = plan->X;
+    const RecordStream &rs = plan->records;
+    if (rs.n_chunks == 0) return CONSTSTN_OK;
+    const RecordFill a = view_of_stream(X, rs);
+    int64_t dims1 = 0;
+    for (int l = 1; l < X->order - 1; ++l) dims1 = std::max(dims1, X->dims[X->mode_order[l]]);
+    const int64_t threads = std::max(std::max(a.total, a.slices + 1), rs.n_chunks);
+    check_records_kernel<<<blocks_for(threads), dim3(256)>>>(a, dims1, rs.q, rs.n_chunks, plan->out_rows, rs.chunk_slice.p, rs.open1.p,
+                                                              X->order == 4 ? rs.open2.p : nullptr, rs.row_of_slice.p, bad_code,
+                                                              bad_chunk, flags);
+    CST_HIP(hipGetLastError());
+    return CONSTSTN_OK;
+}
+
+bool record_stream_fits(const conststn_csf_s *X, int R) {
+    if ((X->order != 3 && X->order != 4) || R < 2 || R > 128) return false;
+    for (int l = 1; l < X->order; ++l)
+        if (X->dims[X->mode_order[l]] > int64_t(kRecIndex) + 1) return false;
+    return X->nodes[X->order - 2] < (int64_t(1) << 31);
+}
+
+conststn_status build_record_stream(conststn_plan_s *plan) {
+    const conststn_csf_s *X = plan->X;
+    RecordStream &rs = plan->records;
+    const int n = X->order, R = plan->rank_of_level[1];
+    rs.levels = n - 1;
+    RecordFill a = view_of_stream(X, rs);
+    rs.slices = a.slices;
+    rs.n_rec = a.n_rec;
+    rs.n_chunks = rs.n_heavy = rs.n_light = rs.n_empty = 0;
+    // Chunks: short enough that every SIMD has several wavefronts even for a small tensor, long enough that
+    // their partial rows (two per chunk) and the loads at their start stay a small part.
+    const int lanes = R <= 16 ? 8 : 16;
+    int64_t q = plan->opt("mttkrp_chunk", 0);
+    if (q <= 0) q = std::max<int64_t>(32, std::min<int64_t>(a.n_rec / (int64_t(plan->n_cus) * 4 * 12 * (64 / lanes)), 512));
+    q = div_up(q, 16) * 16;
+    rs.q = q;
+    if (!plan->compact) {
+        DevBuf<int64_t> flag;
+        CST_TRY(flag.alloc(size_t(plan->out_rows)));
+        if (a.slices < plan->out_rows) {
+            empty_rows_kernel<<<blocks_for(plan->out_rows), dim3(256)>>>(plan->out_rows, a.slices, X->idx[0].p, flag.p);
+            CST_HIP(hipGetLastError());
+            CST_TRY(list_of_flags(flag, plan->out_rows, rs.empty, &rs.n_empty));
+        }
+    }
+    if (a.leaves == 0) return CONSTSTN_OK;
+    rs.n_chunks = div_up(a.n_rec, q);
+    a.total = rs.n_chunks * q;
+    DevBuf<int32_t> fiber_of, node_of;
+    CST_TRY(fiber_of.alloc(size_t(a.leaves)));
+    expand_parents_kernel<<<dim3(unsigned(div_up(a.leaves, kExpandTile))), dim3(256)>>>(a.leaves, a.fibers, a.ptr_fiber, fiber_of.p);
+    CST_HIP(hipGetLastError());
+    if (n == 4) {
+        CST_TRY(node_of.alloc(size_t(a.fibers)));
+        expand_parents_kernel<<<dim3(unsigned(div_up(a.fibers, kExpandTile))), dim3(256)>>>(a.fibers, a.nodes, a.ptr_node, node_of.p);
+        CST_HIP(hipGetLastError());
+    }
+    CST_TRY(rs.code.alloc(size_t(a.total)));
+    CST_TRY(rs.vals.alloc(size_t(a.total)));
+    CST_TRY(rs.slice_rec.alloc(size_t(a.slices) + 1));
+    CST_TRY(rs.row_of_slice.alloc(size_t(a.slices)));
+    CST_TRY(rs.chunk_slice.alloc(size_t(rs.n_chunks)));
+    CST_TRY(rs.open1.alloc(size_t(rs.n_chunks)));
+    if (n == 4) CST_TRY(rs.open2.alloc(size_t(rs.n_chunks)));
+    CST_TRY(rs.partial.alloc(size_t(rs.n_chunks) * 2 * size_t(R)));
+    a.fiber_of = fiber_of.p;
+    a.node_of = node_of.p;
+    a.code = rs.code.p;
+    a.out_vals = rs.vals.p;
+    a.slice_rec = rs.slice_rec.p;
+    record_leaves_kernel<<<blocks_for(a.leaves + a.total - a.n_rec), dim3(256)>>>(a);
+    CST_HIP(hipGetLastError());
+    record_ends_kernel<<<blocks_for(std::max(std::max(a.fibers, a.nodes), a.slices + 1)), dim3(256)>>>(a);
+    CST_HIP(hipGetLastError());
+    record_slices_kernel<<<blocks_for(a.slices), dim3(256)>>>(a);
+    CST_HIP(hipGetLastError());
+    record_chunks_kernel<<<blocks_for(rs.n_chunks), dim3(256)>>>(a, rs.n_chunks, q, rs.chunk_slice.p, rs.open1.p,
+                                                                  n == 4 ? rs.open2.p : nullptr);
+    CST_HIP(hipGetLastError());
+    rows_of_slices_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, X->idx[0].p, plan->compact ? 1 : 0, rs.row_of_slice.p);
+    CST_HIP(hipGetLastError());
+    DevBuf<int64_t> flag;
+    DevBuf<int> widest;
+    CST_TRY(flag.alloc(size_t(a.slices)));
+    CST_TRY(widest.alloc(1));
+    CST_HIP(hipMemset(widest.p, 0, sizeof(int)));
+    record_shared_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, rs.slice_rec.p, q, 1, flag.p, widest.p);
+    CST_HIP(hipGetLastError());
+    CST_TRY(list_of_flags(flag, a.slices, rs.light, &rs.n_light));
+    record_shared_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, rs.slice_rec.p, q, 2, flag.p, widest.p);
+    CST_HIP(hipGetLastError());
+    CST_TRY(list_of_flags(flag, a.slices, rs.heavy, &rs.n_heavy));
+    int span = 0;
+    CST_HIP(hipMemcpy(&span, widest.p, sizeof(int), hipMemcpyDeviceToHost));
+    rs.segments = span > kRecOneBlock ? kRecSegments : 1;
+    if (rs.segments > 1) CST_TRY(rs.heavy_partial.alloc(size_t(rs.n_heavy) * kRecSegments * size_t(R)));
+    CST_HIP(hipDeviceSynchronize());
+    return CONSTSTN_OK;
+}
+
+template <int LEVELS>
+static void launch_records_kernel(const RecordArgs &a, hipStream_t stream) {
+    const int lanes = a.R <= 16 ? 8 : 16;
+    const dim3 grid(unsigned(div_up(a.n_chunks, 256 / lanes))), block(256);
+    if (a.R <= 16) records_kernel<8, 1, LEVELS><<<grid, block, 0, stream>>>(a);
+    else if (a.R <= 32) records_kernel<16, 1, LEVELS><<<grid, block, 0, stream>>>(a);
+    else if (a.R <= 64) records_kernel<16, 2, LEVELS><<<grid, block, 0, stream>>>(a);
+    else if (a.R <= 96) records_kernel<16, 3, LEVELS><<<grid, block, 0, stream>>>(a);
+    else records_kernel<16, 4, LEVELS><<<grid, block, 0, stream>>>(a);
+}
+
+conststn_status launch_record_stream(const conststn_plan_s *plan, const double *const *dense, double *out, hipStream_t stream) {
+    const RecordStream &rs = plan->records;
+    const int n = plan->X->order;
+    RecordArgs a{};
+    a.n_chunks = rs.n_chunks;
+    a.q = int(rs.q);
+    a.R = plan->rank_of_level[1];
+    a.slices = int32_t(rs.slices);
+    a.code = rs.code.p;
+    a.vals = rs.vals.p;
+    a.chunk_slice = rs.chunk_slice.p;
+    a.open1 = rs.open1.p;
+    a.open2 = rs.open2.p;
+    a.row_of_slice = rs.row_of_slice.p;
+    a.f0 = dense[plan->factor_of_level[n - 1]];
+    a.f1 = dense[plan->factor_of_level[n - 2]];
+    a.f2 = n == 4 ? dense[plan->factor_of_level[1]] : nullptr;
+    a.out = out;
+    a.partial = rs.partial.p;
+    if (rs.n_chunks > 0) {
+        ProfScope prof(plan, stream);
+        if (rs.levels == 3) launch_records_kernel<3>(a, stream);
+        else launch_records_kernel<2>(a, stream);
+        CST_HIP(hipGetLastError());
+    }
+    RecordFixArgs f{};
+    f.R = a.R;
+    f.q = a.q;
+    f.segments = rs.segments;
+    f.n_heavy = rs.n_heavy;
+    f.n_light = rs.n_light;
+    f.n_empty = rs.n_empty;
+    f.heavy = rs.heavy.p;
+    f.light = rs.light.p;
+    f.empty = rs.empty.p;
+    f.row_of_slice = rs.row_of_slice.p;
+    f.slice_rec = rs.slice_rec.p;
+    f.partial = rs.partial.p;
+    f.heavy_partial = rs.heavy_partial.p;
+    f.out = out;
+    const int W = a.R <= 16 ? 16 : (a.R <= 32 ? 32 : (a.R <= 64 ? 64 : 128));
+    // A heavy slice's sum is a chain of loads as long as its chunks divided by the lane groups of a workgroup: large
+    // workgroups where one does it alone (150 K nonzeros: 16.5 -> 13.7 us for the whole pass), small ones where several
+    // share it and there are many slices (37 us at 76 M nonzeros against 116).
+    const int threads = rs.segments == 1 ? 1024 : 256;
+    f.heavy_blocks = rs.n_heavy * rs.segments;
+    f.light_blocks = div_up(rs.n_light, threads / W);
+    const int64_t blocks = f.heavy_blocks + f.light_blocks + div_up(rs.n_empty, threads / W);
+    if (blocks == 0) return CONSTSTN_OK;
+    const dim3 grid{unsigned(blocks)}, block{unsigned(threads)};
+    auto run = [&](auto Wc) {
+        constexpr int kW = decltype(Wc)::value;
+        if (threads == 1024) records_fixup_kernel<kW, 1024><<<grid, block, 0, stream>>>(f);
+        else records_fixup_kernel<kW, 256><<<grid, block, 0, stream>>>(f);
+    };
+    if (W == 16) run(std::integral_constant<int, 16>{});
+    else if (W == 32) run(std::integral_constant<int, 32>{});
+    else if (W == 64) run(std::integral_constant<int, 64>{});
+    else run(std::integral_constant<int, 128>{});
+    CST_HIP(hipGetLastError());
+    if (rs.segments > 1 && rs.n_heavy > 0) {
+        records_final_kernel<<<dim3(unsigned(rs.n_heavy)), dim3(128), 0, stream>>>(f);
+        CST_HIP(hipGetLastError());
+    }
+    return CONSTSTN_OK;
+}
+
+}  // namespace cst

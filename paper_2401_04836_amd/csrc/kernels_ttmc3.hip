@@ -124,7 +124,6 @@ ttmc3_mfma_kernel(Ttmc3RowArgs a) {
     // U2 rows, which then come from the CU's L1 for all but the first (measured against giving
     // each XCD one column part of U3: 6 % faster on the 2M x 2M x 25000 tensor, where the U2
     // rows, not U3, are the larger stream).
-    const int parts = a.R3 / (16 * QN);
     // one item per workgroup (its `parts` wavefronts): items differ in length, and a slot shared
     // with a longer item would stay idle until that one is done
     const int part = threadIdx.x / 64;

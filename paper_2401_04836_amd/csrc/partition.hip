@@ -140,17 +140,6 @@ __global__ void hot_slots_kernel(int n_hot, const uint32_t *__restrict__ rows_by
     slot_of_row[rows_by_count[h]] = h;
 }
 
-__global__ void encode_leaves_kernel(int64_t nnz, const int32_t *__restrict__ leaf,
-                                     const int32_t *__restrict__ slot_of_row, uint32_t *code) {
-    int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-    for (; n < nnz; n += stride) {
-        const int32_t k = leaf[n];
-        const int32_t sl = slot_of_row[k];
-        code[n] = sl >= 0 ? (0x80000000u | uint32_t(sl)) : uint32_t(k);
-    }
-}
-
 // mark the last leaf of every fiber (bit 30) and of every slice (bit 29)
 __global__ void mark_ends_kernel(int64_t nodes, const int64_t *__restrict__ leaf_end, uint32_t bit,
                                  uint32_t *code) {
@@ -263,7 +252,7 @@ static conststn_status build_part_tables(MttkrpPart &P, int R, int64_t q) {
 }
 
 
-static conststn_status build_mttkrp3_split(conststn_plan_s *plan, const int32_t *slot_of_row) {
+static conststn_status build_mttkrp3_split(conststn_plan_s *plan, const int32_t *slot_of_row, bool asked) {
     const conststn_csf_s *X = plan->X;
     const int64_t nnz = X->nnz, fibers = X->nodes[1], slices = X->nodes[0];
     const int R = plan->rank_of_level[1];
@@ -276,6 +265,8 @@ static conststn_status build_mttkrp3_split(conststn_plan_s *plan, const int32_t 
     int64_t total_hot = 0;
     CST_TRY(exscan(flag.p, pos_hot.p, nnz, &total_hot));
     flag.release();
+    // both teams need work, of about the same size
+    if (total_hot == 0 || total_hot == nnz || (!asked && total_hot < nnz / 5 * 2)) return CONSTSTN_OK;
     for (int part = 0; part < 2; ++part) {
         MttkrpPart &P = plan->part[part];
         P.nnz = part == 0 ? total_hot : nnz - total_hot;
@@ -314,25 +305,17 @@ static conststn_status build_mttkrp3_split(conststn_plan_s *plan, const int32_t 
         CST_HIP(hipDeviceSynchronize());
     }
     plan->split = true;
-    {
-        // hot and cold wavefronts per workgroup of the one-launch form (44 = four and four); 0 = two launches
-        const int64_t dual = plan->opt("mttkrp_dual", 44);
-        if (dual == 44 || dual == 35 || dual == 53 || dual == 88) {
-            plan->mttkrp_dual = int(dual);
-            CST_TRY(plan->mttkrp_out2.alloc(size_t(plan->out_rows * plan->row_elems)));
-        }
-    }
-    return CONSTSTN_OK;
+    const int64_t dual = plan->opt("mttkrp_dual", 44);
+    plan->mttkrp_dual = dual == 35 || dual == 53 || dual == 88 ? int(dual) : 44;
+    return plan->mttkrp_out2.alloc(size_t(plan->out_rows * plan->row_elems));
 }
 
-static conststn_status build_mttkrp3_r32_encoding(conststn_plan_s *plan) {
+// The form for rank 32 with the most referenced leaf rows in LDS; leaves plan->split false where it does not apply.
+static conststn_status build_mttkrp3_hot(conststn_plan_s *plan, bool asked) {
     const conststn_csf_s *X = plan->X;
     const int64_t nnz = X->nnz;
     const int64_t dim = X->dims[X->mode_order[2]];
     plan->n_hot = 0;
-    if (plan->rank_of_level[1] != 32 || dim >= (int64_t(1) << 28) || nnz == 0 ||
-        X->dims[X->mode_order[1]] >= (int64_t(1) << 28))
-        return CONSTSTN_OK;                               // the kernel indexes factor rows with 32 bits
     int64_t want = plan->opt("mttkrp_hot", 256);
     if (want > dim) want = dim;
     want = std::min<int64_t>(want, 608);                 // 608 rows x 256 B = 152 KB of LDS at most
@@ -368,62 +351,33 @@ static conststn_status build_mttkrp3_r32_encoding(conststn_plan_s *plan) {
     hot_slots_kernel<<<dim3(unsigned(div_up(want, 256))), block>>>(int(want), rows_sorted, slot_of_row.p,
                                                                   plan->hot_rows.p);
     CST_HIP(hipGetLastError());
-    CST_TRY(plan->leaf_code.alloc(size_t(nnz)));
-    encode_leaves_kernel<<<dim3(unsigned(std::min<int64_t>(div_up(nnz, 256), 16384))), block>>>(
-        nnz, X->idx[2].p, slot_of_row.p, plan->leaf_code.p);
-    CST_HIP(hipGetLastError());
-    mark_ends_kernel<<<dim3(unsigned(div_up(X->nodes[1], 256))), block>>>(X->nodes[1], X->ptr[1].p, 0x40000000u,
-                                                                        plan->leaf_code.p);
-    mark_ends_kernel<<<dim3(unsigned(div_up(X->nodes[0], 256))), block>>>(X->nodes[0], plan->slice_leaf.p,
-                                                                        0x20000000u, plan->leaf_code.p);
-    CST_HIP(hipGetLastError());
-    CST_HIP(hipDeviceSynchronize());
     plan->n_hot = int(want);
-    if (plan->opt("mttkrp_split", 1) == 1) CST_TRY(build_mttkrp3_split(plan, slot_of_row.p));
-    return CONSTSTN_OK;
+    CST_TRY(build_mttkrp3_split(plan, slot_of_row.p, asked));
+    CST_HIP(hipDeviceSynchronize());
+    return plan->split ? prepare_mttkrp3_launch(plan) : CONSTSTN_OK;
 }
 
+// Which form.  The record stream (kernels_records.hip) takes every rank and size.  Rank 32 on a large tensor
+// whose leaf index follows a power law has another: the hot leaves, their rows in LDS, and the cold ones as two
+// sub-tensors side by side in one launch.  It pays one more factor row per fiber that has leaves of both kinds,
+// so it needs long fibers: 1.15 against 1.23 ms at 76 M nonzeros with 5.9 leaves per fiber, 0.69 against
+// 0.73 ms at 40 M with 4.7, but 0.86 against 0.84 at 40 M with 3.6 and 0.41 against 0.36 at 20 M.  The plan options
+// mttkrp_dual and mttkrp_hot ask for it whatever the size; mttkrp_split=0 or mttkrp_dual=0 for the stream.
 conststn_status build_mttkrp3_tables(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t nnz = X->nnz;
-    const int R = plan->rank_of_level[1];
-    CST_TRY(make_slice_leaf(plan));
-    // chunk length: short enough for >= ~64K independent lane groups, long enough that the
-    // two partial rows per chunk stay a small fraction of the traffic
-    int64_t q = plan->opt("mttkrp_chunk", 0);
-    if (q <= 0) {
-        q = nnz / 262144;
-        q = std::max<int64_t>(64, std::min<int64_t>(q, 512));
+    const bool asked = plan->options.count("mttkrp_dual") || plan->options.count("mttkrp_hot");
+    const bool large = nnz >= (int64_t(1) << 25) && nnz / 9 * 2 >= X->nodes[1];
+    if (plan->rank_of_level[1] == 32 && nnz > 0 && (asked || large) && plan->opt("mttkrp_split", 1) == 1 &&
+        plan->opt("mttkrp_dual", 44) != 0) {
+        // leaves per chunk: at least about 64 K lane groups, two partial rows per chunk a small part of the traffic
+        int64_t q = plan->opt("mttkrp_chunk", 0);
+        if (q <= 0) q = std::max<int64_t>(64, std::min<int64_t>(nnz / 262144, 512));
+        plan->chunk_q = div_up(q, 16) * 16;              // leaves are read 16 at a time
+        CST_TRY(build_mttkrp3_hot(plan, asked));
+        if (plan->split) return CONSTSTN_OK;
     }
-    q = div_up(q, 16) * 16;                      // the rank-32 kernel reads leaves 16 at a time
-    plan->chunk_q = q;
-    plan->n_chunks = div_up(nnz, q);
-    CST_TRY(plan->chunk_fiber.alloc(size_t(plan->n_chunks)));
-    CST_TRY(plan->chunk_slice.alloc(size_t(plan->n_chunks)));
-    CST_TRY(plan->partial.alloc(size_t(plan->n_chunks) * 2 * size_t(R)));
-    if (plan->n_chunks > 0) {
-        mttkrp_chunks_kernel<<<dim3(unsigned(div_up(plan->n_chunks, 256))), dim3(256)>>>(
-            plan->n_chunks, q, X->nodes[0], X->nodes[1], X->ptr[0].p, X->ptr[1].p,
-            plan->chunk_fiber.p, plan->chunk_slice.p);
-        CST_HIP(hipGetLastError());
-    }
-    // slices shared by many chunks: listed for the two-stage fix-up (at most nnz / (span * q))
-    plan->n_heavy = 0;
-    const int64_t max_heavy = nnz / (int64_t(kHeavySpan) * q) + 1;
-    CST_TRY(plan->heavy_slices.alloc(size_t(max_heavy)));
-    DevBuf<int> hcount;
-    CST_TRY(hcount.alloc(1));
-    CST_HIP(hipMemset(hcount.p, 0, sizeof(int)));
-    if (X->nodes[0] > 0) {
-        heavy_slices_kernel<<<dim3(unsigned(div_up(X->nodes[0], 256))), dim3(256)>>>(
-            X->nodes[0], plan->slice_leaf.p, q, kHeavySpan, plan->heavy_slices.p, hcount.p);
-        CST_HIP(hipGetLastError());
-    }
-    CST_HIP(hipMemcpy(&plan->n_heavy, hcount.p, sizeof(int), hipMemcpyDeviceToHost));
-    CST_TRY(plan->heavy_partial.alloc(size_t(plan->n_heavy) * kHeavySegments * size_t(R)));
-    CST_HIP(hipDeviceSynchronize());
-    CST_TRY(build_mttkrp3_r32_encoding(plan));
-    return prepare_mttkrp3_launch(plan);
+    return build_record_stream(plan);
 }
 
 // ---- TTMc: bounded items inside slices ----------------------------------------------------

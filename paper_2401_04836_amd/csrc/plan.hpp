@@ -149,6 +149,23 @@ struct MttkrpPart {
     int n_heavy = 0;
 };
 
+// MTTKRP of order 3 or 4 as one stream of records, each of which reads one factor row (kernels_records.hip)
+struct RecordStream {
+    int levels = 0;                        // kinds of record: 2 (leaf, end of fiber) or 3 (and end of the node above)
+    int64_t n_rec = 0, q = 0, n_chunks = 0, slices = 0;
+    DevBuf<uint32_t> code;                 // [n_chunks * q] kind (2 bits), last of its slice (1), factor row (28)
+    DevBuf<double> vals;                   // [n_chunks * q] value of a leaf
+    DevBuf<int64_t> slice_rec;             // [slices + 1] first record of each slice
+    DevBuf<int32_t> row_of_slice;          // [slices] row of the result
+    DevBuf<uint32_t> chunk_slice;          // [n_chunks] slice of the chunk's first record; bit 31: it began before
+    DevBuf<int32_t> open1, open2;          // [n_chunks] factor row of the fiber / node the chunk leaves open, or -1
+    DevBuf<double> partial;                // [n_chunks x 2 x R]
+    DevBuf<int32_t> heavy, light, empty;   // slices shared by many / by a few chunks; result rows without nonzeros
+    int64_t n_heavy = 0, n_light = 0, n_empty = 0;
+    int segments = 1;                      // workgroups that share a heavy slice
+    DevBuf<double> heavy_partial;          // [n_heavy x segments x R]
+};
+
 }  // namespace cst
 
 struct conststn_plan_s {
@@ -181,25 +198,18 @@ struct conststn_plan_s {
 
     // --- device tables ---
     cst::DevBuf<int64_t> slice_leaf;       // [slices+1] leaf position where each root slice starts
-    // MTTKRP: equal leaf-count chunks
-    int64_t chunk_q = 0, n_chunks = 0;
-    cst::DevBuf<int64_t> chunk_fiber;      // level-1 fiber containing the chunk's first leaf
-    cst::DevBuf<int32_t> chunk_slice;      // root slice containing that fiber
-    // MTTKRP rank-32 path: private re-encoding of the leaf index stream.  Each entry holds the
-    // leaf index, or -- for the most frequently referenced ("hot") factor rows, which the kernel
-    // keeps in LDS -- the LDS slot, plus end-of-fiber / end-of-slice marks.
-    cst::DevBuf<uint32_t> leaf_code;
+    // MTTKRP: the record stream, or for rank 32 the hot and the cold leaves as two sub-tensors.  Each entry of
+    // their streams holds the leaf index or the LDS slot of its row, with end-of-fiber / end-of-slice marks.
+    bool use_records = false;
+    cst::RecordStream records;
+    int64_t chunk_q = 0;                   // leaves per chunk of the sub-tensors
     cst::DevBuf<int32_t> hot_rows;         // [n_hot] leaf index held by each LDS slot
     int n_hot = 0;
     bool split = false;                    // hot and cold leaves run as two sub-tensors
     std::vector<std::unique_ptr<cst::DevBuf<double>>> gen_densified;   // generic executor: dense copies of further CSF operands
-    int mttkrp_dual = 0;                   // 0: two launches; NH * 10 + NC: one launch, NH hot and NC cold wavefronts per workgroup
+    int mttkrp_dual = 44;                  // NH * 10 + NC: NH hot and NC cold wavefronts per workgroup
     cst::DevBuf<double> mttkrp_out2;       // the cold team's output in that form, added to the result afterwards
     cst::MttkrpPart part[2];
-    // slices shared by very many chunks get a two-stage fix-up
-    cst::DevBuf<int32_t> heavy_slices;
-    cst::DevBuf<double> heavy_partial;     // [n_heavy x kHeavySegments x R]
-    int n_heavy = 0;
     // TTMc: items inside slices
     int64_t n_items = 0, n_partials = 0, n_split = 0;
     cst::DevBuf<cst::SliceItem> items;
@@ -306,6 +316,13 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan);
 conststn_status build_sptn3_tables(conststn_plan_s *plan);
 // whether the LDS of the two-wavefront form of the tiled kernel fits a workgroup (nwords = 32-bit words of the j bit mask)
 bool sptn3_two_waves_fit(int nwords);
+
+// kernels_records.hip
+bool record_stream_fits(const conststn_csf_s *X, int R);
+conststn_status build_record_stream(conststn_plan_s *plan);
+conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_code, unsigned bad_chunk, unsigned *flags);
+conststn_status launch_record_stream(const conststn_plan_s *plan, const double *const *dense, double *out,
+                                     hipStream_t stream);
 
 // kernels_*.hip
 conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const *dense, double *out,

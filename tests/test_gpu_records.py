@@ -1,0 +1,70 @@
+"""MTTKRP of order 3 and 4 on the record stream: ranks on both sides of every lane layout (2, 16, 32, 64, 96 and
+128 entries per group), chunks of one block up to the default, slices inside one chunk, shared by a few chunks and
+by many, empty rows, against the CPU references.  Every stream goes through the table check first; a guard behind
+the result shows that the masked stores stay inside it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2401_04836_amd as cst
+from oracle import nary
+from paper_2401_04836_amd import schedules as S
+
+pytestmark = pytest.mark.gpu
+
+T4 = ("T1[i,j,k,r] = X[i,j,k,l] * D[l,r] | i,j,k,l,r ; T2[i,j,r] = T1[i,j,k,r] * C[k,r] | i,j,k,r ; "
+      "M[i,r] = T2[i,j,r] * B[j,r] | i,j,r")
+RANKS = [2, 3, 8, 15, 16, 17, 25, 31, 32, 33, 50, 64, 65, 96, 97, 128]
+
+
+def _tensor(dims, nnz, heavy, seed):
+    """Distinct coordinates, `heavy` of them in the middle slice."""
+    rng = np.random.default_rng(seed)
+    below = int(np.prod(dims[1:]))
+    keys = np.concatenate([rng.integers(0, dims[0] * below, nnz), (dims[0] // 2) * below + rng.integers(0, below, heavy)])
+    keys = rng.permutation(np.unique(keys))
+    return [x.astype(np.int32) for x in np.unravel_index(keys, dims)], rng.uniform(-1, 1, len(keys)), rng
+
+
+def _run(text, c, v, dims, factors, opts, flags=0):
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, list(range(len(dims))))
+    dev = [torch.from_numpy(f).cuda() for _, f in factors]
+    pl = cst.plan(text, [("X", csf)] + [(n, d) for (n, _), d in zip(factors, dev)], flags=flags, options=opts)
+    pl.check()
+    n = pl.n_rows * pl.row_elems
+    buf = torch.full((n + 8,), 7.0, dtype=torch.float64, device="cuda")
+    cst.execute(pl, dev, out=buf[:n])
+    got = buf.cpu().numpy()
+    assert (got[n:] == 7.0).all()
+    return got[:n].reshape(pl.n_rows, -1), pl
+
+
+@pytest.mark.parametrize("rank", RANKS)
+@pytest.mark.parametrize("dims,nnz,heavy,chunk", [((7, 11, 13), 300, 0, 0), ((1, 50, 900), 20_000, 0, 16),
+                                                  ((400, 30, 50), 3000, 1300, 16), ((30, 20, 40_000), 20_000, 60_000, 32)])
+def test_order3(rank, dims, nnz, heavy, chunk):
+    c, v, rng = _tensor(dims, nnz, heavy, 100 + rank)
+    print("[case] order 3 rank %d dims %s nnz %d chunk %d" % (rank, dims, len(v), chunk), flush=True)
+    B, C = rng.uniform(-1, 1, (dims[1], rank)), rng.uniform(-1, 1, (dims[2], rank))
+    want, S_abs = oracle.mttkrp3(c, v, dims, B, C, 0), oracle.mttkrp3_abs(c, v, dims, B, C, 0)
+    for flags in (0, cst.OUT_COMPACT):
+        got, pl = _run(S.MTTKRP3, c, v, dims, [("C", C), ("B", B)], dict(mttkrp_chunk=chunk), flags)
+        rows = pl.output_rows().cpu().numpy() if flags else slice(None)
+        # at most 80 000 products of three factors per sum, in any order: 80 002 roundings of 1.1e-16
+        assert oracle.rel_err(got, want[rows], S_abs[rows]) <= 8.9e-12
+
+
+@pytest.mark.parametrize("rank", RANKS)
+@pytest.mark.parametrize("dims,nnz,heavy,chunk", [((7, 11, 5, 13), 600, 0, 0), ((1, 5, 50, 90), 9000, 0, 16),
+                                                  ((40, 8, 30, 20), 3000, 4000, 16)])
+def test_order4(rank, dims, nnz, heavy, chunk):
+    c, v, rng = _tensor(dims, nnz, heavy, 200 + rank)
+    print("[case] order 4 rank %d dims %s nnz %d chunk %d" % (rank, dims, len(v), chunk), flush=True)
+    B, C, D = (rng.uniform(-1, 1, (d, rank)) for d in dims[1:])
+    got, pl = _run(T4, c, v, dims, [("D", D), ("C", C), ("B", B)], dict(mttkrp_chunk=chunk))
+    assert "kernels=1 inlined_producers=2" in pl.describe()
+    f, ext = [(B, "jr"), (C, "kr"), (D, "lr")], {"i": dims[0], "r": rank}
+    want, S_abs = nary.contract(c, v, "ijkl", f, "ir", ext), nary.contract_abs(c, v, "ijkl", f, "ir", ext)
+    assert oracle.rel_err(got, want, S_abs) <= 1.0e-12       # at most 9000 products of four factors per sum
+
