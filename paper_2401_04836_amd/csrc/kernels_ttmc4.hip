@@ -104,31 +104,41 @@ ttmc4_kernel(Ttmc4Args a) {
     }
 }
 
-// ---- MFMA kernel (all three ranks equal to 16) ----------------------------------------------
+// ---- MFMA kernel (any ranks up to 16) ---------------------------------------------------------
 //
-// Both dense stages run on the fp64 matrix cores (v_mfma_f64_16x16x4, K = 4):
-//   mid level   T2_f (16x16) = sum over the fiber's pieces  U2[k,:]^T . T1      K = four pieces
-//   slice level Y_i (16x256) += U1[J,:]^T . T2                                  K = four fibers
+// Both dense stages run on the fp64 matrix cores:
+//   mid level   T2_f (R2 x R3)     = sum over the fiber's pieces  U2[k,:]^T . T1   K = four pieces
+//   slice level Y_i  (R1 x R2 R3) += U1[J,:]^T . T2                                K = four fibers
 // A piece is at most two leaves of one (i,j,k) node.  The plan stores the pieces of a fiber four
 // at a time in "groups" (the last group of a fiber padded with empty records) and the fibers of
 // a slice four at a time in "K-steps"; a long node or fiber simply gives several pieces or
 // groups, which is legal by distributivity, so the kernel walks ONE flat stream of groups whatever
 // the skew of the tensor.  Per group: lane (s,c) takes record s -- level-2 index, two leaf indices,
-// two leaf values, 32 bytes -- builds T1_s[r3 = c] and supplies U2[k_s, r2 = c]; one
-// matrix instruction adds the group to the fiber's T2 (accumulator layout: register v of lane
+// two leaf values, 32 bytes -- builds T1_s[r3 = c] and supplies U2[k_s, r2 = c]; one 16x16x4
+// instruction adds the group to the fiber's T2 (accumulator layout: register v of lane
 // (s,c) = T2[r2 = s+4v][r3 = c]).  When a group ends its fiber the tile goes to the wave-private
-// LDS buffer; when it ends its K-step, slot s reads back the tile of fiber s as the B operand
-// of the 16 slice-level instructions, A = U1[j_s, c].  The structure (ends a fiber / ends a
-// K-step / starts a K-step, and the four j of a K-step) travels in the records, so nothing
-// but the stream itself is read.  A fiber costs ceil(pieces/4) mid-level instructions and
-// exactly four slice-level ones, however many pieces it has.
+// LDS buffer, flat over (r2,r3); when it ends its K-step, slot s reads back the tile of fiber s.
+// The structure (ends a fiber / ends a K-step / starts a K-step, and the four j of a K-step) travels
+// in the records, so nothing but the stream itself is read.
+// All ranks 16: sixteen 16x16x4 instructions per K-step, A = U1[j_s, c], B = row r2 of the four tiles.
+// Ranks below 16: the slice level runs on the 4x4x4 instruction with four blocks (16 cycles of a SIMD
+// against 64), whose blocks take sixteen flat elements (r2,r3) as rows and the same four r1, held by
+// every block, as columns: only the products that hold results are issued, ceil(R1/4) per sixteen flat
+// elements.  Which flat element is which row is free, as the operand comes out of LDS: lane (s, 4 b + x)
+// reads elements 32 u + 2 (4 x + b) and the next in one 16-byte read.  Operand lanes beyond a rank
+// repeat its last column; what they produce stays in rows and columns that are not stored.
+// (With all ranks 16 the 4x4x4 form issues 64 instructions for 16 and measured slower: 3.9 ms against
+// 3.07 at 40 M nonzeros.)
 // Records are fetched three groups ahead and the factor rows one group ahead (register rings,
 // loop unrolled four times), so a group waits for no load issued in its own iteration.
+// Ranks below 16 against the general kernel: 8 x 8 x 8, 5.3 M nonzeros, 2.26 -> 0.60 ms;
+// 10 x 12 x 7, 5.4 M, 2.96 -> 0.34 ms and 63 K, 345 -> 33 us.
 typedef double v4d __attribute__((ext_vector_type(4)));
-constexpr int kT2Stride = 16 * 16 + 16;        // doubles per tile in LDS (+16: bank skew)
+typedef double v2d __attribute__((ext_vector_type(2)));
 
 struct Ttmc4RowArgs {
     int64_t n_items;
+    int R1, R2, R3;
     const int64_t *kstep_group;
     const PieceDesc *rec;
     const int32_t *idx0;
@@ -140,34 +150,48 @@ struct Ttmc4RowArgs {
 
 // One wavefront per workgroup: items differ in length, and a wavefront slot shared with three
 // others stays idle until the longest of them is done.
+// MU: 32-element parts of a T2 tile the instance has room for; FULL: all ranks 16.
+template <int MU, bool FULL>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8)))
 ttmc4_mfma_kernel(Ttmc4RowArgs a) {
-    __shared__ double t2buf[4 * kT2Stride];
+    constexpr int kStride = MU * 32 + 16;    // doubles per tile in LDS (+16: bank skew)
+    __shared__ __align__(16) double lds[4 * kStride];
     const int lane = threadIdx.x;
     const int slot = lane >> 4, c = lane & 15;
-    double *lds = t2buf;
-    // tiles of absent fibers (a slice's last K-step may hold fewer than four) are multiplied by a
-    // zero A operand: whatever they hold must be finite
-    for (int e = lane; e < 4 * kT2Stride; e += 64) lds[e] = 0.0;
+    const int R1 = FULL ? 16 : a.R1, R2 = FULL ? 16 : a.R2, R3 = FULL ? 16 : a.R3;
+    const int R23 = R2 * R3;
+    const int nu = (R23 + 31) / 32, nq = (R1 + 3) / 4;
+    const int c2 = FULL ? c : min(c, R2 - 1), c3 = FULL ? c : min(c, R3 - 1);
+    // all ranks 16: tiles of absent fibers are multiplied by a zero A operand, so whatever they hold must be finite
+    if (FULL)
+        for (int e = lane; e < 4 * kStride; e += 64) lds[e] = 0.0;
     const int64_t w = int64_t(blockIdx.x);
     const SliceItem it = a.items[w];
     const int32_t s = __builtin_amdgcn_readfirstlane(it.slice);
     const int64_t dest = uni64(it.dest);
     const int64_t ga = uni64(a.kstep_group[it.begin]), gb = uni64(a.kstep_group[it.end]);
 
-    v4d acc[16];
+    v4d y[FULL ? 16 : 1];                    // all ranks 16: y[t][v] = Y[r1 = slot + 4v][r2 = t][r3 = c]
+    double acc[FULL ? 1 : 2 * MU][4];        // below: acc[2 u + e][q] = Y[r1 = 4 q + c % 4][flat = 32 u + 2 (4 slot + c / 4) + e]
 #pragma unroll
-    for (int t = 0; t < 16; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < (FULL ? 16 : 1); ++t) y[t] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < (FULL ? 1 : 2 * MU); ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[t][q] = 0.0;
     v4d t2 = v4d{0.0, 0.0, 0.0, 0.0};
-    double av = 0.0;                         // U1[j_s, c] of the current K-step
+    double uq[FULL ? 1 : 4];                 // U1[j_s, c], or U1[j_s, 4 q + c % 4], of the current K-step
+#pragma unroll
+    for (int q = 0; q < (FULL ? 1 : 4); ++q) uq[q] = 0.0;
+    bool here = true;                        // the current K-step has a fiber s
     int ft = 0;                              // fibers of the current K-step already parked in LDS
 
     // A group's four records are 128 bytes.  Lane (s, c) fetches dword c mod 8 of record s -- one
     // 4-byte load per lane for the whole group instead of two 16-byte ones -- and the eight
     // dwords of a record are handed round inside the 16-lane row when they are needed.
-    constexpr int kRec = 4;                  // record ring (fetched kRec - 1 groups ahead)
+    constexpr int kRec = 4, kRow = 2;        // record and row rings: fetched kRec - 1 and kRow - 1 groups ahead
     uint32_t raw[kRec];
-    double gu2[2], gx0[2], gx1[2];           // factor-row ring (fetched one group ahead)
+    double gu2[kRow], gx0[kRow], gx1[kRow];
     const uint32_t *words = reinterpret_cast<const uint32_t *>(a.rec);
     auto load_rec = [&](int64_t g) -> uint32_t {
         return words[((g < gb ? g : gb - 1) * 4 + slot) * 8 + (c & 7)];
@@ -193,32 +217,67 @@ ttmc4_mfma_kernel(Ttmc4RowArgs a) {
         const int32_t k = int32_t(uint32_t(kf) & kGrpIndexMask);
         // 32-bit byte offsets against the scalar bases of the factors (their extents stay below 2^25 on
         // this path): one vector instruction per address
-        u2 = *reinterpret_cast<const double *>(U2b + (uint32_t(k * 16 + c) << 3));
-        x0 = *reinterpret_cast<const double *>(U3b + (uint32_t(l0 * 16 + c) << 3));
-        x1 = *reinterpret_cast<const double *>(U3b + (uint32_t(l1 * 16 + c) << 3));
+        u2 = *reinterpret_cast<const double *>(U2b + (uint32_t(k * R2 + c2) << 3));
+        x0 = *reinterpret_cast<const double *>(U3b + (uint32_t(l0 * R3 + c3) << 3));
+        x1 = *reinterpret_cast<const double *>(U3b + (uint32_t(l1 * R3 + c3) << 3));
     };
     auto consume = [&](uint32_t x, double u2, double x0, double x1) {
         const int32_t kf = field(x, W0{});
         const uint32_t flags = uint32_t(__builtin_amdgcn_readfirstlane(kf));            // same on the four records
         if (flags & kGrpStartsKstep) {
-            const int32_t j = field(x, W3{});
-            av = j >= 0 ? *reinterpret_cast<const double *>(U1b + (uint32_t(j * 16 + c) << 3)) : 0.0;
+            const int32_t j = field(x, W3{});                                           // -1: no such fiber
+            if constexpr (FULL) {
+                uq[0] = j >= 0 ? *reinterpret_cast<const double *>(U1b + (uint32_t(j * 16 + c) << 3)) : 0.0;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    uq[q] = *reinterpret_cast<const double *>(U1b + (uint32_t(max(j, 0) * R1 + min(4 * q + (c & 3), R1 - 1)) << 3));
+                here = j >= 0;
+            }
         }
-        // empty records and absent second leaves carry value 0
-        const double t1 = fma(field64(x, W6{}, W7{}), x1, field64(x, W4{}, W5{}) * x0);
+        double t1;
+        if (FULL) {
+            t1 = fma(field64(x, W6{}, W7{}), x1, field64(x, W4{}, W5{}) * x0);         // what is absent carries value 0
+        } else {
+            // absent leaves name a row with value 0: left out, so that a row that is not finite reaches no other result
+            t1 = field64(x, W4{}, W5{}) * x0;
+            t1 = uint32_t(kf) & kRecOneLeaf ? t1 : fma(field64(x, W6{}, W7{}), x1, t1);
+            t1 = uint32_t(kf) & kRecEmpty ? 0.0 : t1;
+            u2 = uint32_t(kf) & kRecEmpty ? 0.0 : u2;
+        }
         t2 = __builtin_amdgcn_mfma_f64_16x16x4f64(u2, t1, t2, 0, 0, 0);
         if (flags & kGrpEndsFiber) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) lds[ft * kT2Stride + (slot + 4 * v) * 16 + c] = t2[v];
+            for (int v = 0; v < 4; ++v)
+                if (FULL || (slot + 4 * v < R2 && c < R3)) lds[ft * kStride + (slot + 4 * v) * R3 + c] = t2[v];
             t2 = v4d{0.0, 0.0, 0.0, 0.0};
             ++ft;
             if (flags & kGrpEndsKstep) {
-                // slot s supplies fiber s; fibers the K-step lacks have av = 0
-                const double a_op = slot < ft ? av : 0.0;
+                if constexpr (FULL) {        // slot s supplies fiber s; fibers the K-step lacks are multiplied by 0
+                    const double a_op = slot < ft ? uq[0] : 0.0;
 #pragma unroll
-                for (int t = 0; t < 16; ++t) {
-                    const double bv = lds[slot * kT2Stride + t * 16 + c];
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_op, bv, acc[t], 0, 0, 0);
+                    for (int t = 0; t < 16; ++t)
+                        y[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_op, lds[slot * kStride + t * 16 + c], y[t], 0, 0, 0);
+                } else {
+                    if (ft < 4) {            // fibers the K-step lacks: both operands are made 0
+                        for (int e = ft * kStride + lane; e < 4 * kStride; e += 64) lds[e] = 0.0;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) uq[q] = here ? uq[q] : 0.0;
+                    }
+                    const double *tile = lds + slot * kStride + 2 * (4 * (c & 3) + (c >> 2));
+#pragma unroll
+                    for (int u = 0; u < MU; ++u) {
+                        if (u < nu) {
+                            const v2d b = *reinterpret_cast<const v2d *>(tile + 32 * u);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                if (q < nq) {
+                                    acc[2 * u][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(b.x, uq[q], acc[2 * u][q], 0, 0, 0);
+                                    acc[2 * u + 1][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(b.y, uq[q], acc[2 * u + 1][q], 0, 0, 0);
+                                }
+                            }
+                        }
+                    }
                 }
                 ft = 0;
             }
@@ -226,24 +285,37 @@ ttmc4_mfma_kernel(Ttmc4RowArgs a) {
     };
 #pragma unroll
     for (int u = 0; u < kRec - 1; ++u) raw[u] = load_rec(ga + u);
-    load_rows(raw[0], gu2[0], gx0[0], gx1[0]);
+#pragma unroll
+    for (int u = 0; u < kRow - 1; ++u) load_rows(raw[u], gu2[u], gx0[u], gx1[u]);
     for (int64_t g0 = ga; g0 < gb; g0 += kRec) {
 #pragma unroll
         for (int u = 0; u < kRec; ++u) {
             const int64_t g = g0 + u;
             raw[(u + kRec - 1) % kRec] = load_rec(g + kRec - 1);
-            load_rows(raw[(u + 1) % kRec], gu2[(u + 1) % 2], gx0[(u + 1) % 2], gx1[(u + 1) % 2]);
-            if (g < gb) consume(raw[u], gu2[u % 2], gx0[u % 2], gx1[u % 2]);
+            load_rows(raw[(u + kRow - 1) % kRec], gu2[(u + kRow - 1) % kRow], gx0[(u + kRow - 1) % kRow], gx1[(u + kRow - 1) % kRow]);
+            if (g < gb) consume(raw[u], gu2[u % kRow], gx0[u % kRow], gx1[u % kRow]);
         }
     }
-    const int64_t RR = 4096;
+    const int64_t RR = int64_t(R1) * R23;
     double *base = dest < 0 ? a.out + (a.compact ? int64_t(s) : int64_t(a.idx0[s])) * RR
                             : a.partial + dest * RR;
-    // acc[t][v] = Y[r1 = slot + 4v][r2 = t][r3 = c]
+    if constexpr (FULL) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+        for (int t = 0; t < 16; ++t)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) base[((slot + 4 * v) * 16 + t) * 16 + c] = acc[t][v];
+            for (int v = 0; v < 4; ++v) base[((slot + 4 * v) * 16 + t) * 16 + c] = y[t][v];
+    } else {
+#pragma unroll
+        for (int u = 0; u < MU; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int flat = 32 * u + 2 * (4 * slot + (c >> 2)), r1 = 4 * q + (c & 3);
+                if (r1 < R1) {
+                    if (flat < R23) base[r1 * R23 + flat] = acc[2 * u][q];
+                    if (flat + 1 < R23) base[r1 * R23 + flat + 1] = acc[2 * u + 1][q];
+                }
+            }
+    }
 }
 
 conststn_status launch_ttmc4(const conststn_plan_s *plan, const double *const *dense, double *out,
@@ -280,6 +352,9 @@ conststn_status launch_ttmc4(const conststn_plan_s *plan, const double *const *d
         if (plan->use_rows) {
             Ttmc4RowArgs ra{};
             ra.n_items = plan->n_items;
+            ra.R1 = a.R1;
+            ra.R2 = a.R2;
+            ra.R3 = a.R3;
             ra.kstep_group = plan->kstep_group.p;
             ra.rec = plan->pieces.p;
             ra.idx0 = a.idx0;
@@ -290,7 +365,12 @@ conststn_status launch_ttmc4(const conststn_plan_s *plan, const double *const *d
             ra.out = out;
             ra.partial = a.partial;
             ra.compact = a.compact;
-            ttmc4_mfma_kernel<<<dim3(unsigned(a.n_items)), dim3(64), 0, stream>>>(ra);
+            const dim3 grid{unsigned(a.n_items)}, block(64);
+            const int parts = (a.R2 * a.R3 + 31) / 32;
+            if (a.R1 == 16 && a.R2 == 16 && a.R3 == 16) ttmc4_mfma_kernel<8, true><<<grid, block, 0, stream>>>(ra);
+            else if (parts > 4) ttmc4_mfma_kernel<8, false><<<grid, block, 0, stream>>>(ra);
+            else if (parts > 2) ttmc4_mfma_kernel<4, false><<<grid, block, 0, stream>>>(ra);
+            else ttmc4_mfma_kernel<2, false><<<grid, block, 0, stream>>>(ra);
         } else
             ttmc4_kernel<<<dim3(unsigned(div_up(a.n_items, 4))), dim3(256), 0, stream>>>(a);
     }

@@ -660,14 +660,15 @@ __global__ void fill_groups_kernel(int64_t fibers, int64_t slices, const int64_t
     for (int64_t n = ptr1[f]; n < ptr1[f + 1]; ++n) {
         const int64_t end = ptr2[n + 1];
         for (int64_t e = ptr2[n]; e < end; e += kPieceLeaves)
-            put(idx2[n], idx3[e], e + 1 < end ? idx3[e + 1] : idx3[e], vals[e], e + 1 < end ? vals[e + 1] : 0.0);
+            put(int32_t(uint32_t(idx2[n]) | (e + 1 < end ? 0u : kRecOneLeaf)), idx3[e], e + 1 < end ? idx3[e + 1] : idx3[e],
+                vals[e], e + 1 < end ? vals[e + 1] : 0.0);
     }
     // Empty records, and the absent second leaf above, name rows the fiber uses anyway and carry the
     // value 0: the kernel then needs no test for them, and a factor row that is not finite spoils only
     // results it belongs to.
     {
         const int64_t n0 = ptr1[f], e0 = ptr2[n0];
-        while ((r - r0) & 3) put(idx2[n0], idx3[e0], idx3[e0], 0.0, 0.0);
+        while ((r - r0) & 3) put(int32_t(uint32_t(idx2[n0]) | kRecEmpty), idx3[e0], idx3[e0], 0.0, 0.0);
     }
     // structure flags on every record of a group; level-1 indices on the first group of a K-step
     const int64_t groups = (r - r0) >> 2;
@@ -687,7 +688,7 @@ static conststn_status build_piece_groups(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t slices = X->nodes[0], fibers = X->nodes[1], nodes = X->nodes[2];
     const int64_t K = X->dims[X->mode_order[2]];
-    if (K >= (int64_t(1) << 28)) { set_error("level-2 extent of 2^28 or more"); return CONSTSTN_EUNSUPPORTED; }
+    if (K > int64_t(kGrpIndexMask)) { set_error("level-2 extent of 2^26 or more"); return CONSTSTN_EUNSUPPORTED; }
     const dim3 block(256);
     DevBuf<int64_t> cnt, piece_off, groups_of, grp_off, ksteps_of;
     CST_TRY(cnt.alloc(nodes));
@@ -930,14 +931,16 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
     const bool small_extents = order != 4 || (X4->dims[X4->mode_order[1]] < (int64_t(1) << 25) &&
                                               X4->dims[X4->mode_order[2]] < (int64_t(1) << 25) &&
                                               X4->dims[X4->mode_order[3]] < (int64_t(1) << 25));
-    if (order == 4 && plan->rank_of_level[1] == 16 && plan->rank_of_level[2] == 16 && small_extents &&
-        plan->rank_of_level[3] == 16 && plan->opt("ttmc4_mfma", 1) == 1) {
+    if (order == 4 && plan->rank_of_level[1] <= 16 && plan->rank_of_level[2] <= 16 && small_extents &&
+        plan->rank_of_level[3] <= 16 && plan->opt("ttmc4_mfma", 1) == 1) {
         plan->use_rows = true;
         CST_TRY(build_piece_groups(plan));
         unit_ptr = plan->slice_row.p;                 // items are ranges of K-steps (four fibers each)
-        // (with the items ordered by cost their length matters little: 2.95 ms per launch on the 40 M-nonzero
-        // tensor for 64 to 128 K-steps per item, and the fewer partial row blocks the shorter the fix-up pass)
-        split = plan->opt("ttmc4_ksplit", std::min<int64_t>(std::max<int64_t>(plan->n_rows_tab / 8192, 64), 128));
+        // Short items fill the chip and end together, long ones leave fewer partial row blocks to the fix-up
+        // pass.  Best of 8 to 256 K-steps per item: 8 at 15 K K-steps in all (33 us; 64: 118), 24 at 0.1 M (84 us;
+        // 64: 150), 24 to 32 at 0.5 M (343 us; 64: 391), 128 at 2.4 M (3.1 ms; 32: 3.8).
+        const int64_t n = plan->n_rows_tab;
+        split = plan->opt("ttmc4_ksplit", std::min<int64_t>(std::max<int64_t>({int64_t(8), std::min<int64_t>(n / 4096, 32), n / 16384}), 128));
     }
     CST_TRY(build_items_core(slices, unit_ptr, split, 0, order, X->ptr[0].p, X->ptr[1].p, plan->row_elems,
                              plan->items, plan->n_items, plan->n_partials, plan->n_split, plan->split_slices,
