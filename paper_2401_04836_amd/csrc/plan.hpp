@@ -128,7 +128,9 @@ struct alignas(32) PieceDesc {
 static_assert(kPieceLeaves == 2, "PieceDesc holds two leaves");
 // structure flags carried in PieceDesc::k (the same on the four records of a group)
 constexpr uint32_t kGrpEndsFiber = 1u << 28, kGrpEndsKstep = 1u << 29, kGrpStartsKstep = 1u << 30,
-                   kGrpIndexMask = (1u << 28) - 1u;
+                   kGrpIndexMask = (1u << 26) - 1u;
+// flags of one record: it pads its group, or its second leaf is absent
+constexpr uint32_t kRecEmpty = 1u << 26, kRecOneLeaf = 1u << 27;
 
 // One of the two sub-tensors of the split rank-32 MTTKRP path: the leaves whose factor row is
 // "hot" (kept in LDS) or the rest.  X = X_hot + X_cold and the contraction is linear in X, so each
