@@ -113,6 +113,8 @@ struct Sptn3TileArgs {
     const double *uvals;
     const int64_t *w_root_of_k;
     const uint32_t *wmask, *wfirst;
+    const int32_t *wcell_ptr;              // cells of a root of W, see SpCell
+    const SpCell *wcells;
     const double *wtiles;
     uint32_t zero_tile;
     const double *V;
@@ -447,20 +449,35 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 
 // ---- tiled kernel with two wavefronts per SIMD ------------------------------------------------
 // The kernel above keeps Z^t for all m tiles of its l tiles in 200 accumulator registers, which
-// leaves room for one wavefront per SIMD; fp64 matrix instructions then issue at two thirds of
-// the rate two wavefronts reach, and every vector instruction in between costs three times as
-// much.  Here a workgroup has eight wavefronts (two per SIMD).  The producer is unchanged: in a
-// *round* wavefront w computes T^t of l tile 8 r + w.  The consumer is split by m instead of by
+// leaves room for one wavefront per SIMD and puts the accumulators into the upper half of the register
+// file, where an fp64 matrix instruction takes 105 cycles instead of 64.  Here a workgroup has eight
+// wavefronts (two per SIMD).  Only the blocks of sixteen l below which W holds anything under the k at
+// hand are taken (a list made with the plan): T is read nowhere else.  Eight of them make a *round*, in
+// which wavefront w computes T^t of the w-th as above.  The consumer is split by m instead of by
 // l: wavefront w owns the m tiles w, w + 8, w + 16, w + 24 (four accumulator tiles, kept in
 // registers across all k of the workgroup), the eight T^t of a round go through LDS, and after
 // a barrier every wavefront multiplies its own W tiles of all eight l tiles.  The W tiles of a
-// round are fetched by the eight wavefronts in turn, one per producer batch, and parked in a pool
-// of LDS slots shared by the workgroup (slot = rank of the tile among the round's tiles); what
-// does not fit, or exceeds eight tiles per batch, is fetched when it is used.
+// round, which follow one another in memory, are fetched by the eight wavefronts in turn, one per
+// producer batch, and parked in a pool of LDS slots shared by the workgroup (slot = rank of the tile
+// among the round's tiles); what does not fit, or exceeds eight tiles per batch, is fetched when it is used.
+// 2000 x 2000 x 400 with blocks of 100 x 100 x 20, 12 % of the blocks of l empty: 26.8 ms with every block
+// taken and the tiles found by ballots and reads across lanes, 24.1 with the list, 23.4 with the places
+// below.  Of these 23.4 (switched off in a copy): W's fetches and parking 3.4, consumer 5.0, everything but the
+// loop over batches 2.2, V's addresses made one cache line 0.8; the producer alone 11.8, of which 6.4 are the
+// matrix instructions at 64 cycles each.  A ring of three batches takes as long as two.
 constexpr int kOwnWaves = 8;
 constexpr int kRingO = 2;                                             // batches in flight in this kernel
 constexpr int kOwnZ = (kSpMaxMTiles + kOwnWaves - 1) / kOwnWaves;       // accumulator tiles per wavefront
 constexpr int kPool = 48;                                             // W tiles parked per round
+
+// Workgroup -> place in the list of pairs.  Pairs of equal cost stand in the order (k chunk, group), and
+// neighbouring groups read the same W tiles and largely the same rows of V: of every 64 places XCD x takes the
+// eight from 8 x on, instead of every eighth (24.1 -> 23.4 ms; runs of 4: 23.4, of 16: 24.1).
+constexpr int kSpRun = 8;
+__device__ inline int sp_place(int b, int n) {
+    const int base = b / (8 * kSpRun) * (8 * kSpRun), r = b - base;
+    return base + 8 * kSpRun <= n ? base + (r & 7) * kSpRun + (r >> 3) : b;
+}
 
 struct SpPipeO {
     double Vr[kRingO][kBatch], Ur[kRingO][kBatch];
@@ -485,14 +502,13 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     const int n_wg = a.n_groups * a.n_kc, per_xcd = (n_wg + 7) / 8;
     if (int(blockIdx.x) >= n_wg && !a.xcd_ranges) return;
     const int logical = a.xcd_ranges ? (int(blockIdx.x) % 8) * per_xcd + int(blockIdx.x) / 8
-                                     : (a.wg_order ? a.wg_order[blockIdx.x] : int(blockIdx.x));
+                                     : (a.wg_order ? a.wg_order[sp_place(int(blockIdx.x), n_wg)] : int(blockIdx.x));
     if (logical >= n_wg) return;
     const int group = logical % a.n_groups, kc = logical / a.n_groups;
     const int64_t s0 = int64_t(group) * kSpGroup;
     const int64_t k_lo = int64_t(kc) * a.k_per, k_hi = k_lo + a.k_per;
     const int64_t L = a.L;
     const int L32 = int(a.L);
-    const int LT = int(a.LT);
     const char *Vbytes = reinterpret_cast<const char *>(a.V);
     const uint32_t lane16 = uint32_t(lane) * 16u;
     const int nwords = a.nwords;
@@ -514,7 +530,6 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     v4d accZ[kOwnZ];
 #pragma unroll
     for (int x = 0; x < kOwnZ; ++x) accZ[x] = v4d{0.0, 0.0, 0.0, 0.0};
-    const int rounds = (LT + kOwnWaves - 1) / kOwnWaves;
 
     for (;;) {
         const int32_t kk = cur < end ? a.uidx1[cur] : INT32_MAX;
@@ -621,25 +636,26 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
         if (n_union > 0) prepare(0, np, npad, std::true_type{});
         while (p0 < n_union) {
             const int nBt = npad / (4 * kBatch);                          // batches per l tile
+            // the l tiles below which W holds anything under this k, and how many rounds of eight they make
+            const int cell0 = __builtin_amdgcn_readfirstlane(a.wcell_ptr[root]);
+            const int cells = __builtin_amdgcn_readfirstlane(a.wcell_ptr[root + 1]) - cell0;
+            const int rounds = (cells + kOwnWaves - 1) / kOwnWaves;
             for (int r0 = 0; r0 < rounds; r0 += 8) {                      // 8 rounds = 64 l tiles: one mask per lane
                 const int NR = min(8, rounds - r0);
-                uint32_t mreg = 0u, freg = a.zero_tile;
-                if (8 * r0 + lane < LT) {
-                    const int64_t cell = root * a.LT + (8 * r0 + lane);
-                    mreg = a.wmask[cell];
-                    freg = mreg ? a.wfirst[cell] : a.zero_tile;
+                uint32_t mreg = 0u, freg = 0u;
+                int lreg = 0;                                             // absent cells: mask 0, any l tile
+                if (8 * r0 + lane < cells) {
+                    const SpCell cell = a.wcells[cell0 + 8 * r0 + lane];
+                    mreg = cell.mask;
+                    freg = cell.first;
+                    lreg = cell.l_tile;
                 }
-                // tiles of the lane's round before the lane's l tile (rounds are groups of 8 lanes)
-                int preg;
-                {
-                    const int pc = __popc(mreg);
-                    int incl = pc;
+                // W tiles of the lane's round up to and with the lane's l tile (rounds are groups of 8 lanes)
+                int ireg = __popc(mreg);
 #pragma unroll
-                    for (int d = 1; d < 8; d <<= 1) {
-                        const int up = __shfl_up(incl, d, 8);
-                        if ((lane & 7) >= d) incl += up;
-                    }
-                    preg = incl - pc;
+                for (int d = 1; d < 8; d <<= 1) {
+                    const int up = __shfl_up(ireg, d, 8);
+                    if ((lane & 7) >= d) ireg += up;
                 }
                 const int TB = NR * nBt;
                 SpPipeO P;
@@ -647,36 +663,36 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                 int t0 = 0, q0 = 0;                                       // batch being consumed: (round, batch in it)
                 int t2 = 0, q2 = 0;                                       // batch whose V/U/W loads are issued
                 int q3 = 0;                                               // batch whose j offsets are read
-                // The W tiles of round t2, in the order (l tile, m tile), are fetched by the eight wavefronts
-                // in turn: tile n by wavefront n % 8 with its batch n / 8, into pool slot n.
-
+                // The W tiles of round t2, in the order (l tile, m tile), follow one another in memory.  They are
+                // fetched by the eight wavefronts in turn: tile n by wavefront n % 8 with its batch n / 8, into
+                // pool slot n.
+                int col2 = 0, parked2 = 0;                                // of round t2: this lane's column of V, tiles to park
+                uint32_t first2 = 0u;                                     // ... and its first W tile
+                auto start_round = [&]() {
+                    const int tt = min(t2, NR - 1);
+                    col2 = min(16 * __builtin_amdgcn_readlane(lreg, 8 * tt + wave) + c, L32 - 1);
+                    first2 = __builtin_amdgcn_readlane(freg, 8 * tt);
+                    parked2 = t2 < NR ? min(__builtin_amdgcn_readlane(ireg, 8 * tt + 7), kPool) : 0;
+                };
                 auto read_j = [&](int32_t (&J)[kBatch]) {
 #pragma unroll
                     for (int ks = 0; ks < kBatch; ++ks) J[ks] = jl[q3 * (4 * kBatch) + ks * 4 + slot];
                     q3 = q3 + 1 == nBt ? 0 : q3 + 1;
                 };
                 auto issue = [&](const int32_t (&J)[kBatch], double (&Vv)[kBatch], double (&Uu)[kBatch], v2d (&Ww)[2], int &S) {
-                    const int tt = min(t2, NR - 1);
-                    const int col = min(16 * (8 * (r0 + tt) + wave) + c, L32 - 1);
 #pragma unroll
                     for (int ks = 0; ks < kBatch; ++ks) {
-                        Vv[ks] = *reinterpret_cast<const double *>(Vbytes + (uint32_t(J[ks] + col) << 3));
+                        Vv[ks] = *reinterpret_cast<const double *>(Vbytes + (uint32_t(J[ks] + col2) << 3));
                         Uu[ks] = Uc[q2 * (64 * kBatch) + ks * 64 + lane];
                     }
-                    // W tile n = wave + 8 q2 of round t2, found without a loop or a branch: the l tile it
-                    // lies under is the last lane of the round's group whose prefix does not exceed n
                     const int n = wave + kOwnWaves * q2;
-                    const uint64_t below = __ballot((lane >> 3) == tt && n >= preg);
-                    const int ln = 8 * tt + __popcll(below) - 1;          // the group's first lane always counts
-                    const uint32_t full = __builtin_amdgcn_readlane(mreg, ln);
-                    const int base = __builtin_amdgcn_readlane(preg, ln);
-                    const bool ok = t2 < NR && n < base + __popc(full) && n < kPool;
-                    const uint32_t tile = ok ? __builtin_amdgcn_readlane(freg, ln) + uint32_t(n - base) : a.zero_tile;
+                    const bool ok = n < parked2;
+                    const uint32_t tile = ok ? first2 + uint32_t(n) : a.zero_tile;
                     S = ok ? n : -1;
                     const char *tb = reinterpret_cast<const char *>(a.wtiles + int64_t(tile) * 256);
                     Ww[0] = *reinterpret_cast<const v2d *>(tb + lane16);     // unconditional (the all-zero tile when there
                     Ww[1] = *reinterpret_cast<const v2d *>(tb + lane16 + 1024);  // is none): skipping the fetch measured slower
-                    if (q2 + 1 == nBt) { q2 = 0; ++t2; } else ++q2;
+                    if (q2 + 1 == nBt) { q2 = 0; ++t2; start_round(); } else ++q2;
                 };
                 auto consume = [&](int b, const double (&Vv)[kBatch], const double (&Uu)[kBatch], const v2d (&Ww)[2], int S) {
                     if (b < TB) {
@@ -699,14 +715,14 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                             // ... and every wavefront multiplies the W tiles of its m tiles with the eight T^t,
                             // even and odd l tiles into two accumulators (two independent instruction chains)
                             uint32_t fm[8], any = 0u;
-                            int pre[8], seen = 0;
+                            int pre[8];
 #pragma unroll
                             for (int t = 0; t < 8; ++t) {
                                 fm[t] = __builtin_amdgcn_readlane(mreg, 8 * t0 + t);
-                                pre[t] = seen;
-                                seen += __popc(fm[t]);
+                                pre[t] = t ? int(__builtin_amdgcn_readlane(ireg, 8 * t0 + t - 1)) : 0;
                                 any |= fm[t];
                             }
+                            const int seen = __builtin_amdgcn_readlane(ireg, 8 * t0 + 7);
                             // Parked tiles first, in a loop without global loads (a load that may or may not
                             // have been issued makes the compiler wait for every load in flight, the
                             // pipeline's included); the tiles that were not parked follow in a loop of their own.
@@ -730,7 +746,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                                                     w0 = rp[0];
                                                     w1 = rp[64];
                                                 } else {
-                                                    const uint32_t tile = __builtin_amdgcn_readlane(freg, 8 * t0 + t) + uint32_t(r);
+                                                    const uint32_t tile = __builtin_amdgcn_readlane(freg, 8 * t0) + uint32_t(n);
                                                     const char *tb = reinterpret_cast<const char *>(a.wtiles + int64_t(tile) * 256);
                                                     w0 = *reinterpret_cast<const v2d *>(tb + lane16);
                                                     w1 = *reinterpret_cast<const v2d *>(tb + lane16 + 1024);
@@ -763,6 +779,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                 };
 
                 if (TB > 0) {
+                    start_round();
 #pragma unroll
                     for (int u = 0; u < kRingO; ++u) read_j(P.Jr[u]);
 #pragma unroll
@@ -846,6 +863,8 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     a.w_root_of_k = plan->w_root_of_k.p;
     a.wmask = plan->w_tile_mask.p;
     a.wfirst = plan->w_tile_first.p;
+    a.wcell_ptr = plan->w_cell_ptr.p;
+    a.wcells = plan->w_cells.p;
     a.wtiles = plan->w_tiles.p;
     a.zero_tile = uint32_t(plan->n_w_tiles);
     a.V = dense[0];

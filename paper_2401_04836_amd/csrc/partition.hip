@@ -1075,6 +1075,20 @@ static conststn_status build_sp_wg_order(conststn_plan_s *plan) {
     return CONSTSTN_OK;
 }
 
+__global__ void w_cell_flag_kernel(int64_t n, const uint32_t *__restrict__ mask, int64_t *flag) {
+    const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (x < n) flag[x] = mask[x] ? 1 : 0;
+}
+
+__global__ void w_cell_fill_kernel(int64_t n, int64_t LT, const uint32_t *__restrict__ mask, const int64_t *__restrict__ first,
+                                   const int64_t *__restrict__ place, int64_t total, int32_t *cell_ptr, SpCell *cells) {
+    const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (x >= n) return;
+    if (x == 0) cell_ptr[n / LT] = int32_t(total);
+    if (x % LT == 0) cell_ptr[x / LT] = int32_t(place[x]);
+    if (mask[x]) cells[place[x]] = SpCell{int32_t(x % LT), mask[x], uint32_t(first[x])};
+}
+
 static conststn_status build_w_tiles(conststn_plan_s *plan) {
     const conststn_csf_s *U = plan->X, *W = plan->W;
     const int64_t J = U->dims[U->mode_order[2]];
@@ -1120,6 +1134,17 @@ static conststn_status build_w_tiles(conststn_plan_s *plan) {
     CST_HIP(hipGetLastError());
     CST_TRY(plan->w_tile_first.alloc(size_t(cells)));
     w_first_u32_kernel<<<cgrid, block>>>(cells, first.p, plan->w_tile_first.p);
+    CST_HIP(hipGetLastError());
+    // (every cell of the list holds a tile, so their number stays below 2^31 too)
+    int64_t n_cells = 0;
+    w_cell_flag_kernel<<<cgrid, block>>>(cells, plan->w_tile_mask.p, cnt.p);
+    CST_HIP(hipGetLastError());
+    DevBuf<int64_t> place;
+    CST_TRY(place.alloc(size_t(cells)));
+    CST_TRY(exscan(cnt.p, place.p, cells, &n_cells));
+    CST_TRY(plan->w_cells.alloc(size_t(n_cells)));
+    CST_TRY(plan->w_cell_ptr.alloc(size_t(roots) + 1));
+    w_cell_fill_kernel<<<cgrid, block>>>(cells, LT, plan->w_tile_mask.p, first.p, place.p, n_cells, plan->w_cell_ptr.p, plan->w_cells.p);
     CST_HIP(hipGetLastError());
     // slices go in groups of 16; the k range is cut into chunks so that the grid fills the chip
     const int64_t groups = div_up(U->nodes[0], kSpGroup);

@@ -132,6 +132,13 @@ constexpr uint32_t kGrpEndsFiber = 1u << 28, kGrpEndsKstep = 1u << 29, kGrpStart
 // flags of one record: it pads its group, or its second leaf is absent
 constexpr uint32_t kRecEmpty = 1u << 26, kRecOneLeaf = 1u << 27;
 
+// A block of sixteen l under one root of W that holds something: its place, the m tiles present, and the first of
+// them among the dense tiles (those of a root follow one another).
+struct SpCell {
+    int32_t l_tile;
+    uint32_t mask, first;
+};
+
 // One of the two sub-tensors of the split rank-32 MTTKRP path: the leaves whose factor row is
 // "hot" (kept in LDS) or the rest.  X = X_hot + X_cold and the contraction is linear in X, so each
 // part is a CSF tensor of its own (only the slices and fibers that keep a leaf) with its own
@@ -246,6 +253,8 @@ struct conststn_plan_s {
     int64_t n_w_tiles = 0;
     cst::DevBuf<uint32_t> w_tile_mask;     // [roots x ceil(L/16)] m tiles present
     cst::DevBuf<uint32_t> w_tile_first;    // [roots x ceil(L/16)] index of the first of them
+    cst::DevBuf<cst::SpCell> w_cells;      // the cells with a tile, root after root
+    cst::DevBuf<int32_t> w_cell_ptr;       // [roots + 1] first of them of each root
     cst::DevBuf<double> w_tiles;           // [(tiles + 1) x 256], the last one all zero
     bool sp_xcd_ranges = false;            // contiguous workgroup ranges per XCD
     cst::DevBuf<int32_t> sp_wg_order;      // [groups x k chunks] pairs by falling number of U leaves, or empty
