@@ -4,8 +4,8 @@
 //   1. pack each coordinate tuple, permuted into level order, into one 64-bit key (outermost
 //      level in the most significant bits) and check ranges; tuples that need 65 to 128 bits get a
 //      second, more significant word holding the outer levels (no level straddles the two words);
-//   2. stable radix sort of (key, original position) -- lexicographic order in mode_order
-//      (own LSD sort, 8 bits per pass, see below);
+//   2. stable radix sort of (key, value) -- lexicographic order in mode_order (own LSD sort, see
+//      below; its first pass does step 1); with two-word keys of (key, original position);
 //   3. per tile, count for every level the positions where the key prefix of that level
 //      changes ("head" of a node); a duplicate coordinate is a position whose full key
 //      equals its predecessor's;
@@ -14,6 +14,7 @@
 // The result is the canonical array layout documented in include/conststn.h.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "plan.hpp"
 
@@ -85,11 +86,6 @@ __device__ __forceinline__ bool same_prefix(const Levels &lv, int l, Key2 a, Key
     return (!WIDE || a.hi == b.hi) && prefix_of(a.lo, lv.shift[l]) == prefix_of(b.lo, lv.shift[l]);
 }
 
-__device__ __forceinline__ unsigned wave_sum(unsigned v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return v;
-}
-
 // For every level the number of node heads inside each tile; leaf-level non-heads are duplicates.
 template <bool WIDE>
 __global__ void __launch_bounds__(kTileThreads)
@@ -97,30 +93,35 @@ count_heads_kernel(int64_t nnz, Levels lv, const uint64_t *__restrict__ keys, co
                    unsigned *__restrict__ tile_counts, int64_t ntiles, int *flags) {
     __shared__ unsigned wsum[CONSTSTN_MAX_ORDER][kTileThreads / 64];
     const int64_t tile = blockIdx.x;
-    const int64_t base = tile * kTile + int64_t(threadIdx.x) * kItems;
-    unsigned cnt[CONSTSTN_MAX_ORDER];
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    unsigned cnt[CONSTSTN_MAX_ORDER];                 // the same in every lane of a wavefront
+#pragma unroll
     for (int l = 0; l < CONSTSTN_MAX_ORDER; ++l) cnt[l] = 0;
-    Key2 prev{0, 0};
-    bool have_prev = false;
-    if (base > 0 && base <= nnz) { prev = load_key<WIDE>(keys, keys_hi, base - 1); have_prev = true; }
     bool dup = false;
+    Key2 k[kItems], prev[kItems];
+#pragma unroll
     for (int i = 0; i < kItems; ++i) {
-        const int64_t n = base + i;
-        if (n >= nnz) break;
-        const Key2 k = load_key<WIDE>(keys, keys_hi, n);
-        for (int l = 0; l < lv.order; ++l) {
-            const bool head = !have_prev || !same_prefix<WIDE>(lv, l, k, prev);
-            cnt[l] += head ? 1u : 0u;
-            if (l == lv.order - 1 && !head) dup = true;
+        const int64_t n = tile * kTile + i * kTileThreads + int(threadIdx.x), at = n < nnz ? n : nnz - 1;
+        k[i] = load_key<WIDE>(keys, keys_hi, at);
+        prev[i] = load_key<WIDE>(keys, keys_hi, at > 0 ? at - 1 : 0);
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int64_t n = tile * kTile + i * kTileThreads + int(threadIdx.x);
+        const bool live = n < nnz;
+#pragma unroll
+        for (int l = 0; l < CONSTSTN_MAX_ORDER; ++l) {
+            if (l < lv.order) {
+                const bool head = live && (n == 0 || !same_prefix<WIDE>(lv, l, k[i], prev[i]));
+                cnt[l] += unsigned(__popcll(__builtin_amdgcn_ballot_w64(head)));
+                if (l == lv.order - 1 && live && !head) dup = true;
+            }
         }
-        prev = k;
-        have_prev = true;
     }
     if (dup) atomicOr(&flags[1], 1);
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    for (int l = 0; l < lv.order; ++l) {
-        unsigned s = wave_sum(cnt[l]);
-        if (lane == 0) wsum[l][wave] = s;
+    if (lane == 0) {
+#pragma unroll
+        for (int l = 0; l < CONSTSTN_MAX_ORDER; ++l) wsum[l][wave] = cnt[l];
     }
     __syncthreads();
     if (threadIdx.x < lv.order) {
@@ -133,13 +134,14 @@ count_heads_kernel(int64_t nnz, Levels lv, const uint64_t *__restrict__ keys, co
 // Exclusive scan of the tile counts of every level (one block per level); totals[l] = node count.
 // The block walks its row in chunks of 4096 counts, four adjacent ones per thread, and carries the
 // running total from chunk to chunk.
+template <typename OFF>
 __global__ void __launch_bounds__(1024)
-scan_tiles_kernel(const unsigned *__restrict__ tile_counts, int64_t *__restrict__ tile_offsets,
+scan_tiles_kernel(const unsigned *__restrict__ tile_counts, OFF *__restrict__ tile_offsets,
                   int64_t ntiles, int64_t *totals) {
     __shared__ int64_t wtot[16];
     const int l = blockIdx.x;
     const unsigned *in = tile_counts + int64_t(l) * ntiles;
-    int64_t *out = tile_offsets + int64_t(l) * ntiles;
+    OFF *out = tile_offsets + int64_t(l) * ntiles;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     int64_t carry = 0;
     for (int64_t t0 = 0; t0 < ntiles; t0 += 4096) {
@@ -165,7 +167,7 @@ scan_tiles_kernel(const unsigned *__restrict__ tile_counts, int64_t *__restrict_
         int64_t run = carry + before + inc - mine;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (t + k < ntiles) out[t + k] = run;
+            if (t + k < ntiles) out[t + k] = OFF(run);
             run += v[k];
         }
         carry += total;
@@ -174,86 +176,137 @@ scan_tiles_kernel(const unsigned *__restrict__ tile_counts, int64_t *__restrict_
     if (threadIdx.x == 0) totals[l] = carry;
 }
 
-// ---- stable LSD radix sort of (key, position) pairs, 8 bits per pass ------------------------
+// ---- stable LSD radix sort of (key, payload) pairs, 8 or 9 bits per pass ---------------------
 //
 // A workgroup of four wavefronts owns a tile of kSortTile consecutive pairs, wavefront w the w-th
 // quarter of it.  Per pass: (1) every workgroup counts the digits of its tile; (2) scan_tiles_kernel
 // (one block per digit value) turns the counts into the tile's starting offset inside each digit's
-// bucket, a one-wave kernel turns the bucket totals into bucket bases; (3) every workgroup re-reads
-// its tile, ranks each pair among the pairs of the tile with the same digit that come before it (in
-// a wavefront: 64 pairs at a time, eight ballots narrow the set of peers; across wavefronts: their
-// digit counts), lays the tile out by digit in LDS and writes it from there, so that neighbouring
-// threads write neighbouring addresses of a bucket.  Tiles are visited in index order inside a
-// bucket and pairs in order inside a tile, so the sort is stable, which the CSF needs: equal keys
-// (duplicates) must keep input order.
+// bucket; (3) every workgroup re-reads its tile, ranks each pair among the pairs of the tile with the
+// same digit that come before it (in a wavefront: 64 pairs at a time, one ballot per bit narrows the set
+// of peers; across wavefronts: their digit counts), lays the keys out by digit in LDS and writes them
+// from there, so that neighbouring threads write neighbouring addresses of a bucket, and then the
+// payload through the same LDS.  Tiles are visited in index order inside a bucket and pairs in order
+// inside a tile, so the sort is stable, which the CSF needs: equal keys (duplicates) must keep input
+// order.
+// The first pass of a CSF build reads the coordinates and packs the keys itself (COORDS), and the payload
+// is the value: 8 bytes more per pair and pass than the position, but the values are then not read at random
+// afterwards, a cache line each (emission at 76 M nonzeros: 1.75 -> 0.45 ms, a scatter 0.44 -> 0.55).
+// Bound: memory; a pass moves 40 bytes per pair (32 with positions).  Neighbouring tiles write neighbouring
+// runs (16 or 8 pairs on average) of a bucket, and neighbouring counts: consecutive tiles are given to one
+// XCD, whose L2 puts the parts of a cache line together (in launch order a build takes 0.7 ms longer).
+// Build of 76 M nonzeros, 43 key bits: 7.2 ms with a packing pass, six passes of 8 bits and positions ->
+// 4.55 ms (per pass: counts 0.17, their scan 0.03, scatter 0.55 = 5.5 TB/s in the scatter).
 constexpr int kSortItems = 16;
 constexpr int kSortWave = kSortItems * 64;            // pairs of one wavefront
 constexpr int kSortTile = 4 * kSortWave;
 
+// key[i] = keys (one word) of the nonzeros min(first + i * step, n - 1), i < COUNT; of fields that begin below bit
+// `below` only.  The level is the outer loop: a lane's loads of one level are in flight together.
+template <int COUNT, typename KEY>
+__device__ __forceinline__ bool keys_of(const Levels &lv, int64_t first, int step, int64_t n, int below, KEY (&key)[COUNT]) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) key[i] = 0;
+    for (int l = 0; l < lv.order; ++l) {
+        const int shift = lv.shift[l];
+        if (shift >= below) continue;
+        const int32_t *coord = lv.coord[l];
+        int32_t c[COUNT];
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) {
+            const int64_t e = first + int64_t(i) * step;
+            c[i] = coord[e < n ? e : n - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) {
+            const bool out = c[i] < 0 || int64_t(c[i]) >= lv.dim[l];
+            bad = bad || out;
+            key[i] |= KEY(uint32_t(out ? 0 : c[i])) << shift;
+        }
+    }
+    return bad;
+}
+
+template <int BITS, bool COORDS>
 __global__ void __launch_bounds__(256)
-radix_count_kernel(int64_t n, const uint64_t *__restrict__ keys, int shift, unsigned *__restrict__ tile_counts,
+radix_count_kernel(int64_t n, const uint64_t *__restrict__ keys, Levels lv, int shift, unsigned *__restrict__ tile_counts,
                    int64_t ntiles) {
-    __shared__ unsigned hist[256];
-    const int64_t tile = blockIdx.x;
-    hist[threadIdx.x] = 0;
+    constexpr int kBins = 1 << BITS;
+    __shared__ unsigned hist[kBins];
+    // each XCD takes a contiguous range of tiles, as in the scatter: its L2 puts their counts together
+    const int64_t per_xcd = (ntiles + 7) / 8, tile = int64_t(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (tile >= ntiles) return;
+    for (int d = threadIdx.x; d < kBins; d += 256) hist[d] = 0;
     __syncthreads();
     const int64_t base = tile * kSortTile;
-#pragma unroll 4
-    for (int i = 0; i < kSortItems; ++i) {
-        const int64_t e = base + int64_t(i) * 256 + threadIdx.x;
-        if (e < n) atomicAdd(&hist[unsigned(keys[e] >> shift) & 255u], 1u);
+    const int live = int(n - base < kSortTile ? n - base : int64_t(kSortTile));
+    if (COORDS) {
+        uint32_t key[kSortItems];                     // (what is out of range is reported by the scatter)
+        keys_of(lv, base + int(threadIdx.x), 256, n, BITS, key);
+#pragma unroll
+        for (int i = 0; i < kSortItems; ++i)
+            if (i * 256 + int(threadIdx.x) < live) atomicAdd(&hist[key[i] & (kBins - 1)], 1u);
+    } else {
+        // two keys per load (tiles begin at multiples of 32 KB of a buffer that is aligned to 16 bytes)
+        const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(keys + base);
+        ulonglong2 k[kSortItems / 2];
+#pragma unroll
+        for (int i = 0; i < kSortItems / 2; ++i) {
+            const int m = i * 256 + int(threadIdx.x);
+            k[i] = pairs[2 * m < live ? m : 0];       // (an odd last key: the buffers' allocations end on 256 bytes)
+        }
+#pragma unroll
+        for (int i = 0; i < kSortItems / 2; ++i) {
+            const int m = 2 * (i * 256 + int(threadIdx.x));
+            if (m < live) atomicAdd(&hist[unsigned(k[i].x >> shift) & (kBins - 1)], 1u);
+            if (m + 1 < live) atomicAdd(&hist[unsigned(k[i].y >> shift) & (kBins - 1)], 1u);
+        }
     }
     __syncthreads();
-    tile_counts[int64_t(threadIdx.x) * ntiles + tile] = hist[threadIdx.x];
+    for (int d = threadIdx.x; d < kBins; d += 256) tile_counts[int64_t(d) * ntiles + tile] = hist[d];
 }
 
-__global__ void radix_bases_kernel(const int64_t *__restrict__ totals, int64_t *__restrict__ bases) {
-    // one wave: exclusive scan of the 256 bucket totals
-    const int lane = threadIdx.x;
-    int64_t v[4], s = 0;
-    for (int i = 0; i < 4; ++i) { v[i] = totals[lane * 4 + i]; s += v[i]; }
-    int64_t inc = s;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t t = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += t;
-    }
-    int64_t run = inc - s;
-    for (int i = 0; i < 4; ++i) { bases[lane * 4 + i] = run; run += v[i]; }
-}
-
-__global__ void __launch_bounds__(256)
-radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ pay_in,
-                     uint64_t *__restrict__ keys_out, uint32_t *__restrict__ pay_out, int shift,
-                     const int64_t *__restrict__ tile_offsets, const int64_t *__restrict__ bases, int64_t ntiles) {
-    __shared__ uint64_t lkey[kSortTile];
-    __shared__ uint32_t lpay[kSortTile];
-    __shared__ unsigned run[4][256];                  // per wavefront: pairs of each digit seen so far
-    __shared__ unsigned start[4][256];                // first place in the tile's layout of a wavefront's pairs of a digit
-    __shared__ int64_t gbase[256];                    // address of the tile's place p holding digit d: gbase[d] + p
-    __shared__ unsigned wsum[4];
+template <int BITS, bool COORDS, typename PAY>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BITS == 9 || sizeof(PAY) == 8 ? 3 : 4)))
+radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY *__restrict__ pay_in, Levels lv, int *flags,
+                     uint64_t *__restrict__ keys_out, PAY *__restrict__ pay_out, int shift,
+                     const uint32_t *__restrict__ tile_offsets, const int64_t *__restrict__ totals, int64_t ntiles) {
+    constexpr int kBins = 1 << BITS, kPer = kBins / 256;      // digits of a thread
+    __shared__ uint64_t lkey[kSortTile];                      // the tile's keys by digit, then its positions
+    __shared__ unsigned run[4][kBins];                        // per wavefront: pairs of each digit seen so far, then the place of the next
+    __shared__ uint32_t gbase[kBins];                         // address of the tile's place p holding digit d: gbase[d] + p (mod 2^32)
+    __shared__ unsigned wsum[2][4];
     const int wv = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int64_t tile = blockIdx.x;
+    // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of tiles
+    const int64_t per_xcd = (ntiles + 7) / 8, tile = int64_t(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (tile >= ntiles) return;
     const int64_t base = tile * kSortTile + int64_t(wv) * kSortWave;
-    for (int w = 0; w < 4; ++w) run[w][threadIdx.x] = 0;
+    for (int d = threadIdx.x; d < 4 * kBins; d += 256) (&run[0][0])[d] = 0;
     __syncthreads();
     const unsigned long long lt = (1ull << lane) - 1ull;
     uint64_t key[kSortItems];
-    uint32_t pay[kSortItems];
-    unsigned rank[kSortItems];                        // among the wavefront's earlier pairs of the same digit
+    PAY pay[kSortItems];
+    unsigned rank[kSortItems];                                // among the wavefront's earlier pairs of the same digit
     // pairs past the end sort last: all-ones keys, and they are the last pairs of the last tile
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const int64_t e = base + int64_t(i) * 64 + lane;
-        const bool live = e < n;
-        key[i] = live ? keys_in[e] : ~uint64_t(0);
-        pay[i] = live ? pay_in[e] : 0u;
+    if (COORDS) {
+        const bool bad = keys_of(lv, base + lane, 64, n, 64, key);
+        if (bad) atomicOr(&flags[0], 1);
     }
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        const unsigned digit = unsigned(key[i] >> shift) & 255u;
+        const int64_t e = base + int64_t(i) * 64 + lane, at = e < n ? e : n - 1;
+        if (!COORDS) key[i] = keys_in[at];
+        pay[i] = pay_in[at];
+    }
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i)
+        if (base + int64_t(i) * 64 + lane >= n) key[i] = ~uint64_t(0);
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const unsigned digit = unsigned(key[i] >> shift) & (kBins - 1);
         unsigned long long peers = ~0ull;
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
+        for (int b = 0; b < BITS; ++b) {
             const bool bit = (digit >> b) & 1u;
             const unsigned long long m = __builtin_amdgcn_ballot_w64(bit);
             peers &= bit ? m : ~m;
@@ -266,122 +319,148 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const uint
     }
     __syncthreads();
     {
-        // thread d: where digit d begins in the tile's layout, and inside that where each wavefront's share begins
-        const int d = threadIdx.x;
-        unsigned c[4], total = 0;
-        for (int w = 0; w < 4; ++w) { c[w] = run[w][d]; total += c[w]; }
-        unsigned inc = total;
-        for (int off = 1; off < 64; off <<= 1) {
-            const unsigned up = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += up;
+        // a thread's digits: where they begin in the buckets' array and in the tile's layout, and inside that
+        // where each wavefront's share begins
+        const int d0 = int(threadIdx.x) * kPer;
+        unsigned mine = 0, all = 0;
+        for (int x = 0; x < kPer; ++x) {
+            for (int w = 0; w < 4; ++w) mine += run[w][d0 + x];
+            all += unsigned(totals[d0 + x]);
         }
-        if (lane == 63) wsum[wv] = inc;
+        unsigned inc = mine, inc_all = all;
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned up = __shfl_up(inc, off, 64), up_all = __shfl_up(inc_all, off, 64);
+            if (lane >= off) { inc += up; inc_all += up_all; }
+        }
+        if (lane == 63) { wsum[0][wv] = inc; wsum[1][wv] = inc_all; }
         __syncthreads();
-        unsigned first = inc - total;
-        for (int w = 0; w < wv; ++w) first += wsum[w];
-        gbase[d] = bases[d] + tile_offsets[int64_t(d) * ntiles + tile] - int64_t(first);
-        for (int w = 0; w < 4; ++w) { start[w][d] = first; first += c[w]; }
+        unsigned first = inc - mine, bucket = inc_all - all;
+        for (int w = 0; w < wv; ++w) { first += wsum[0][w]; bucket += wsum[1][w]; }
+        for (int x = 0; x < kPer; ++x) {
+            const int d = d0 + x;
+            gbase[d] = bucket + tile_offsets[int64_t(d) * ntiles + tile] - first;
+            bucket += unsigned(totals[d]);
+            for (int w = 0; w < 4; ++w) {
+                const unsigned c = run[w][d];
+                run[w][d] = first;
+                first += c;
+            }
+        }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        const unsigned digit = unsigned(key[i] >> shift) & 255u;
-        const unsigned p = start[wv][digit] + rank[i];
-        lkey[p] = key[i];
-        lpay[p] = pay[i];
+        rank[i] += run[wv][unsigned(key[i] >> shift) & (kBins - 1)];       // place in the tile's layout
+        lkey[rank[i]] = key[i];
     }
     __syncthreads();
     const int64_t rest = n - tile * kSortTile;
     const int live_pairs = rest < kSortTile ? int(rest) : kSortTile;
-#pragma unroll 4
+    uint32_t pos[kSortItems];
+#pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
         const int p = i * 256 + int(threadIdx.x);
-        if (p < live_pairs) {
-            const uint64_t k = lkey[p];
-            const int64_t pos = gbase[unsigned(k >> shift) & 255u] + p;
-            keys_out[pos] = k;
-            pay_out[pos] = lpay[p];
-        }
+        const uint64_t k = lkey[p];
+        pos[i] = gbase[unsigned(k >> shift) & (kBins - 1)] + unsigned(p);
+        if (p < live_pairs) keys_out[pos[i]] = k;
+    }
+    __syncthreads();
+    PAY *lpay = reinterpret_cast<PAY *>(lkey);
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) lpay[rank[i]] = pay[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const int p = i * 256 + int(threadIdx.x);
+        if (p < live_pairs) pay_out[pos[i]] = lpay[p];
     }
 }
 
-// Sorts n (key, payload) pairs by the low `bits` bits of the key, stably; a and b are two buffers of n
-// entries each, the input is in a, the result in whichever *keys_sorted / *pay_sorted name.  Waits
-// for the stream before it returns (the pass tables are released then).
 static size_t up256(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+constexpr int kSortBins = 512;                        // the pass tables hold digits of up to 9 bits
 
 // bytes of pass tables a sort of n pairs needs (handed in by callers that keep one allocation for all their
 // temporaries; every device allocation and release costs a fraction of a millisecond)
 size_t radix_sort_scratch_bytes(int64_t n) {
     const size_t stiles = size_t(div_up(std::max<int64_t>(n, 1), kSortTile));
-    return up256(stiles * 256 * sizeof(unsigned)) + up256(stiles * 256 * sizeof(int64_t)) + 2 * up256(256 * sizeof(int64_t));
+    return 2 * up256(stiles * kSortBins * sizeof(unsigned)) + up256(kSortBins * sizeof(int64_t));
 }
 
+// Queues the passes on `stream` without waiting.  lv: not null for a first pass that packs the keys (of one word)
+// from the coordinates and takes the payload from pay_first; keys_a and pay_a are then only work space.
+template <typename PAY>
+static conststn_status radix_passes(uint64_t *keys_a, uint64_t *keys_b, PAY *pay_a, PAY *pay_b, int64_t n, int bits,
+                                    hipStream_t stream, const uint64_t **keys_sorted, const PAY **pay_sorted, void *scratch,
+                                    const Levels *lv, const PAY *pay_first, int *flags) {
+    const int64_t stiles = div_up(n, kSortTile);
+    char *at = static_cast<char *>(scratch);
+    unsigned *counts = reinterpret_cast<unsigned *>(at);
+    at += up256(size_t(stiles) * kSortBins * sizeof(unsigned));
+    uint32_t *offsets = reinterpret_cast<uint32_t *>(at);
+    at += up256(size_t(stiles) * kSortBins * sizeof(unsigned));
+    int64_t *totals = reinterpret_cast<int64_t *>(at);
+    uint64_t *kin = keys_a, *kout = keys_b;
+    PAY *pin = pay_a, *pout = pay_b;
+    const dim3 grid{unsigned(div_up(stiles, 8) * 8)}, block(256);
+    const Levels none{};
+    // 9 bits where that saves a pass: 5 instead of 6 at 43 bits, 0.17 ms less at 76 M pairs (a pass of 9 bits costs
+    // more than one of 8, so where the number is the same 8 are taken)
+    const bool nine = (bits + 8) / 9 < (bits + 7) / 8;
+    auto pass = [&](auto digit_bits, auto coords, int shift) {
+        constexpr int B = decltype(digit_bits)::value;
+        constexpr bool C = decltype(coords)::value;
+        radix_count_kernel<B, C><<<grid, block, 0, stream>>>(n, kin, C ? *lv : none, shift, counts, stiles);
+        scan_tiles_kernel<uint32_t><<<dim3(1u << B), dim3(1024), 0, stream>>>(counts, offsets, stiles, totals);
+        radix_scatter_kernel<B, C><<<grid, block, 0, stream>>>(n, kin, C ? pay_first : pin, C ? *lv : none, flags, kout, pout, shift, offsets, totals, stiles);
+    };
+    using std::integral_constant;
+    for (int shift = 0; shift < bits; shift += nine ? 9 : 8) {
+        const bool coords = lv && shift == 0;
+        if constexpr (sizeof(PAY) == 8) {                     // (only the CSF build sorts values)
+            if (nine && coords) pass(integral_constant<int, 9>{}, std::true_type{}, shift);
+            if (!nine && coords) pass(integral_constant<int, 8>{}, std::true_type{}, shift);
+        }
+        if (nine && !coords) pass(integral_constant<int, 9>{}, std::false_type{}, shift);
+        if (!nine && !coords) pass(integral_constant<int, 8>{}, std::false_type{}, shift);
+        CST_HIP(hipGetLastError());
+        std::swap(kin, kout);
+        std::swap(pin, pout);
+    }
+    *keys_sorted = kin;
+    *pay_sorted = pin;
+    return CONSTSTN_OK;
+}
+
+// Sorts n (key, payload) pairs by the low `bits` bits of the key, stably; a and b are two buffers of n
+// entries each (keys aligned to 16 bytes), the input is in a, the result in whichever *keys_sorted / *pay_sorted
+// name.  Waits for the stream before it returns where the pass tables are its own (they are released then).
 conststn_status radix_sort_pairs_u64(uint64_t *keys_a, uint64_t *keys_b, uint32_t *pay_a, uint32_t *pay_b, int64_t n,
                                      int bits, hipStream_t stream, const uint64_t **keys_sorted,
                                      const uint32_t **pay_sorted, void *scratch) {
     *keys_sorted = keys_a;
     *pay_sorted = pay_a;
     if (bits <= 0 || n <= 1) return CONSTSTN_OK;
-    const int64_t stiles = div_up(n, kSortTile);
     DevBuf<char> own;
-    if (!scratch) {
+    const bool lent = scratch != nullptr;
+    if (!lent) {
         CST_TRY(own.alloc(radix_sort_scratch_bytes(n)));
         scratch = own.p;
     }
-    struct { unsigned *p; } scounts;
-    struct { int64_t *p; } soffsets, stotals, sbases;
-    {
-        char *at = static_cast<char *>(scratch);
-        scounts.p = reinterpret_cast<unsigned *>(at);
-        at += up256(size_t(stiles) * 256 * sizeof(unsigned));
-        soffsets.p = reinterpret_cast<int64_t *>(at);
-        at += up256(size_t(stiles) * 256 * sizeof(int64_t));
-        stotals.p = reinterpret_cast<int64_t *>(at);
-        at += up256(256 * sizeof(int64_t));
-        sbases.p = reinterpret_cast<int64_t *>(at);
-    }
-    uint64_t *kin = keys_a, *kout = keys_b;
-    uint32_t *pin = pay_a, *pout = pay_b;
-    const dim3 sgrid{unsigned(stiles)}, sblock(256);
-    for (int shift = 0; shift < bits; shift += 8) {
-        radix_count_kernel<<<sgrid, sblock, 0, stream>>>(n, kin, shift, scounts.p, stiles);
-        scan_tiles_kernel<<<dim3(256), dim3(1024), 0, stream>>>(scounts.p, soffsets.p, stiles, stotals.p);
-        radix_bases_kernel<<<dim3(1), dim3(64), 0, stream>>>(stotals.p, sbases.p);
-        radix_scatter_kernel<<<sgrid, sblock, 0, stream>>>(n, kin, pin, kout, pout, shift, soffsets.p, sbases.p, stiles);
-        CST_HIP(hipGetLastError());
-        std::swap(kin, kout);
-        std::swap(pin, pout);
-    }
-    CST_HIP(hipStreamSynchronize(stream));
-    *keys_sorted = kin;
-    *pay_sorted = pin;
+    CST_TRY(radix_passes(keys_a, keys_b, pay_a, pay_b, n, bits, stream, keys_sorted, pay_sorted, scratch, nullptr, static_cast<const uint32_t *>(nullptr), nullptr));
+    if (!lent) CST_HIP(hipStreamSynchronize(stream));
     return CONSTSTN_OK;
-}
-
-__device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned *wtot /*[4]*/) {
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    unsigned inc = v;
-    for (int off = 1; off < 64; off <<= 1) {
-        unsigned t = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += t;
-    }
-    if (lane == 63) wtot[wave] = inc;
-    __syncthreads();
-    unsigned add = 0;
-    for (int w = 0; w < wave; ++w) add += wtot[w];
-    __syncthreads();
-    return add + inc - v;
 }
 
 // Rank heads and write the level arrays.  A head at level l is also a head at every deeper
 // level, so its child pointer is simply its own rank one level down.  Thread t of a tile takes the
 // pairs t, t + 256, ...: every read and write of a wavefront is to neighbouring addresses, the tile's
-// keys go through LDS so that each pair sees the one before it, and the values (one read through
-// the sorted position per pair, at random) are requested before anything else is done.  A pair's
+// keys go through LDS so that each pair sees the one before it, and the values are requested before
+// anything else is done.  A pair's
 // rank among the heads of a level is its rank in its wavefront's ballot plus the heads of the
 // wavefronts and chunks of 256 before it in the tile.
-template <bool WIDE>
+// VALS: the values come in key order (vals_in), otherwise through the sorted positions.
+template <bool WIDE, bool VALS>
 __global__ void __launch_bounds__(kTileThreads)
 emit_levels_kernel(int64_t nnz, Levels lv, const uint64_t *__restrict__ keys, const uint64_t *__restrict__ keys_hi,
                    const uint32_t *__restrict__ payload, const double *__restrict__ vals_in,
@@ -396,16 +475,21 @@ emit_levels_kernel(int64_t nnz, Levels lv, const uint64_t *__restrict__ keys, co
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     Key2 k[kItems];
     double v[kItems];
+    uint32_t from[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {               // (clamped, so that no load waits for a test)
+        const int64_t n = base + i * kTileThreads + int(threadIdx.x), at = n < nnz ? n : nnz - 1;
+        if (!VALS) from[i] = payload[at];
+        else v[i] = vals_in[at];
+        k[i] = load_key<WIDE>(keys, keys_hi, at);
+    }
+    if (!VALS) {
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) v[i] = vals_in[from[i]];
+    }
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const int m = i * kTileThreads + int(threadIdx.x);
-        const int64_t n = base + m;
-        k[i] = Key2{0, 0};
-        v[i] = 0.0;
-        if (n < nnz) {
-            k[i] = load_key<WIDE>(keys, keys_hi, n);
-            v[i] = vals_in[payload[n]];
-        }
         lkey[1 + m] = k[i].lo;
         if (WIDE) lkey_hi[1 + m] = k[i].hi;
     }
@@ -466,7 +550,7 @@ emit_levels_kernel(int64_t nnz, Levels lv, const uint64_t *__restrict__ keys, co
                     // (the sort is stable); without duplicates the run has length one
                     double sum = v[i];
                     if (has_dups)
-                        for (int64_t m = n + 1; m < nnz && keys[m] == k[i].lo && (!WIDE || keys_hi[m] == k[i].hi); ++m) sum += vals_in[payload[m]];
+                        for (int64_t m = n + 1; m < nnz && keys[m] == k[i].lo && (!WIDE || keys_hi[m] == k[i].hi); ++m) sum += vals_in[VALS ? m : int64_t(payload[m])];
                     vals_out[pos[l]] = sum;
                 }
             }
@@ -536,8 +620,10 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
 
     // every temporary of the build in one allocation
     const int64_t ntiles = div_up(nnz, kTile);
+    const bool fused = !wide && total_bits > 0 && nnz > 1;            // the sort packs the keys and carries the values
+    const size_t pay_bytes = size_t(nnz) * (fused ? 8 : 4);
     const size_t sort_bytes = radix_sort_scratch_bytes(nnz);
-    const size_t arena_bytes = 2 * up256(size_t(nnz) * 8) + 2 * up256(size_t(nnz) * 4) + up256(2 * sizeof(int)) +
+    const size_t arena_bytes = 2 * up256(size_t(nnz) * 8) + 2 * up256(pay_bytes) + up256(2 * sizeof(int)) +
                                (wide ? 2 * up256(size_t(nnz) * 8) : 0) + sort_bytes +
                                up256(size_t(ntiles) * order * sizeof(unsigned)) + up256(size_t(ntiles) * order * sizeof(int64_t)) +
                                up256(CONSTSTN_MAX_ORDER * sizeof(int64_t));
@@ -546,7 +632,7 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
     size_t arena_at = 0;
     auto take = [&](size_t bytes) { char *q = arena.p + arena_at; arena_at += up256(bytes); return q; };
     struct { uint64_t *p; } keys_a{reinterpret_cast<uint64_t *>(take(size_t(nnz) * 8))}, keys_b{reinterpret_cast<uint64_t *>(take(size_t(nnz) * 8))};
-    struct { uint32_t *p; } pay_a{reinterpret_cast<uint32_t *>(take(size_t(nnz) * 4))}, pay_b{reinterpret_cast<uint32_t *>(take(size_t(nnz) * 4))};
+    struct { uint32_t *p; } pay_a{reinterpret_cast<uint32_t *>(take(pay_bytes))}, pay_b{reinterpret_cast<uint32_t *>(take(pay_bytes))};
     struct { int *p; } dflags{reinterpret_cast<int *>(take(2 * sizeof(int)))};
     CST_HIP(hipMemsetAsync(dflags.p, 0, 2 * sizeof(int), stream));
     struct { uint64_t *p; } lo_orig{nullptr}, hi_orig{nullptr};      // two-word keys only: the words in input order
@@ -555,17 +641,19 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
         hi_orig.p = reinterpret_cast<uint64_t *>(take(size_t(nnz) * 8));
     }
     void *sort_scratch = take(sort_bytes);
-    {
+    const uint64_t *skeys = keys_a.p, *skeys_hi = nullptr;
+    const uint32_t *spay = pay_a.p;
+    const uint64_t *svals = nullptr;                                   // the values in key order, where the sort carried them
+    if (!fused) {
         const int64_t blocks = std::min<int64_t>(div_up(nnz, 256), 65536);
         pack_keys_kernel<<<dim3(unsigned(blocks)), dim3(256), 0, stream>>>(nnz, lv, wide ? lo_orig.p : keys_a.p,
                                                                           wide ? hi_orig.p : nullptr, pay_a.p, dflags.p);
         CST_HIP(hipGetLastError());
     }
-
-    const uint64_t *skeys = keys_a.p, *skeys_hi = nullptr;
-    const uint32_t *spay = pay_a.p;
     if (!wide) {
-        CST_TRY(radix_sort_pairs_u64(keys_a.p, keys_b.p, pay_a.p, pay_b.p, nnz, total_bits, stream, &skeys, &spay, sort_scratch));
+        if (fused)
+            CST_TRY(radix_passes(keys_a.p, keys_b.p, reinterpret_cast<uint64_t *>(pay_a.p), reinterpret_cast<uint64_t *>(pay_b.p), nnz,
+                                 total_bits, stream, &skeys, &svals, sort_scratch, &lv, reinterpret_cast<const uint64_t *>(vals), dflags.p));
     } else {
         // least significant word first: sort (low word, position), bring the high words into that order, sort
         // again by the high word (stable), then fetch the low words in the final order
@@ -595,8 +683,8 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
         count_heads_kernel<false><<<dim3(unsigned(ntiles)), dim3(kTileThreads), 0, stream>>>(
             nnz, lv, skeys, nullptr, tile_counts.p, ntiles, dflags.p);
     CST_HIP(hipGetLastError());
-    scan_tiles_kernel<<<dim3(unsigned(order)), dim3(1024), 0, stream>>>(tile_counts.p, tile_offsets.p,
-                                                                      ntiles, totals.p);
+    scan_tiles_kernel<int64_t><<<dim3(unsigned(order)), dim3(1024), 0, stream>>>(tile_counts.p, tile_offsets.p,
+                                                                               ntiles, totals.p);
     CST_HIP(hipGetLastError());
 
     int hflags[2] = {0, 0};
@@ -625,11 +713,15 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
     CST_TRY(csf->vals.alloc(size_t(htotals[order - 1])));
     csf->nnz = htotals[order - 1];
 
+    const dim3 egrid{unsigned(ntiles)}, eblock(kTileThreads);
     if (wide)
-        emit_levels_kernel<true><<<dim3(unsigned(ntiles)), dim3(kTileThreads), 0, stream>>>(
+        emit_levels_kernel<true, false><<<egrid, eblock, 0, stream>>>(
             nnz, lv, skeys, skeys_hi, spay, vals, tile_offsets.p, ntiles, lo, csf->vals.p, hflags[1]);
+    else if (svals)
+        emit_levels_kernel<false, true><<<egrid, eblock, 0, stream>>>(
+            nnz, lv, skeys, nullptr, nullptr, reinterpret_cast<const double *>(svals), tile_offsets.p, ntiles, lo, csf->vals.p, hflags[1]);
     else
-        emit_levels_kernel<false><<<dim3(unsigned(ntiles)), dim3(kTileThreads), 0, stream>>>(
+        emit_levels_kernel<false, false><<<egrid, eblock, 0, stream>>>(
             nnz, lv, skeys, nullptr, spay, vals, tile_offsets.p, ntiles, lo, csf->vals.p, hflags[1]);
     CST_HIP(hipGetLastError());
     close_ptrs_kernel<<<dim3(1), dim3(64), 0, stream>>>(lo, order, totals.p);

@@ -1,0 +1,46 @@
+"""CSF builds whose sort takes one to six passes of 8 or 9 bits, at numbers of nonzeros beside the sort's tiles (4096) and
+their rounds over the eight XCDs, without and with duplicates (added in input order), and with a coordinate
+out of range in the last place, bit for bit against the reference build."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2401_04836_amd as cst
+from oracle.csf_ref import csf_build
+
+pytestmark = pytest.mark.gpu
+
+# extents: 1, 7, 8, 9, 10, 17, 18, 25, 43 and 48 key bits
+DIMS = [(2, 1, 1), (4, 8, 4), (8, 4, 8), (8, 8, 8), (3, 100, 2), (64, 32, 64), (64, 50, 60), (300, 200, 400),
+        (12_000, 9_000, 29_000), (1 << 16, 3, (1 << 30) - 1)]
+
+
+@pytest.mark.parametrize("dims", DIMS)
+@pytest.mark.parametrize("n", [2, 4095, 4096, 4097, 8 * 4096, 8 * 4096 + 1, 70_001])
+def test_passes_and_tiles(dims, n):
+    rng = np.random.default_rng(n + sum(dims))
+    c = [rng.integers(0, d, n).astype(np.int32) for d in dims]
+    v = rng.uniform(-1, 1, n)
+    order = [1, 2, 0]
+    print("[case] dims %s n %d" % (dims, n), flush=True)
+    lev = [c[m].astype(np.int64) for m in order]
+    at = np.lexsort(lev[::-1])                             # stable: equal tuples keep input order
+    head = np.ones(n, bool)
+    head[1:] = np.any([x[at][1:] != x[at][:-1] for x in lev], axis=0)
+    first = np.flatnonzero(head)
+    sums = v[at][first].copy()
+    for d in range(1, int(np.diff(np.append(first, n)).max())):      # one more duplicate of every tuple at a time
+        more = (first + d < n) & (d < np.diff(np.append(first, n)))
+        sums[more] += v[at][first[more] + d]
+    idx, ptr, vals, _ = csf_build([x[at][first].astype(np.int32) for x in c], sums, dims, order)
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, order, flags=cst.COALESCE_DUPS)
+    for l in range(3):
+        gi, gp, gv = csf.export(l)
+        np.testing.assert_array_equal(gi.cpu().numpy(), idx[l])
+        if l < 2:
+            np.testing.assert_array_equal(gp.cpu().numpy(), ptr[l])
+        else:
+            np.testing.assert_array_equal(gv.cpu().numpy(), vals)
+    c[2][n - 1] = dims[2]
+    with pytest.raises(Exception, match="below its mode extent"):
+        cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, order, flags=cst.COALESCE_DUPS)
