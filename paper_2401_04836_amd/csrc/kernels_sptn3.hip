@@ -450,7 +450,7 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 // ---- tiled kernel with two wavefronts per SIMD ------------------------------------------------
 // The kernel above keeps Z^t for all m tiles of its l tiles in 200 accumulator registers, which
 // leaves room for one wavefront per SIMD and puts the accumulators into the upper half of the register
-// file, where an fp64 matrix instruction takes 105 cycles instead of 64.  Here a workgroup has eight
+// file, where an fp64 matrix instruction takes 44 ns of its SIMD instead of 27.  Here a workgroup has eight
 // wavefronts (two per SIMD).  Only the blocks of sixteen l below which W holds anything under the k at
 // hand are taken (a list made with the plan): T is read nowhere else.  Eight of them make a *round*, in
 // which wavefront w computes T^t of the w-th as above.  The consumer is split by m instead of by
@@ -464,7 +464,7 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 // taken and the tiles found by ballots and reads across lanes, 24.1 with the list, 23.4 with the places
 // below.  Of these 23.4 (switched off in a copy): W's fetches and parking 3.4, consumer 5.0, everything but the
 // loop over batches 2.2, V's addresses made one cache line 0.8; the producer alone 11.8, of which 6.4 are the
-// matrix instructions at 64 cycles each.  A ring of three batches takes as long as two.
+// matrix instructions at 27 ns each.  A ring of three batches takes as long as two.
 constexpr int kOwnWaves = 8;
 constexpr int kRingO = 2;                                             // batches in flight in this kernel
 constexpr int kOwnZ = (kSpMaxMTiles + kOwnWaves - 1) / kOwnWaves;       // accumulator tiles per wavefront

@@ -121,8 +121,8 @@ ttmc4_kernel(Ttmc4Args a) {
 // The structure (ends a fiber / ends a K-step / starts a K-step, and the four j of a K-step) travels
 // in the records, so nothing but the stream itself is read.
 // All ranks 16: sixteen 16x16x4 instructions per K-step, A = U1[j_s, c], B = row r2 of the four tiles.
-// Ranks below 16: the slice level runs on the 4x4x4 instruction with four blocks (16 cycles of a SIMD
-// against 64), whose blocks take sixteen flat elements (r2,r3) as rows and the same four r1, held by
+// Ranks below 16: the slice level runs on the 4x4x4 instruction with four blocks (7 ns of a SIMD
+// against 27), whose blocks take sixteen flat elements (r2,r3) as rows and the same four r1, held by
 // every block, as columns: only the products that hold results are issued, ceil(R1/4) per sixteen flat
 // elements.  Which flat element is which row is free, as the operand comes out of LDS: lane (s, 4 b + x)
 // reads elements 32 u + 2 (4 x + b) and the next in one 16-byte read.  Operand lanes beyond a rank
