@@ -202,14 +202,16 @@ constexpr int kSortTile = 4 * kSortWave;
 
 // key[i] = keys (one word) of the nonzeros min(first + i * step, n - 1), i < COUNT; of fields that begin below bit
 // `below` only.  The level is the outer loop: a lane's loads of one level are in flight together.
-template <int COUNT, typename KEY>
+// ALL: every level's coordinates are read and tested, also of a level that holds no bit of the key (extent 1 above
+// fields that fill 64 bits: its shift is 64); the result says whether one was out of range.
+template <bool ALL, int COUNT, typename KEY>
 __device__ __forceinline__ bool keys_of(const Levels &lv, int64_t first, int step, int64_t n, int below, KEY (&key)[COUNT]) {
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < COUNT; ++i) key[i] = 0;
     for (int l = 0; l < lv.order; ++l) {
         const int shift = lv.shift[l];
-        if (shift >= below) continue;
+        if (!ALL && shift >= below) continue;
         const int32_t *coord = lv.coord[l];
         int32_t c[COUNT];
 #pragma unroll
@@ -221,7 +223,7 @@ __device__ __forceinline__ bool keys_of(const Levels &lv, int64_t first, int ste
         for (int i = 0; i < COUNT; ++i) {
             const bool out = c[i] < 0 || int64_t(c[i]) >= lv.dim[l];
             bad = bad || out;
-            key[i] |= KEY(uint32_t(out ? 0 : c[i])) << shift;
+            if (shift < below) key[i] |= KEY(uint32_t(out ? 0 : c[i])) << shift;
         }
     }
     return bad;
@@ -242,7 +244,7 @@ radix_count_kernel(int64_t n, const uint64_t *__restrict__ keys, Levels lv, int 
     const int live = int(n - base < kSortTile ? n - base : int64_t(kSortTile));
     if (COORDS) {
         uint32_t key[kSortItems];                     // (what is out of range is reported by the scatter)
-        keys_of(lv, base + int(threadIdx.x), 256, n, BITS, key);
+        keys_of<false>(lv, base + int(threadIdx.x), 256, n, BITS, key);
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i)
             if (i * 256 + int(threadIdx.x) < live) atomicAdd(&hist[key[i] & (kBins - 1)], 1u);
@@ -289,7 +291,7 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY 
     unsigned rank[kSortItems];                                // among the wavefront's earlier pairs of the same digit
     // pairs past the end sort last: all-ones keys, and they are the last pairs of the last tile
     if (COORDS) {
-        const bool bad = keys_of(lv, base + lane, 64, n, 64, key);
+        const bool bad = keys_of<true>(lv, base + lane, 64, n, 64, key);
         if (bad) atomicOr(&flags[0], 1);
     }
 #pragma unroll

@@ -44,3 +44,23 @@ def test_passes_and_tiles(dims, n):
     c[2][n - 1] = dims[2]
     with pytest.raises(Exception, match="below its mode extent"):
         cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, order, flags=cst.COALESCE_DUPS)
+
+
+@pytest.mark.parametrize("bad", [-1, 1, 7, 2 ** 31 - 1])
+@pytest.mark.parametrize("at", [0, 4999])
+def test_range_of_a_level_without_key_bits(bad, at):
+    """Fields that fill exactly 64 key bits below an outer mode of extent 1, which then holds no bit of the key: its
+    coordinates are tested all the same."""
+    dims, n = (1, 1 << 22, 1 << 21, 1 << 21), 5000
+    rng = np.random.default_rng(7)
+    c = [rng.integers(0, d, n).astype(np.int32) for d in dims]
+    v = rng.uniform(-1, 1, n)
+    print("[case] 64 key bits, %d at %d of mode 0" % (bad, at), flush=True)
+    order = np.lexsort([x.astype(np.int64) for x in c[::-1]])
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2, 3])
+    csf.check()
+    np.testing.assert_array_equal(csf.export(3)[2].cpu().numpy(), v[order])
+    c[0][at] = bad
+    with pytest.raises(cst.ConststnError) as e:
+        cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2, 3])
+    assert e.value.status_name == "ERANGE"
