@@ -327,7 +327,7 @@ static conststn_status match_rerooted(conststn_plan_s *plan) {
 // rank extents the tuned kernels are built for
 static bool tuned_kernel_fits(const conststn_plan_s *plan) {
     switch (plan->family) {
-        case FAM_MTTKRP3: return plan->use_records;
+        case FAM_MTTKRP3: return plan->rank_of_level[1] <= 128;
         case FAM_TTMC3: return plan->rank_of_level[1] <= 64 && plan->rank_of_level[2] <= 64;
         case FAM_TTMC4: return plan->rank_of_level[1] <= 16 && plan->rank_of_level[2] <= 16 && plan->rank_of_level[3] <= 16;
         default: return true;
@@ -795,7 +795,8 @@ conststn_status conststn_execute(const conststn_plan_t *plan, const double *cons
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (plan->family) {
         case FAM_MTTKRP3:
-            return plan->split ? launch_mttkrp3(plan, dense_factors, out, st) : launch_record_stream(plan, dense_factors, out, st);
+            if (plan->split) return launch_mttkrp3(plan, dense_factors, out, st);
+            return plan->use_records ? launch_record_stream(plan, dense_factors, out, st) : launch_mttkrp3_csf(plan, dense_factors, out, st);
         case FAM_TTMC3: return launch_ttmc3(plan, dense_factors, out, st);
         case FAM_TTMC4: return launch_ttmc4(plan, dense_factors, out, st);
         case FAM_SPTN3: return launch_sptn3(plan, dense_factors, out, st);

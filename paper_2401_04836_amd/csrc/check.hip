@@ -72,7 +72,7 @@ check_level_kernel(CsfView v, int l, unsigned *flags) {
     if (bad) atomicOr(flags, bad);
 }
 
-// MTTKRP tables of one of the two sub-tensors
+// MTTKRP tables of one of the two sub-tensors, or of the tensor itself
 struct MttkrpView {
     int64_t slices, fibers, nnz, q, n_chunks, out_rows, dim1, dim2;
     const int64_t *ptr0, *ptr1, *slice_leaf, *chunk_fiber;
@@ -362,7 +362,12 @@ extern "C" conststn_status conststn_plan_check(const conststn_plan_t *plan) {
             CST_HIP(hipGetLastError());
             return CONSTSTN_OK;
         };
-        for (int part = 0; part < 2; ++part) {
+        const MttkrpPart &W = plan->part[0];
+        if (!plan->split)
+            CST_TRY(launch(MttkrpView{W.slices, W.fibers, W.nnz, W.chunk_q, W.n_chunks, plan->out_rows, dim1, dim2,
+                                      X->ptr[0].p, X->ptr[1].p, W.slice_leaf.p, W.chunk_fiber.p, W.chunk_slice.p, nullptr,
+                                      X->idx[1].p, nullptr, 0, 0}));
+        for (int part = 0; plan->split && part < 2; ++part) {
             const MttkrpPart &P = plan->part[part];
             MttkrpView m{P.slices, P.fibers, P.nnz, P.chunk_q, P.n_chunks, plan->out_rows, dim1, dim2,
                          P.ptr0.p, P.ptr1.p, P.slice_leaf.p, P.chunk_fiber.p, P.chunk_slice.p, P.row_of_slice.p,

@@ -4,15 +4,17 @@
 // fused on the loops i and j, so the intermediate shrinks to one length-R vector per (i,j)
 // fiber (the reduced-order dense workspace of Fig. 3b); r is a batch index.
 //
-// This file holds the form for rank 32 on large power-law tensors: the leaves whose factor row is among the most
-// referenced ("hot") ones and the others as two sub-tensors, walked side by side by two teams of wavefronts.  All
-// other MTTKRPs run on the record stream (kernels_records.hip); build_mttkrp3_tables chooses.
+// Most MTTKRPs run on the record stream (kernels_records.hip); build_mttkrp3_tables chooses.  This file holds
+//   - the form for rank 32 on large power-law tensors: the leaves whose factor row is among the most referenced
+//     ("hot") ones and the others as two sub-tensors, walked side by side by two teams of wavefronts;
+//   - the form that walks the CSF itself, for what the records cannot name: rank 1 (a lane takes a pair of
+//     entries there) and extents above 2^28.
 //
-// The leaf array of a sub-tensor is cut into equal chunks (partition.hip).  A group of 16 lanes owns one chunk and
-// walks it leaf by leaf; each lane keeps two rank entries of the fiber vector T and of the slice accumulator in
-// registers.  At a fiber end the group folds T * B[j,:] into the accumulator; at a slice end it adds the row to
-// the result (slice wholly inside the chunk) or stores a partial row (slice shared with neighbouring chunks).  A
-// second kernel adds the partial rows of shared slices in chunk order, so results are bit-reproducible.
+// The leaf array is cut into equal chunks (partition.hip).  A group of lanes owns one chunk and walks it leaf by
+// leaf; each lane keeps two rank entries of the fiber vector T and of the slice accumulator in registers.  At a
+// fiber end the group folds T * B[j,:] into the accumulator; at a slice end it puts the row into the result (slice
+// wholly inside the chunk) or stores a partial row (slice shared with neighbouring chunks).  A second kernel adds
+// the partial rows of shared slices in chunk order, so results are bit-reproducible.
 #include "plan.hpp"
 
 namespace cst {
@@ -21,7 +23,9 @@ struct MttkrpArgs {
     int64_t nnz, q, n_chunks, slices;
     int R;
     const int64_t *ptr0, *ptr1;
-    const int32_t *idx0, *idx1;                // result row of every slice; level-1 index of every fiber
+    const int32_t *idx0, *idx1, *idx2;         // result row of every slice; level-1 index of every fiber; leaves
+    int compact;                               // 1: the result row is the slice's number
+    int add;                                   // 1: rows are added to what the result holds (the two sub-tensors)
     const double *vals;
     const int64_t *chunk_fiber;
     const int32_t *chunk_slice;
@@ -34,6 +38,115 @@ struct MttkrpArgs {
 };
 
 typedef double v2f64_u __attribute__((ext_vector_type(2), aligned(8)));       // a pair of row entries at any double
+
+// ---- on the CSF itself ------------------------------------------------------------------------
+//
+// Groups of LPR lanes, the smallest power of two with 2 LPR >= R.  PAIRS: an even rank, whose rows are read and
+// written two entries at a time.  Slower than the stream wherever that applies (rank 50, 20 M nonzeros: 1.51 ms
+// against 0.91): the loads of a step depend on the pointer arrays.
+template <bool PAIRS>
+__device__ __forceinline__ void load2(const double *__restrict__ row, int r0, int R, double &x, double &y) {
+    if (PAIRS) {
+        const v2f64_u v = *reinterpret_cast<const v2f64_u *>(row + r0);
+        x = v[0];
+        y = v[1];
+    } else {
+        x = r0 < R ? row[r0] : 0.0;
+        y = r0 + 1 < R ? row[r0 + 1] : 0.0;
+    }
+}
+
+template <bool PAIRS>
+__device__ __forceinline__ void store2(double *__restrict__ row, int r0, int R, double x, double y) {
+    if (PAIRS) {
+        *reinterpret_cast<v2f64_u *>(row + r0) = v2f64_u{x, y};
+    } else {
+        if (r0 < R) row[r0] = x;
+        if (r0 + 1 < R) row[r0 + 1] = y;
+    }
+}
+
+template <int LPR, bool PAIRS>
+__global__ void __launch_bounds__(256)
+mttkrp3_csf_kernel(MttkrpArgs a) {
+    const int64_t gid = (int64_t(blockIdx.x) * 256 + threadIdx.x) / LPR;
+    const int gl = threadIdx.x % LPR;
+    if (gid >= a.n_chunks) return;
+    const int r0 = 2 * gl;
+    const int R = a.R;
+    if (PAIRS && r0 >= R) return;
+    const int64_t n0 = gid * a.q;
+    const int64_t n1 = n0 + a.q < a.nnz ? n0 + a.q : a.nnz;
+    int64_t f = a.chunk_fiber[gid];
+    int32_t s = a.chunk_slice[gid];
+    const int32_t s_first = s;
+    int64_t fiber_end = a.ptr1[f + 1];
+    if (fiber_end > n1) fiber_end = n1;
+    int64_t slice_fend = a.ptr0[s + 1];
+    int32_t j = a.idx1[f];
+    double t0 = 0.0, t1 = 0.0, acc0 = 0.0, acc1 = 0.0;
+
+    auto emit = [&](int32_t sl, double x, double y) {
+        const int64_t lo = a.slice_leaf[sl], hi = a.slice_leaf[sl + 1];
+        if (lo >= n0 && hi <= n1) {
+            const int64_t row = a.compact ? int64_t(sl) : int64_t(a.idx0[sl]);
+            store2<PAIRS>(a.out + row * R, r0, R, x, y);
+        } else {
+            const int64_t slot = 2 * gid + (sl == s_first ? 0 : 1);
+            store2<PAIRS>(a.partial + slot * R, r0, R, x, y);
+        }
+    };
+    auto fiber_done = [&](int64_t n) {          // n = position after the fiber's last leaf in this chunk
+        double b0, b1;
+        load2<PAIRS>(a.B + int64_t(j) * R, r0, R, b0, b1);
+        acc0 = fma(b0, t0, acc0);
+        acc1 = fma(b1, t1, acc1);
+        t0 = 0.0;
+        t1 = 0.0;
+        if (n < n1) {
+            ++f;
+            if (f == slice_fend) {
+                emit(s, acc0, acc1);
+                acc0 = 0.0;
+                acc1 = 0.0;
+                ++s;
+                slice_fend = a.ptr0[s + 1];
+            }
+            j = a.idx1[f];
+            fiber_end = a.ptr1[f + 1];
+            if (fiber_end > n1) fiber_end = n1;
+        }
+    };
+
+    constexpr int U = 4;
+    int64_t n = n0;
+    while (n + U <= n1) {
+        int32_t kk[U];
+        double vv[U], c0[U], c1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { kk[u] = a.idx2[n + u]; vv[u] = a.vals[n + u]; }
+#pragma unroll
+        for (int u = 0; u < U; ++u) load2<PAIRS>(a.C + int64_t(kk[u]) * R, r0, R, c0[u], c1[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            t0 = fma(vv[u], c0[u], t0);
+            t1 = fma(vv[u], c1[u], t1);
+            ++n;
+            if (n == fiber_end) fiber_done(n);
+        }
+    }
+    for (; n < n1;) {
+        const int32_t k = a.idx2[n];
+        const double v = a.vals[n];
+        double c0, c1;
+        load2<PAIRS>(a.C + int64_t(k) * R, r0, R, c0, c1);
+        t0 = fma(v, c0, t0);
+        t1 = fma(v, c1, t1);
+        ++n;
+        if (n == fiber_end) fiber_done(n);
+    }
+    emit(s, acc0, acc1);
+}
 
 // ---- rank-32 path ---------------------------------------------------------------------------
 //
@@ -301,9 +414,11 @@ __device__ __forceinline__ void mttkrp3_fixup_body(const MttkrpArgs &a, int64_t 
             x += red[(gg * LPR + gl) * 2];
             y += red[(gg * LPR + gl) * 2 + 1];
         }
-        const int64_t row = a.idx0[s];
-        if (r0 < R) x += a.out[row * R + r0];
-        if (r0 + 1 < R) y += a.out[row * R + r0 + 1];
+        const int64_t row = a.compact ? s : int64_t(a.idx0[s]);
+        if (a.add) {
+            if (r0 < R) x += a.out[row * R + r0];
+            if (r0 + 1 < R) y += a.out[row * R + r0 + 1];
+        }
         if (r0 < R) a.out[row * R + r0] = x;
         if (r0 + 1 < R) a.out[row * R + r0 + 1] = y;
     }
@@ -347,12 +462,12 @@ __device__ __forceinline__ void mttkrp3_fixup_final_body(const MttkrpArgs &a, in
     double x = 0.0;
     for (int seg = 0; seg < kHeavySegments; ++seg)
         x += a.heavy_partial[(h * kHeavySegments + seg) * a.R + r];
-    const int64_t row = a.idx0[s];
-    x += a.out[row * a.R + r];
+    const int64_t row = a.compact ? s : int64_t(a.idx0[s]);
+    if (a.add) x += a.out[row * a.R + r];
     a.out[row * a.R + r] = x;
 }
 // The three passes for the two sub-tensors, which write different outputs, in one launch each: the
-// first blocks take the first sub-tensor's slices (heavy slices), the others the second's.
+// first blocks take the first sub-tensor's slices (heavy slices), the others the second's (none: a tensor by itself).
 struct MttkrpPairArgs { MttkrpArgs first, second; };
 template <int LPR>
 __global__ void __launch_bounds__(256)
@@ -422,6 +537,7 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
         aa.base.ptr1 = P.ptr1.p;
         aa.base.idx0 = P.row_of_slice.p;
         aa.base.idx1 = P.idx1.p;
+        aa.base.add = 1;
         aa.base.vals = P.vals.p;
         aa.base.chunk_fiber = P.chunk_fiber.p;
         aa.base.chunk_slice = P.chunk_slice.p;
@@ -460,6 +576,60 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
         reinterpret_cast<v2f64_u *>(out), reinterpret_cast<const v2f64_u *>(plan->mttkrp_out2.p), n / 2);
     CST_HIP(hipGetLastError());
     return CONSTSTN_OK;
+}
+
+template <int LPR>
+static conststn_status launch_csf(const conststn_plan_s *plan, const MttkrpArgs &a, hipStream_t stream) {
+    const dim3 grid(unsigned(div_up(a.n_chunks, 256 / LPR))), block(256);
+    {
+        ProfScope prof(plan, stream);
+        if (a.R % 2 == 0) mttkrp3_csf_kernel<LPR, true><<<grid, block, 0, stream>>>(a);
+        else mttkrp3_csf_kernel<LPR, false><<<grid, block, 0, stream>>>(a);
+    }
+    CST_HIP(hipGetLastError());
+    return launch_fixup_pair<LPR>(a, MttkrpArgs{}, stream);
+}
+
+conststn_status launch_mttkrp3_csf(const conststn_plan_s *plan, const double *const *dense, double *out, hipStream_t stream) {
+    const conststn_csf_s *X = plan->X;
+    const MttkrpPart &P = plan->part[0];                    // chunk tables over X itself
+    MttkrpArgs a{};
+    a.nnz = X->nnz;
+    a.q = P.chunk_q;
+    a.n_chunks = P.n_chunks;
+    a.slices = X->nodes[0];
+    a.R = plan->rank_of_level[1];
+    a.ptr0 = X->ptr[0].p;
+    a.ptr1 = X->ptr[1].p;
+    a.idx0 = X->idx[0].p;
+    a.idx1 = X->idx[1].p;
+    a.idx2 = X->idx[2].p;
+    a.compact = plan->compact ? 1 : 0;
+    a.vals = X->vals.p;
+    a.chunk_fiber = P.chunk_fiber.p;
+    a.chunk_slice = P.chunk_slice.p;
+    a.slice_leaf = P.slice_leaf.p;
+    a.B = dense[plan->factor_of_level[1]];
+    a.C = dense[plan->factor_of_level[2]];
+    a.out = out;
+    a.partial = P.partial.p;
+    a.heavy_slices = P.heavy_slices.p;
+    a.heavy_partial = P.heavy_partial.p;
+    a.n_heavy = P.n_heavy;
+    if (!plan->compact && a.slices < plan->out_rows)        // rows of empty slices are zero
+        CST_TRY(zero_fill(out, plan->out_rows * plan->row_elems, stream));
+    if (a.nnz == 0) return CONSTSTN_OK;
+    int lpr = 1;
+    while (2 * lpr < a.R) lpr *= 2;
+    switch (lpr) {
+        case 1: return launch_csf<1>(plan, a, stream);
+        case 2: return launch_csf<2>(plan, a, stream);
+        case 4: return launch_csf<4>(plan, a, stream);
+        case 8: return launch_csf<8>(plan, a, stream);
+        case 16: return launch_csf<16>(plan, a, stream);
+        case 32: return launch_csf<32>(plan, a, stream);
+        default: return launch_csf<64>(plan, a, stream);
+    }
 }
 
 }  // namespace cst

@@ -220,23 +220,19 @@ __global__ void part_fill_slices_kernel(int64_t slices, const int64_t *__restric
     row_out[spos[s]] = compact ? int32_t(s) : idx0[s];
 }
 
-static conststn_status build_part_tables(MttkrpPart &P, int R, int64_t q) {
+// Chunk tables over the tree of P.slices, P.fibers and P.nnz nodes that the pointer arrays describe.
+static conststn_status build_chunk_tables(MttkrpPart &P, const int64_t *ptr0, const int64_t *ptr1, int R, int64_t q) {
     const dim3 block(256);
     CST_TRY(P.slice_leaf.alloc(size_t(P.slices) + 1));
-    slice_leaf_kernel<<<dim3(unsigned(div_up(P.slices + 1, 256))), block>>>(P.slices, 2, P.ptr0.p, P.ptr1.p, nullptr,
-                                                                          P.slice_leaf.p);
-    CST_HIP(hipGetLastError());
-    mark_ends_kernel<<<dim3(unsigned(div_up(P.fibers, 256))), block>>>(P.fibers, P.ptr1.p, 0x40000000u, P.code.p);
-    mark_ends_kernel<<<dim3(unsigned(div_up(P.slices, 256))), block>>>(P.slices, P.slice_leaf.p, 0x20000000u, P.code.p);
+    slice_leaf_kernel<<<dim3(unsigned(div_up(P.slices + 1, 256))), block>>>(P.slices, 2, ptr0, ptr1, nullptr, P.slice_leaf.p);
     CST_HIP(hipGetLastError());
     P.chunk_q = q;
     P.n_chunks = div_up(P.nnz, q);
     CST_TRY(P.chunk_fiber.alloc(size_t(P.n_chunks)));
     CST_TRY(P.chunk_slice.alloc(size_t(P.n_chunks)));
     CST_TRY(P.partial.alloc(size_t(P.n_chunks) * 2 * size_t(R)));
-    mttkrp_chunks_kernel<<<dim3(unsigned(div_up(P.n_chunks, 256))), block>>>(P.n_chunks, q, P.slices, P.fibers,
-                                                                           P.ptr0.p, P.ptr1.p, P.chunk_fiber.p,
-                                                                           P.chunk_slice.p);
+    mttkrp_chunks_kernel<<<dim3(unsigned(div_up(P.n_chunks, 256))), block>>>(P.n_chunks, q, P.slices, P.fibers, ptr0, ptr1,
+                                                                           P.chunk_fiber.p, P.chunk_slice.p);
     CST_HIP(hipGetLastError());
     const int64_t max_heavy = P.nnz / (int64_t(kHeavySpan) * q) + 1;
     CST_TRY(P.heavy_slices.alloc(size_t(max_heavy)));
@@ -251,6 +247,14 @@ static conststn_status build_part_tables(MttkrpPart &P, int R, int64_t q) {
     return CONSTSTN_OK;
 }
 
+static conststn_status build_part_tables(MttkrpPart &P, int R, int64_t q) {
+    const dim3 block(256);
+    CST_TRY(build_chunk_tables(P, P.ptr0.p, P.ptr1.p, R, q));
+    mark_ends_kernel<<<dim3(unsigned(div_up(P.fibers, 256))), block>>>(P.fibers, P.ptr1.p, 0x40000000u, P.code.p);
+    mark_ends_kernel<<<dim3(unsigned(div_up(P.slices, 256))), block>>>(P.slices, P.slice_leaf.p, 0x20000000u, P.code.p);
+    CST_HIP(hipGetLastError());
+    return CONSTSTN_OK;
+}
 
 static conststn_status build_mttkrp3_split(conststn_plan_s *plan, const int32_t *slot_of_row, bool asked) {
     const conststn_csf_s *X = plan->X;
@@ -357,8 +361,8 @@ static conststn_status build_mttkrp3_hot(conststn_plan_s *plan, bool asked) {
     return plan->split ? prepare_mttkrp3_launch(plan) : CONSTSTN_OK;
 }
 
-// Which form.  The record stream (kernels_records.hip) takes every rank and size.  Rank 32 on a large tensor
-// whose leaf index follows a power law has another: the hot leaves, their rows in LDS, and the cold ones as two
+// Which form.  The record stream (kernels_records.hip) takes ranks from 2 to 128 over extents up to 2^28; for rank 1
+// and larger extents the CSF itself is walked.  Rank 32 on a large tensor whose leaf index follows a power law has another: the hot leaves, their rows in LDS, and the cold ones as two
 // sub-tensors side by side in one launch.  It pays one more factor row per fiber that has leaves of both kinds,
 // so it needs long fibers: 1.15 against 1.23 ms at 76 M nonzeros with 5.9 leaves per fiber, 0.69 against
 // 0.73 ms at 40 M with 4.7, but 0.86 against 0.84 at 40 M with 3.6 and 0.41 against 0.36 at 20 M.  The plan options
@@ -366,14 +370,27 @@ static conststn_status build_mttkrp3_hot(conststn_plan_s *plan, bool asked) {
 conststn_status build_mttkrp3_tables(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t nnz = X->nnz;
+    // leaves per chunk where leaves are counted: at least about 64 K lane groups, two partial rows per chunk a small
+    // part of the traffic; in whole blocks of 16
+    int64_t q = plan->opt("mttkrp_chunk", 0);
+    if (q <= 0) q = std::max<int64_t>(64, std::min<int64_t>(nnz / 262144, 512));
+    q = div_up(q, 16) * 16;
+    if (!plan->use_records) {
+        MttkrpPart &P = plan->part[0];
+        P.slices = X->nodes[0];
+        P.fibers = X->nodes[1];
+        P.nnz = nnz;
+        P.chunk_q = q;
+        if (nnz == 0) return CONSTSTN_OK;
+        CST_TRY(build_chunk_tables(P, X->ptr[0].p, X->ptr[1].p, plan->rank_of_level[1], q));
+        CST_HIP(hipDeviceSynchronize());
+        return CONSTSTN_OK;
+    }
     const bool asked = plan->options.count("mttkrp_dual") || plan->options.count("mttkrp_hot");
     const bool large = nnz >= (int64_t(1) << 25) && nnz / 9 * 2 >= X->nodes[1];
     if (plan->rank_of_level[1] == 32 && nnz > 0 && (asked || large) && plan->opt("mttkrp_split", 1) == 1 &&
         plan->opt("mttkrp_dual", 44) != 0) {
-        // leaves per chunk: at least about 64 K lane groups, two partial rows per chunk a small part of the traffic
-        int64_t q = plan->opt("mttkrp_chunk", 0);
-        if (q <= 0) q = std::max<int64_t>(64, std::min<int64_t>(nnz / 262144, 512));
-        plan->chunk_q = div_up(q, 16) * 16;              // leaves are read 16 at a time
+        plan->chunk_q = q;
         CST_TRY(build_mttkrp3_hot(plan, asked));
         if (plan->split) return CONSTSTN_OK;
     }

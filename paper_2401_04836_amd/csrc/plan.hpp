@@ -142,7 +142,8 @@ struct SpCell {
 // One of the two sub-tensors of the split rank-32 MTTKRP path: the leaves whose factor row is
 // "hot" (kept in LDS) or the rest.  X = X_hot + X_cold and the contraction is linear in X, so each
 // part is a CSF tensor of its own (only the slices and fibers that keep a leaf) with its own
-// chunk tables; the second part accumulates onto the output of the first.
+// chunk tables; the second part accumulates onto the output of the first.  The form that walks the CSF itself
+// uses the chunk tables of the first part alone.
 struct MttkrpPart {
     int64_t slices = 0, fibers = 0, nnz = 0;
     DevBuf<int32_t> row_of_slice, idx1;
@@ -338,6 +339,8 @@ conststn_status launch_record_stream(const conststn_plan_s *plan, const double *
 // kernels_*.hip
 conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const *dense, double *out,
                                hipStream_t stream);
+conststn_status launch_mttkrp3_csf(const conststn_plan_s *plan, const double *const *dense, double *out,
+                                   hipStream_t stream);
 conststn_status launch_ttmc3(const conststn_plan_s *plan, const double *const *dense, double *out,
                              hipStream_t stream);
 // the same with the partial row blocks in the library's static scratch array instead of the plan's buffer

@@ -69,3 +69,59 @@ def test_ttmc3_every_mode_and_level_order(levels, ranks):
     if levels[1] > levels[2]:                                       # GPU rows are [middle, leaf]
         out = out.permute(0, 2, 1).contiguous()
     assert compare(out, want, S_abs) <= TOL
+
+
+# the three trees whose result is indexed by a level below the root, X stored i > j > k
+NOT_THE_ROOT = [("T[i,j,r] = X[i,j,k] * C[k,r] | i,j,k,r ; M[j,r] = T[i,j,r] * A[i,r] | i,j,r", 1, ("C", "A")),
+                ("T[i,j,k,r] = X[i,j,k] * A[i,r] | i,j,k,r ; M[k,r] = T[i,j,k,r] * B[j,r] | i,j,k,r", 2, ("A", "B")),
+                ("T[i,j,k,r] = X[i,j,k] * B[j,r] | i,j,k,r ; M[k,r] = T[i,j,k,r] * A[i,r] | i,j,k,r", 2, ("B", "A"))]
+
+
+@pytest.mark.parametrize("rank", [1, 2, 128])
+@pytest.mark.parametrize("text,mode,names", NOT_THE_ROOT)
+def test_mttkrp_of_a_level_below_the_root_at_the_smallest_ranks(text, mode, names, rank):
+    """The result is [extent of its mode, rank] and the same in every run; compact rows are those of its own mode."""
+    wl = w.make(2, small=True, dims=(301, 211, 503), nnz=20_003, rank=rank)
+    X = wl.sparse["X"]
+    F = dict(zip("ABC", _factors(79, X.dims, (rank,) * 3)))
+    _say("mttkrp of level %d, rank %d" % (mode, rank))
+    dc, dv = to_dev(X)
+    csf = cst.build_csf(dc, dv, X.dims, [0, 1, 2])
+    dev = [F[n].cuda() for n in names]
+    c, v = X.numpy()
+    Fa, Fb = (F["ABC"[m]].numpy() for m in range(3) if m != mode)
+    want = oracle.mttkrp3(c, v, X.dims, Fa, Fb, mode)
+    S_abs = oracle.mttkrp3_abs(c, v, X.dims, Fa, Fb, mode)
+    for flags in (0, cst.OUT_COMPACT):
+        pl = cst.plan(text, [("X", csf)] + list(zip(names, dev)), flags=flags)
+        rows = pl.output_rows() if flags else None
+        assert (pl.n_rows, pl.row_elems) == (len(np.unique(c[mode])) if flags else X.dims[mode], rank)
+        pl.check()
+        out = cst.execute(pl, dev).reshape(pl.n_rows, rank)
+        assert compare(out, want, S_abs, rows=rows) <= TOL
+        for _ in range(5):
+            assert torch.equal(cst.execute(pl, dev).reshape(pl.n_rows, rank), out)
+
+
+def test_mttkrp_over_a_mode_of_more_than_2_28_indices():
+    """A middle mode beyond what a 28-bit index names, as the root's neighbour and below the result's level."""
+    dims, n, R = ((1 << 28) + 77, 40, 50), 30_011, 2
+    g = torch.Generator(device="cuda").manual_seed(5)
+    c = [torch.randint(0, d, (n,), generator=g, device="cuda", dtype=torch.int32) for d in dims]
+    c[0][:4] = torch.tensor([0, dims[0] - 1, (1 << 28) - 1, 1 << 28], dtype=torch.int32)
+    v = torch.rand(n, generator=g, dtype=torch.float64, device="cuda") + 0.5
+    A = torch.rand(dims[0], R, generator=g, dtype=torch.float64, device="cuda")
+    B, C = (torch.rand(d, R, generator=g, dtype=torch.float64, device="cuda") for d in dims[1:])
+    _say("mttkrp over a mode of %d indices" % dims[0])
+    a, b, ck = (f[x.long()] for f, x in zip((A, B, C), c))
+    csf = cst.build_csf(c, v, dims, [1, 0, 2], flags=cst.COALESCE_DUPS)                    # j > i > k
+    for text, names, terms, at, rows in (
+            ("T[j,i,r] = X[j,i,k] * C[k,r] | j,i,k,r ; M[j,r] = T[j,i,r] * A[i,r] | j,i,r", ("C", "A"), v[:, None] * ck * a, c[1], 40),
+            ("T[j,i,k,r] = X[j,i,k] * A[i,r] | j,i,k,r ; M[k,r] = T[j,i,k,r] * B[j,r] | j,i,k,r", ("A", "B"), v[:, None] * a * b, c[2], 50)):
+        dev = [dict(A=A, B=B, C=C)[m] for m in names]
+        pl = cst.plan(text, [("X", csf)] + list(zip(names, dev)))
+        assert (pl.n_rows, pl.row_elems) == (rows, R)
+        pl.check()
+        got = cst.execute(pl, dev).reshape(rows, R)
+        want = torch.zeros(rows, R, dtype=torch.float64, device="cuda").index_add_(0, at.long(), terms)
+        assert (got / want - 1).abs().max().item() <= 1e-12        # sums of about 700 positive terms
