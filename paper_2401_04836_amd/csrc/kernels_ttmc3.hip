@@ -284,7 +284,10 @@ ttmc3_mfma_kernel(Ttmc3RowArgs a) {
 // the tiles (kRaggedEven, kRaggedOdd): a lane beyond the end of a factor row reads the row's last two entries
 // instead -- the rows and columns of the row block that they feed are beyond the ranks and never stored, so
 // neither the gathers nor the matrix instructions need a test -- and only the stores are masked.  An odd rank
-// leaves one lane with half a pair; it moves the second entry it read into the first place.
+// leaves one lane with half a pair; it moves the second entry it read into the first place.  At these ranks a row
+// shorter than the longest of its K-step, or absent, takes no product of the leaf that it repeats, so that an
+// infinite factor row makes sums infinite and never NaN, as in the general kernel (full tiles multiply it by 0).
+// Only K-steps of rows of different lengths test for that: 631 -> 639 us at the size below.
 // Before, such ranks took the general kernel, which sums one leaf at a time per wavefront: 7.1 ms at
 // 12 007 x 9 001 x 28 999, 5 M nonzeros, ranks 50 x 50.
 // (A ring of packets with ready flags instead of the barrier, letting the producers
@@ -325,6 +328,11 @@ __device__ __forceinline__ void lds_barrier() {
 enum RankFit { kFullTiles = 0, kRaggedEven = 1, kRaggedOdd = 2 };
 typedef double v2f64_u __attribute__((ext_vector_type(2), aligned(8)));   // a pair at any element
 
+// x where `keep`, otherwise some finite number (x without its sign and exponent), for a product with 0
+__device__ __forceinline__ double finite_or(bool keep, double x) {
+    return __hiloint2double(keep ? __double2hiint(x) : 0, __double2loint(x));
+}
+
 template <int PN, int NC, int NP, int FIT>
 __global__ void __launch_bounds__(64 * (NP + NC))
 ttmc3_stream_kernel(Ttmc3StreamArgs a) {
@@ -354,7 +362,7 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
 #pragma unroll
         for (int q = 0; q < NC; ++q) u3_at[q] = FIT == kFullTiles ? 32 * q + 2 * c : min(32 * q + 2 * c, R3 - 2);
         struct Rows { int64_t leaf; int cnt; int32_t j; bool live; };
-        struct Feed { int32_t k; double v; int maxcnt; v2f64 av[APV]; };
+        struct Feed { int32_t k; double v; int cnt, maxcnt; bool even; v2f64 av[APV]; };
         typedef int v4i32 __attribute__((ext_vector_type(4)));
         auto kstep_of = [&](int r) -> KStepDesc {
             int g = ka + r * NP + wave;
@@ -380,6 +388,7 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
             const double v = a.vals[r.leaf + ci];
             const bool keep = (c < r.cnt) & r.live;     // no short circuit: a branch here draws the load under it
             f.v = keep ? v : 0.0;
+            f.cnt = r.live ? r.cnt : 0;
             const double *src = a.U2 + int64_t(r.j) * R2;
 #pragma unroll
             for (int x = 0; x < APV; ++x) {
@@ -393,6 +402,7 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
             const int c0 = __builtin_amdgcn_readlane(r.cnt, 0), c1 = __builtin_amdgcn_readlane(r.cnt, 16),
                       c2 = __builtin_amdgcn_readlane(r.cnt, 32), c3 = __builtin_amdgcn_readlane(r.cnt, 48);
             f.maxcnt = max(max(c0, c1), max(c2, c3));
+            f.even = FIT == kFullTiles || (f.maxcnt == min(min(c0, c1), min(c2, c3)) && __builtin_amdgcn_readlane(int(r.live), 48));
             return f;
         };
         KStepDesc d1 = kstep_of(1), d2 = kstep_of(2);
@@ -425,7 +435,7 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
             // leaf steps t0 .. t0+N-1 of the four rows: 2N gathers in flight, then the products.  N is exact
             // (not rounded up to four): most K-steps of a power-law tensor hold rows of a single leaf, and
             // every gather instruction counts.
-            auto batch = [&](auto T0, auto NN) {
+            auto batch = [&](auto T0, auto NN, auto EVEN) {
                 constexpr int t0 = decltype(T0)::value, N = decltype(NN)::value;
                 int32_t kk[4] = {row_bcast_i32<t0>(cur.k), 0, 0, 0};
                 double vv[4] = {row_bcast_f64<t0>(cur.v), 0.0, 0.0, 0.0};
@@ -448,29 +458,35 @@ ttmc3_stream_kernel(Ttmc3StreamArgs a) {
                 for (int u = 0; u < N; ++u)
 #pragma unroll
                     for (int q = 0; q < NC; ++q) {
-                        t[q][0] = fma(vv[u], uu[u][q][0], t[q][0]);
-                        t[q][1] = fma(vv[u], uu[u][q][1], t[q][1]);
+                        t[q][0] = fma(vv[u], EVEN ? uu[u][q][0] : finite_or(t0 + u < cur.cnt, uu[u][q][0]), t[q][0]);
+                        t[q][1] = fma(vv[u], EVEN ? uu[u][q][1] : finite_or(t0 + u < cur.cnt, uu[u][q][1]), t[q][1]);
                     }
             };
-            auto chunk = [&](auto T0, int n) {
+            auto chunk = [&](auto T0, int n, auto EVEN) {
                 using I1 = std::integral_constant<int, 1>;
                 using I2 = std::integral_constant<int, 2>;
                 using I3 = std::integral_constant<int, 3>;
                 using I4 = std::integral_constant<int, 4>;
-                if (n >= 4) batch(T0, I4{});
-                else if (n == 3) batch(T0, I3{});
-                else if (n == 2) batch(T0, I2{});
-                else batch(T0, I1{});
+                if (n >= 4) batch(T0, I4{}, EVEN);
+                else if (n == 3) batch(T0, I3{}, EVEN);
+                else if (n == 2) batch(T0, I2{}, EVEN);
+                else batch(T0, I1{}, EVEN);
             };
             const int maxcnt = cur.maxcnt;
-            chunk(std::integral_constant<int, 0>{}, maxcnt);
-            if (maxcnt > 4) {
-                chunk(std::integral_constant<int, 4>{}, maxcnt - 4);
-                if (maxcnt > 8) {
-                    chunk(std::integral_constant<int, 8>{}, maxcnt - 8);
-                    if (maxcnt > 12) chunk(std::integral_constant<int, 12>{}, maxcnt - 12);
+            auto leaves = [&](auto EVEN) {
+                chunk(std::integral_constant<int, 0>{}, maxcnt, EVEN);
+                if (maxcnt > 4) {
+                    chunk(std::integral_constant<int, 4>{}, maxcnt - 4, EVEN);
+                    if (maxcnt > 8) {
+                        chunk(std::integral_constant<int, 8>{}, maxcnt - 8, EVEN);
+                        if (maxcnt > 12) chunk(std::integral_constant<int, 12>{}, maxcnt - 12, EVEN);
+                    }
                 }
-            }
+            };
+            // rows of a slice lie from long to short, so four of one length are the rule and need no tests
+            if constexpr (FIT == kFullTiles) leaves(std::true_type{});
+            else if (cur.even) leaves(std::true_type{});
+            else leaves(std::false_type{});
             if (FIT == kRaggedOdd) {
 #pragma unroll
                 for (int q = 0; q < NC; ++q) t[q][0] = 32 * q + 2 * c == R3 - 1 ? t[q][1] : t[q][0];

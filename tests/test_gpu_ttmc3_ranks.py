@@ -39,3 +39,34 @@ def test_ranks_beside_the_tile_edges(ranks, dims, nnz):
         # sums of at most 3000 products of three factors in any order: 3002 roundings of 1.1e-16
         assert oracle.rel_err(got[shift:shift + n].reshape(want.shape), want, S_abs) <= 3.4e-13
         assert (got[:shift] == 7.0).all() and (got[shift + n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("ranks", [(2, 2), (7, 10), (10, 7), (33, 64), (50, 50), (63, 63)])
+def test_rows_that_are_not_finite(ranks):
+    """Positive terms, and a few entries of the factors that are infinite: a sum with an infinite term is infinite
+    (never NaN from an absent leaf or row that is multiplied by 0), every other one is what it is without them."""
+    R2, R3 = ranks
+    dims = (40, 30, 50)
+    rng = np.random.default_rng(R2 * 100 + R3)
+    keys = rng.permutation(np.unique(rng.integers(0, np.prod(dims), 6000)))
+    c = [x.astype(np.int32) for x in np.unravel_index(keys, dims)]
+    v = rng.uniform(0.5, 1, len(keys))
+    U2, U3 = rng.uniform(0.5, 1, (dims[1], R2)), rng.uniform(0.5, 1, (dims[2], R3))
+    clean = oracle.ttmc3(c, v, dims, U2, U3, 0)
+    hit2, hit3 = np.zeros_like(U2), np.zeros_like(U3)
+    for hit in (hit2, hit3):
+        hit[rng.integers(0, hit.shape[0], 2), rng.integers(0, hit.shape[1], 2)] = 1.0
+        hit[-1, -1] = 1.0
+    ones = np.ones_like
+    struct = lambda a, b: oracle.ttmc3(c, ones(v), dims, a, b, 0)
+    infinite = struct(hit2, ones(U3)) + struct(ones(U2), hit3) > 0
+    U2[hit2 > 0], U3[hit3 > 0] = np.inf, np.inf
+    print("[case] ranks %s with infinite entries" % (ranks,), flush=True)
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2])
+    u2, u3 = torch.from_numpy(U2).cuda(), torch.from_numpy(U3).cuda()
+    for opts in (dict(ttmc3_rowsplit=8), {}, dict(ttmc3_mfma=0)):
+        pl = cst.plan(S.TTMC3, [("X", csf), ("U3", u3), ("U2", u2)], options=opts)
+        got = cst.execute(pl, [u3, u2]).cpu().numpy().reshape(clean.shape)
+        assert not np.isnan(got).any(), opts
+        np.testing.assert_array_equal(np.isinf(got), infinite)
+        np.testing.assert_allclose(got[~infinite], clean[~infinite], rtol=1e-12)
