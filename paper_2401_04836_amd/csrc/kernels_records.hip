@@ -6,6 +6,7 @@
 //     leaf             t   += v * F_leaf[index]
 //     end of a fiber   acc += t * F_1[index], t = 0         (order 4: u += t * F_2[index], t = 0)
 //     end of a node    acc += u * F_1[index], u = 0         (order 4 only)
+//     nothing          an end whose vector the chunks before it have used up; reads a row of zeros
 // and the last record of a slice is marked.  The stream is cut into chunks of q records; LPR lanes own a chunk
 // and hold NV pairs of rank entries each.  The four (eight) lane groups of a wavefront walk their chunks in
 // lock step, one record per step: a step is NV gathers in which every group takes part, whatever its record is.
@@ -32,7 +33,8 @@ namespace cst {
 
 namespace {
 
-constexpr uint32_t kRecFiberEnd = 1u << 30, kRecNodeEnd = 2u << 30, kRecSliceEnd = 1u << 29, kRecIndex = (1u << 28) - 1;
+constexpr uint32_t kRecFiberEnd = 1u << 30, kRecNodeEnd = 2u << 30, kRecNothing = 3u << 30, kRecSliceEnd = 1u << 29,
+                   kRecIndex = (1u << 28) - 1;
 constexpr uint32_t kChunkInside = 1u << 31;           // the chunk begins inside its first slice
 
 typedef double v2f64_u __attribute__((ext_vector_type(2), aligned(8)));
@@ -50,6 +52,7 @@ struct RecordArgs {
     const int32_t *open1, *open2;                      // rows of the fiber / node left open at a chunk's end, or -1
     const int32_t *row_of_slice;
     const double *f0, *f1, *f2;                        // factors of the leaves, of the fibers, of the nodes above them
+    const double *zeros;                               // R zeros, the row of a record that adds nothing
     double *out, *partial;
 };
 
@@ -124,6 +127,7 @@ records_kernel(RecordArgs a) {
         const double *base = a.f0;
         if (kind == 1) base = a.f1;
         if (LEVELS == 3 && kind == 2) base = a.f2;
+        if (kind == 3) base = a.zeros;
         const uint64_t addr = reinterpret_cast<uint64_t>(base) + uint64_t(code_cur & kRecIndex) * row_bytes;
         const int addr_lo = int(uint32_t(addr)), addr_hi = int(uint32_t(addr >> 32));
         const int val_lo = __double2loint(val_cur), val_hi = __double2hiint(val_cur);
@@ -417,11 +421,23 @@ record_chunks_kernel(RecordFill a, int64_t n_chunks, int64_t q, uint32_t *chunk_
     const int64_t s = parent_of(a.slice_rec, a.slices, r0);
     chunk_slice[c] = uint32_t(s) | (a.slice_rec[s] == r0 ? 0u : kChunkInside);
     const uint32_t kind = a.code[r1 - 1] >> 30;
-    int32_t o1 = -1, o2 = -1;
+    int32_t o1 = -1, o2 = -1;                          // (nothing is open behind the last record)
     if (kind == 0) o1 = a.idx_fiber[first_end(a.fibers, r1, [&](int64_t f) { return fiber_end_record(a, f); })];
-    if (a.nodes && kind != 2) o2 = a.idx_node[first_end(a.nodes, r1, [&](int64_t n) { return node_end_record(a, n); })];
+    if (a.nodes && kind != 2 && r1 < a.n_rec) o2 = a.idx_node[first_end(a.nodes, r1, [&](int64_t n) { return node_end_record(a, n); })];
     open1[c] = o1;
     if (open2) open2[c] = o2;
+}
+
+// A chunk that begins with the end of a fiber or of a node (or, at order 4, of both) has added nothing to that vector,
+// and the chunk before has taken it with the row: 0 times the row would make NaN of an infinite one.
+__global__ void __launch_bounds__(256)
+record_spent_ends_kernel(int64_t n_chunks, int64_t q, int64_t n_rec, uint32_t *code) {
+    const int64_t c = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (c >= n_chunks) return;
+    for (int64_t r = c * q; r < c * q + 2 && r < n_rec; ++r) {
+        if (code[r] >> 30 == 0) break;
+        code[r] = kRecNothing | (code[r] & kRecSliceEnd);
+    }
 }
 
 // 0: inside one chunk; 1: shared by a few chunks; 2: by many
@@ -499,6 +515,9 @@ check_records_kernel(RecordFill a, int64_t dims1, int64_t q, int64_t n_chunks, i
             want = t == end_of(f) ? (kRecFiberEnd | uint32_t(a.idx_fiber[f])) : uint32_t(a.idx_leaf[t - f - nf]);
         }
         const int64_t s = parent_of(a.slice_rec, a.slices, t);
+        // the ends that open a chunk (two of them at order 4: the record before is in the chunk and an end, too)
+        const int64_t in_chunk = t % q;
+        if (want >> 30 != 0 && (in_chunk == 0 || (in_chunk == 1 && a.code[t - 1] >> 30 == 3))) want = kRecNothing;
         if (a.slice_rec[s + 1] == t + 1) want |= kRecSliceEnd;
         if (a.code[t] != want) bad |= bad_code;
     } else if (t < a.total && (a.code[t] >> 29 != 0 || a.out_vals[t] != 0.0)) bad |= bad_code;
@@ -622,6 +641,10 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     record_chunks_kernel<<<blocks_for(rs.n_chunks), dim3(256)>>>(a, rs.n_chunks, q, rs.chunk_slice.p, rs.open1.p,
                                                                   n == 4 ? rs.open2.p : nullptr);
     CST_HIP(hipGetLastError());
+    record_spent_ends_kernel<<<blocks_for(rs.n_chunks), dim3(256)>>>(rs.n_chunks, q, a.n_rec, rs.code.p);
+    CST_HIP(hipGetLastError());
+    CST_TRY(rs.zeros.alloc(size_t(R)));
+    CST_TRY(zero_fill(rs.zeros.p, R, hipStream_t(0)));
     rows_of_slices_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, X->idx[0].p, plan->compact ? 1 : 0, rs.row_of_slice.p);
     CST_HIP(hipGetLastError());
     DevBuf<int64_t> flag;
@@ -668,6 +691,7 @@ conststn_status launch_record_stream(const conststn_plan_s *plan, const double *
     a.open1 = rs.open1.p;
     a.open2 = rs.open2.p;
     a.row_of_slice = rs.row_of_slice.p;
+    a.zeros = rs.zeros.p;
     a.f0 = dense[plan->factor_of_level[n - 1]];
     a.f1 = dense[plan->factor_of_level[n - 2]];
     a.f2 = n == 4 ? dense[plan->factor_of_level[1]] : nullptr;

@@ -170,6 +170,7 @@ struct RecordStream {
     DevBuf<uint32_t> chunk_slice;          // [n_chunks] slice of the chunk's first record; bit 31: it began before
     DevBuf<int32_t> open1, open2;          // [n_chunks] factor row of the fiber / node the chunk leaves open, or -1
     DevBuf<double> partial;                // [n_chunks x 2 x R]
+    DevBuf<double> zeros;                  // [R] the row of a record that adds nothing
     DevBuf<int32_t> heavy, light, empty;   // slices shared by many / by a few chunks; result rows without nonzeros
     int64_t n_heavy = 0, n_light = 0, n_empty = 0;
     int segments = 1;                      // workgroups that share a heavy slice

@@ -68,3 +68,32 @@ def test_order4(rank, dims, nnz, heavy, chunk):
     want, S_abs = nary.contract(c, v, "ijkl", f, "ir", ext), nary.contract_abs(c, v, "ijkl", f, "ir", ext)
     assert oracle.rel_err(got, want, S_abs) <= 1.0e-12       # at most 9000 products of four factors per sum
 
+
+
+@pytest.mark.parametrize("rank", [2, 7, 25, 32, 50, 128])
+@pytest.mark.parametrize("order", [3, 4])
+def test_factor_rows_that_are_not_finite(order, rank):
+    """Positive terms, and a few infinite entries in every factor: the sums with such a term are infinite wherever the
+    chunks end -- a chunk that begins with the end of a fiber or node adds nothing of it -- and the others as without."""
+    dims = (40, 8, 30, 20)[:order] if order == 4 else (40, 30, 50)
+    c, _, rng = _tensor(dims, 3000, 1500, 300 + rank)
+    v = rng.uniform(0.5, 1, len(c[0]))
+    F = [rng.uniform(0.5, 1, (d, rank)) for d in dims[1:]]
+    hits = [np.zeros_like(f) for f in F]
+    for h in hits:
+        h[rng.integers(0, h.shape[0], 2), rng.integers(0, rank, 2)] = 1.0
+    letters = "ijkl"[:order]
+    ext = {"i": dims[0], "r": rank}
+    con = lambda vals, fs: nary.contract(c, vals, letters, [(f, m + "r") for f, m in zip(fs, letters[1:])], "ir", ext)
+    clean = con(v, F)
+    ones = [np.ones_like(f) for f in F]
+    infinite = sum(con(np.ones_like(v), ones[:m] + [h] + ones[m + 1:]) for m, h in enumerate(hits)) > 0
+    for f, h in zip(F, hits):
+        f[h > 0] = np.inf
+    names = [("B", F[0]), ("C", F[1])] if order == 3 else [("B", F[0]), ("C", F[1]), ("D", F[2])]
+    for chunk in (16, 32, 48, 0):
+        print("[case] order %d rank %d chunk %d with infinite entries" % (order, rank, chunk), flush=True)
+        got, pl = _run(S.MTTKRP3 if order == 3 else T4, c, v, dims, names[::-1], dict(mttkrp_chunk=chunk, **({"mttkrp_split": 0} if order == 3 else {})))
+        assert not np.isnan(got).any()
+        np.testing.assert_array_equal(np.isinf(got), infinite)
+        np.testing.assert_allclose(got[~infinite], clean[~infinite], rtol=1e-12)
