@@ -916,6 +916,43 @@ static conststn_status order_items_by_cost(conststn_plan_s *plan) {
     return CONSTSTN_OK;
 }
 
+// counts[k] = partial row blocks of slices cut into items of c.rows[k] rows
+struct SplitChoices { int n; int64_t rows[16]; };
+__global__ void __launch_bounds__(256)
+count_partials_kernel(int64_t slices, const int64_t *__restrict__ slice_row, SplitChoices c, unsigned long long *counts) {
+    const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t len = s < slices ? slice_row[s + 1] - slice_row[s] : 0;
+    for (int k = 0; k < c.n; ++k) {
+        int64_t n = len > c.rows[k] ? (len + c.rows[k] - 1) / c.rows[k] : 0;
+        for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off, 64);
+        if (threadIdx.x % 64 == 0 && n > 0) atomicAdd(&counts[k], (unsigned long long)n);
+    }
+}
+
+// Rows per item at ranks that the general kernel had: its items are up to `leaves` leaves long (4096 by default), so
+// plans whose partial row blocks fitted the static area then must have items long enough that they still do.  `split`
+// becomes the smallest of itself, 5/4 of it, ... and `leaves` for which they fit, and stays where not even the last
+// does: leaves are no fewer than rows, so the general kernel's did not fit either.  (Longer items balance worse: mean
+// of six tensors of 5 M nonzeros at 50 x 50: 623 us with 256 rows, 626 with 320, 635 with 512, 639 with 640.)
+static conststn_status rows_per_item(const conststn_plan_s *plan, int64_t leaves, int64_t &split) {
+    const int64_t fit = int64_t(CONSTSTN_STATIC_SCRATCH_BYTES) / (plan->row_elems * 8);
+    if (2 * plan->n_rows_tab / split <= fit) return CONSTSTN_OK;             // a slice of len > split rows: at most 2 len / split items
+    SplitChoices c{};
+    for (int64_t rows = split; rows < leaves && c.n < 15; rows += std::max<int64_t>(rows / 4, 1)) c.rows[c.n++] = rows;
+    c.rows[c.n++] = leaves;
+    DevBuf<unsigned long long> counts;
+    CST_TRY(counts.alloc(16));
+    unsigned long long n[16] = {0};
+    CST_HIP(hipMemcpy(counts.p, n, sizeof(n), hipMemcpyHostToDevice));
+    const int64_t slices = plan->X->nodes[0];
+    count_partials_kernel<<<dim3(unsigned(div_up(slices, 256))), dim3(256)>>>(slices, plan->slice_row.p, c, counts.p);
+    CST_HIP(hipGetLastError());
+    CST_HIP(hipMemcpy(n, counts.p, sizeof(n), hipMemcpyDeviceToHost));
+    for (int k = 0; k < c.n; ++k)
+        if (int64_t(n[k]) <= fit) { split = c.rows[k]; break; }
+    return CONSTSTN_OK;
+}
+
 conststn_status build_ttmc_tables(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t slices = X->nodes[0];
@@ -940,7 +977,9 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
         unit_ptr = plan->slice_row.p;
         // larger items mean fewer partial row blocks for the fix-up pass to add; keep at least
         // about 8192 items for the chip
+        const int64_t leaves = std::max<int64_t>(split, 4096);
         split = plan->opt("ttmc3_rowsplit", std::min<int64_t>(std::max<int64_t>(plan->n_rows_tab / 8192, 256), 2048));
+        if (!rows16 && !plan->options.count("ttmc3_rowsplit")) CST_TRY(rows_per_item(plan, leaves, split));
         order = 0;                                   // items carry no 'first fiber'
     }
     // (extents below 2^25: the matrix-core kernel reaches the factor rows with 32-bit byte offsets)

@@ -53,3 +53,27 @@ def test_execute_static_rejects_what_it_cannot_take():
     with pytest.raises(cst.ConststnError) as e:
         cst.execute_static(pl, [C, B], out)
     assert e.value.status_name == "EUNSUPPORTED"
+
+
+@pytest.mark.parametrize("ranks", [(63, 63), (50, 50), (64, 33)])
+def test_execute_static_takes_a_flat_tensor_at_any_ranks(ranks):
+    """300 slices of 3 300 leaves each, most of them in fibers of their own: no slice is long enough that its partial
+    row blocks must exceed the array."""
+    g = torch.Generator(device="cuda").manual_seed(11)
+    dims, nnz = (300, 20_000, 500), 1_000_000
+    keys = torch.unique(torch.randint(0, dims[0] * dims[1] * dims[2], (nnz,), generator=g, device="cuda"))
+    keys = keys[torch.randperm(keys.numel(), generator=g, device="cuda")]
+    coords = [x.to(torch.int32) for x in (keys // (dims[1] * dims[2]), keys // dims[2] % dims[1], keys % dims[2])]
+    vals = torch.rand(keys.numel(), generator=g, dtype=torch.float64, device="cuda")
+    U2, U3 = (torch.rand(d, r, generator=g, dtype=torch.float64, device="cuda") for d, r in zip(dims[1:], ranks))
+    print("[case] execute_static, flat tensor, ranks %s" % (ranks,), flush=True)
+    csf = cst.build_csf(coords, vals, dims, [0, 1, 2])
+    pl = cst.plan(S.TTMC3, [("X", csf), ("U3", U3), ("U2", U2)])
+    want = cst.execute(pl, [U3, U2])
+    got = torch.full_like(want, float("nan"))
+    cst.execute_static(pl, [U3, U2], got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    general = cst.plan(S.TTMC3, [("X", csf), ("U3", U3), ("U2", U2)], options=dict(ttmc3_mfma=0))
+    # positive terms, at most 3 500 per sum
+    assert (cst.execute(general, [U3, U2]) / got - 1).abs().max().item() <= 4e-13
