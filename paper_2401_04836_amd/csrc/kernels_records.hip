@@ -596,7 +596,7 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     const int lanes = R <= 16 ? 8 : 16;
     int64_t q = plan->opt("mttkrp_chunk", 0);
     if (q <= 0) q = std::max<int64_t>(32, std::min<int64_t>(a.n_rec / (int64_t(plan->n_cus) * 4 * 12 * (64 / lanes)), 512));
-    q = div_up(q, 16) * 16;
+    q = div_up(std::min<int64_t>(q, std::max<int64_t>(a.n_rec, 1)), 16) * 16;      // (the last chunk is filled up)
     rs.q = q;
     if (!plan->compact) {
         DevBuf<int64_t> flag;

@@ -97,3 +97,20 @@ def test_factor_rows_that_are_not_finite(order, rank):
         assert not np.isnan(got).any()
         np.testing.assert_array_equal(np.isinf(got), infinite)
         np.testing.assert_allclose(got[~infinite], clean[~infinite], rtol=1e-12)
+
+
+def test_chunks_longer_than_the_stream():
+    """A chunk length far above the number of records gives one chunk of them, not one filled up to that length."""
+    dims, rank = (40, 30, 50), 32
+    c, v, rng = _tensor(dims, 3000, 0, 9)
+    B, C = rng.uniform(-1, 1, (dims[1], rank)), rng.uniform(-1, 1, (dims[2], rank))
+    print("[case] chunks of 2^24 records over %d nonzeros" % len(v), flush=True)
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2])
+    f = [torch.from_numpy(x).cuda() for x in (C, B)]
+    free = torch.cuda.mem_get_info()[0]
+    pl = cst.plan(S.MTTKRP3, [("X", csf), ("C", f[0]), ("B", f[1])], options=dict(mttkrp_chunk=1 << 24))
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+    pl.check()
+    got = cst.execute(pl, f).cpu().numpy().reshape(dims[0], rank)
+    # at most 1500 products of three factors per sum
+    assert oracle.rel_err(got, oracle.mttkrp3(c, v, dims, B, C, 0), oracle.mttkrp3_abs(c, v, dims, B, C, 0)) <= 1.7e-13
