@@ -598,10 +598,12 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     if (q <= 0) q = std::max<int64_t>(32, std::min<int64_t>(a.n_rec / (int64_t(plan->n_cus) * 4 * 12 * (64 / lanes)), 512));
     q = div_up(std::min<int64_t>(q, std::max<int64_t>(a.n_rec, 1)), 16) * 16;      // (the last chunk is filled up)
     rs.q = q;
-    if (!plan->compact) {
-        DevBuf<int64_t> flag;
-        CST_TRY(flag.alloc(size_t(plan->out_rows)));
-        if (a.slices < plan->out_rows) {
+    if (!plan->compact && a.slices < plan->out_rows) {
+        // up to 2^24 empty rows the fix-up launch clears them (128 threads each at most, and a launch takes fewer than 2^32)
+        rs.zero_all = plan->out_rows - a.slices > (int64_t(1) << 24);
+        if (!rs.zero_all) {
+            DevBuf<int64_t> flag;
+            CST_TRY(flag.alloc(size_t(plan->out_rows)));
             empty_rows_kernel<<<blocks_for(plan->out_rows), dim3(256)>>>(plan->out_rows, a.slices, X->idx[0].p, flag.p);
             CST_HIP(hipGetLastError());
             CST_TRY(list_of_flags(flag, plan->out_rows, rs.empty, &rs.n_empty));
@@ -697,6 +699,7 @@ conststn_status launch_record_stream(const conststn_plan_s *plan, const double *
     a.f2 = n == 4 ? dense[plan->factor_of_level[1]] : nullptr;
     a.out = out;
     a.partial = rs.partial.p;
+    if (rs.zero_all) CST_TRY(zero_fill(out, plan->out_rows * plan->row_elems, stream));
     if (rs.n_chunks > 0) {
         ProfScope prof(plan, stream);
         if (rs.levels == 3) launch_records_kernel<3>(a, stream);

@@ -173,6 +173,7 @@ struct RecordStream {
     DevBuf<double> zeros;                  // [R] the row of a record that adds nothing
     DevBuf<int32_t> heavy, light, empty;   // slices shared by many / by a few chunks; result rows without nonzeros
     int64_t n_heavy = 0, n_light = 0, n_empty = 0;
+    bool zero_all = false;                 // too many empty rows for a list: the whole result is cleared first
     int segments = 1;                      // workgroups that share a heavy slice
     DevBuf<double> heavy_partial;          // [n_heavy x segments x R]
 };

@@ -114,3 +114,27 @@ def test_chunks_longer_than_the_stream():
     got = cst.execute(pl, f).cpu().numpy().reshape(dims[0], rank)
     # at most 1500 products of three factors per sum
     assert oracle.rel_err(got, oracle.mttkrp3(c, v, dims, B, C, 0), oracle.mttkrp3_abs(c, v, dims, B, C, 0)) <= 1.7e-13
+
+
+@pytest.mark.parametrize("rows,rank", [((1 << 24) + 40, 3), ((1 << 28) + 40, 2)])
+def test_more_empty_rows_than_a_launch_has_threads_for(rows, rank):
+    """A root mode of 2^24 to 2^28 indices of which forty hold anything: every other row is cleared."""
+    dims = (rows, 30, 50)
+    rng = np.random.default_rng(rows)
+    at = np.sort(rng.choice(rows, 40, replace=False))
+    at[-1] = rows - 1
+    n = 4000
+    i = rng.integers(0, 40, n)
+    keys = np.unique((i * 30 + rng.integers(0, 30, n)) * 50 + rng.integers(0, 50, n))
+    c = [x.astype(np.int32) for x in np.unravel_index(keys, (40, 30, 50))]
+    v, B, C = rng.uniform(-1, 1, len(keys)), rng.uniform(-1, 1, (30, rank)), rng.uniform(-1, 1, (50, rank))
+    want, S_abs = oracle.mttkrp3(c, v, (40, 30, 50), B, C, 0), oracle.mttkrp3_abs(c, v, (40, 30, 50), B, C, 0)
+    print("[case] %d rows, rank %d" % (rows, rank), flush=True)
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in (at[c[0]].astype(np.int32), c[1], c[2])], torch.from_numpy(v).cuda(), dims, [0, 1, 2])
+    f = [torch.from_numpy(x).cuda() for x in (C, B)]
+    pl = cst.plan(S.MTTKRP3, [("X", csf), ("C", f[0]), ("B", f[1])])
+    out = torch.full((rows * rank,), 7.0, dtype=torch.float64, device="cuda")
+    cst.execute(pl, f, out=out)
+    got = out.view(rows, rank)[torch.from_numpy(at).cuda()].cpu().numpy()
+    assert oracle.rel_err(got, want, S_abs) <= 1.3e-14        # at most 100 products of three factors per sum
+    assert int(torch.count_nonzero(out)) == np.count_nonzero(want)
