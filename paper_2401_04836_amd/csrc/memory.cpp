@@ -5,14 +5,15 @@
 // handed out again, and a program that builds tensor after tensor outruns that: 45 to 90 ms per build where the
 // kernels take 7.  Blocks of destroyed objects are therefore kept and reused, under these rules:
 //   - at most kCachedBytes are kept; the block unused for longest goes first;
-//   - when no CSF and no plan is alive, everything goes back to the driver, and so it does, before a retry,
-//     when an allocation fails;
+//   - when no CSF and no plan is alive, everything goes back to the driver, and so it does when an allocation
+//     fails, before it is tried again, in the end with no rounding;
 //   - releasing a block waits for the device, as hipFree does, so a block never reaches its next owner while
 //     work on any stream may still touch it;
 //   - one mutex guards the lists: any thread may allocate and release.
 #include <algorithm>
 #include <list>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 
 #include "common.hpp"
@@ -39,12 +40,13 @@ Cache &cache() {
     return *c;
 }
 
-// Sizes are rounded up to an eighth of their leading power of two (256 bytes at least), so that tensors of
-// about the same size share blocks.
+// Sizes are rounded up to an eighth of their leading power of two (256 bytes at least, 2 MiB at most), so that
+// tensors of about the same size share blocks; an idle block serves a request that is up to an eighth smaller.
+size_t up_to(size_t bytes, size_t step) { return (bytes + step - 1) / step * step; }
 size_t rounded(size_t bytes) {
     size_t step = 256;
-    while (step * 16 <= bytes) step *= 2;
-    return (bytes + step - 1) / step * step;
+    while (step * 16 <= bytes && step < (size_t(2) << 20)) step *= 2;
+    return up_to(bytes, step);
 }
 
 void give_back(Cache &c, size_t keep) {
@@ -68,27 +70,43 @@ hipError_t device_alloc(void **p, size_t bytes) {
     std::lock_guard<std::mutex> lock(c.m);
     auto best = c.idle.end();
     for (auto it = c.idle.begin(); it != c.idle.end(); ++it)
-        if (it->device == device && it->bytes >= want && it->bytes <= want + want / 4 &&
+        if (it->device == device && it->bytes >= want && it->bytes <= want + want / 8 &&
             (best == c.idle.end() || it->bytes < best->bytes))
             best = it;
     if (best != c.idle.end()) {
+        try {
+            c.used[best->p] = *best;
+        } catch (const std::bad_alloc &) {
+            return hipErrorOutOfMemory;
+        }
         *p = best->p;
         c.idle_bytes -= best->bytes;
-        c.used[*p] = *best;
         c.idle.erase(best);
         return hipSuccess;
     }
-    e = hipMalloc(p, want);
+    size_t got = want;
+    e = hipMalloc(p, got);
     if (e != hipSuccess && !c.idle.empty()) {
         (void)hipGetLastError();
         give_back(c, 0);
-        e = hipMalloc(p, want);
+        e = hipMalloc(p, got);
+    }
+    if (e != hipSuccess && up_to(bytes, 256) < want) {
+        (void)hipGetLastError();
+        got = up_to(bytes, 256);
+        e = hipMalloc(p, got);
     }
     if (e != hipSuccess) {
         *p = nullptr;
         return e;
     }
-    c.used[*p] = Block{*p, want, device};
+    try {
+        c.used[*p] = Block{*p, got, device};
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(*p);
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
     return hipSuccess;
 }
 
@@ -113,7 +131,12 @@ void device_free(void *p) {
         (void)hipFree(p);
         return;
     }
-    c.idle.push_back(b);
+    try {
+        c.idle.push_back(b);
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(p);
+        return;
+    }
     c.idle_bytes += b.bytes;
     give_back(c, kCachedBytes);
 }

@@ -42,3 +42,14 @@ def test_schedule_front_end_under_sanitizers(tmp_path):
            "-o", exe]
     subprocess.check_call(cmd)
     assert "san_schedule: ok" in _run(exe)
+
+
+@pytest.mark.parametrize("sanitize", ["address,undefined", "thread"])
+def test_block_cache_over_a_small_device(tmp_path, sanitize):
+    exe = str(tmp_path / "san_memory")
+    lib = ["-static-libasan"] if "address" in sanitize else ["-static-libtsan"]
+    cmd = ["g++", "-O1", "-g", "-std=c++17", "-fno-omit-frame-pointer", "-fsanitize=" + sanitize, "-D__HIP_PLATFORM_AMD__",
+           "-w", "-I/opt/rocm/include", "-I" + CSRC] + lib + [os.path.join(CSRC, "memory.cpp"), os.path.join(SAN, "san_memory.cpp"),
+           "-lpthread", "-o", exe]
+    subprocess.check_call(cmd)
+    assert "san_memory: ok" in _run(exe)
