@@ -110,6 +110,20 @@ hipError_t device_alloc(void **p, size_t bytes) {
     return hipSuccess;
 }
 
+hipError_t device_free_bytes(size_t *bytes) {
+    size_t free_b = 0, total_b = 0;
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipMemGetInfo(&free_b, &total_b);
+    if (e != hipSuccess) return e;
+    Cache &c = cache();
+    std::lock_guard<std::mutex> lock(c.m);
+    for (const Block &b : c.idle)
+        if (b.device == device) free_b += b.bytes;
+    *bytes = free_b;
+    return hipSuccess;
+}
+
 void device_free(void *p) {
     if (!p) return;
     Cache &c = cache();

@@ -1174,8 +1174,8 @@ static conststn_status build_w_tiles(conststn_plan_s *plan) {
     // The dense tiles pay off when they are reasonably full.  A scattered W (about one nonzero per
     // tile) would be blown up 256-fold: below one nonzero in sixteen cells, or when the tiles do not fit
     // the free device memory, the baseline kernel (which needs no tiles) takes the plan instead.
-    size_t free_b = 0, total_b = 0;
-    CST_HIP(hipMemGetInfo(&free_b, &total_b));
+    size_t free_b = 0;
+    CST_HIP(device_free_bytes(&free_b));
     if (plan->opt("sptn3_tiled", 1) != 2 && (n_tiles * 16 > W->nnz || size_t(n_tiles + 1) * 2048 > free_b / 2)) {
         plan->w_tile_mask.release();
         return CONSTSTN_OK;

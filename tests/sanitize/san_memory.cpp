@@ -37,6 +37,11 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { ++syncs; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMemGetInfo(size_t *free_b, size_t *total_b) {
+    *free_b = kDevice - in_use;
+    *total_b = kDevice;
+    return hipSuccess;
+}
 }
 
 #define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
@@ -52,6 +57,8 @@ int main() {
         CHECK(in_use <= 22 * MiB + 100);                        // rounded up by 2 MiB at most
         device_free(a);
         CHECK(syncs == 1 && in_use > 0);                        // kept while an object is alive ...
+        size_t free_b = 0;
+        CHECK(device_free_bytes(&free_b) == hipSuccess && free_b == kDevice);      // ... counts as free ...
         const size_t before = mallocs;
         CHECK(device_alloc(&b, 19 * MiB) == hipSuccess && b == a && mallocs == before);   // ... and reused
         CHECK(device_alloc(&a, 64) == hipSuccess);
