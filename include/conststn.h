@@ -327,6 +327,12 @@ conststn_status conststn_plan_kernel_times(conststn_plan_t *plan, float *ms, int
 conststn_status conststn_measure_peak(int what, int64_t size, int repeats, conststn_stream stream,
                                       double *result);
 
+/* Device memory of destroyed CSFs and plans and of finished builds is kept for reuse, 8 GiB at most and while any CSF
+ * or plan is alive (memory that goes back to the driver is cleared before it is handed out again, which takes longer
+ * than a build).  This call gives it back at once, so that other allocators of the process can have it; handles in
+ * use are not touched.  It waits for the device, and may be called from any thread. */
+void conststn_release_memory(void);
+
 /* Message of the last failure on this thread ("" if none). */
 const char *conststn_last_error(void);
 

@@ -26,7 +26,7 @@ EXPORTED_SYMBOLS = [
     "conststn_plan_output_rows", "conststn_plan_output_csf", "conststn_plan_describe", "conststn_plan_destroy",
     "conststn_execute", "conststn_last_error", "conststn_version",
     "conststn_plan_profile", "conststn_plan_kernel_times", "conststn_measure_peak", "conststn_execute_static",
-    "conststn_csf_check", "conststn_plan_check",
+    "conststn_csf_check", "conststn_plan_check", "conststn_release_memory",
 ]
 
 
@@ -80,6 +80,8 @@ def _load():
     L.conststn_measure_peak.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int, vp, ctypes.POINTER(ctypes.c_double)]
     L.conststn_csf_check.argtypes = [vp]
     L.conststn_plan_check.argtypes = [vp]
+    L.conststn_release_memory.argtypes = []
+    L.conststn_release_memory.restype = None
     for name in EXPORTED_SYMBOLS:
         getattr(L, name)
     return L
@@ -94,6 +96,11 @@ def library_path():
 
 def version():
     return _lib.conststn_version().decode()
+
+
+def release_memory():
+    """conststn_release_memory: device memory that the library keeps for reuse goes back to the driver."""
+    _lib.conststn_release_memory()
 
 
 PEAK_COPY, PEAK_WRITE, PEAK_MFMA_F64, PEAK_MFMA_CLOCK, PEAK_VALU_CLOCK = 0, 1, 2, 3, 4

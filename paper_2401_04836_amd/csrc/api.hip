@@ -354,6 +354,7 @@ using namespace cst;
 extern "C" {
 
 const char *conststn_last_error(void) { return get_error(); }
+void conststn_release_memory(void) { release_idle_memory(); }
 const char *conststn_version(void) { return "conststn 0.1 (gfx950)"; }
 
 conststn_status conststn_build_csf(int order, const int64_t *dims, int64_t nnz,

@@ -38,6 +38,7 @@ void clear_error();
 // ---- device memory (memory.cpp): hipMalloc / hipFree with a bounded cache of released blocks ------
 hipError_t device_alloc(void **p, size_t bytes);      // on the current device
 void device_free(void *p);                             // waits for the device
+void release_idle_memory();                            // every block kept for reuse goes back to the driver
 hipError_t device_free_bytes(size_t *bytes);           // free on the current device, blocks kept for reuse included
 
 // Held by every CSF and every plan, as the first member (so that it outlives the buffers beside it): while

@@ -7,6 +7,7 @@
 //   - at most kCachedBytes are kept; the block unused for longest goes first;
 //   - when no CSF and no plan is alive, everything goes back to the driver, and so it does when an allocation
 //     fails, before it is tried again, in the end with no rounding;
+//   - conststn_release_memory gives them back at once, for programs whose other allocators need the room;
 //   - releasing a block waits for the device, as hipFree does, so a block never reaches its next owner while
 //     work on any stream may still touch it;
 //   - one mutex guards the lists: any thread may allocate and release.
@@ -153,6 +154,12 @@ void device_free(void *p) {
     }
     c.idle_bytes += b.bytes;
     give_back(c, kCachedBytes);
+}
+
+void release_idle_memory() {
+    Cache &c = cache();
+    std::lock_guard<std::mutex> lock(c.m);
+    give_back(c, 0);
 }
 
 MemoryUser::MemoryUser() {

@@ -62,8 +62,10 @@ int main() {
         const size_t before = mallocs;
         CHECK(device_alloc(&b, 19 * MiB) == hipSuccess && b == a && mallocs == before);   // ... and reused
         CHECK(device_alloc(&a, 64) == hipSuccess);
-        device_free(a);
         device_free(b);
+        release_idle_memory();
+        CHECK(live.size() == 1 && live.count(a) == 1);          // what is in use stays
+        device_free(a);
         // what is kept does not stand in the way of a larger request, nor does the rounding: 63.5 MiB would be 64
         CHECK(device_alloc(&a, 63 * MiB + MiB / 2) == hipSuccess && live.size() == 1);
         CHECK(device_alloc(&b, 257 * 1024) == hipErrorOutOfMemory && b == nullptr);

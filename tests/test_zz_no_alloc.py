@@ -77,3 +77,19 @@ def test_execute_static_takes_a_flat_tensor_at_any_ranks(ranks):
     general = cst.plan(S.TTMC3, [("X", csf), ("U3", U3), ("U2", U2)], options=dict(ttmc3_mfma=0))
     # positive terms, at most 3 500 per sum
     assert (cst.execute(general, [U3, U2]) / got - 1).abs().max().item() <= 4e-13
+
+
+def test_memory_of_destroyed_objects_is_given_back_on_demand():
+    n = 4_000_000
+    coords = [torch.randperm(n, device="cuda").to(torch.int32) for _ in range(3)]
+    vals = torch.rand(n, dtype=torch.float64, device="cuda")
+    print("[case] build, destroy, release", flush=True)
+    alive = cst.build_csf(coords, vals, (n, n, n), [0, 1, 2])
+    torch.cuda.synchronize()
+    cst.release_memory()
+    before = torch.cuda.mem_get_info()[0]
+    cst.build_csf(coords, vals, (n, n, n), [1, 2, 0]).destroy()
+    assert torch.cuda.mem_get_info()[0] < before              # kept for the next build
+    cst.release_memory()
+    assert torch.cuda.mem_get_info()[0] == before
+    alive.check()
