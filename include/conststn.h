@@ -48,6 +48,8 @@ typedef void *conststn_stream;                    /* a hipStream_t (NULL = the d
 
 /* flags of conststn_build_csf */
 #define CONSTSTN_COALESCE_DUPS 1u   /* sum duplicate coordinates in input order instead of failing  */
+#define CONSTSTN_LEAN_BUILD 2u      /* 25 instead of 33 bytes of work space per nonzero, a little slower;
+                                       a build that runs out of memory is tried again in this way      */
 /* flags of conststn_plan */
 #define CONSTSTN_OUT_COMPACT 1u     /* output holds one row block per NONEMPTY root index only      */
 
@@ -66,7 +68,7 @@ typedef void *conststn_stream;                    /* a hipStream_t (NULL = the d
  *   coords     host pointer to `order` DEVICE pointers; coords[m][n] = index of nonzero n in mode m
  *   vals       device pointer, nnz values (stored zeros are kept as structural nonzeros)
  *   mode_order host pointer, a permutation of 0..order-1
- *   flags      0 or CONSTSTN_COALESCE_DUPS
+ *   flags      0 or CONSTSTN_COALESCE_DUPS | CONSTSTN_LEAN_BUILD (the result is the same bit for bit)
  *   stream     the work is enqueued on this stream and the call waits for it: on return the
  *              CSF is complete and range / duplicate errors have been reported
  *   out        receives the handle; the library owns every array inside it (the inputs are

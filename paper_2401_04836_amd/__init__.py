@@ -17,6 +17,7 @@ MAX_ORDER = 8
 OK, EINVAL, ERANGE, EDUP, ESCHED, EUNSUPPORTED, ENOMEM, EHIP = range(8)
 _STATUS_NAMES = ["OK", "EINVAL", "ERANGE", "EDUP", "ESCHED", "EUNSUPPORTED", "ENOMEM", "EHIP"]
 COALESCE_DUPS = 1
+LEAN_BUILD = 2
 OUT_COMPACT = 1
 OPERAND_CSF, OPERAND_DENSE = 0, 1
 

@@ -368,7 +368,7 @@ conststn_status conststn_build_csf(int order, const int64_t *dims, int64_t nnz,
     if (!dims || !mode_order || !coords) { set_error("null argument"); return CONSTSTN_EINVAL; }
     if (nnz < 0) { set_error("nnz is negative"); return CONSTSTN_EINVAL; }
     if (nnz >= (int64_t(1) << 31)) { set_error("nnz of 2^31 or more is not implemented"); return CONSTSTN_EUNSUPPORTED; }
-    if (flags & ~CONSTSTN_COALESCE_DUPS) { set_error("unknown flag bits"); return CONSTSTN_EINVAL; }
+    if (flags & ~(CONSTSTN_COALESCE_DUPS | CONSTSTN_LEAN_BUILD)) { set_error("unknown flag bits"); return CONSTSTN_EINVAL; }
     bool seen[CONSTSTN_MAX_ORDER] = {false};
     for (int l = 0; l < order; ++l) {
         if (dims[l] < 1 || dims[l] > 0x7fffffffll) { set_error("extent of mode %d outside 1..2^31-1", l); return CONSTSTN_EINVAL; }

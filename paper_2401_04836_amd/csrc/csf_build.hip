@@ -565,10 +565,10 @@ __global__ void close_ptrs_kernel(LevelOut out, int order, const int64_t *totals
     if (l < order - 1) out.ptr[l][totals[l]] = totals[l + 1];
 }
 
-conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
-                                 const int32_t *const *coords, const double *vals,
-                                 const int *mode_order, unsigned flags, hipStream_t stream,
-                                 conststn_csf_s *csf) {
+static conststn_status build_levels(int order, const int64_t *dims, int64_t nnz,
+                                    const int32_t *const *coords, const double *vals,
+                                    const int *mode_order, unsigned flags, hipStream_t stream,
+                                    conststn_csf_s *csf) {
     Levels lv{};
     lv.order = order;
     int total_bits = 0;
@@ -622,7 +622,8 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
 
     // every temporary of the build in one allocation
     const int64_t ntiles = div_up(nnz, kTile);
-    const bool fused = !wide && total_bits > 0 && nnz > 1;            // the sort packs the keys and carries the values
+    // the sort packs the keys and carries the values; or, with a third less work space, it carries positions
+    const bool fused = !wide && total_bits > 0 && nnz > 1 && !(flags & CONSTSTN_LEAN_BUILD);
     const size_t pay_bytes = size_t(nnz) * (fused ? 8 : 4);
     const size_t sort_bytes = radix_sort_scratch_bytes(nnz);
     const size_t arena_bytes = 2 * up256(size_t(nnz) * 8) + 2 * up256(pay_bytes) + up256(2 * sizeof(int)) +
@@ -653,7 +654,9 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
         CST_HIP(hipGetLastError());
     }
     if (!wide) {
-        if (fused)
+        if (!fused)
+            CST_TRY(radix_sort_pairs_u64(keys_a.p, keys_b.p, pay_a.p, pay_b.p, nnz, total_bits, stream, &skeys, &spay, sort_scratch));
+        else
             CST_TRY(radix_passes(keys_a.p, keys_b.p, reinterpret_cast<uint64_t *>(pay_a.p), reinterpret_cast<uint64_t *>(pay_b.p), nnz,
                                  total_bits, stream, &skeys, &svals, sort_scratch, &lv, reinterpret_cast<const uint64_t *>(vals), dflags.p));
     } else {
@@ -730,6 +733,23 @@ conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
     CST_HIP(hipGetLastError());
     CST_HIP(hipStreamSynchronize(stream));
     return CONSTSTN_OK;
+}
+
+conststn_status build_csf_device(int order, const int64_t *dims, int64_t nnz,
+                                 const int32_t *const *coords, const double *vals,
+                                 const int *mode_order, unsigned flags, hipStream_t stream,
+                                 conststn_csf_s *csf) {
+    conststn_status st = build_levels(order, dims, nnz, coords, vals, mode_order, flags, stream, csf);
+    if (st != CONSTSTN_ENOMEM || (flags & CONSTSTN_LEAN_BUILD)) return st;
+    // once more with the smaller work space, and with what is kept for reuse given back
+    for (int l = 0; l < order; ++l) {
+        csf->idx[l].release();
+        csf->ptr[l].release();
+    }
+    csf->vals.release();
+    release_idle_memory();
+    clear_error();
+    return build_levels(order, dims, nnz, coords, vals, mode_order, flags | CONSTSTN_LEAN_BUILD, stream, csf);
 }
 
 // ---- a second layout of a tensor that is already a CSF ------------------------------------------

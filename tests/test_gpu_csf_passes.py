@@ -64,3 +64,38 @@ def test_range_of_a_level_without_key_bits(bad, at):
     with pytest.raises(cst.ConststnError) as e:
         cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2, 3])
     assert e.value.status_name == "ERANGE"
+
+
+@pytest.mark.parametrize("dims", DIMS + [(1, 1, 1)])
+@pytest.mark.parametrize("n", [1, 2, 4097, 70_001])
+def test_lean_build_gives_the_same_arrays(dims, n):
+    """The sort that carries positions (the work space of a build that ran out of memory) against the one that carries
+    values, with duplicates and with an index out of range."""
+    rng = np.random.default_rng(n + sum(dims))
+    c = [torch.from_numpy(rng.integers(0, d, n).astype(np.int32)).cuda() for d in dims]
+    v = torch.from_numpy(rng.uniform(-1, 1, n)).cuda()
+    print("[case] lean build, dims %s n %d" % (dims, n), flush=True)
+    one, two = (cst.build_csf(c, v, dims, [1, 2, 0], flags=cst.COALESCE_DUPS | f) for f in (0, cst.LEAN_BUILD))
+    for l in range(3):
+        for a, b in zip(one.export(l), two.export(l)):
+            assert (a is None and b is None) or torch.equal(a, b)
+    c[2][n - 1] = dims[2]
+    with pytest.raises(Exception, match="below its mode extent"):
+        cst.build_csf(c, v, dims, [1, 2, 0], flags=cst.COALESCE_DUPS | cst.LEAN_BUILD)
+
+
+def test_lean_build_needs_less_work_space():
+    n = 30_000_000
+    c = [torch.randint(0, 1 << 30, (n,), device="cuda", dtype=torch.int32) for _ in range(2)]
+    v = torch.rand(n, dtype=torch.float64, device="cuda")
+    print("[case] work space of a build of %d nonzeros" % n, flush=True)
+    alive = cst.build_csf([x[:1] for x in c], v[:1], (1 << 30, 1 << 30), [0, 1])
+    spent = []
+    for flags in (0, cst.LEAN_BUILD):
+        cst.release_memory()
+        before = torch.cuda.mem_get_info()[0]
+        csf = cst.build_csf(c, v, (1 << 30, 1 << 30), [0, 1], flags=cst.COALESCE_DUPS | flags)
+        spent.append(before - torch.cuda.mem_get_info()[0])        # the CSF, and the work space kept for reuse
+        csf.destroy()
+    alive.check()
+    assert spent[0] - spent[1] >= 7.5 * n, spent
