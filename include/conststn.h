@@ -150,6 +150,11 @@ void conststn_csf_destroy(conststn_csf_t *csf);
  * executor (one pass per statement, intermediates held whole in device memory; plan option
  * generic_max_gb bounds them, default 64).  A legal schedule outside all of
  * these gives CONSTSTN_EUNSUPPORTED with the reason.
+ * Memory: the MTTKRP kernels walk a stream of 12 bytes per leaf, fiber and (order 4) node, the order-3 TTMc kernel
+ * row descriptors of 16 bytes per fiber or 16 leaves, the order-4 TTMc kernel records of 32 bytes per 2 leaves of a node,
+ * all of them made and held by the plan (and about twice that while it is made).  Where that cannot be
+ * allocated the plan is made again for the slower kernels that walk the CSF itself (as with the options
+ * mttkrp_records=0, ttmc3_mfma=0, ttmc4_mfma=0).
  * The plan keeps pointers into the CSF handles: destroy the plan first.
  */
 typedef enum { CONSTSTN_OPERAND_CSF = 0, CONSTSTN_OPERAND_DENSE = 1 } conststn_operand_kind;
@@ -175,7 +180,8 @@ conststn_status conststn_plan(const char *schedule, const int *fusion, int n_ope
  * kernel exists), generic_max_gb (64), generic_span (4096), generic_densify (1: a tree over several CSF operands runs on the generic executor, which walks the
  * largest and keeps dense copies of the others; 0 = such trees are refused), generic_fuse (1; 0 = the generic
  * executor stores every intermediate whole even where the schedule fuses), reroot (1; 0 = no private re-sorted copy of the
- * tensor for MTTKRP / TTMc of a non-root level: the generic executor takes those), mttkrp_split (1), mttkrp_dual (44 = hot and cold sub-tensor in one launch, four
+ * tensor for MTTKRP / TTMc of a non-root level: the generic executor takes those), mttkrp_records (1; 0 = no second copy
+ * of the tensor as a stream of records: the CSF itself is walked, at order 4 by the generic executor), mttkrp_split (1), mttkrp_dual (44 = hot and cold sub-tensor in one launch, four
  * wavefronts of a workgroup each; 35, 53, 88 likewise; 0 = two launches), mttkrp_hot (256),
  * mttkrp_chunk (0 = by tensor size), ttmc3_mfma (1), ttmc3_stream (1), ttmc3_producers (4),
  * ttmc3_batch (2048), ttmc3_itemcost (2), ttmc3_qn (2), ttmc3_split (4096), ttmc3_rowsplit (by size),

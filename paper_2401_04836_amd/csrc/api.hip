@@ -92,7 +92,7 @@ static conststn_status match_chain(conststn_plan_s *plan) {
             if (plan->rank_of_level[l] != plan->rank_of_level[1]) { set_error("batch index with two extents"); return CONSTSTN_ESCHED; }
         // order 4 belongs to the generic executor, which runs the whole chain as one kernel; where its options
         // ask for nothing else, that kernel is the record stream's
-        plan->use_records = record_stream_fits(X.csf, plan->rank_of_level[1]) &&
+        plan->use_records = record_stream_fits(X.csf, plan->rank_of_level[1]) && plan->opt("mttkrp_records", 1) == 1 &&
                             (n == 3 || (plan->opt("generic_fuse", 1) == 1 && !plan->options.count("generic_span")));
         if (n == 4 && !plan->use_records) { set_error("MTTKRP kernels exist for order-3 tensors only"); return CONSTSTN_EUNSUPPORTED; }
         plan->family = n == 3 ? FAM_MTTKRP3 : FAM_GENERIC;
@@ -319,7 +319,7 @@ static conststn_status match_rerooted(conststn_plan_s *plan) {
     plan->factor_of_level[2] = facs[b].ordinal;
     plan->rank_of_level[2] = facs[b].extent;
     plan->family = mttkrp ? FAM_MTTKRP3 : FAM_TTMC3;
-    plan->use_records = mttkrp && record_stream_fits(plan->rerooted_x.get(), plan->rank_of_level[1]);
+    plan->use_records = mttkrp && record_stream_fits(plan->rerooted_x.get(), plan->rank_of_level[1]) && plan->opt("mttkrp_records", 1) == 1;
     plan->row_elems = mttkrp ? facs[a].extent : int64_t(facs[a].extent) * facs[b].extent;
     return CONSTSTN_OK;
 }
@@ -483,6 +483,7 @@ struct PlanOptionRange { const char *name; int64_t lo, hi; int64_t listed[5]; };
 static const PlanOptionRange kPlanOptions[] = {
     {"force_generic", 0, 1, {}},       {"generic_max_gb", 1, 4096, {}},   {"generic_span", 1, int64_t(1) << 30, {}},
     {"generic_fuse", 0, 1, {}},        {"generic_densify", 0, 1, {}},     {"reroot", 0, 1, {}},
+    {"mttkrp_records", 0, 1, {}},
     {"mttkrp_split", 0, 1, {}},        {"mttkrp_dual", 1, 0, {0, 35, 44, 53, 88}},
     {"mttkrp_hot", 1, int64_t(1) << 20, {}},                              {"mttkrp_chunk", 0, int64_t(1) << 24, {}},
     {"ttmc3_mfma", 0, 1, {}},          {"ttmc3_stream", 0, 1, {}},        {"ttmc3_producers", 1, 0, {2, 3, 4, 6, 8}},
@@ -547,19 +548,25 @@ static conststn_status parse_plan_options(const char *text, conststn_plan_s *pla
     return CONSTSTN_OK;
 }
 
-conststn_status conststn_plan_options(const char *schedule, const int *fusion, int n_operands,
-                                      const conststn_operand_desc *operands, unsigned flags,
-                                      const char *options, conststn_plan_t **out) {
-    clear_error();
-    if (!out) { set_error("out is null"); return CONSTSTN_EINVAL; }
-    *out = nullptr;
+// lean: the kernels that need no second copy of the tensor.  *retry: whether a lean plan would have needed less memory.
+static conststn_status make_plan(const char *schedule, const int *fusion, int n_operands,
+                                 const conststn_operand_desc *operands, unsigned flags,
+                                 const char *options, bool lean, bool *retry, conststn_plan_t **out) {
     if (flags & ~CONSTSTN_OUT_COMPACT) { set_error("unknown flag bits"); return CONSTSTN_EINVAL; }
     conststn_plan_s *plan = new (std::nothrow) conststn_plan_s();
     if (!plan) { set_error("host allocation failed"); return CONSTSTN_ENOMEM; }
-    struct Guard { conststn_plan_s *p; ~Guard() { delete p; } } guard{plan};
+    struct Guard {
+        conststn_plan_s *p;
+        bool *retry;
+        ~Guard() {
+            if (p) *retry = p->use_records || p->use_rows;
+            delete p;
+        }
+    } guard{plan, retry};
     plan->flags = flags;
     plan->compact = (flags & CONSTSTN_OUT_COMPACT) != 0;
     CST_TRY(parse_plan_options(options, plan));
+    if (lean) plan->options["mttkrp_records"] = plan->options["ttmc3_mfma"] = plan->options["ttmc4_mfma"] = 0;
     {
         int dev = 0;
         CST_HIP(hipGetDevice(&dev));
@@ -712,6 +719,20 @@ conststn_status conststn_plan_options(const char *schedule, const int *fusion, i
     guard.p = nullptr;
     *out = plan;
     return CONSTSTN_OK;
+}
+
+conststn_status conststn_plan_options(const char *schedule, const int *fusion, int n_operands,
+                                      const conststn_operand_desc *operands, unsigned flags,
+                                      const char *options, conststn_plan_t **out) {
+    clear_error();
+    if (!out) { set_error("out is null"); return CONSTSTN_EINVAL; }
+    *out = nullptr;
+    bool retry = false;
+    const conststn_status st = make_plan(schedule, fusion, n_operands, operands, flags, options, false, &retry, out);
+    if (st != CONSTSTN_ENOMEM || !retry) return st;
+    release_idle_memory();
+    clear_error();
+    return make_plan(schedule, fusion, n_operands, operands, flags, options, true, &retry, out);
 }
 
 conststn_status conststn_plan_output_size(const conststn_plan_t *plan, int64_t *n_rows, int64_t *row_elems) {

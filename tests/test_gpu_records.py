@@ -138,3 +138,26 @@ def test_more_empty_rows_than_a_launch_has_threads_for(rows, rank):
     got = out.view(rows, rank)[torch.from_numpy(at).cuda()].cpu().numpy()
     assert oracle.rel_err(got, want, S_abs) <= 1.3e-14        # at most 100 products of three factors per sum
     assert int(torch.count_nonzero(out)) == np.count_nonzero(want)
+
+
+@pytest.mark.parametrize("rank", [2, 3, 16, 17, 50, 128])
+def test_without_a_copy_of_the_tensor(rank):
+    """mttkrp_records=0: order 3 walks the CSF itself, order 4 runs on the generic executor; slices inside one chunk,
+    shared by a few chunks and by many."""
+    dims = (40, 30, 5000)
+    c, v, rng = _tensor(dims, 3000, 20_000, 500 + rank)
+    B, C = rng.uniform(-1, 1, (dims[1], rank)), rng.uniform(-1, 1, (dims[2], rank))
+    want, S_abs = oracle.mttkrp3(c, v, dims, B, C, 0), oracle.mttkrp3_abs(c, v, dims, B, C, 0)
+    for chunk in (0, 16):
+        for flags in (0, cst.OUT_COMPACT):
+            print("[case] no copy, order 3 rank %d chunk %d flags %d" % (rank, chunk, flags), flush=True)
+            got, pl = _run(S.MTTKRP3, c, v, dims, [("C", C), ("B", B)], dict(mttkrp_chunk=chunk, mttkrp_records=0), flags)
+            assert "record" not in pl.describe()
+            rows = pl.output_rows().cpu().numpy() if flags else slice(None)
+            assert oracle.rel_err(got, want[rows], S_abs[rows]) <= 2.3e-12       # at most 20 500 products of three per sum
+    dims4 = (12, 8, 30, 20)
+    c, v, rng = _tensor(dims4, 3000, 1500, 600 + rank)
+    F = [rng.uniform(-1, 1, (d, rank)) for d in dims4[1:]]
+    got, pl = _run(T4, c, v, dims4, [("D", F[2]), ("C", F[1]), ("B", F[0])], dict(mttkrp_records=0))
+    f, ext = [(F[0], "jr"), (F[1], "kr"), (F[2], "lr")], {"i": dims4[0], "r": rank}
+    assert oracle.rel_err(got, nary.contract(c, v, "ijkl", f, "ir", ext), nary.contract_abs(c, v, "ijkl", f, "ir", ext)) <= 4e-13

@@ -70,3 +70,24 @@ def test_rows_that_are_not_finite(ranks):
         assert not np.isnan(got).any(), opts
         np.testing.assert_array_equal(np.isinf(got), infinite)
         np.testing.assert_allclose(got[~infinite], clean[~infinite], rtol=1e-12)
+
+
+@pytest.mark.parametrize("ranks", [(63, 63), (64, 64)])
+def test_a_plan_that_does_not_fit_is_made_for_the_general_kernel(ranks):
+    """Items of one row over twelve million rows ask for more partial row blocks than any device holds."""
+    g = torch.Generator(device="cuda").manual_seed(12)
+    dims, n = (1200, 100_000, 40_000), 13_000_000
+    keys = torch.unique(torch.randint(0, dims[0] * dims[1] * dims[2], (n,), generator=g, device="cuda"))
+    keys = keys[torch.randperm(keys.numel(), generator=g, device="cuda")]
+    c = [x.to(torch.int32) for x in (keys // (dims[1] * dims[2]), keys // dims[2] % dims[1], keys % dims[2])]
+    v = torch.rand(keys.numel(), generator=g, dtype=torch.float64, device="cuda")
+    u2, u3 = (torch.rand(d, r, generator=g, dtype=torch.float64, device="cuda") for d, r in zip(dims[1:], ranks))
+    print("[case] ranks %s, partial row blocks beyond the device's memory" % (ranks,), flush=True)
+    csf = cst.build_csf(c, v, dims, [0, 1, 2])
+    ops = [("X", csf), ("U3", u3), ("U2", u2)]
+    pl = cst.plan(S.TTMC3, ops, options=dict(ttmc3_rowsplit=1))
+    assert "kernel=" not in pl.describe().split("|")[0]
+    usual = cst.plan(S.TTMC3, ops)
+    assert "kernel=stream" in usual.describe()
+    a, b = cst.execute(pl, [u3, u2]), cst.execute(usual, [u3, u2])
+    assert (a / b - 1).abs().max().item() <= 2.7e-12              # positive terms, at most 12 000 per sum
