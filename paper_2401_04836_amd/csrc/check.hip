@@ -26,6 +26,7 @@ enum : unsigned {
     kBadLeafTable = 1u << 12,  // a table of first leaves per node that is not the composition of the pointer arrays
     kBadSegment = 1u << 13,    // segments of a long sum that do not tile the children (or leaves) of their result node in order
     kBadHeavy = 1u << 14,      // the list of result nodes with many segments names a node that is not one, or misses one
+    kBadRowList = 1u << 15,    // the lists of rows that several chunks share, or that are empty, name another or miss one
 };
 
 struct CsfView {
@@ -233,9 +234,10 @@ conststn_status report(unsigned bits, const char *what) {
                                         "slice_leaf off the pointer arrays", "a re-encoded leaf out of range or with a wrong end mark",
                                         "a row descriptor out of range", "a K-step out of range", "workgroup batches that are not whole items in order",
                                         "an item outside its slice", "a first-leaf table off the pointer arrays",
-                                        "segments that do not tile their result node", "a wrong list of nodes with many segments"};
+                                        "segments that do not tile their result node", "a wrong list of nodes with many segments",
+                                        "a wrong list of rows that several chunks share or that are empty"};
     std::string msg;
-    for (int b = 0; b < 15; ++b)
+    for (int b = 0; b < 16; ++b)
         if (bits & (1u << b)) { if (!msg.empty()) msg += "; "; msg += names[b]; }
     set_error("%s: %s", what, msg.c_str());
     return CONSTSTN_EINVAL;
@@ -343,7 +345,7 @@ extern "C" conststn_status conststn_plan_check(const conststn_plan_t *plan) {
     CST_HIP(hipMemset(flags.p, 0, sizeof(unsigned)));
     CST_TRY(run_csf_check(X, flags.p));                    // the tensor the kernels walk (the private copy, if one was made)
     if (plan->use_records && !plan->split) {
-        CST_TRY(check_record_stream(plan, kBadCode, kBadChunk, flags.p));
+        CST_TRY(check_record_stream(plan, kBadCode, kBadChunk, kBadRowList, flags.p));
         unsigned hr = 0;
         CST_HIP(hipMemcpy(&hr, flags.p, sizeof(hr), hipMemcpyDeviceToHost));
         return report(hr, "plan tables");

@@ -492,45 +492,90 @@ conststn_status list_of_flags(DevBuf<int64_t> &flag, int64_t n, DevBuf<int32_t> 
     return CONSTSTN_OK;
 }
 
-// Every record recomputed from the level arrays, every chunk and row table against what it indexes.
-__global__ void __launch_bounds__(256)
-check_records_kernel(RecordFill a, int64_t dims1, int64_t q, int64_t n_chunks, int64_t out_rows, const uint32_t *chunk_slice,
-                     const int32_t *open1, const int32_t *open2, const int32_t *row_of_slice, unsigned bad_code, unsigned bad_chunk,
-                     unsigned *flags) {
-    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    unsigned bad = 0;
-    if (t < a.n_rec) {
-        uint32_t want;
-        int64_t n = 0, n_end = -1;
-        if (a.nodes) {
-            n = first_end(a.nodes, t, [&](int64_t x) { return node_end_record(a, x); });
-            n_end = node_end_record(a, n);
-        }
-        if (t == n_end) want = kRecNodeEnd | uint32_t(a.idx_node[n]);
-        else {
-            // records before t that belong to fibers: t minus the node ends before it
-            auto end_of = [&](int64_t f) { return a.ptr_fiber[f + 1] + f + (a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0); };
-            const int64_t f = first_end(a.fibers, t, end_of);
-            const int64_t nf = a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0;
-            want = t == end_of(f) ? (kRecFiberEnd | uint32_t(a.idx_fiber[f])) : uint32_t(a.idx_leaf[t - f - nf]);
-        }
-        const int64_t s = parent_of(a.slice_rec, a.slices, t);
-        // the ends that open a chunk (two of them at order 4: the record before is in the chunk and an end, too)
-        const int64_t in_chunk = t % q;
-        if (want >> 30 != 0 && (in_chunk == 0 || (in_chunk == 1 && a.code[t - 1] >> 30 == 3))) want = kRecNothing;
-        if (a.slice_rec[s + 1] == t + 1) want |= kRecSliceEnd;
-        if (a.code[t] != want) bad |= bad_code;
-    } else if (t < a.total && (a.code[t] >> 29 != 0 || a.out_vals[t] != 0.0)) bad |= bad_code;
-    if (t <= a.slices) {
-        if (t == a.slices ? a.slice_rec[t] != a.n_rec : (a.slice_rec[t] < 0 || a.slice_rec[t + 1] <= a.slice_rec[t])) bad |= bad_chunk;
-        if (t < a.slices && (row_of_slice[t] < 0 || row_of_slice[t] >= out_rows)) bad |= bad_chunk;
+// Every record and its value recomputed from the level arrays, every chunk's slice and open rows, the row of every
+// slice, and the lists of rows that the fix-up launch works through against what they must name.
+struct RecordCheck {
+    RecordFill a;
+    int64_t q, n_chunks, out_rows, n_light, n_heavy, n_empty;
+    const uint32_t *chunk_slice;
+    const int32_t *open1, *open2, *row_of_slice, *light, *heavy, *empty, *idx0;
+    int compact;
+    unsigned bad_code, bad_chunk, bad_list;
+};
+
+// whether x is in the ascending list
+__device__ __forceinline__ bool listed(const int32_t *list, int64_t n, int64_t x) {
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (list[mid] < x) lo = mid + 1; else hi = mid;
     }
-    if (t < n_chunks) {
-        const int64_t s = chunk_slice[t] & ~kChunkInside;
-        if (s >= a.slices || a.slice_rec[s] > t * q || a.slice_rec[s + 1] <= t * q ||
-            (a.slice_rec[s] != t * q) != ((chunk_slice[t] & kChunkInside) != 0))
-            bad |= bad_chunk;
-        if (open1[t] >= dims1 || (open2 && open2[t] >= dims1)) bad |= bad_chunk;
+    return lo < n && list[lo] == x;
+}
+
+__global__ void __launch_bounds__(256)
+check_records_kernel(RecordCheck c, int64_t threads, unsigned *flags) {
+    const RecordFill &a = c.a;
+    const int64_t q = c.q;
+    unsigned bad = 0;
+    for (int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x; t < threads; t += int64_t(gridDim.x) * 256) {
+        if (t < a.n_rec) {
+            uint32_t want;
+            double value = 0.0;
+            int64_t n = 0, n_end = -1;
+            if (a.nodes) {
+                n = first_end(a.nodes, t, [&](int64_t x) { return node_end_record(a, x); });
+                n_end = node_end_record(a, n);
+            }
+            if (t == n_end) want = kRecNodeEnd | uint32_t(a.idx_node[n]);
+            else {
+                // records before t that belong to fibers: t minus the node ends before it
+                auto end_of = [&](int64_t f) { return a.ptr_fiber[f + 1] + f + (a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0); };
+                const int64_t f = first_end(a.fibers, t, end_of);
+                const int64_t nf = a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0;
+                if (t == end_of(f)) want = kRecFiberEnd | uint32_t(a.idx_fiber[f]);
+                else {
+                    want = uint32_t(a.idx_leaf[t - f - nf]);
+                    value = a.vals[t - f - nf];
+                }
+            }
+            // the ends that open a chunk (two of them at order 4: the record before is in the chunk and an end, too)
+            const int64_t in_chunk = t % q;
+            if (want >> 30 != 0 && (in_chunk == 0 || (in_chunk == 1 && a.code[t - 1] >> 30 == 3))) want = kRecNothing;
+            const int64_t s = parent_of(a.slice_rec, a.slices, t);
+            if (a.slice_rec[s + 1] == t + 1) want |= kRecSliceEnd;
+            if (a.code[t] != want || __double_as_longlong(a.out_vals[t]) != __double_as_longlong(value)) bad |= c.bad_code;
+        } else if (t < a.total && (a.code[t] >> 29 != 0 || a.code[t] != uint32_t(a.idx_leaf[a.leaves - 1]) || a.out_vals[t] != 0.0)) bad |= c.bad_code;
+        if (a.slices && t <= a.slices) {
+            if (t == a.slices ? a.slice_rec[t] != a.n_rec : (a.slice_rec[t] < 0 || a.slice_rec[t + 1] <= a.slice_rec[t])) bad |= c.bad_chunk;
+            else if (t < a.slices) {
+                if (c.row_of_slice[t] != (c.compact ? int32_t(t) : c.idx0[t]) || c.row_of_slice[t] >= c.out_rows) bad |= c.bad_chunk;
+                const int share = share_of(a.slice_rec, t, q);
+                if (listed(c.light, c.n_light, t) != (share == 1) || listed(c.heavy, c.n_heavy, t) != (share == 2)) bad |= c.bad_list;
+            }
+        }
+        if (t < c.n_chunks) {
+            const int64_t s = c.chunk_slice[t] & ~kChunkInside;
+            if (s >= a.slices || a.slice_rec[s] > t * q || a.slice_rec[s + 1] <= t * q ||
+                (a.slice_rec[s] != t * q) != ((c.chunk_slice[t] & kChunkInside) != 0))
+                bad |= c.bad_chunk;
+            // what is open behind the chunk: the fiber and the node of the next record, unless the chunk ends them
+            const int64_t r1 = (t + 1) * q;
+            int32_t o1 = -1, o2 = -1;
+            if (r1 < a.n_rec) {
+                if (a.code[r1 - 1] >> 30 == 0) o1 = a.idx_fiber[first_end(a.fibers, r1, [&](int64_t f) { return a.ptr_fiber[f + 1] + f + (a.nodes ? parent_of(a.ptr_node, a.nodes, f) : 0); })];
+                if (a.nodes && a.code[r1 - 1] >> 30 != 2) o2 = a.idx_node[first_end(a.nodes, r1, [&](int64_t n) { return node_end_record(a, n); })];
+            }
+            if (c.open1[t] != o1 || (c.open2 && c.open2[t] != o2)) bad |= c.bad_chunk;
+        }
+        // the lists ascend (so that the searches above find what is there) and hold nothing else
+        if (t < c.n_light && (t > 0 && c.light[t - 1] >= c.light[t])) bad |= c.bad_list;
+        if (t < c.n_heavy && (t > 0 && c.heavy[t - 1] >= c.heavy[t])) bad |= c.bad_list;
+        if (t < c.n_light && (c.light[t] < 0 || c.light[t] >= a.slices)) bad |= c.bad_list;
+        if (t < c.n_heavy && (c.heavy[t] < 0 || c.heavy[t] >= a.slices)) bad |= c.bad_list;
+        if (t < c.n_empty && (c.empty[t] < 0 || c.empty[t] >= c.out_rows || (t > 0 && c.empty[t - 1] >= c.empty[t]) ||
+                              listed(c.idx0, a.slices, c.empty[t])))
+            bad |= c.bad_list;
     }
     if (bad) atomicOr(flags, bad);
 }
@@ -560,17 +605,37 @@ RecordFill view_of_stream(const conststn_csf_s *X, const RecordStream &rs) {
 
 }  // namespace
 
-conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_code, unsigned bad_chunk, unsigned *flags) {
+conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_code, unsigned bad_chunk, unsigned bad_list,
+                                    unsigned *flags) {
     const conststn_csf_s *X = plan->X;
     const RecordStream &rs = plan->records;
-    if (rs.n_chunks == 0) return CONSTSTN_OK;
-    const RecordFill a = view_of_stream(X, rs);
-    int64_t dims1 = 0;
-    for (int l = 1; l < X->order - 1; ++l) dims1 = std::max(dims1, X->dims[X->mode_order[l]]);
-    const int64_t threads = std::max(std::max(a.total, a.slices + 1), rs.n_chunks);
-    check_records_kernel<<<blocks_for(threads), dim3(256)>>>(a, dims1, rs.q, rs.n_chunks, plan->out_rows, rs.chunk_slice.p, rs.open1.p,
-                                                              X->order == 4 ? rs.open2.p : nullptr, rs.row_of_slice.p, bad_code,
-                                                              bad_chunk, flags);
+    RecordCheck c{};
+    c.a = view_of_stream(X, rs);
+    if (!plan->compact && !rs.zero_all && rs.n_empty != plan->out_rows - c.a.slices) {
+        set_error("plan tables: %lld rows to clear where %lld are empty", (long long)rs.n_empty, (long long)(plan->out_rows - c.a.slices));
+        return CONSTSTN_EINVAL;
+    }
+    c.q = rs.q;
+    c.n_chunks = rs.n_chunks;
+    c.out_rows = plan->out_rows;
+    c.n_light = rs.n_light;
+    c.n_heavy = rs.n_heavy;
+    c.n_empty = rs.n_empty;
+    c.chunk_slice = rs.chunk_slice.p;
+    c.open1 = rs.open1.p;
+    c.open2 = rs.open2.p;
+    c.row_of_slice = rs.row_of_slice.p;
+    c.light = rs.light.p;
+    c.heavy = rs.heavy.p;
+    c.empty = rs.empty.p;
+    c.idx0 = X->idx[0].p;
+    c.compact = plan->compact ? 1 : 0;
+    c.bad_code = bad_code;
+    c.bad_chunk = bad_chunk;
+    c.bad_list = bad_list;
+    const int64_t threads = std::max({c.a.total, c.a.slices + 1, rs.n_chunks, rs.n_empty});
+    const dim3 grid{unsigned(std::min<int64_t>(div_up(threads, 256), int64_t(1) << 20))};
+    check_records_kernel<<<grid, dim3(256)>>>(c, threads, flags);
     CST_HIP(hipGetLastError());
     return CONSTSTN_OK;
 }

@@ -334,7 +334,8 @@ bool sptn3_two_waves_fit(int nwords);
 // kernels_records.hip
 bool record_stream_fits(const conststn_csf_s *X, int R);
 conststn_status build_record_stream(conststn_plan_s *plan);
-conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_code, unsigned bad_chunk, unsigned *flags);
+conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_code, unsigned bad_chunk,
+                                    unsigned bad_list, unsigned *flags);
 conststn_status launch_record_stream(const conststn_plan_s *plan, const double *const *dense, double *out,
                                      hipStream_t stream);
 
