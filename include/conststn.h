@@ -177,14 +177,16 @@ conststn_status conststn_plan(const char *schedule, const int *fusion, int n_ope
  * options choose among kernel forms and partition sizes that compute the same result; they are read
  * while the plan is built and stored in it -- nothing is read from the environment, and an execute
  * reads no option.  Names (default): force_generic (0; 1 = the generic executor also where a tuned
- * kernel exists), generic_max_gb (64), generic_span (4096), generic_densify (1: a tree over several CSF operands runs on the generic executor, which walks the
+ * kernel exists), generic_max_gb (64), generic_span (4096; another value sends an order-4 MTTKRP to the generic executor), generic_densify (1: a tree over several CSF operands runs on the generic executor, which walks the
  * largest and keeps dense copies of the others; 0 = such trees are refused), generic_fuse (1; 0 = the generic
  * executor stores every intermediate whole even where the schedule fuses), reroot (1; 0 = no private re-sorted copy of the
  * tensor for MTTKRP / TTMc of a non-root level: the generic executor takes those), mttkrp_records (1; 0 = no second copy
- * of the tensor as a stream of records: the CSF itself is walked, at order 4 by the generic executor), mttkrp_split (1), mttkrp_dual (44 = hot and cold sub-tensor in one launch, four
- * wavefronts of a workgroup each; 35, 53, 88 likewise; 0 = two launches), mttkrp_hot (256),
- * mttkrp_chunk (0 = by tensor size), ttmc3_mfma (1), ttmc3_stream (1), ttmc3_producers (4),
- * ttmc3_batch (2048), ttmc3_itemcost (2), ttmc3_qn (2), ttmc3_split (4096), ttmc3_rowsplit (by size),
+ * of the tensor as a stream of records: the CSF itself is walked, at order 4 by the generic executor), mttkrp_split (1: rank 32
+ * on large power-law tensors runs as a hot and a cold sub-tensor in one launch; 0 = the record stream),
+ * mttkrp_dual (44 = four wavefronts of a workgroup for each of the two; 35, 53, 88 = three and five, ..., and the two
+ * sub-tensors whatever the tensor's size; 0 = the record stream), mttkrp_hot (256 = rows kept on chip; another value
+ * likewise asks for the two sub-tensors), mttkrp_chunk (0 = by tensor size), ttmc3_mfma (1), ttmc3_stream (1),
+ * ttmc3_producers (4; another value only where the ranks are multiples of 16 and 32), ttmc3_batch (by size, 2048 at most), ttmc3_itemcost (2), ttmc3_qn (2), ttmc3_split (4096), ttmc3_rowsplit (by size),
  * ttmc4_mfma (1), ttmc4_split (256), ttmc4_ksplit (by size), sptn3_tiled (1; 0 = baseline kernel, 2 = tiled kernel
  * also where W fills its 16 x 16 tiles to less than a sixteenth),
  * sptn3_waves (2), sptn3_wgs (8000), sptn3_xcd (0), spchain3_form (1; 2 = general numeric pass),

@@ -93,7 +93,7 @@ static conststn_status match_chain(conststn_plan_s *plan) {
         // order 4 belongs to the generic executor, which runs the whole chain as one kernel; where its options
         // ask for nothing else, that kernel is the record stream's
         plan->use_records = record_stream_fits(X.csf, plan->rank_of_level[1]) && plan->opt("mttkrp_records", 1) == 1 &&
-                            (n == 3 || (plan->opt("generic_fuse", 1) == 1 && !plan->options.count("generic_span")));
+                            (n == 3 || (plan->opt("generic_fuse", 1) == 1 && plan->opt("generic_span", kGenSpan) == kGenSpan));
         if (n == 4 && !plan->use_records) { set_error("MTTKRP kernels exist for order-3 tensors only"); return CONSTSTN_EUNSUPPORTED; }
         plan->family = n == 3 ? FAM_MTTKRP3 : FAM_GENERIC;
         plan->gen_rooted = n == 4;

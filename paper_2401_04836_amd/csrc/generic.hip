@@ -702,7 +702,7 @@ conststn_status build_generic(conststn_plan_s *plan) {
 
     // one thread summing a whole subtree is fine for short fibers and hopeless for a power-law slice:
     // beyond span_limit nodes below one result node the sum is cut into segments (two passes)
-    const int64_t span_limit = plan->opt("generic_span", 4096);
+    const int64_t span_limit = plan->opt("generic_span", kGenSpan);
     std::map<std::pair<int, int>, int64_t> span_cache;
     conststn_status span_status = CONSTSTN_OK;
     auto max_span = [&](int d_out, int d_in) -> int64_t {

@@ -366,7 +366,8 @@ static conststn_status build_mttkrp3_hot(conststn_plan_s *plan, bool asked) {
 // sub-tensors side by side in one launch.  It pays one more factor row per fiber that has leaves of both kinds,
 // so it needs long fibers: 1.15 against 1.23 ms at 76 M nonzeros with 5.9 leaves per fiber, 0.69 against
 // 0.73 ms at 40 M with 4.7, but 0.86 against 0.84 at 40 M with 3.6 and 0.41 against 0.36 at 20 M.  The plan options
-// mttkrp_dual and mttkrp_hot ask for it whatever the size; mttkrp_split=0 or mttkrp_dual=0 for the stream.
+// mttkrp_dual and mttkrp_hot ask for it whatever the size where their value is not the default; mttkrp_split=0 or
+// mttkrp_dual=0 for the stream.
 conststn_status build_mttkrp3_tables(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t nnz = X->nnz;
@@ -386,7 +387,7 @@ conststn_status build_mttkrp3_tables(conststn_plan_s *plan) {
         CST_HIP(hipDeviceSynchronize());
         return CONSTSTN_OK;
     }
-    const bool asked = plan->options.count("mttkrp_dual") || plan->options.count("mttkrp_hot");
+    const bool asked = plan->opt("mttkrp_dual", 44) != 44 || plan->opt("mttkrp_hot", 256) != 256;
     const bool large = nnz >= (int64_t(1) << 25) && nnz / 9 * 2 >= X->nodes[1];
     if (plan->rank_of_level[1] == 32 && nnz > 0 && (asked || large) && plan->opt("mttkrp_split", 1) == 1 &&
         plan->opt("mttkrp_dual", 44) != 0) {

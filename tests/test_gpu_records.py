@@ -161,3 +161,21 @@ def test_without_a_copy_of_the_tensor(rank):
     got, pl = _run(T4, c, v, dims4, [("D", F[2]), ("C", F[1]), ("B", F[0])], dict(mttkrp_records=0))
     f, ext = [(F[0], "jr"), (F[1], "kr"), (F[2], "lr")], {"i": dims4[0], "r": rank}
     assert oracle.rel_err(got, nary.contract(c, v, "ijkl", f, "ir", ext), nary.contract_abs(c, v, "ijkl", f, "ir", ext)) <= 4e-13
+
+
+def test_an_option_at_its_default_changes_nothing():
+    dims, rank = (40, 30, 500), 32
+    c, v, rng = _tensor(dims, 5000, 2000, 77)
+    B, C = rng.uniform(-1, 1, (dims[1], rank)), rng.uniform(-1, 1, (dims[2], rank))
+    print("[case] options at their defaults", flush=True)
+    base, pl = _run(S.MTTKRP3, c, v, dims, [("C", C), ("B", B)], None)
+    for opts in (dict(mttkrp_hot=256), dict(mttkrp_dual=44), dict(mttkrp_split=1, mttkrp_records=1, mttkrp_chunk=0)):
+        got, p = _run(S.MTTKRP3, c, v, dims, [("C", C), ("B", B)], opts)
+        assert p.describe() == pl.describe() and np.array_equal(got, base), opts
+    dims = (12, 8, 30, 20)
+    c, v, rng = _tensor(dims, 3000, 1500, 78)
+    B, C, D = (rng.uniform(-1, 1, (d, rank)) for d in dims[1:])
+    base, pl = _run(T4, c, v, dims, [("D", D), ("C", C), ("B", B)], None)
+    for opts in (dict(generic_span=4096), dict(generic_fuse=1, force_generic=0)):
+        got, p = _run(T4, c, v, dims, [("D", D), ("C", C), ("B", B)], opts)
+        assert p.describe() == pl.describe() and np.array_equal(got, base), opts
