@@ -30,15 +30,28 @@ PLAN_OPTIONS = None          # tuning options handed to every plan (--generic, -
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
 CSRC = os.path.join(ROOT, "paper_2401_04836_amd", "csrc")
-KERNEL_SOURCES = {"mttkrp3": ["kernels_mttkrp3.hip", "partition.hip"],
+KERNEL_SOURCES = {"mttkrp3": ["kernels_mttkrp3.hip", "kernels_records.hip", "partition.hip"],
                   "ttmc3": ["kernels_ttmc3.hip", "partition.hip"],
                   "ttmc4": ["kernels_ttmc4.hip", "partition.hip"],
                   "sptn3": ["kernels_sptn3.hip", "partition.hip"],
                   "spchain3": ["kernels_spchain3.hip"], "sppair4": ["kernels_sppair4.hip"]}
-KERNEL_NAMES = {"mttkrp3": "mttkrp3_r32_dual_kernel<4,4> (hot and cold sub-tensor as two teams of wavefronts in one launch)",
-                "ttmc3": "ttmc3_stream_kernel<4,2,4>", "ttmc4": "ttmc4_mfma_kernel<8,true>", "sptn3": "sptn3_owned_kernel",
+# by family and, where a family has several forms, by the "kernel=..." of the plan's description
+KERNEL_NAMES = {"mttkrp3 hot": "mttkrp3_r32_dual_kernel<4,4> (hot and cold sub-tensor as two teams of wavefronts in one launch)",
+                "mttkrp3 records": "records_kernel", "mttkrp3 csf": "mttkrp3_csf_kernel", "generic records": "records_kernel",
+                "ttmc3 stream": "ttmc3_stream_kernel", "ttmc3 rows": "ttmc3_mfma_kernel", "ttmc3 general": "ttmc3_kernel",
+                "ttmc4 mfma": "ttmc4_mfma_kernel", "ttmc4 general": "ttmc4_kernel", "sptn3": "sptn3_owned_kernel",
                 "spchain3": "spchain3_local_kernel", "sppair4": "sppair4_kernel",
                 "generic": "generic executor (generic_fused_kernel + generic_segsum kernels, or one kernel per statement)"}
+
+
+def kernel_name(desc):
+    """The dominant kernel of a plan, from its description."""
+    words = desc.split()
+    family = words[0].split("=")[1]
+    form = [x[7:] for x in words if x.startswith("kernel=")]
+    return KERNEL_NAMES.get("%s %s" % (family, form[0]) if form else family, KERNEL_NAMES.get(family, family))
+
+
 # what bounds the dominant kernel of each family: the order-3 forms stream far more bytes than they
 # compute (HBM); the order-4 TTMc and the three-tensor network are dense contractions per fiber
 # (fp64 matrix cores)
@@ -509,7 +522,7 @@ def run_config(cst, S, dev, args, cid, cpu_budget):
 
     desc = launches[0]["plan"].describe().split("|")[0]
     family = desc.split()[0].split("=")[1]
-    if family == "generic":
+    if family == "generic" and "kernel=records" not in desc:
         name += " [generic executor]"
     plain = not (args.small or args.restricted or args.all_modes or args.mttkrp4)
     rec = {
@@ -525,7 +538,7 @@ def run_config(cst, S, dev, args, cid, cpu_budget):
                              if CSF_ONLY else {})),
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(family, cid if plain else None),
-                     "kernel": KERNEL_NAMES.get(family, family),
+                     "kernel": kernel_name(desc),
                      "kernel_ms_avg": avg_kernel_ms, "launches_timed": len(kernel_ms),
                      "kernel_ms_per_contraction": per_launch_ms,
                      "algorithmic_bytes_per_launch": alg_bytes,
@@ -632,7 +645,7 @@ def main():
     cpu_budget = 400_000_000 if len(cids) == 1 else 1_200_000_000
     recs = [run_config(cst, S, dev, args, cid, cpu_budget) for cid in cids]
     if args.config == 0 and not args.mttkrp4:
-        # beside the configurations: the order-4 MTTKRP on configuration 3's tensor (a fused chain in one generic kernel)
+        # beside the configurations: the order-4 MTTKRP on configuration 3's tensor (a fused chain as one walk over records)
         args.mttkrp4 = True
         extra = run_config(cst, S, dev, args, 3, cpu_budget)
         extra["config_id"] = 8

@@ -663,6 +663,15 @@ static conststn_status make_plan(const char *schedule, const int *fusion, int n_
             snprintf(b, sizeof(b), " kernel=baseline");
         plan->description += b;
     }
+    if (plan->use_records && !plan->split) {
+        char b[96];
+        snprintf(b, sizeof(b), " kernel=records chunks %lld of %lld", (long long)plan->records.n_chunks, (long long)plan->records.q);
+        plan->description += b;
+    } else if (plan->family == FAM_MTTKRP3) {
+        plan->description += plan->split ? " kernel=hot and cold" : " kernel=csf";
+    }
+    if (plan->family == FAM_TTMC4 || (plan->family == FAM_TTMC3 && !plan->use_rows))
+        plan->description += plan->use_rows ? " kernel=mfma" : " kernel=general";
     if (plan->family == FAM_TTMC3 && plan->use_rows) {
         char b[128];
         if (plan->use_stream)
@@ -681,17 +690,16 @@ static conststn_status make_plan(const char *schedule, const int *fusion, int n_
     }
     if (plan->family == FAM_GENERIC) {
         int fused = 0, pairs = 0, stmts = int(plan->gen.size());
-        if (plan->use_records) {                     // one kernel, every producer inlined
+        if (plan->use_records) {                     // the record stream: one traversal for the whole chain
             stmts = int(plan->sched.stmts.size());
             fused = stmts - 1;
-            pairs = plan->rank_of_level[1] % 2 == 0 ? 1 : 0;
         }
         for (const GenStmt &g : plan->gen) { fused += g.skip; pairs += (g.fused && !g.skip && g.fused_pairs) ? 1 : 0; }
         char b[96];
         snprintf(b, sizeof(b), " kernels=%d inlined_producers=%d", stmts - fused, fused);
         plan->description += b;
         snprintf(b, sizeof(b), " two_elements_per_lane=%d", pairs);
-        plan->description += b;
+        if (!plan->use_records) plan->description += b;
         if (!plan->gen_densified.empty()) {
             snprintf(b, sizeof(b), " dense_copies_of_csf_operands=%d", int(plan->gen_densified.size()));
             plan->description += b;

@@ -1007,7 +1007,8 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
     plan->use_stream = stream && plan->use_rows;
     if (plan->use_stream) {
         int np = int(plan->opt("ttmc3_producers", 4));
-        plan->stream_producers = np == 2 || np == 3 || np == 6 || np == 8 ? np : 4;
+        const bool whole = R2 % 16 == 0 && R3 % 32 == 0;         // other ranks have the form with four only
+        plan->stream_producers = whole && (np == 2 || np == 3 || np == 6 || np == 8) ? np : 4;
         CST_TRY(build_stream_tables(plan));
     }
     return CONSTSTN_OK;

@@ -86,10 +86,11 @@ def test_mttkrp_order4_and_fusion_choices():
             "T2[i,j,r] = T1[i,j,k,r] * C[k,r] | i,j,k,r ; "
             "M[i,r] = T2[i,j,r] * B[j,r] | i,j,r")
     f = [(B, "jr"), (C, "kr"), (D, "lr")]
-    for fusion in (None, [0, 0, 0], [1, 2, 0], [3, 1, 0]):
-        _say("order-4 MTTKRP, fusion %s" % (fusion,))
-        got, _ = _run(text, (coords, vals, dims), [0, 1, 2, 3], [("D", D), ("C", C), ("B", B)], (40, 24),
-                      fusion=fusion)
+    for fusion, opts in ((None, None), (None, "force_generic=1"), ([0, 0, 0], None), ([1, 2, 0], None), ([3, 1, 0], None)):
+        _say("order-4 MTTKRP, fusion %s, options %s" % (fusion, opts))
+        got, pl = _run(text, (coords, vals, dims), [0, 1, 2, 3], [("D", D), ("C", C), ("B", B)], (40, 24),
+                       fusion=fusion, options=opts)
+        assert ("kernel=records" in pl.describe()) == (fusion is None and opts is None)
         _check(got, coords, vals, "ijkl", f, "ir", {"i": 40, "r": 24})
 
 
@@ -193,8 +194,8 @@ def test_fused_leaf_producer_is_inlined_and_equals_the_stored_intermediate():
     B4, C4, D4 = _dense(397, 14, 8), _dense(398, 12, 8), _dense(399, 11, 8)
     t4 = ("T1[i,j,k,r] = X[i,j,k,l] * D[l,r] | i,j,k,l,r ; T2[i,j,r] = T1[i,j,k,r] * C[k,r] | i,j,k,r ; "
           "M[i,r] = T2[i,j,r] * B[j,r] | i,j,r")
-    got, pl = _run(t4, (c4, v4, dims4), [0, 1, 2, 3], [("D", D4), ("C", C4), ("B", B4)], (30, 8))
-    assert "kernels=1 inlined_producers=2" in pl.describe(), pl.describe()
+    got, pl = _run(t4, (c4, v4, dims4), [0, 1, 2, 3], [("D", D4), ("C", C4), ("B", B4)], (30, 8), options="force_generic=1")
+    assert "kernels=1 inlined_producers=2" in pl.describe() and "kernel=records" not in pl.describe(), pl.describe()
     _check(got, c4, v4, "ijkl", [(B4, "jr"), (C4, "kr"), (D4, "lr")], "ir", {"i": 30, "r": 8})
     _say("a slice of 40 000 leaves in 20 000 fibers: more segments than one thread adds in the second pass")
     dimsh = (10, 20000, 4)
@@ -348,7 +349,7 @@ def test_fused_chain_of_producers_is_one_kernel():
         f = [(B, "jr"), (C, "rk"), (D, "lr")]
         _say("order 4, rank %d" % R)
         got, pl = _run(text, x, [0, 1, 2, 3], ops, (40, R))
-        assert "kernels=1 inlined_producers=2" in pl.describe(), pl.describe()
+        assert "kernels=1 inlined_producers=2" in pl.describe() and "kernel=records" not in pl.describe(), pl.describe()
         _check(got, coords, vals, "ijkl", f, "ir", {"i": 40, "r": R})
         stored, pl = _run(text, x, [0, 1, 2, 3], ops, (40, R), options="generic_fuse=0")
         assert "kernels=3 inlined_producers=0" in pl.describe(), pl.describe()
@@ -369,9 +370,11 @@ def test_fused_chain_of_producers_is_one_kernel():
         csf = cst.build_csf([c.cuda() for c in coords], vals.cuda(), dims, [0, 1, 2, 3])
         dev = [D.cuda(), Ct.cuda(), torch.zeros(B.numel() + 1, dtype=torch.float64).cuda()[1:].view_as(B).copy_(B.cuda())]
         assert dev[2].data_ptr() % 16 == 8
-        pl = cst.plan(text2, [("X", csf), ("D", dev[0]), ("C", dev[1]), ("B", dev[2])])
-        one = cst.execute(pl, dev).cpu().numpy().reshape(40, R)
-        np.testing.assert_allclose(one, got, rtol=0, atol=1e-10)
+        for opts in ("force_generic=1", None):               # None: the record stream, which reads pairs at any double
+            pl = cst.plan(text2, [("X", csf), ("D", dev[0]), ("C", dev[1]), ("B", dev[2])], options=opts)
+            assert ("kernel=records" in pl.describe()) == (opts is None)
+            one = cst.execute(pl, dev).cpu().numpy().reshape(40, R)
+            np.testing.assert_allclose(one, got, rtol=0, atol=1e-10)
         pair, pl = _run(text, x, [0, 1, 2, 3], ops, (40, R), fusion=[3, 1, 0])       # the second pair fused on i only
         assert "kernels=2 inlined_producers=1" in pl.describe(), pl.describe()
         np.testing.assert_allclose(pair, got, rtol=0, atol=1e-10)

@@ -228,14 +228,16 @@ def test_mttkrp_compact_rows_with_empty_and_heavy_slices(rank):
 
 
 @pytest.mark.parametrize("dual", [0, 35, 53, 88])
-def test_mttkrp_hot_and_cold_passes_in_one_launch_or_two(dual):
-    """The default runs the hot and the cold sub-tensor as two teams of wavefronts in one launch (the cold
-    team into a buffer of its own, added afterwards); other team sizes and the two-launch form must agree."""
+def test_mttkrp_hot_and_cold_teams_of_any_size(dual):
+    """The hot and the cold sub-tensor as two teams of wavefronts in one launch (the cold team into a buffer of its
+    own, added afterwards), which a team size other than the default's asks for at any size of tensor; 0: the record
+    stream instead."""
     _say("mttkrp rank 32, mttkrp_dual=%d" % dual)
     wl = w.make(2, small=True, dims=(4001, 211, 503), nnz=40_003, rank=32)
     want, S_abs = run_oracle(wl)
     for flags in (0, cst.OUT_COMPACT):
         out, pl, _ = run_gpu(wl, flags=flags, options={"mttkrp_dual": dual})
+        assert ("kernel=hot and cold" if dual else "kernel=records") in pl.describe()
         assert compare(out, want, S_abs, rows=pl.output_rows() if flags else None) <= TOL
     wl = w.make(2, small=True)
     out, pl, _ = run_gpu(wl, options={"mttkrp_dual": dual})

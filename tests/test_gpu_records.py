@@ -51,6 +51,7 @@ def test_order3(rank, dims, nnz, heavy, chunk):
     for flags in (0, cst.OUT_COMPACT):
         got, pl = _run(S.MTTKRP3, c, v, dims, [("C", C), ("B", B)], dict(mttkrp_chunk=chunk), flags)
         rows = pl.output_rows().cpu().numpy() if flags else slice(None)
+        assert "kernel=records" in pl.describe()
         # at most 80 000 products of three factors per sum, in any order: 80 002 roundings of 1.1e-16
         assert oracle.rel_err(got, want[rows], S_abs[rows]) <= 8.9e-12
 
@@ -63,7 +64,7 @@ def test_order4(rank, dims, nnz, heavy, chunk):
     print("[case] order 4 rank %d dims %s nnz %d chunk %d" % (rank, dims, len(v), chunk), flush=True)
     B, C, D = (rng.uniform(-1, 1, (d, rank)) for d in dims[1:])
     got, pl = _run(T4, c, v, dims, [("D", D), ("C", C), ("B", B)], dict(mttkrp_chunk=chunk))
-    assert "kernels=1 inlined_producers=2" in pl.describe()
+    assert "kernels=1 inlined_producers=2" in pl.describe() and "kernel=records" in pl.describe()
     f, ext = [(B, "jr"), (C, "kr"), (D, "lr")], {"i": dims[0], "r": rank}
     want, S_abs = nary.contract(c, v, "ijkl", f, "ir", ext), nary.contract_abs(c, v, "ijkl", f, "ir", ext)
     assert oracle.rel_err(got, want, S_abs) <= 1.0e-12       # at most 9000 products of four factors per sum
@@ -152,7 +153,7 @@ def test_without_a_copy_of_the_tensor(rank):
         for flags in (0, cst.OUT_COMPACT):
             print("[case] no copy, order 3 rank %d chunk %d flags %d" % (rank, chunk, flags), flush=True)
             got, pl = _run(S.MTTKRP3, c, v, dims, [("C", C), ("B", B)], dict(mttkrp_chunk=chunk, mttkrp_records=0), flags)
-            assert "record" not in pl.describe()
+            assert "kernel=csf" in pl.describe()
             rows = pl.output_rows().cpu().numpy() if flags else slice(None)
             assert oracle.rel_err(got, want[rows], S_abs[rows]) <= 2.3e-12       # at most 20 500 products of three per sum
     dims4 = (12, 8, 30, 20)
