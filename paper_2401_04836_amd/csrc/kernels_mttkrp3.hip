@@ -22,7 +22,7 @@ namespace cst {
 struct MttkrpArgs {
     int64_t nnz, q, n_chunks, slices;
     int R;
-    const int64_t *ptr0, *ptr1;
+    const int64_t *ptr0, *ptr1;                // on the CSF itself only, as idx2 and compact
     const int32_t *idx0, *idx1, *idx2;         // result row of every slice; level-1 index of every fiber; leaves
     int compact;                               // 1: the result row is the slice's number
     int add;                                   // 1: rows are added to what the result holds (the two sub-tensors)
@@ -167,7 +167,6 @@ struct MttkrpR32Args {
     const uint32_t *code;
     const int32_t *hot_rows;
     int n_hot;
-    int64_t fibers;
 };
 
 struct lds_pair { double x, y; };
@@ -533,8 +532,6 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
         aa.base.n_chunks = P.n_chunks;
         aa.base.slices = P.slices;
         aa.base.R = plan->rank_of_level[1];
-        aa.base.ptr0 = P.ptr0.p;
-        aa.base.ptr1 = P.ptr1.p;
         aa.base.idx0 = P.row_of_slice.p;
         aa.base.idx1 = P.idx1.p;
         aa.base.add = 1;
@@ -552,7 +549,6 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
         aa.code = P.code.p;
         aa.hot_rows = plan->hot_rows.p;
         aa.n_hot = plan->n_hot;
-        aa.fibers = P.fibers;
     }
     const MttkrpDualArgs d{pa[0], pa[1]};
     // wavefronts per workgroup, and as many workgroups per CU as its LDS and its registers (96 per

@@ -705,8 +705,6 @@ __global__ void fill_groups_kernel(int64_t fibers, int64_t slices, const int64_t
 static conststn_status build_piece_groups(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t slices = X->nodes[0], fibers = X->nodes[1], nodes = X->nodes[2];
-    const int64_t K = X->dims[X->mode_order[2]];
-    if (K > int64_t(kGrpIndexMask)) { set_error("level-2 extent of 2^26 or more"); return CONSTSTN_EUNSUPPORTED; }
     const dim3 block(256);
     DevBuf<int64_t> cnt, piece_off, groups_of, grp_off, ksteps_of;
     CST_TRY(cnt.alloc(nodes));

@@ -127,7 +127,7 @@ struct alignas(32) PieceDesc {
     double v0, v1;          // leaf values (v1 = 0 when absent)
 };
 static_assert(kPieceLeaves == 2, "PieceDesc holds two leaves");
-// structure flags carried in PieceDesc::k (the same on the four records of a group)
+// structure flags carried in PieceDesc::k (the same on the four records of a group; extents are below 2^25 here)
 constexpr uint32_t kGrpEndsFiber = 1u << 28, kGrpEndsKstep = 1u << 29, kGrpStartsKstep = 1u << 30,
                    kGrpIndexMask = (1u << 26) - 1u;
 // flags of one record: it pads its group, or its second leaf is absent
