@@ -58,3 +58,27 @@ def test_a_row_that_is_not_finite_reaches_its_own_results_only(factor):
     assert np.isinf(out[0]).any() and np.isfinite(out[0]).any() and not np.isnan(out[0]).any()
     np.testing.assert_array_equal(np.isinf(out[0]), np.isinf(out[1]))
     assert not np.isnan(out[1]).any()
+
+
+@pytest.mark.parametrize("ranks,longer", [((16, 16, 16), True), ((10, 12, 7), False)])
+def test_items_of_a_large_tensor(ranks, longer):
+    """About 0.3 M K-steps in 300 slices: at ranks 16 x 16 x 16 items of 64 K-steps (16 per slice and fewer), at smaller
+    row blocks of 32."""
+    g = torch.Generator(device="cuda").manual_seed(31)
+    dims, n = (300, 20_000, 900, 700), 1_250_000
+    keys = torch.unique(torch.randint(0, int(np.prod(np.array(dims, dtype=np.int64))), (n,), generator=g, device="cuda"))
+    keys = keys[torch.randperm(keys.numel(), generator=g, device="cuda")]
+    c = []
+    for d in reversed(dims):
+        c.append((keys % d).to(torch.int32))
+        keys = keys // d
+    v = torch.rand(c[0].numel(), generator=g, dtype=torch.float64, device="cuda")
+    print("[case] order-4 TTMc, ranks %s, %d nonzeros" % (ranks, v.numel()), flush=True)
+    csf = cst.build_csf(c[::-1], v, dims, [0, 1, 2, 3])
+    U = [torch.rand(d, r, generator=g, dtype=torch.float64, device="cuda") for d, r in zip(dims[1:], ranks)]
+    ops = [("X", csf)] + list(zip(("U3", "U2", "U1"), U[::-1]))
+    pl, general = cst.plan(S.TTMC4, ops), cst.plan(S.TTMC4, ops, options=dict(ttmc4_mfma=0))
+    blocks = int(pl.describe().split("partial_blocks=")[1].split()[0])
+    assert 300 * 13 <= blocks <= 300 * 17 if longer else 300 * 26 <= blocks <= 300 * 33, blocks
+    a, b = cst.execute(pl, U[::-1]), cst.execute(general, U[::-1])
+    assert (a / b - 1).abs().max().item() <= 9.5e-13              # positive terms, at most 4 200 per sum
