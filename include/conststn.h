@@ -135,9 +135,9 @@ void conststn_csf_destroy(conststn_csf_t *csf);
  *     equals the consumer's prefix position by position ("Consumer constraints"), and every
  *     statement between the two shares it ("Statements between producer and consumer").
  * Kernel choice.  Tuned kernels take: TTMc of order 3 (ranks up to 64) and order 4 (ranks up to
- * 16), MTTKRP of order 3 (rank up to 128), each with the sparse prefix fully fused, and the
- * three-tensor network (U.V).W fused on its two outer loops.  The chain of three sparse tensors of
- * Sec. 5.1 (every operand a CSF handle, sparse result: see conststn_plan_output_csf),
+ * 16), MTTKRP of order 3 (rank up to 128) and order 4 (rank 2 to 128, extents below the root up to 2^28; one of the
+ * generic executor's forms), each with the sparse prefix fully fused, and the three-tensor network (U.V).W
+ * fused on its two outer loops.  The chain of three sparse tensors of Sec. 5.1 (every operand a CSF handle, sparse result: see conststn_plan_output_csf),
  *      "T[K,i,v] = I[K,u,v] * C[i,u] | K,i,u,v ; E[K,i,m] = T[K,i,v] * P[m,v] | K,i,m,v"
  * and its restricted form with a statement "F[K,i,v] = T[K,i,v] * L[K,i] | K,i,v" in between,
  * fused on the two outer loops, has a kernel of its own, and so has the four-index product of the
@@ -186,7 +186,9 @@ conststn_status conststn_plan(const char *schedule, const int *fusion, int n_ope
  * mttkrp_dual (44 = four wavefronts of a workgroup for each of the two; 35, 53, 88 = three and five, ..., and the two
  * sub-tensors whatever the tensor's size; 0 = the record stream), mttkrp_hot (256 = rows kept on chip; another value
  * likewise asks for the two sub-tensors), mttkrp_chunk (0 = by tensor size), ttmc3_mfma (1), ttmc3_stream (1),
- * ttmc3_producers (4; another value only where the ranks are multiples of 16 and 32), ttmc3_batch (by size, 2048 at most), ttmc3_itemcost (2), ttmc3_qn (2), ttmc3_split (4096), ttmc3_rowsplit (by size),
+ * ttmc3_producers (4; another value only where the ranks are multiples of 16 and 32), ttmc3_batch (by size, 2048 at
+ * most), ttmc3_itemcost (2), ttmc3_qn (2), ttmc3_split (4096 = leaves per work item of the general kernel),
+ * ttmc3_rowsplit (by size = rows per work item of the matrix-core kernels),
  * ttmc4_mfma (1), ttmc4_split (256), ttmc4_ksplit (by size), sptn3_tiled (1; 0 = baseline kernel, 2 = tiled kernel
  * also where W fills its 16 x 16 tiles to less than a sixteenth),
  * sptn3_waves (2), sptn3_wgs (8000), sptn3_xcd (0), spchain3_form (1; 2 = general numeric pass),
@@ -259,7 +261,8 @@ conststn_status conststn_plan_output_csf(const conststn_plan_t *plan, const cons
 /* Debugging aid: the kernels trust the tables a plan holds (an index out of range there is a memory
  * fault, not an error code).  This pass checks, on the device, that every table of an order-3 MTTKRP
  * or TTMc plan (Sec. 5.2, 5.3) stays inside the arrays it indexes: chunk tables against the pointer arrays,
- * the re-encoded leaf stream (LDS slots, factor rows, end-of-fiber / end-of-slice marks), row
+ * the re-encoded leaf stream (LDS slots, factor rows, end-of-fiber / end-of-slice marks), the record stream of
+ * order-3 and order-4 MTTKRP plans (every record, value, open row and row list against the level arrays), row
  * descriptors, items, K-steps and workgroup batches of the TTMc kernels, and the tensor the kernels
  * walk (conststn_csf_check of it).  For a plan of the generic executor: the segment tables of its long
  * sums (every result node's children, or leaves, tiled in order by segments of the stated length), the

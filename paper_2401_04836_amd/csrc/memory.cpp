@@ -1,6 +1,6 @@
 // Device memory of the library's objects: a bounded cache of released blocks.
 //
-// A CSF build of 76 M nonzeros takes 2.0 GB of temporaries and hands out 1.2 GB of level arrays.  hipMalloc and
+// A CSF build of 76 M nonzeros takes 2.5 GB of temporaries and hands out 1.2 GB of level arrays.  hipMalloc and
 // hipFree of these cost 1 ms by themselves, but memory that goes back to the driver is cleared before it is
 // handed out again, and a program that builds tensor after tensor outruns that: 45 to 90 ms per build where the
 // kernels take 7.  Blocks of destroyed objects are therefore kept and reused, under these rules:
