@@ -12,8 +12,8 @@
 // lock step, one record per step: a step is NV gathers in which every group takes part, whatever its record is.
 // With the rows of ended fibers read beside the leaf rows, as a stream of leaves needs it, half the gathers serve
 // 1.4 of 4 groups.  The bound is the L1 pipeline, which takes 16 cycles for such a gather (64 bytes a cycle) and
-// more where it misses: busy in 95 % of the cycles at 76 M nonzeros, rank 32, 89 M records (its address unit 92 %,
-// 71 % of its requests hit the L2), 89 % at 20 M and rank 50, 91 % at order 4 (L2 hits 55 and 67 %).  Neither fewer
+// more where it misses: busy in 96 % of the cycles at 76 M nonzeros, rank 32, 89 M records (its address unit 95 %,
+// 72 % of its requests hit the L2), 91 % at 20 M and rank 50, 93 % at order 4 (L2 hits 55 and 67 %).  Neither fewer
 // instructions per record (groups of 4 or 8 lanes with 4 or 2 pairs each: 1.54, 1.28 against 1.23 ms), nor
 // selects in place of branches (1.25), nor twice the rows in flight (1.20), nor the most named rows in LDS (1.20)
 // change it by more than that.
