@@ -910,12 +910,12 @@ static conststn_status order_items_by_cost(conststn_plan_s *plan) {
     return CONSTSTN_OK;
 }
 
-// counts[k] = partial row blocks of slices cut into items of c.rows[k] rows
+// counts[k] = partial row blocks of slices cut into items of c.rows[k] units (rows, or leaves)
 struct SplitChoices { int n; int64_t rows[16]; };
 __global__ void __launch_bounds__(256)
-count_partials_kernel(int64_t slices, const int64_t *__restrict__ slice_row, SplitChoices c, unsigned long long *counts) {
+count_partials_kernel(int64_t slices, const int64_t *__restrict__ unit_ptr, SplitChoices c, unsigned long long *counts) {
     const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t len = s < slices ? slice_row[s + 1] - slice_row[s] : 0;
+    const int64_t len = s < slices ? unit_ptr[s + 1] - unit_ptr[s] : 0;
     for (int k = 0; k < c.n; ++k) {
         int64_t n = len > c.rows[k] ? (len + c.rows[k] - 1) / c.rows[k] : 0;
         for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off, 64);
@@ -947,6 +947,32 @@ static conststn_status rows_per_item(const conststn_plan_s *plan, int64_t leaves
     return CONSTSTN_OK;
 }
 
+// Order 3 at ranks that do not fill the streaming kernel's tiles: whether the general kernel, a wavefront per slice, is
+// the faster one.  It is where slices are short and none is long enough to be cut, at row blocks that leave most of the
+// 16 x 64 tiles empty: fibers per slice, ranks, general against streaming, us: 1.6, 2 x 60: 734, 925; 2.3, 3 x 40: 612, 844;
+// 10, 2 x 33: 275, 339; 40, 2 x 33: 264, 256; 10, 4 x 60: 438, 334; with 70 % of the leaves in one slice, 1.7, 3 x 60: 920, 658.
+// And where a slice is about one leaf and its row block a few numbers: 1.6, 2 x 8: 412, 481; 2.3: 350, 310.
+// (Two million nonzeros each.)
+static conststn_status general_is_faster(const conststn_plan_s *plan, bool *yes) {
+    const conststn_csf_s *X = plan->X;
+    const int64_t slices = X->nodes[0], fibers = X->nodes[1];
+    const int R2 = plan->rank_of_level[1], R3 = plan->rank_of_level[2];
+    *yes = (R2 <= 3 && R3 > 32 && fibers <= 16 * slices) || (R2 * R3 <= 16 && fibers <= 2 * slices);
+    if (!*yes) return CONSTSTN_OK;
+    SplitChoices c{};
+    c.n = 1;
+    c.rows[0] = 4096;                                     // leaves, here
+    DevBuf<unsigned long long> counts;
+    CST_TRY(counts.alloc(1));
+    unsigned long long n = 0;
+    CST_HIP(hipMemcpy(counts.p, &n, sizeof(n), hipMemcpyHostToDevice));
+    count_partials_kernel<<<dim3(unsigned(div_up(slices, 256))), dim3(256)>>>(slices, plan->slice_leaf.p, c, counts.p);
+    CST_HIP(hipGetLastError());
+    CST_HIP(hipMemcpy(&n, counts.p, sizeof(n), hipMemcpyDeviceToHost));
+    *yes = n == 0;
+    return CONSTSTN_OK;
+}
+
 conststn_status build_ttmc_tables(conststn_plan_s *plan) {
     const conststn_csf_s *X = plan->X;
     const int64_t slices = X->nodes[0];
@@ -963,8 +989,13 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
     // form's pairs of column tiles would be half empty, and factors of 4 GiB and more.
     const int R2 = plan->rank_of_level[1], R3 = plan->rank_of_level[2];
     const bool rows16 = order == 3 && R2 % 16 == 0 && R3 % 16 == 0 && R2 <= 64 && R3 <= 64;
-    const bool stream = order == 3 && R2 >= 2 && R3 >= 2 && R2 <= 64 && R3 <= 64 && !(rows16 && R3 % 32 != 0) &&
-                        X->dims[X->mode_order[2]] * R3 * 8 < (int64_t(1) << 32) && plan->opt("ttmc3_stream", 1) == 1;
+    bool stream = order == 3 && R2 >= 2 && R3 >= 2 && R2 <= 64 && R3 <= 64 && !(rows16 && R3 % 32 != 0) &&
+                  X->dims[X->mode_order[2]] * R3 * 8 < (int64_t(1) << 32) && plan->opt("ttmc3_stream", 1) == 1;
+    if (stream && !rows16 && plan->opt("ttmc3_mfma", 1) == 1) {
+        bool general = false;
+        CST_TRY(general_is_faster(plan, &general));
+        stream = !general;
+    }
     plan->use_rows = (rows16 || stream) && plan->opt("ttmc3_mfma", 1) == 1;
     if (plan->use_rows) {
         CST_TRY(build_rows(plan));

@@ -92,3 +92,31 @@ def test_a_plan_that_does_not_fit_is_made_for_the_general_kernel(ranks):
     assert "kernel=stream" in usual.describe()
     a, b = cst.execute(pl, [u3, u2]), cst.execute(usual, [u3, u2])
     assert (a / b - 1).abs().max().item() <= 2.7e-12              # positive terms, at most 12 000 per sum
+
+
+@pytest.mark.parametrize("ranks,per_slice,heavy,kernel", [((3, 40), 4, 0, "general"), ((4, 40), 4, 0, "stream"), ((3, 32), 4, 0, "stream"),
+                                                          ((3, 40), 30, 0, "stream"), ((3, 40), 4, 9000, "stream"),
+                                                          ((2, 8), 1, 0, "general"), ((2, 8), 5, 0, "stream"), ((3, 8), 1, 0, "stream")])
+def test_short_slices_with_small_row_blocks(ranks, per_slice, heavy, kernel):
+    """Row blocks that leave the streaming kernel's tiles nearly empty stay with the general kernel where slices are short and
+    none is long."""
+    R2, R3 = ranks
+    dims = (2000, 60, 400)
+    rng = np.random.default_rng(R2 * 100 + R3 + per_slice)
+    keys = rng.integers(0, np.prod(dims), dims[0] * per_slice)
+    if heavy:
+        keys = np.concatenate([keys, 777 * 24_000 + rng.integers(0, 24_000, heavy)])
+    keys = rng.permutation(np.unique(keys))
+    c = [x.astype(np.int32) for x in np.unravel_index(keys, dims)]
+    v = rng.uniform(-1, 1, len(keys))
+    U2, U3 = rng.uniform(-1, 1, (dims[1], R2)), rng.uniform(-1, 1, (dims[2], R3))
+    print("[case] ranks %s, %d leaves per slice, %d in one" % (ranks, per_slice, heavy), flush=True)
+    csf = cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, [0, 1, 2])
+    u2, u3 = torch.from_numpy(U2).cuda(), torch.from_numpy(U3).cuda()
+    want, S_abs = oracle.ttmc3(c, v, dims, U2, U3, 0), oracle.ttmc3_abs(c, v, dims, U2, U3, 0)
+    for flags in (0, cst.OUT_COMPACT):
+        pl = cst.plan(S.TTMC3, [("X", csf), ("U3", u3), ("U2", u2)], flags=flags)
+        assert "kernel=" + kernel in pl.describe(), pl.describe()
+        rows = pl.output_rows().cpu().numpy() if flags else slice(None)
+        got = cst.execute(pl, [u3, u2]).cpu().numpy().reshape(-1, R2, R3)
+        assert oracle.rel_err(got, want[rows], S_abs[rows]) <= 1e-12      # at most 8000 products of three factors per sum
