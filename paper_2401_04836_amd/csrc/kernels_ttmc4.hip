@@ -135,6 +135,7 @@ ttmc4_kernel(Ttmc4Args a) {
 // 10 x 12 x 7, 5.4 M, 2.96 -> 0.34 ms and 63 K, 345 -> 33 us.
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
+typedef double v2d_u __attribute__((ext_vector_type(2), aligned(8)));     // a pair at any element
 
 struct Ttmc4RowArgs {
     int64_t n_items;
@@ -311,8 +312,9 @@ ttmc4_mfma_kernel(Ttmc4RowArgs a) {
             for (int q = 0; q < 4; ++q) {
                 const int flat = 32 * u + 2 * (4 * slot + (c >> 2)), r1 = 4 * q + (c & 3);
                 if (r1 < R1) {
-                    if (flat < R23) base[r1 * R23 + flat] = acc[2 * u][q];
-                    if (flat + 1 < R23) base[r1 * R23 + flat + 1] = acc[2 * u + 1][q];
+                    double *at = base + r1 * R23 + flat;
+                    if (flat + 1 < R23) *reinterpret_cast<v2d_u *>(at) = v2d_u{acc[2 * u][q], acc[2 * u + 1][q]};
+                    else if (flat < R23) *at = acc[2 * u][q];
                 }
             }
     }
