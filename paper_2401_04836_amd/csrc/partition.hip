@@ -1020,11 +1020,11 @@ conststn_status build_ttmc_tables(conststn_plan_s *plan) {
         // Short items fill the chip and end together, long ones leave fewer partial row blocks to the fix-up
         // pass.  At 10 x 12 x 7, best of 8 to 256 K-steps per item: 8 at 15 K K-steps in all (33 us; 64: 118), 24 at
         // 0.1 M (84 us; 64: 150), 24 to 32 at 0.5 M (343 us; 64: 391).  Partial blocks of 16 x 16 x 16 are five times
-        // as large, and from 0.3 M K-steps on longer items pay: 32 and 64 measured 525 and 439 us at 0.33 M, 707 and
-        // 612 at 0.5 M, 42 and 84 887 and 825 at 0.7 M; at 0.25 M they are level (355 and 360), below 32 is better.
+        // as large, and from 0.2 M K-steps on longer items pay: 32 and 64 measured 312 and 290 us at 0.2 M, 525 and
+        // 439 at 0.33 M, 707 and 612 at 0.5 M, 42 and 84 887 and 825 at 0.7 M; at 0.25 M they are level (355 and 360).
         const int64_t n = plan->n_rows_tab;
         const bool full = plan->rank_of_level[1] == 16 && plan->rank_of_level[2] == 16 && plan->rank_of_level[3] == 16;
-        const int64_t by_size = full && n >= (int64_t(1) << 18) ? std::max<int64_t>(n / 8192, 64)
+        const int64_t by_size = full && n >= (int64_t(1) << 17) ? std::max<int64_t>(n / 8192, 64)
                                                                 : std::max<int64_t>({int64_t(8), std::min<int64_t>(n / 4096, 32), n / 16384});
         split = plan->opt("ttmc4_ksplit", std::min<int64_t>(by_size, 128));
     }
