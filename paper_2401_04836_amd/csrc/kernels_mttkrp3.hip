@@ -466,7 +466,7 @@ __device__ __forceinline__ void mttkrp3_fixup_final_body(const MttkrpArgs &a, in
     a.out[row * a.R + r] = x;
 }
 // The three passes for the two sub-tensors, which write different outputs, in one launch each: the
-// first blocks take the first sub-tensor's slices (heavy slices), the others the second's (none: a tensor by itself).
+// first blocks take the first sub-tensor's slices (heavy slices), the others the second's.
 struct MttkrpPairArgs { MttkrpArgs first, second; };
 template <int LPR>
 __global__ void __launch_bounds__(256)
@@ -574,6 +574,25 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
     return CONSTSTN_OK;
 }
 
+// A tensor by itself.  (With 1.3 M slices of 1.6 leaves the passes are most of the time, and the pair's kernels, which read
+// twice the arguments and a branch more per slice, cost 10 % of the whole.)
+template <int LPR>
+__global__ void __launch_bounds__(256)
+mttkrp3_fixup_kernel(MttkrpArgs a) {
+    __shared__ double red[256 * 2];
+    mttkrp3_fixup_body<LPR>(a, blockIdx.x, red);
+}
+template <int LPR>
+__global__ void __launch_bounds__(256)
+mttkrp3_fixup_heavy_kernel(MttkrpArgs a) {
+    __shared__ double red[256 * 2];
+    mttkrp3_fixup_heavy_body<LPR>(a, blockIdx.x, int(blockIdx.y), red);
+}
+__global__ void __launch_bounds__(128)
+mttkrp3_fixup_final_kernel(MttkrpArgs a) {
+    mttkrp3_fixup_final_body(a, blockIdx.x);
+}
+
 template <int LPR>
 static conststn_status launch_csf(const conststn_plan_s *plan, const MttkrpArgs &a, hipStream_t stream) {
     const dim3 grid(unsigned(div_up(a.n_chunks, 256 / LPR))), block(256);
@@ -583,7 +602,15 @@ static conststn_status launch_csf(const conststn_plan_s *plan, const MttkrpArgs 
         else mttkrp3_csf_kernel<LPR, false><<<grid, block, 0, stream>>>(a);
     }
     CST_HIP(hipGetLastError());
-    return launch_fixup_pair<LPR>(a, MttkrpArgs{}, stream);
+    mttkrp3_fixup_kernel<LPR><<<dim3(unsigned(a.slices)), block, 0, stream>>>(a);
+    CST_HIP(hipGetLastError());
+    if (a.n_heavy > 0) {
+        mttkrp3_fixup_heavy_kernel<LPR><<<dim3(unsigned(a.n_heavy), kHeavySegments), block, 0, stream>>>(a);
+        CST_HIP(hipGetLastError());
+        mttkrp3_fixup_final_kernel<<<dim3(unsigned(a.n_heavy)), dim3(128), 0, stream>>>(a);
+        CST_HIP(hipGetLastError());
+    }
+    return CONSTSTN_OK;
 }
 
 conststn_status launch_mttkrp3_csf(const conststn_plan_s *plan, const double *const *dense, double *out, hipStream_t stream) {
