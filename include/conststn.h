@@ -151,8 +151,8 @@ void conststn_csf_destroy(conststn_csf_t *csf);
  * generic_max_gb bounds them, default 64).  A legal schedule outside all of
  * these gives CONSTSTN_EUNSUPPORTED with the reason.
  * Memory: the MTTKRP kernels walk a stream of 12 bytes per leaf, fiber and (order 4) node, the order-3 TTMc kernel
- * row descriptors of 16 bytes per fiber or 16 leaves, the order-4 TTMc kernel records of 32 bytes per 2 leaves of a node,
- * all of them made and held by the plan (and about twice that while it is made).  Where that cannot be
+ * row descriptors of 16 bytes per fiber or 16 leaves, the order-4 TTMc kernel records of 32 bytes per 2 leaves of a node
+ * (four per fiber at least), all of them made and held by the plan (and about twice that while it is made).  Where that cannot be
  * allocated the plan is made again for the slower kernels that walk the CSF itself (as with the options
  * mttkrp_records=0, ttmc3_mfma=0, ttmc4_mfma=0).
  * The plan keeps pointers into the CSF handles: destroy the plan first.
