@@ -15,6 +15,8 @@
 // fiber end the group folds T * B[j,:] into the accumulator; at a slice end it puts the row into the result (slice
 // wholly inside the chunk) or stores a partial row (slice shared with neighbouring chunks).  A second kernel adds
 // the partial rows of shared slices in chunk order, so results are bit-reproducible.
+#include <algorithm>
+
 #include "plan.hpp"
 
 namespace cst {
@@ -381,10 +383,7 @@ mttkrp3_r32_dual_kernel(MttkrpDualArgs d) {
 
 __global__ void __launch_bounds__(256)
 mttkrp3_add_kernel(v2f64_u *__restrict__ out, const v2f64_u *__restrict__ add, int64_t n) {
-    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (e < n) {
-        out[e] += add[e];
-    }
+    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < n; e += int64_t(gridDim.x) * 256) out[e] += add[e];
 }
 
 // Rows of slices shared by several chunks: add the partial rows in chunk order.
@@ -467,13 +466,17 @@ __device__ __forceinline__ void mttkrp3_fixup_final_body(const MttkrpArgs &a, in
 }
 // The three passes for the two sub-tensors, which write different outputs, in one launch each: the
 // first blocks take the first sub-tensor's slices (heavy slices), the others the second's.
+// A launch takes fewer than 2^32 threads (more are cut off without an error), so the slices from s0 on go 2^23 at a time
+// (a loop over slices in the kernel costs 20 % of the whole at rank 1 over a million short slices).
 struct MttkrpPairArgs { MttkrpArgs first, second; };
+constexpr int64_t kFixupBlocks = int64_t(1) << 23;
 template <int LPR>
 __global__ void __launch_bounds__(256)
-mttkrp3_fixup_pair_kernel(MttkrpPairArgs p) {
+mttkrp3_fixup_pair_kernel(MttkrpPairArgs p, int64_t s0) {
     __shared__ double red[256 * 2];
-    if (int64_t(blockIdx.x) < p.first.slices) mttkrp3_fixup_body<LPR>(p.first, blockIdx.x, red);
-    else mttkrp3_fixup_body<LPR>(p.second, int64_t(blockIdx.x) - p.first.slices, red);
+    const int64_t s = s0 + blockIdx.x;
+    if (s < p.first.slices) mttkrp3_fixup_body<LPR>(p.first, s, red);
+    else mttkrp3_fixup_body<LPR>(p.second, s - p.first.slices, red);
 }
 template <int LPR>
 __global__ void __launch_bounds__(256)
@@ -491,8 +494,10 @@ mttkrp3_fixup_final_pair_kernel(MttkrpPairArgs p) {
 template <int LPR>
 static conststn_status launch_fixup_pair(const MttkrpArgs &a0, const MttkrpArgs &a1, hipStream_t stream) {
     const MttkrpPairArgs p{a0, a1};
-    mttkrp3_fixup_pair_kernel<LPR><<<dim3(unsigned(a0.slices + a1.slices)), dim3(256), 0, stream>>>(p);
-    CST_HIP(hipGetLastError());
+    for (int64_t s0 = 0, n = a0.slices + a1.slices; s0 < n; s0 += kFixupBlocks) {
+        mttkrp3_fixup_pair_kernel<LPR><<<dim3(unsigned(std::min(n - s0, kFixupBlocks))), dim3(256), 0, stream>>>(p, s0);
+        CST_HIP(hipGetLastError());
+    }
     const int nh = a0.n_heavy + a1.n_heavy;
     if (nh > 0) {
         mttkrp3_fixup_heavy_pair_kernel<LPR><<<dim3(unsigned(nh), kHeavySegments), dim3(256), 0, stream>>>(p);
@@ -568,7 +573,7 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
         CST_HIP(hipGetLastError());
     }
     CST_TRY(launch_fixup_pair<16>(pa[0].base, pa[1].base, stream));
-    mttkrp3_add_kernel<<<dim3(unsigned(div_up(n / 2, 256))), dim3(256), 0, stream>>>(
+    mttkrp3_add_kernel<<<dim3(unsigned(std::min(div_up(n / 2, 256), kFixupBlocks))), dim3(256), 0, stream>>>(
         reinterpret_cast<v2f64_u *>(out), reinterpret_cast<const v2f64_u *>(plan->mttkrp_out2.p), n / 2);
     CST_HIP(hipGetLastError());
     return CONSTSTN_OK;
@@ -578,9 +583,9 @@ conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const 
 // twice the arguments and a branch more per slice, cost 10 % of the whole.)
 template <int LPR>
 __global__ void __launch_bounds__(256)
-mttkrp3_fixup_kernel(MttkrpArgs a) {
+mttkrp3_fixup_kernel(MttkrpArgs a, int64_t s0) {
     __shared__ double red[256 * 2];
-    mttkrp3_fixup_body<LPR>(a, blockIdx.x, red);
+    mttkrp3_fixup_body<LPR>(a, s0 + blockIdx.x, red);
 }
 template <int LPR>
 __global__ void __launch_bounds__(256)
@@ -602,8 +607,10 @@ static conststn_status launch_csf(const conststn_plan_s *plan, const MttkrpArgs 
         else mttkrp3_csf_kernel<LPR, false><<<grid, block, 0, stream>>>(a);
     }
     CST_HIP(hipGetLastError());
-    mttkrp3_fixup_kernel<LPR><<<dim3(unsigned(a.slices)), block, 0, stream>>>(a);
-    CST_HIP(hipGetLastError());
+    for (int64_t s0 = 0; s0 < a.slices; s0 += kFixupBlocks) {
+        mttkrp3_fixup_kernel<LPR><<<dim3(unsigned(std::min(a.slices - s0, kFixupBlocks))), block, 0, stream>>>(a, s0);
+        CST_HIP(hipGetLastError());
+    }
     if (a.n_heavy > 0) {
         mttkrp3_fixup_heavy_kernel<LPR><<<dim3(unsigned(a.n_heavy), kHeavySegments), block, 0, stream>>>(a);
         CST_HIP(hipGetLastError());

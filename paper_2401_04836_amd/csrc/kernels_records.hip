@@ -665,7 +665,8 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     q = div_up(std::min<int64_t>(q, std::max<int64_t>(a.n_rec, 1)), 16) * 16;      // (the last chunk is filled up)
     rs.q = q;
     if (!plan->compact && a.slices < plan->out_rows) {
-        // up to 2^24 empty rows the fix-up launch clears them (128 threads each at most, and a launch takes fewer than 2^32)
+        // up to 2^24 empty rows the fix-up launch clears them (128 threads each at most, and a launch takes fewer
+        // than 2^32; more are cut off without an error)
         rs.zero_all = plan->out_rows - a.slices > (int64_t(1) << 24);
         if (!rs.zero_all) {
             DevBuf<int64_t> flag;

@@ -362,7 +362,8 @@ static conststn_status build_mttkrp3_hot(conststn_plan_s *plan, bool asked) {
 }
 
 // Which form.  The record stream (kernels_records.hip) takes ranks from 2 to 128 over extents up to 2^28; for rank 1
-// and larger extents the CSF itself is walked.  Rank 32 on a large tensor whose leaf index follows a power law has another: the hot leaves, their rows in LDS, and the cold ones as two
+// and larger extents the CSF itself is walked.  Rank 32 on a large tensor whose leaf index follows a power law has
+// another: the hot leaves, their rows in LDS, and the cold ones as two
 // sub-tensors side by side in one launch.  It pays one more factor row per fiber that has leaves of both kinds,
 // so it needs long fibers: 1.15 against 1.23 ms at 76 M nonzeros with 5.9 leaves per fiber, 0.69 against
 // 0.73 ms at 40 M with 4.7, but 0.86 against 0.84 at 40 M with 3.6 and 0.41 against 0.36 at 20 M.  The plan options

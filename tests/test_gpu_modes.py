@@ -125,3 +125,24 @@ def test_mttkrp_over_a_mode_of_more_than_2_28_indices():
         got = cst.execute(pl, dev).reshape(rows, R)
         want = torch.zeros(rows, R, dtype=torch.float64, device="cuda").index_add_(0, at.long(), terms)
         assert (got / want - 1).abs().max().item() <= 1e-12        # sums of about 700 positive terms
+
+
+@pytest.mark.parametrize("flags", [0, cst.OUT_COMPACT])
+def test_rank_one_over_more_than_2_24_slices(flags):
+    """As many slices as a launch of one workgroup each does not take: two leaves per slice, a heavy slice among them."""
+    n, dims = (1 << 24) + 5000, ((1 << 24) + 70_000, 40, 30)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    i = torch.cat([torch.randperm(dims[0], generator=g, device="cuda")[:n], torch.full((60_000,), 12_345, device="cuda")])
+    j, k = (torch.randint(0, d, (i.numel(),), generator=g, device="cuda") for d in dims[1:])
+    v = torch.rand(i.numel(), generator=g, dtype=torch.float64, device="cuda") + 0.5
+    B, C = (torch.rand(d, 1, generator=g, dtype=torch.float64, device="cuda") for d in dims[1:])
+    _say("mttkrp of rank 1 over %d slices" % n)
+    csf = cst.build_csf([x.to(torch.int32) for x in (i, j, k)], v, dims, [0, 1, 2], flags=cst.COALESCE_DUPS)
+    pl = cst.plan(S.MTTKRP3, [("X", csf), ("C", C), ("B", B)], flags=flags)
+    pl.check()
+    got = cst.execute(pl, [C, B])
+    want = torch.zeros(dims[0], dtype=torch.float64, device="cuda").index_add_(0, i, v * B[j, 0] * C[k, 0])
+    if flags:
+        want = want[pl.output_rows().long()]
+    scale = want.abs().clamp(min=1e-300)
+    assert ((got - want).abs() / scale).max().item() <= 1.4e-11      # positive terms, at most 60 001 of them
