@@ -759,24 +759,27 @@ static conststn_status launch_ttmc3_with(const conststn_plan_s *plan, const doub
         ra.out = out;
         ra.partial = a.partial;
         ra.compact = a.compact;
-        switch (a.R2 / 16) {
-            case 1: CST_TRY(launch_mfma_pn<1>(plan, ra, stream)); break;
-            case 2: CST_TRY(launch_mfma_pn<2>(plan, ra, stream)); break;
-            case 3: CST_TRY(launch_mfma_pn<3>(plan, ra, stream)); break;
-            default: CST_TRY(launch_mfma_pn<4>(plan, ra, stream)); break;
-        }
-        CST_HIP(hipGetLastError());
+        CST_TRY(in_item_ranges(ra, [&](const Ttmc3RowArgs &r) -> conststn_status {
+            switch (a.R2 / 16) {
+                case 1: return launch_mfma_pn<1>(plan, r, stream);
+                case 2: return launch_mfma_pn<2>(plan, r, stream);
+                case 3: return launch_mfma_pn<3>(plan, r, stream);
+                default: return launch_mfma_pn<4>(plan, r, stream);
+            }
+        }));
         return launch_ttmc_fixup(plan, out, stream, partial);
     }
-    const dim3 grid(unsigned(div_up(a.n_items, 4))), block(256);
     {
         ProfScope prof(plan, stream);
-        if (a.R2 <= 8) ttmc3_kernel<8><<<grid, block, 0, stream>>>(a);
-        else if (a.R2 <= 16) ttmc3_kernel<16><<<grid, block, 0, stream>>>(a);
-        else if (a.R2 <= 32) ttmc3_kernel<32><<<grid, block, 0, stream>>>(a);
-        else ttmc3_kernel<64><<<grid, block, 0, stream>>>(a);
+        CST_TRY(in_item_ranges(a, [&](const Ttmc3Args &r) -> conststn_status {
+            const dim3 grid(unsigned(div_up(r.n_items, 4))), block(256);
+            if (r.R2 <= 8) ttmc3_kernel<8><<<grid, block, 0, stream>>>(r);
+            else if (r.R2 <= 16) ttmc3_kernel<16><<<grid, block, 0, stream>>>(r);
+            else if (r.R2 <= 32) ttmc3_kernel<32><<<grid, block, 0, stream>>>(r);
+            else ttmc3_kernel<64><<<grid, block, 0, stream>>>(r);
+            return CONSTSTN_OK;
+        }));
     }
-    CST_HIP(hipGetLastError());
     return launch_ttmc_fixup(plan, out, stream, partial);
 }
 

@@ -367,14 +367,20 @@ conststn_status launch_ttmc4(const conststn_plan_s *plan, const double *const *d
             ra.out = out;
             ra.partial = a.partial;
             ra.compact = a.compact;
-            const dim3 grid{unsigned(a.n_items)}, block(64);
             const int parts = (a.R2 * a.R3 + 31) / 32;
-            if (a.R1 == 16 && a.R2 == 16 && a.R3 == 16) ttmc4_mfma_kernel<8, true><<<grid, block, 0, stream>>>(ra);
-            else if (parts > 4) ttmc4_mfma_kernel<8, false><<<grid, block, 0, stream>>>(ra);
-            else if (parts > 2) ttmc4_mfma_kernel<4, false><<<grid, block, 0, stream>>>(ra);
-            else ttmc4_mfma_kernel<2, false><<<grid, block, 0, stream>>>(ra);
+            CST_TRY(in_item_ranges(ra, [&](const Ttmc4RowArgs &r) -> conststn_status {
+                const dim3 grid{unsigned(r.n_items)}, block(64);
+                if (r.R1 == 16 && r.R2 == 16 && r.R3 == 16) ttmc4_mfma_kernel<8, true><<<grid, block, 0, stream>>>(r);
+                else if (parts > 4) ttmc4_mfma_kernel<8, false><<<grid, block, 0, stream>>>(r);
+                else if (parts > 2) ttmc4_mfma_kernel<4, false><<<grid, block, 0, stream>>>(r);
+                else ttmc4_mfma_kernel<2, false><<<grid, block, 0, stream>>>(r);
+                return CONSTSTN_OK;
+            }));
         } else
-            ttmc4_kernel<<<dim3(unsigned(div_up(a.n_items, 4))), dim3(256), 0, stream>>>(a);
+            CST_TRY(in_item_ranges(a, [&](const Ttmc4Args &r) -> conststn_status {
+                ttmc4_kernel<<<dim3(unsigned(div_up(r.n_items, 4))), dim3(256), 0, stream>>>(r);
+                return CONSTSTN_OK;
+            }));
     }
     CST_HIP(hipGetLastError());
     return launch_ttmc_fixup(plan, out, stream);

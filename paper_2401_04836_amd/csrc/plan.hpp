@@ -340,6 +340,21 @@ conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_co
 conststn_status launch_record_stream(const conststn_plan_s *plan, const double *const *dense, double *out,
                                      hipStream_t stream);
 
+// A launch takes fewer than 2^32 threads (more are cut off without an error): work items, of up to four wavefronts each,
+// go 2^23 at a time.  launch(args) queues the kernel over args.n_items items from args.items on.
+template <class Args, class F>
+conststn_status in_item_ranges(Args args, F &&launch) {
+    const int64_t total = args.n_items, most = int64_t(1) << 23;
+    const SliceItem *items = args.items;
+    for (int64_t first = 0; first < total; first += most) {
+        args.items = items + first;
+        args.n_items = total - first < most ? total - first : most;
+        CST_TRY(launch(args));
+        CST_HIP(hipGetLastError());
+    }
+    return CONSTSTN_OK;
+}
+
 // kernels_*.hip
 conststn_status launch_mttkrp3(const conststn_plan_s *plan, const double *const *dense, double *out,
                                hipStream_t stream);

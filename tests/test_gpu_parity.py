@@ -394,3 +394,24 @@ def test_unsupported_and_illegal_plans():
     with pytest.raises(cst.ConststnError) as e:      # loop order against the CSF layout
         cst.plan(S.TTMC3.replace("| i,j,k,s", "| j,i,k,s"), [("X", csf), ("U3", U3), ("U2", U2)])
     assert e.value.status_name == "ESCHED"
+
+
+@pytest.mark.parametrize("order,options", [(3, {}), (4, {}), (4, dict(ttmc4_mfma=0))])
+def test_ttmc_over_more_than_2_26_slices(order, options):
+    """As many items as one launch of a wavefront each does not take: a leaf per slice, ranks 1."""
+    n = (1 << 26) + 3000
+    _say("ttmc order %d, %d slices of one leaf" % (order, n))
+    g = torch.Generator(device="cuda").manual_seed(9)
+    dims = (n + 10, 4, 3, 2)[:order]
+    c = [torch.arange(n, dtype=torch.int32, device="cuda")] + [torch.randint(0, d, (n,), generator=g, device="cuda", dtype=torch.int32) for d in dims[1:]]
+    v = torch.rand(n, generator=g, dtype=torch.float64, device="cuda") + 0.5
+    U = [torch.rand(d, 1, generator=g, dtype=torch.float64, device="cuda") for d in dims[1:]]
+    csf = cst.build_csf(c, v, dims, list(range(order)))
+    names = ("U3", "U2", "U1")[:order - 1]
+    pl = cst.plan(S.TTMC3 if order == 3 else S.TTMC4, [("X", csf)] + list(zip(names, U[::-1])), flags=cst.OUT_COMPACT, options=options)
+    want = v.clone()
+    for u, x in zip(U, c[1:]):
+        want *= u[x.long(), 0]
+    del c
+    got = cst.execute(pl, U[::-1])
+    assert got.numel() == n and ((got - want).abs() / want).max().item() <= 1e-15      # three or four roundings
