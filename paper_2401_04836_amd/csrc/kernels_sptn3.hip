@@ -106,7 +106,8 @@ constexpr int kRing = 3;              // batches in flight (loads issued kRing -
 
 struct Sptn3TileArgs {
     int64_t slices, L, M, LT;
-    int MT, nwords, n_groups, n_kc;
+    int MT, nwords, n_groups, n_kc;        // n_kc: partial results of a row
+    int l_parts;                           // of every chunk of the k range (two wavefronts per SIMD)
     int64_t k_per;
     const int64_t *uptr0, *uptr1;
     const int32_t *uidx0, *uidx1, *uidx2;
@@ -120,6 +121,10 @@ struct Sptn3TileArgs {
     const double *V;
     double *out, *partial;
     int compact, xcd_ranges;
+    const int64_t *chunk_fiber;            // [(k chunks + 1) x slices] first fiber of a slice in a k chunk
+    const int32_t *chunk_k;                // ... and the k there
+    const int32_t *work;                   // pairs of the workgroups with two wavefronts per SIMD, entry n for workgroup
+    int64_t work_end;                      // n % workgroups; -1: no more
     const int32_t *wg_order;               // workgroup -> (k chunk, group) pair, heaviest pairs first (or null)
 };
 
@@ -448,371 +453,486 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 }
 
 // ---- tiled kernel with two wavefronts per SIMD ------------------------------------------------
-// The kernel above keeps Z^t for all m tiles of its l tiles in 200 accumulator registers, which
-// leaves room for one wavefront per SIMD and puts the accumulators into the upper half of the register
-// file, where an fp64 matrix instruction takes 44 ns of its SIMD instead of 27.  Here a workgroup has eight
-// wavefronts (two per SIMD).  Only the blocks of sixteen l below which W holds anything under the k at
-// hand are taken (a list made with the plan): T is read nowhere else.  Eight of them make a *round*, in
-// which wavefront w computes T^t of the w-th as above.  The consumer is split by m instead of by
-// l: wavefront w owns the m tiles w, w + 8, w + 16, w + 24 (four accumulator tiles, kept in
-// registers across all k of the workgroup), the eight T^t of a round go through LDS, and after
-// a barrier every wavefront multiplies its own W tiles of all eight l tiles.  The W tiles of a
-// round, which follow one another in memory, are fetched by the eight wavefronts in turn, one per
-// producer batch, and parked in a pool of LDS slots shared by the workgroup (slot = rank of the tile
-// among the round's tiles); what does not fit, or exceeds eight tiles per batch, is fetched when it is used.
-// 2000 x 2000 x 400 with blocks of 100 x 100 x 20, 12 % of the blocks of l empty: 26.8 ms with every block
-// taken and the tiles found by ballots and reads across lanes, 24.1 with the list, 23.4 with the places
-// below.  Of these 23.4 (switched off in a copy): W's fetches and parking 3.4, consumer 5.0, everything but the
-// loop over batches 2.2, V's addresses made one cache line 0.8; the producer alone 11.8, of which 6.4 are the
-// matrix instructions at 27 ns each.  A ring of three batches takes as long as two.
+// The kernel above reads one operand from memory and one from LDS for every matrix instruction, and its 200
+// accumulator registers leave room for one wavefront per SIMD.  Here a workgroup of eight wavefronts takes 32 slices
+// (two *halves* of sixteen) and only the blocks of sixteen l below which W holds anything under the k at hand (a list
+// made with the plan; T is read nowhere else).  Sixteen blocks make a *round*:
+//   producer: wavefront w computes T^t of the blocks w and w + 8 for both halves, so that four operands (two
+//     8-byte pieces of V's rows, one 16-byte read of Uc) feed four matrix instructions.  The union rows stand in the
+//     order (first half only, both, second half only): a batch of eight rows that a half does not hold costs that
+//     half nothing, so 32 slices never take more matrix instructions than twice 16 would.
+//   consumer: split by m.  Wavefront w owns half w % 2 and the m tiles x = (w / 2) mod 4, + 4, + 8, ... (seven
+//     accumulator tiles, kept in registers across all k of the workgroup).  The two wavefronts of a SIMD own tiles of
+//     one parity: a block of W spans two or three neighbouring tiles, which so spread over the SIMDs.  The T^t of a
+//     round go through LDS; W's tiles come straight from memory, four ahead, the first four of them before the
+//     producer starts.  A wavefront finds its tiles of a round by a prefix sum over the blocks' masks.
+// Two barriers a round, around the writes of T^t: a wavefront with few tiles goes on to the next round's producer.
+// V's loads run three batches ahead across rounds; a round is padded to whole groups of four batches, whose empty
+// batches load and do nothing.
+// 2000 x 2000 x 400 in blocks of 100 x 100 x 20 (356 M matrix instructions, 9.7 ms at the 28 ns one takes): 23.2 -> 15.6 ms.
+// The form before took 16 slices at a time: one 8-byte piece of V and one of Uc for every instruction, 363 M of them.
+// Of a workgroup's time the producer takes 40 % (8.4 us a round of 9.1 us of matrix instructions: it is bound by
+// them), the consumer 26 %, waiting at the two barriers 18 %, finding W's tiles 4 %, everything between two k 12 %
+// (16 us of latencies).  V's addresses made one cache line change nothing.
 constexpr int kOwnWaves = 8;
-constexpr int kRingO = 2;                                             // batches in flight in this kernel
-constexpr int kOwnZ = (kSpMaxMTiles + kOwnWaves - 1) / kOwnWaves;       // accumulator tiles per wavefront
-constexpr int kPool = 48;                                             // W tiles parked per round
+constexpr int kOwnHalves = 2;
+constexpr int kOwnCap = kSpUnionRows;                                   // union rows of Uc per pass (78 KB)
+constexpr int kOwnHeld = 24;                                            // leaves per lane kept between mask and scatter
+constexpr int kOwnRows = 8;                                             // union rows of a batch (two K-steps)
+constexpr int kOwnRing = 4;                                             // batches of a group = stages of V's ring
+constexpr int kOwnBlocks = 2 * kOwnWaves;                               // blocks of l in a round
+constexpr int kOwnChunk = 8;                                            // rounds whose blocks a wavefront holds (128 blocks)
+constexpr int kOwnClasses = 4;                                          // m tile mod 4 -> pair of wavefronts
+constexpr int kOwnZ = (kSpMaxMTiles + kOwnClasses - 1) / kOwnClasses;   // accumulator tiles per wavefront
+constexpr int kOwnList = 128;                                           // places for a wavefront's W tiles of a round
+constexpr int kOwnOffsets = (kOwnCap + kOwnRows * kOwnRing - 1) / (kOwnRows * kOwnRing) * (kOwnRows * kOwnRing);
+constexpr int kOwnWRing = 8;                                            // W tiles in flight in the consumer ...
+constexpr int kOwnWAhead = 4;                                           // ... and beside the producer
+static_assert(kOwnBlocks * kOwnZ + 2 * kOwnWRing <= kOwnList && kOwnList == 2 * 64, "a wavefront's list of W tiles lies in two registers");
+static_assert(kSpGroupWide == 16 * kOwnHalves && kOwnZ == 7, "slices of a workgroup; accumulators that the consumer tests for");
 
-// Workgroup -> place in the list of pairs.  Pairs of equal cost stand in the order (k chunk, group), and
-// neighbouring groups read the same W tiles and largely the same rows of V: of every 64 places XCD x takes the
-// eight from 8 x on, instead of every eighth (24.1 -> 23.4 ms; runs of 4: 23.4, of 16: 24.1).
-constexpr int kSpRun = 8;
-__device__ inline int sp_place(int b, int n) {
-    const int base = b / (8 * kSpRun) * (8 * kSpRun), r = b - base;
-    return base + 8 * kSpRun <= n ? base + (r & 7) * kSpRun + (r >> 3) : b;
+__host__ __device__ constexpr size_t sptn3_owned_lds(int nwords) {
+    return size_t(kOwnCap * 32 + kOwnBlocks * 2 * 256) * 8 + size_t(nwords) * 16 + size_t(kOwnOffsets) * 4 +
+           size_t(kOwnWaves * kOwnList) * 2 + 256;
 }
 
-struct SpPipeO {
-    double Vr[kRingO][kBatch], Ur[kRingO][kBatch];
-    int32_t Jr[kRingO][kBatch];
-    v2d Wr[kRingO][2];
-    int Sr[kRingO];                                                    // pool slot of the W tile (-1: not parked)
-};
+// orders LDS between the wavefronts of a workgroup without waiting for loads from memory in flight
+__device__ __forceinline__ void sp_lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ inline uint64_t shfl_up_u64(uint64_t x, int d) {
+    const uint32_t lo = __shfl_up(uint32_t(x), d), hi = __shfl_up(uint32_t(x >> 32), d);
+    return uint64_t(hi) << 32 | lo;
+}
 
 __global__ void __launch_bounds__(64 * kOwnWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 sptn3_owned_kernel(Sptn3TileArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    double *Uc = reinterpret_cast<double *>(smem);                        // kCap x 16
-    double *Pool = Uc + kCap * 16;                                        // kPool x 256
-    double *Tx = Pool + kPool * 256;                                      // 8 x 256: T^t of the round's l tiles
-    int32_t *jl = reinterpret_cast<int32_t *>(Tx + kOwnWaves * 256);      // kCap: row offset j*L
-    uint32_t *mask = reinterpret_cast<uint32_t *>(jl + kCap);             // nwords
-    int32_t *wpre = reinterpret_cast<int32_t *>(mask + a.nwords);         // nwords
-    int32_t *scan = wpre + a.nwords;                                      // 8
+    double *Uc = reinterpret_cast<double *>(smem);                        // kOwnCap x 16 columns x 2 halves
+    double *Tx = Uc + kOwnCap * 32;                                       // kOwnBlocks x 2 halves x 256
+    uint64_t *wpre = reinterpret_cast<uint64_t *>(Tx + kOwnBlocks * 2 * 256);  // nwords: ranks, 21 bits a category
+    uint32_t *jl = reinterpret_cast<uint32_t *>(wpre + a.nwords);         // kOwnOffsets: byte offsets of V's rows
+    uint32_t *mask = jl + kOwnOffsets;                                    // 2 x nwords
+    uint16_t *lists = reinterpret_cast<uint16_t *>(mask + 2 * a.nwords);  // kOwnWaves x kOwnList
+    uint64_t *scan = reinterpret_cast<uint64_t *>(smem + sptn3_owned_lds(a.nwords) - 64);  // kOwnWaves
 
     const int tid = threadIdx.x, lane = tid & 63, slot = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_wg = a.n_groups * a.n_kc, per_xcd = (n_wg + 7) / 8;
-    if (int(blockIdx.x) >= n_wg && !a.xcd_ranges) return;
-    const int logical = a.xcd_ranges ? (int(blockIdx.x) % 8) * per_xcd + int(blockIdx.x) / 8
-                                     : (a.wg_order ? a.wg_order[sp_place(int(blockIdx.x), n_wg)] : int(blockIdx.x));
-    if (logical >= n_wg) return;
-    const int group = logical % a.n_groups, kc = logical / a.n_groups;
-    const int64_t s0 = int64_t(group) * kSpGroup;
-    const int64_t k_lo = int64_t(kc) * a.k_per, k_hi = k_lo + a.k_per;
     const int64_t L = a.L;
     const int L32 = int(a.L);
     const char *Vbytes = reinterpret_cast<const char *>(a.V);
     const uint32_t lane16 = uint32_t(lane) * 16u;
     const int nwords = a.nwords;
-    const lds_v2d *PoolV = (const lds_v2d *)(Pool);
+    const lds_v2d *UcV = (const lds_v2d *)(Uc);
     const lds_v2d *TxV = (const lds_v2d *)(Tx);
-    // m tiles of this wavefront, as a mask over the 25
-    uint32_t own = 0u;
+    const int my_half = wave & 1, my_class = wave >> 1;
+    uint32_t own = 0u;                                                    // m tiles of this wavefront
 #pragma unroll
-    for (int x = 0; x < kOwnZ; ++x)
-        if (wave + kOwnWaves * x < a.MT) own |= 1u << (wave + kOwnWaves * x);
+    for (int x = 0; x < kOwnZ; ++x) own |= 1u << (my_class + kOwnClasses * x);
+    uint16_t *list = lists + wave * kOwnList;
 
-    // lane c (in each of the four lane rows) holds the cursor of slice s0 + c
+    // A workgroup per compute unit, with a list of (k chunk, part of l, group) triples made by the plan.
+    for (int64_t item = blockIdx.x; item < a.work_end; item += gridDim.x) {
+    const int logical = __builtin_amdgcn_readfirstlane(a.work[item]);
+    if (logical < 0) break;
+    const int group = logical % a.n_groups, kc = logical / a.n_groups, chunk = kc / a.l_parts, part = kc % a.l_parts;
+    const int64_t s0 = int64_t(group) * kSpGroupWide;
+    // lane sl (and sl + 32) holds the cursor of slice s0 + sl, its place in the k chunk, and the k there
     int64_t cur = 0, end = 0;
-    if (s0 + c < a.slices) {
-        const int64_t na = a.uptr0[s0 + c], nb = a.uptr0[s0 + c + 1];
-        cur = lower_bound_i32(a.uidx1, na, nb, k_lo);
-        end = lower_bound_i32(a.uidx1, cur, nb, k_hi);
+    int32_t kk = INT32_MAX;
+    if (s0 + (lane & 31) < a.slices) {
+        const int64_t at = int64_t(chunk) * a.slices + s0 + (lane & 31);
+        cur = a.chunk_fiber[at];
+        end = a.chunk_fiber[at + a.slices];
+        kk = a.chunk_k[at];
     }
     v4d accZ[kOwnZ];
 #pragma unroll
     for (int x = 0; x < kOwnZ; ++x) accZ[x] = v4d{0.0, 0.0, 0.0, 0.0};
 
-    for (;;) {
-        const int32_t kk = cur < end ? a.uidx1[cur] : INT32_MAX;
+    // Walk over the k that any of the slices holds.  What a k needs from the tables is fetched while the one before it
+    // is prepared: its fibers' leaves, its root in W, and (kk) the k that follows in every slice.
+    int64_t la = 0, lb = 0, root = -1;
+    auto next_k = [&]() -> int {
         int32_t kmin = kk;
-        kmin = min(kmin, __shfl_xor(kmin, 8, 16));
-        kmin = min(kmin, __shfl_xor(kmin, 4, 16));
-        kmin = min(kmin, __shfl_xor(kmin, 2, 16));
-        kmin = min(kmin, __shfl_xor(kmin, 1, 16));
-        kmin = __builtin_amdgcn_readfirstlane(kmin);
-        if (kmin == INT32_MAX) break;
-        const bool has = kk == kmin;
-        const int64_t f = cur;
-        cur += has ? 1 : 0;
-        const int64_t root = a.w_root_of_k[kmin];                         // same address in every lane
-        if (root < 0) continue;                                           // W has nothing at this k
-        int64_t la = 0, lb = 0;
-        if (has) { la = a.uptr1[f]; lb = a.uptr1[f + 1]; }
-        // two lane rows per slice: slice 2*wave + slot/2, leaves of parity slot%2
-        const int irow = 2 * wave + (slot >> 1), half = slot & 1;
-        const int64_t ea = __shfl(la, irow), eb = __shfl(lb, irow);
-        __syncthreads();                                                  // LDS of the previous k is free
-        for (int w = tid; w < nwords; w += 64 * kOwnWaves) mask[w] = 0u;
-        __syncthreads();
-        // the first kHeldO leaves per lane stay in registers for the scatter below
-        constexpr int kHeldO = kHeld / 2;
-        int32_t jheld[kHeldO];
-        double vheld[kHeldO];
 #pragma unroll
-        for (int h = 0; h < kHeldO; ++h) {
-            const int64_t e = ea + c + 16 * (2 * h + half);
+        for (int d = 16; d; d >>= 1) kmin = min(kmin, __shfl_xor(kmin, d, 32));
+        kmin = __builtin_amdgcn_readfirstlane(kmin);
+        la = lb = 0;
+        if (kmin != INT32_MAX) {
+            root = a.w_root_of_k[kmin];                                   // same address in every lane
+            if (kk == kmin) {
+                la = a.uptr1[cur];
+                lb = a.uptr1[cur + 1];
+                ++cur;
+                kk = cur < end ? a.uidx1[cur] : INT32_MAX;
+            }
+        }
+        return kmin;
+    };
+    for (int kmin = next_k(); kmin != INT32_MAX;) {
+        const bool known = root >= 0;                                     // W has something at this k
+        // the blocks of l below which it has, this pair's share of them
+        const int64_t cell_row = known ? root : 0;
+        const int cell_all = __builtin_amdgcn_readfirstlane(a.wcell_ptr[cell_row]);
+        const int n_all = __builtin_amdgcn_readfirstlane(a.wcell_ptr[cell_row + 1]) - cell_all;
+        const int cell0 = cell_all + n_all * part / a.l_parts;
+        const int cells = cell_all + n_all * (part + 1) / a.l_parts - cell0;
+        // one lane row per slice: slice 4*wave + slot, of half wave / 4
+        const int irow = 4 * wave + slot;
+        const int64_t ea = __shfl(la, irow), eb = known ? __shfl(lb, irow) : ea;
+        uint32_t *my_mask = mask + (wave >> 2) * nwords;
+        double *my_col = Uc + (irow & 15) * 2 + (wave >> 2);
+        // the first leaves of a lane stay in registers for the scatter below
+        int32_t jheld[kOwnHeld];
+        double vheld[kOwnHeld];
+#pragma unroll
+        for (int h = 0; h < kOwnHeld; ++h) {
+            const int64_t e = ea + c + 16 * h;
             jheld[h] = e < eb ? a.uidx2[e] : -1;
             vheld[h] = e < eb ? a.uvals[e] : 0.0;
         }
+        sp_lds_barrier();                                                 // LDS of the previous k is free
+        for (int w = tid; w < 2 * nwords; w += 64 * kOwnWaves) mask[w] = 0u;
+        for (int x = tid; x < min(kOwnCap, 32 * nwords) * 16; x += 64 * kOwnWaves) reinterpret_cast<v2d *>(Uc)[x] = v2d{0.0, 0.0};
+        for (int x = tid; x < kOwnOffsets; x += 64 * kOwnWaves) jl[x] = 0u;
+        sp_lds_barrier();
+        // (neighbouring leaves tend to share a word, on which the lanes' atomics would queue: the bits of the lanes of a
+        // row with the word of its first lane are joined first)
 #pragma unroll
-        for (int h = 0; h < kHeldO; ++h)
-            if (jheld[h] >= 0) atomicOr(&mask[jheld[h] >> 5], 1u << (jheld[h] & 31));
-        for (int64_t e = ea + c + 16 * (2 * kHeldO + half); e < eb; e += 32) {
+        for (int h = 0; h < kOwnHeld; ++h) {
+            const int word = jheld[h] >> 5;                               // (-1: no leaf)
+            const uint32_t bit = jheld[h] >= 0 ? 1u << (jheld[h] & 31) : 0u;
+            const int word0 = row_first(word);
+            const uint32_t joined = row_or(word == word0 ? bit : 0u);
+            if (bit && (c == 0 || word != word0)) atomicOr(&my_mask[word], c == 0 ? joined : bit);
+        }
+        for (int64_t e = ea + c + 16 * kOwnHeld; e < eb; e += 16) {
             const int32_t j = a.uidx2[e];
-            atomicOr(&mask[j >> 5], 1u << (j & 31));
+            atomicOr(&my_mask[j >> 5], 1u << (j & 31));
         }
-        __syncthreads();
-        {   // exclusive prefix of the set-bit counts of the mask words (thread t: words 2t, 2t+1)
-            int cnt[2], mine = 0;
+        kmin = next_k();
+        sp_lds_barrier();
+        // Ranks of the union rows: exclusive prefix of the set bits of every category (first half only, both, second
+        // only; thread t: words 2t, 2t+1), the categories one behind the other.  At most 32768 a category.
+        uint64_t cnt[2], mine = 0;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int w = 2 * tid + q;
-                cnt[q] = w < nwords ? __popc(mask[w]) : 0;
-                mine += cnt[q];
+        for (int q = 0; q < 2; ++q) {
+            const int w = 2 * tid + q;
+            cnt[q] = 0;
+            if (w < nwords) {
+                const uint32_t m0 = mask[w], m1 = mask[nwords + w];
+                cnt[q] = uint64_t(__popc(m0 & ~m1)) | uint64_t(__popc(m0 & m1)) << 21 | uint64_t(__popc(m1 & ~m0)) << 42;
             }
-            int incl = mine;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int up = __shfl_up(incl, d);
-                if (lane >= d) incl += up;
-            }
-            if (lane == 63) scan[wave] = incl;
-            __syncthreads();
-            int base = 0;
-            for (int w = 0; w < wave; ++w) base += scan[w];
-            int run = base + incl - mine;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int w = 2 * tid + q;
-                if (w < nwords) wpre[w] = run;
-                run += cnt[q];
-            }
+            mine += cnt[q];
         }
-        int n_union = 0;
+        uint64_t incl = mine;
 #pragma unroll
-        for (int w = 0; w < kOwnWaves; ++w) n_union += scan[w];
-        n_union = __builtin_amdgcn_readfirstlane(n_union);
-        __syncthreads();
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t up = shfl_up_u64(incl, d);
+            if (lane >= d) incl += up;
+        }
+        if (lane == 63) scan[wave] = incl;
+        sp_lds_barrier();
+        uint64_t base = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kOwnWaves; ++w) {
+            const uint64_t s = scan[w];
+            base += w < wave ? s : 0;
+            total += s;
+        }
+        const int n_one = __builtin_amdgcn_readfirstlane(int(total & 0x1fffff));
+        const int n_both = __builtin_amdgcn_readfirstlane(int(total >> 21 & 0x1fffff));
+        const int end0 = n_one + n_both;                                  // rows [0, end0) hold the first half,
+        const int n_union = end0 + __builtin_amdgcn_readfirstlane(int(total >> 42));   // [n_one, n_union) the second
+        uint64_t run = base + incl - mine + (uint64_t(n_one) << 21 | uint64_t(end0) << 42);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int w = 2 * tid + q;
+            if (w < nwords) wpre[w] = run;
+            run += cnt[q];
+        }
 
-        auto prepare = [&](int p0, int np, int npad, auto first) {
-            for (int x = tid; x < npad * 16; x += 64 * kOwnWaves) Uc[x] = 0.0;
-            if (tid < npad - np) jl[np + tid] = 0;
-            for (int w = tid; w < nwords; w += 64 * kOwnWaves) {
-                uint32_t m = mask[w];
-                int r = wpre[w] - p0;
-                while (m) {
-                    const int b = __builtin_ctz(m);
-                    m &= m - 1u;
-                    if (r >= 0 && r < np) jl[r] = int32_t(int64_t(w * 32 + b) * L);
-                    ++r;
+        // Prepare one pass: union rows [p0, p0 + np) -> Uc rows and V offsets (row r of batch r / 8, K-step
+        // (r / 4) % 2, lane row r % 4).  The first pass takes the leaves held in registers and finds both cleared.
+        auto prepare = [&](int p0, int np, auto first) {
+            if (!decltype(first)::value) {
+                for (int x = tid; x < kOwnCap * 16; x += 64 * kOwnWaves) reinterpret_cast<v2d *>(Uc)[x] = v2d{0.0, 0.0};
+                for (int x = tid; x < kOwnOffsets; x += 64 * kOwnWaves) jl[x] = 0u;
+                sp_lds_barrier();
+            }
+            // the place of j in the pass, for one that is in the union
+            auto place_of = [&](uint32_t bit, uint32_t m0, uint32_t m1, uint64_t pre) {
+                const uint32_t in0 = m0 & bit ? ~0u : 0u, in1 = m1 & bit ? ~0u : 0u;
+                const uint32_t same = ~(m0 ^ in0) & ~(m1 ^ in1);           // the rows of j's category
+                return int(pre >> (in1 ? in0 ? 21 : 42 : 0) & 0x1fffff) + __popc(same & (bit - 1u)) - p0;
+            };
+            for (int x = tid; x < 8 * nwords; x += 64 * kOwnWaves) {      // four bits of a mask word each
+                const int w = x >> 3;
+                const uint32_t m0 = mask[w], m1 = mask[nwords + w];
+                const uint64_t pre = wpre[w];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int j = 4 * x + b;
+                    const uint32_t bit = 1u << (j & 31);
+                    const int r = place_of(bit, m0, m1, pre);
+                    if (((m0 | m1) & bit) && r >= 0 && r < np)
+                        jl[(r & ~31) + (r & 3) * 8 + ((r >> 2) & 7)] = uint32_t(j) * uint32_t(L) << 3;
                 }
             }
-            __syncthreads();
             auto place = [&](int32_t j, double v) {
-                const int r = wpre[j >> 5] + __popc(mask[j >> 5] & ((1u << (j & 31)) - 1u)) - p0;
-                if (r >= 0 && r < np) Uc[r * 16 + irow] = v;
+                const int r = place_of(1u << (j & 31), mask[j >> 5], mask[nwords + (j >> 5)], wpre[j >> 5]);
+                if (r >= 0 && r < np) my_col[r * 32] = v;
             };
             if (decltype(first)::value) {
 #pragma unroll
-                for (int h = 0; h < kHeldO; ++h)
+                for (int h = 0; h < kOwnHeld; ++h)
                     if (jheld[h] >= 0) place(jheld[h], vheld[h]);
             }
-            for (int64_t e = ea + c + 16 * ((decltype(first)::value ? 2 * kHeldO : 0) + half); e < eb; e += 32)
+            for (int64_t e = ea + c + (decltype(first)::value ? 16 * kOwnHeld : 0); e < eb; e += 16)
                 place(a.uidx2[e], a.uvals[e]);
-            __syncthreads();
+            sp_lds_barrier();
         };
+        sp_lds_barrier();
         int p0 = 0;
-        int np = min(kCap, n_union);
-        int npad = (np + 4 * kBatch - 1) & ~(4 * kBatch - 1);                 // whole batches
-        if (n_union > 0) prepare(0, np, npad, std::true_type{});
+        if (n_union > 0) prepare(0, min(kOwnCap, n_union), std::true_type{});
         while (p0 < n_union) {
-            const int nBt = npad / (4 * kBatch);                          // batches per l tile
-            // the l tiles below which W holds anything under this k, and how many rounds of eight they make
-            const int cell0 = __builtin_amdgcn_readfirstlane(a.wcell_ptr[root]);
-            const int cells = __builtin_amdgcn_readfirstlane(a.wcell_ptr[root + 1]) - cell0;
-            const int rounds = (cells + kOwnWaves - 1) / kOwnWaves;
-            for (int r0 = 0; r0 < rounds; r0 += 8) {                      // 8 rounds = 64 l tiles: one mask per lane
-                const int NR = min(8, rounds - r0);
-                uint32_t mreg = 0u, freg = 0u;
-                int lreg = 0;                                             // absent cells: mask 0, any l tile
-                if (8 * r0 + lane < cells) {
-                    const SpCell cell = a.wcells[cell0 + 8 * r0 + lane];
-                    mreg = cell.mask;
-                    freg = cell.first;
-                    lreg = cell.l_tile;
+            const int np = min(kOwnCap, n_union - p0);
+            const int n_groups = (np + kOwnRows * kOwnRing - 1) / (kOwnRows * kOwnRing);
+            const int row_end0 = min(end0 - p0, np), row_one = n_one - p0;
+            for (int c0 = 0; c0 < cells; c0 += kOwnChunk * kOwnBlocks) {
+                const int here = min(kOwnChunk * kOwnBlocks, cells - c0);
+                const int rounds = (here + kOwnBlocks - 1) / kOwnBlocks;
+                // lane x holds the blocks x and x + 64 of the chunk (absent ones: no tile, any l)
+                uint32_t mreg[2], freg[2];
+                int lreg[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const SpCell cell = a.wcells[cell0 + c0 + min(64 * h + lane, here - 1)];
+                    mreg[h] = 64 * h + lane < here ? cell.mask : 0u;
+                    freg[h] = cell.first;
+                    lreg[h] = cell.l_tile;
                 }
-                // W tiles of the lane's round up to and with the lane's l tile (rounds are groups of 8 lanes)
-                int ireg = __popc(mreg);
+                // byte offset of this lane's column of V in the wavefront's blocks of a round
+                auto columns = [&](int r, uint32_t (&col)[2]) {
 #pragma unroll
-                for (int d = 1; d < 8; d <<= 1) {
-                    const int up = __shfl_up(ireg, d, 8);
-                    if ((lane & 7) >= d) ireg += up;
-                }
-                const int TB = NR * nBt;
-                SpPipeO P;
-                v4d accT0 = v4d{0.0, 0.0, 0.0, 0.0}, accT1 = accT0;
-                int t0 = 0, q0 = 0;                                       // batch being consumed: (round, batch in it)
-                int t2 = 0, q2 = 0;                                       // batch whose V/U/W loads are issued
-                int q3 = 0;                                               // batch whose j offsets are read
-                // The W tiles of round t2, in the order (l tile, m tile), follow one another in memory.  They are
-                // fetched by the eight wavefronts in turn: tile n by wavefront n % 8 with its batch n / 8, into
-                // pool slot n.
-                int col2 = 0, parked2 = 0;                                // of round t2: this lane's column of V, tiles to park
-                uint32_t first2 = 0u;                                     // ... and its first W tile
-                auto start_round = [&]() {
-                    const int tt = min(t2, NR - 1);
-                    col2 = min(16 * __builtin_amdgcn_readlane(lreg, 8 * tt + wave) + c, L32 - 1);
-                    first2 = __builtin_amdgcn_readlane(freg, 8 * tt);
-                    parked2 = t2 < NR ? min(__builtin_amdgcn_readlane(ireg, 8 * tt + 7), kPool) : 0;
-                };
-                auto read_j = [&](int32_t (&J)[kBatch]) {
-#pragma unroll
-                    for (int ks = 0; ks < kBatch; ++ks) J[ks] = jl[q3 * (4 * kBatch) + ks * 4 + slot];
-                    q3 = q3 + 1 == nBt ? 0 : q3 + 1;
-                };
-                auto issue = [&](const int32_t (&J)[kBatch], double (&Vv)[kBatch], double (&Uu)[kBatch], v2d (&Ww)[2], int &S) {
-#pragma unroll
-                    for (int ks = 0; ks < kBatch; ++ks) {
-                        Vv[ks] = *reinterpret_cast<const double *>(Vbytes + (uint32_t(J[ks] + col2) << 3));
-                        Uu[ks] = Uc[q2 * (64 * kBatch) + ks * 64 + lane];
-                    }
-                    const int n = wave + kOwnWaves * q2;
-                    const bool ok = n < parked2;
-                    const uint32_t tile = ok ? first2 + uint32_t(n) : a.zero_tile;
-                    S = ok ? n : -1;
-                    const char *tb = reinterpret_cast<const char *>(a.wtiles + int64_t(tile) * 256);
-                    Ww[0] = *reinterpret_cast<const v2d *>(tb + lane16);     // unconditional (the all-zero tile when there
-                    Ww[1] = *reinterpret_cast<const v2d *>(tb + lane16 + 1024);  // is none): skipping the fetch measured slower
-                    if (q2 + 1 == nBt) { q2 = 0; ++t2; start_round(); } else ++q2;
-                };
-                auto consume = [&](int b, const double (&Vv)[kBatch], const double (&Uu)[kBatch], const v2d (&Ww)[2], int S) {
-                    if (b < TB) {
-                        if (S >= 0) {                                     // park the W tile that came with this batch
-                            double *wp = Pool + S * 256 + lane * 2;
-                            *reinterpret_cast<v2d *>(wp) = Ww[0];
-                            *reinterpret_cast<v2d *>(wp + 128) = Ww[1];
-                        }
-                        accT0 = __builtin_amdgcn_mfma_f64_16x16x4f64(Vv[0], Uu[0], accT0, 0, 0, 0);
-                        accT1 = __builtin_amdgcn_mfma_f64_16x16x4f64(Vv[1], Uu[1], accT1, 0, 0, 0);
-                        accT0 = __builtin_amdgcn_mfma_f64_16x16x4f64(Vv[2], Uu[2], accT0, 0, 0, 0);
-                        accT1 = __builtin_amdgcn_mfma_f64_16x16x4f64(Vv[3], Uu[3], accT1, 0, 0, 0);
-                        if (q0 + 1 == nBt) {
-                            // end of the round: T^t of this wavefront's l tile goes to LDS ...
-                            const v4d T = accT0 + accT1;
-                            double *tp = Tx + wave * 256 + lane * 2;
-                            *reinterpret_cast<v2d *>(tp) = v2d{T.x, T.y};
-                            *reinterpret_cast<v2d *>(tp + 128) = v2d{T.z, T.w};
-                            __syncthreads();
-                            // ... and every wavefront multiplies the W tiles of its m tiles with the eight T^t,
-                            // even and odd l tiles into two accumulators (two independent instruction chains)
-                            uint32_t fm[8], any = 0u;
-                            int pre[8];
-#pragma unroll
-                            for (int t = 0; t < 8; ++t) {
-                                fm[t] = __builtin_amdgcn_readlane(mreg, 8 * t0 + t);
-                                pre[t] = t ? int(__builtin_amdgcn_readlane(ireg, 8 * t0 + t - 1)) : 0;
-                                any |= fm[t];
-                            }
-                            const int seen = __builtin_amdgcn_readlane(ireg, 8 * t0 + 7);
-                            // Parked tiles first, in a loop without global loads (a load that may or may not
-                            // have been issued makes the compiler wait for every load in flight, the
-                            // pipeline's included); the tiles that were not parked follow in a loop of their own.
-                            const int parked = min(kPool, kOwnWaves * nBt);      // tiles n < parked lie in the pool
-                            auto multiply = [&](auto from_pool) {
-#pragma unroll
-                                for (int x = 0; x < kOwnZ; ++x) {
-                                    const int mt = wave + kOwnWaves * x;
-                                    if ((any >> mt) & 1u) {
-                                        v4d z0 = accZ[x], z1 = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                                        for (int t = 0; t < 8; ++t) {
-                                            const int r = __popc(fm[t] & ((1u << mt) - 1u));
-                                            const int n = pre[t] + r;                 // place in the round's tile sequence
-                                            if (((fm[t] >> mt) & 1u) && (n < parked) == decltype(from_pool)::value) {
-                                                const lds_v2d *tr = TxV + (t * 128 + lane);
-                                                const v2d Ta = tr[0], Tb = tr[64];
-                                                v2d w0, w1;
-                                                if (decltype(from_pool)::value) {
-                                                    const lds_v2d *rp = PoolV + (n * 128 + lane);
-                                                    w0 = rp[0];
-                                                    w1 = rp[64];
-                                                } else {
-                                                    const uint32_t tile = __builtin_amdgcn_readlane(freg, 8 * t0) + uint32_t(n);
-                                                    const char *tb = reinterpret_cast<const char *>(a.wtiles + int64_t(tile) * 256);
-                                                    w0 = *reinterpret_cast<const v2d *>(tb + lane16);
-                                                    w1 = *reinterpret_cast<const v2d *>(tb + lane16 + 1024);
-                                                }
-                                                v4d z = (t & 1) ? z1 : z0;
-                                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(w0.x, Ta.x, z, 0, 0, 0);
-                                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(w0.y, Ta.y, z, 0, 0, 0);
-                                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(w1.x, Tb.x, z, 0, 0, 0);
-                                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(w1.y, Tb.y, z, 0, 0, 0);
-                                                if (t & 1) z1 = z; else z0 = z;
-                                            }
-                                        }
-                                        accZ[x] = z0 + z1;
-                                    }
-                                }
-                            };
-                            if (any & own) {
-                                multiply(std::true_type{});
-                                if (seen > parked) multiply(std::false_type{});
-                            }
-                            __syncthreads();                              // T^t and the pool are free for the next round
-                            accT0 = v4d{0.0, 0.0, 0.0, 0.0};
-                            accT1 = accT0;
-                            q0 = 0;
-                            ++t0;
-                        } else {
-                            ++q0;
-                        }
+                    for (int d = 0; d < 2; ++d) {
+                        const int x = (r & 3) * kOwnBlocks + d * kOwnWaves + wave;
+                        const int lt = r < 4 ? __builtin_amdgcn_readlane(lreg[0], x) : __builtin_amdgcn_readlane(lreg[1], x);
+                        col[d] = uint32_t(min(16 * lt + c, L32 - 1)) << 3;
                     }
                 };
+                double V[kOwnRing][2][2];                                 // [batch of the group][K-step][block]
+                v2d U[2][2];                                              // [parity of the batch][K-step] halves
+                uint4 J[2];                                               // V offsets of the group's eight K-steps
+                auto offset = [&](int i) -> uint32_t {
+                    const uint4 &q = J[i >> 2];
+                    return (i & 3) == 0 ? q.x : (i & 3) == 1 ? q.y : (i & 3) == 2 ? q.z : q.w;
+                };
+                auto read_j = [&](int g) {
+                    const uint4 *p = reinterpret_cast<const uint4 *>(jl + g * 32 + slot * 8);
+                    J[0] = p[0];
+                    J[1] = p[1];
+                };
+                auto issue = [&](double (&v)[2][2], int u, const uint32_t (&col)[2]) {
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int d = 0; d < 2; ++d)
+                            v[ks][d] = *reinterpret_cast<const double *>(Vbytes + (offset(2 * u + ks) + col[d]));
+                };
+                auto read_u = [&](v2d (&u)[2], int b) {                   // (batches behind the last row read T^t: unused)
+                    u[0] = UcV[b * 128 + lane];
+                    u[1] = UcV[b * 128 + 64 + lane];
+                };
+                uint32_t col[2], col_next[2];
+                columns(0, col);
+                read_j(0);
+#pragma unroll
+                for (int u = 0; u < kOwnRing - 1; ++u) issue(V[u], u, col);
+                read_u(U[0], 0);
 
-                if (TB > 0) {
-                    start_round();
+                for (int r = 0; r < rounds; ++r) {
+                    columns(min(r + 1, rounds - 1), col_next);
+                    // ---- this wavefront's W tiles of the round: a list (tile - first, block, accumulator) ----
+                    const int src = (r & 3) * kOwnBlocks + c;
+                    const uint32_t bm = __shfl(r < 4 ? mreg[0] : mreg[1], src);
+                    const uint32_t bf = __shfl(r < 4 ? freg[0] : freg[1], src);
+                    const uint32_t first = __builtin_amdgcn_readfirstlane(bf);
+                    uint32_t todo = lane < kOwnBlocks ? bm & own : 0u;
+                    int upto = __popc(todo);
 #pragma unroll
-                    for (int u = 0; u < kRingO; ++u) read_j(P.Jr[u]);
+                    for (int d = 1; d < 16; d <<= 1) {
+                        const int up = __shfl_up(upto, d, 16);
+                        if (c >= d) upto += up;
+                    }
+                    // (nothing to do where the half holds no slice with this k)
+                    const bool idle = my_half ? n_union == n_one : end0 == 0;
+                    const int n_tiles = idle ? 0 : __builtin_amdgcn_readlane(upto, kOwnBlocks - 1);
+                    int at = upto - __popc(todo);
+                    while (todo) {
+                        const int b = __builtin_ctz(todo);
+                        todo &= todo - 1u;
+                        list[at++] = uint16_t((bf - first + __popc(bm & ((1u << b) - 1u))) | uint32_t(c) << 9 |
+                                              uint32_t(b >> 2) << 13);
+                    }
+                    // (behind the list's end: the round's first tile, added to nothing)
+                    if (lane < 2 * kOwnWRing) list[n_tiles + lane] = uint16_t(kOwnZ << 13);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    const uint32_t code0 = list[lane], code1 = list[64 + lane];
+                    const char *round_tiles = reinterpret_cast<const char *>(a.wtiles + int64_t(first) * 256);
+                    v2d W[kOwnWRing][2];
+                    uint32_t code[kOwnWRing];
+                    auto fetch = [&](int u, uint32_t codes, int e) {      // codes: the half of the list that holds e
+                        code[u] = __builtin_amdgcn_readlane(codes, e & 63);
+                        const uint32_t at = lane16 + ((code[u] & 511u) << 11);
+                        W[u][0] = *reinterpret_cast<const v2d *>(round_tiles + at);
+                        W[u][1] = *reinterpret_cast<const v2d *>(round_tiles + at + 1024);
+                    };
 #pragma unroll
-                    for (int u = 0; u < kRingO - 1; ++u) issue(P.Jr[u], P.Vr[u], P.Ur[u], P.Wr[u], P.Sr[u]);
-                    for (int b = 0; b < TB; b += kRingO) {
+                    for (int u = 0; u < kOwnWAhead; ++u) fetch(u, code0, u);
+
+                    // ---- producer ----
+                    v4d T[2][2];                                          // [block][half]
 #pragma unroll
-                        for (int u = 0; u < kRingO; ++u) {
-                            const int su = (u + kRingO - 1) % kRingO;
-                            issue(P.Jr[su], P.Vr[su], P.Ur[su], P.Wr[su], P.Sr[su]);
-                            read_j(P.Jr[u]);
-                            consume(b + u, P.Vr[u], P.Ur[u], P.Wr[u], P.Sr[u]);
+                    for (int d = 0; d < 2; ++d)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) T[d][h] = v4d{0.0, 0.0, 0.0, 0.0};
+                    // (simple tests without alternatives: an if / else around matrix instructions makes the compiler copy
+                    // the accumulators where the paths meet)
+                    const bool two = here - r * kOwnBlocks > kOwnWaves + wave, some = here - r * kOwnBlocks > wave;
+                    const int stop0[2] = {some ? row_end0 : 0, two ? row_end0 : 0};
+                    const int stop1[2] = {some ? np : 0, two ? np : 0};
+                    auto group = [&](int g) {
+                        const bool last = g + 1 == n_groups;
+                        const uint32_t coln[2] = {last ? col_next[0] : col[0], last ? col_next[1] : col[1]};
+#pragma unroll
+                        for (int u = 0; u < kOwnRing; ++u) {
+                            if (u == 0) {
+                                issue(V[kOwnRing - 1], kOwnRing - 1, col);
+                                read_j(last ? 0 : g + 1);
+                            } else {
+                                issue(V[u - 1], u - 1, coln);
+                            }
+                            const int b = g * kOwnRing + u, row = b * kOwnRows;
+                            read_u(U[(u + 1) & 1], u + 1 == kOwnRing && last ? 0 : b + 1);
+                            const int row1 = row + kOwnRows > row_one ? row : INT32_MAX;
+#pragma unroll
+                            for (int d = 0; d < 2; ++d) {
+                                if (row < stop0[d]) {
+                                    T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][0][d], U[u & 1][0].x, T[d][0], 0, 0, 0);
+                                    T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][1][d], U[u & 1][1].x, T[d][0], 0, 0, 0);
+                                }
+                                if (row1 < stop1[d]) {
+                                    T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][0][d], U[u & 1][0].y, T[d][1], 0, 0, 0);
+                                    T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][1][d], U[u & 1][1].y, T[d][1], 0, 0, 0);
+                                }
+                            }
+                        }
+                    };
+                    // the groups whose rows both halves hold, then those with tests
+                    int g = 0;
+                    if (n_one <= p0) {
+                        const int whole = min(min(row_end0, np) / (kOwnRows * kOwnRing), n_groups - 1);
+                        for (; g < whole; ++g) {
+#pragma unroll
+                            for (int u = 0; u < kOwnRing; ++u) {
+                                if (u == 0) {
+                                    issue(V[kOwnRing - 1], kOwnRing - 1, col);
+                                    read_j(g + 1);
+                                } else {
+                                    issue(V[u - 1], u - 1, col);
+                                }
+                                read_u(U[(u + 1) & 1], g * kOwnRing + u + 1);
+                                __builtin_amdgcn_sched_barrier(0);        // (the loads stay this far ahead)
+#pragma unroll
+                                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                                    for (int d = 0; d < 2; ++d) {
+                                        T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][ks][d], U[u & 1][ks].x, T[d][0], 0, 0, 0);
+                                        T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][ks][d], U[u & 1][ks].y, T[d][1], 0, 0, 0);
+                                    }
+                            }
+                        }
+                    }
+                    for (; g < n_groups; ++g) group(g);
+                    col[0] = col_next[0];
+                    col[1] = col_next[1];
+
+                    // ---- exchange ----
+                    sp_lds_barrier();                                     // T^t of the round before has been read
+#pragma unroll
+                    for (int d = 0; d < 2; ++d)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            double *tp = Tx + ((d * kOwnWaves + wave) * 2 + h) * 256 + lane * 2;
+                            *reinterpret_cast<v2d *>(tp) = v2d{T[d][h].x, T[d][h].y};
+                            *reinterpret_cast<v2d *>(tp + 128) = v2d{T[d][h].z, T[d][h].w};
+                        }
+                    // (into the registers that T^t has left)
+#pragma unroll
+                    for (int u = kOwnWAhead; u < kOwnWRing; ++u) fetch(u, code0, u);
+                    sp_lds_barrier();
+
+                    // ---- consumer: T^t of the next tile is read while a tile is multiplied ----
+                    v2d Tr[2][2];
+                    auto read_t = [&](v2d (&t)[2], uint32_t code) {
+                        const lds_v2d *tp = TxV + (code >> 9 & 15u) * 256 + my_half * 128 + lane;
+                        t[0] = tp[0];
+                        t[1] = tp[64];
+                    };
+                    read_t(Tr[0], code[0]);
+                    for (int e0 = 0; e0 < n_tiles; e0 += kOwnWRing) {
+                        const uint32_t codes = e0 + kOwnWRing < 64 ? code0 : code1;
+#pragma unroll
+                        for (int u = 0; u < kOwnWRing; ++u) {
+                            read_t(Tr[(u + 1) & 1], code[(u + 1) % kOwnWRing]);
+                            // one bit per accumulator, its origin hidden: tests that the compiler can see to exclude one
+                            // another become a switch, and accumulators are copied where its cases meet
+                            uint32_t hot = 1u << (code[u] >> 13);
+                            asm("" : "+s"(hot));
+                            auto add = [&](v4d &z) {
+                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(W[u][0].x, Tr[u & 1][0].x, z, 0, 0, 0);
+                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(W[u][0].y, Tr[u & 1][0].y, z, 0, 0, 0);
+                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(W[u][1].x, Tr[u & 1][1].x, z, 0, 0, 0);
+                                z = __builtin_amdgcn_mfma_f64_16x16x4f64(W[u][1].y, Tr[u & 1][1].y, z, 0, 0, 0);
+                            };
+                            if (hot & 0x0fu) {
+                                if (hot & 0x01u) add(accZ[0]);
+                                if (hot & 0x02u) add(accZ[1]);
+                                if (hot & 0x04u) add(accZ[2]);
+                                if (hot & 0x08u) add(accZ[3]);
+                            }
+                            if (hot & 0x70u) {
+                                if (hot & 0x10u) add(accZ[4]);
+                                if (hot & 0x20u) add(accZ[5]);
+                                if (hot & 0x40u) add(accZ[6]);
+                            }
+                            fetch(u, codes, e0 + u + kOwnWRing);
                         }
                     }
                 }
             }
-            p0 += kCap;
+            p0 += kOwnCap;
             if (p0 < n_union) {
-                np = min(kCap, n_union - p0);
-                npad = (np + 4 * kBatch - 1) & ~(4 * kBatch - 1);
-                prepare(p0, np, npad, std::false_type{});
+                sp_lds_barrier();                                         // Uc and the offsets have been read
+                prepare(p0, min(kOwnCap, n_union - p0), std::false_type{});
             }
         }
     }
 
     // ---- store the group's rows: lane holds Z^t[m = 16 mt + slot + 4 v][i = c] ----------------------
     const int64_t M = a.M;
-    const int64_t s = s0 + c;
+    const int64_t s = s0 + 16 * my_half + c;
     if (s < a.slices) {
         const int64_t row = a.compact ? s : int64_t(a.uidx0[s]);
         double *dst = a.n_kc == 1 ? a.out + row * M : a.partial + (int64_t(kc) * a.slices + s) * M;
 #pragma unroll
         for (int x = 0; x < kOwnZ; ++x) {
-            const int mt = wave + kOwnWaves * x;
+            const int mt = my_class + kOwnClasses * x;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * mt + slot + 4 * v;
@@ -820,22 +940,35 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
             }
         }
     }
+    }
 }
 
-// sums the partial results of the k chunks in chunk order
-__global__ void sptn3_fixup_kernel(int64_t slices, int64_t M, int n_kc, const int32_t *__restrict__ uidx0,
-                                   const double *__restrict__ partial, double *out, int compact) {
+// Sums the partial results of the k chunks in chunk order; of those marked `present` where the others were not written.
+// Sixteen loads in flight: a chain of single ones took 12 us over 44 chunks, this 4.
+// Row r of the result is that of slice r, or of slice_of_row[r] (-1: none, zeros).
+__global__ void sptn3_fixup_kernel(int64_t rows, int64_t slices, int64_t M, int n_kc, const int32_t *__restrict__ slice_of_row,
+                                   const double *__restrict__ partial, const uint8_t *__restrict__ present, int n_groups,
+                                   double *out) {
     const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (x >= slices * M) return;
-    const int64_t s = x / M, m = x - s * M;
+    if (x >= rows * M) return;
+    const int64_t row = x / M, m = x - row * M, s = slice_of_row ? slice_of_row[row] : row;
+    if (s < 0) {
+        out[x] = 0.0;
+        return;
+    }
     double z = 0.0;
-    for (int kc = 0; kc < n_kc; ++kc) z += partial[(int64_t(kc) * slices + s) * M + m];
-    const int64_t row = compact ? s : int64_t(uidx0[s]);
-    out[row * M + m] = z;
-}
-
-static size_t sptn3_owned_lds(int nwords) {
-    return size_t(kCap * 16 + kPool * 256 + kOwnWaves * 256) * 8 + size_t(kCap) * 4 + size_t(nwords) * 8 + 64;
+    for (int kc = 0; kc < n_kc; kc += 16) {
+        double v[16];
+        bool has[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            has[u] = kc + u < n_kc && (!present || present[int64_t(min(kc + u, n_kc - 1)) * n_groups + s / kSpGroupWide]);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = partial[(int64_t(min(kc + u, n_kc - 1)) * slices + s) * M + m];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) z += has[u] ? v[u] : 0.0;
+    }
+    out[x] = z;
 }
 
 bool sptn3_two_waves_fit(int nwords) { return sptn3_owned_lds(nwords) <= 160 * 1024; }
@@ -851,8 +984,9 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     a.MT = int((a.M + 15) / 16);
     const int64_t J = U->dims[U->mode_order[2]];
     a.nwords = int((J + 31) / 32);
-    a.n_groups = int((a.slices + kSpGroup - 1) / kSpGroup);
-    a.n_kc = plan->sp_kc;
+    a.n_groups = int((a.slices + plan->sp_group() - 1) / plan->sp_group());
+    a.n_kc = plan->sp_kc * plan->sp_l_parts;
+    a.l_parts = plan->sp_l_parts;
     a.k_per = plan->sp_k_per;
     a.uptr0 = U->ptr[0].p;
     a.uptr1 = U->ptr[1].p;
@@ -871,11 +1005,16 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     a.out = out;
     a.partial = plan->partial.p;
     a.compact = plan->compact ? 1 : 0;
+    a.chunk_fiber = plan->sp_chunk_fiber.p;
+    a.chunk_k = plan->sp_chunk_k.p;
+    a.work = plan->sp_work.p;
+    a.work_end = int64_t(plan->sp_work.n);
     a.wg_order = plan->sp_xcd_ranges ? nullptr : plan->sp_wg_order.p;
     a.xcd_ranges = plan->sp_xcd_ranges ? 1 : 0;      // measured: halves the HBM fetch, 4 % slower
     const size_t lds_bytes = size_t(kCap) * 16 * 8 + size_t(4 * kStage) * 256 * 8 + size_t(a.MT) * 256 * 8 +
                              size_t(kCap) * 4 + size_t(a.nwords) * 8 + 64;
-    if (!plan->compact && a.slices < plan->out_rows)
+    // (with partial results the rows of absent slices are cleared by the pass that adds those up)
+    if (!plan->compact && a.slices < plan->out_rows && (a.n_kc == 1 || a.slices == 0))
         CST_TRY(zero_fill(out, plan->out_rows * plan->row_elems, stream));
     if (a.slices == 0) return CONSTSTN_OK;
     // two wavefronts per SIMD (m tiles owned by wavefronts) when the plan chose it, else one (l tiles owned)
@@ -884,14 +1023,16 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     {
         ProfScope prof(plan, stream);
         const unsigned n_wg = unsigned(a.n_groups) * unsigned(a.n_kc);
-        if (owned) sptn3_owned_kernel<<<dim3((n_wg + 7) / 8 * 8), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
+        if (owned) sptn3_owned_kernel<<<dim3(unsigned(plan->sp_workers)), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
         else sptn3_tiled_kernel<<<dim3((n_wg + 7) / 8 * 8), dim3(256), lds_bytes, stream>>>(a);
     }
     CST_HIP(hipGetLastError());
     if (a.n_kc > 1) {
-        const int64_t n = a.slices * a.M;
-        sptn3_fixup_kernel<<<dim3(unsigned((n + 255) / 256)), dim3(256), 0, stream>>>(
-            a.slices, a.M, a.n_kc, a.uidx0, a.partial, out, a.compact);
+        const bool all = plan->compact || a.slices == plan->out_rows;
+        const int64_t rows = plan->compact ? a.slices : plan->out_rows;
+        sptn3_fixup_kernel<<<dim3(unsigned((rows * a.M + 255) / 256)), dim3(256), 0, stream>>>(
+            rows, a.slices, a.M, a.n_kc, all ? nullptr : plan->sp_slice_of_row.p, a.partial, owned ? plan->sp_present.p : nullptr,
+            a.n_groups, out);
         CST_HIP(hipGetLastError());
     }
     return CONSTSTN_OK;

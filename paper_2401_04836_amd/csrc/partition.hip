@@ -11,6 +11,10 @@
 #include <algorithm>
 
 #include <cstdlib>
+#include <functional>
+#include <new>
+#include <utility>
+#include <vector>
 
 #include "plan.hpp"
 
@@ -1117,30 +1121,132 @@ __global__ void w_first_u32_kernel(int64_t n, const int64_t *__restrict__ first,
     if (x < n) out[x] = uint32_t(first[x]);
 }
 
-// Leaves of U per (k chunk, group of 16 slices) pair: the workgroups of the tiled kernels take the pairs
-// in falling order of it, so that the last round of workgroups holds the light ones.
-__global__ void sp_pair_cost_kernel(int64_t fibers, int64_t slices, const int64_t *__restrict__ ptr0,
-                                    const int64_t *__restrict__ ptr1, const int32_t *__restrict__ idx1,
-                                    int64_t k_per, int n_groups, unsigned *cost) {
-    const int64_t f = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (f >= fibers) return;
-    const int64_t s = root_of_fiber(ptr0, slices, f);
-    const int64_t pair = (int64_t(idx1[f]) / k_per) * n_groups + s / kSpGroup;
-    atomicAdd(&cost[pair], unsigned(ptr1[f + 1] - ptr1[f]));
+// Cost of a (k chunk, group of slices) pair in matrix instructions, one workgroup per pair: the tiled kernels take the
+// pairs in falling order of it.  Per k: the producer's rows of the union of each half's j (rounded to batches of eight)
+// x blocks of l / 4, the consumer's W tiles x 4 per half and pass over the union, and what a pass and its rounds of
+// sixteen blocks cost beside them (20 us and 4 us of a workgroup at 2000 x 2000 x 400, which has four SIMDs); per pair 5 us.
+constexpr int kSpCostPair = 700, kSpCostPass = 3000, kSpCostRound = 600;
+__global__ void __launch_bounds__(256)
+sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int64_t *__restrict__ ptr1, const int32_t *__restrict__ idx1,
+                    const int32_t *__restrict__ idx2, const int64_t *__restrict__ w_root_of_k, const int32_t *__restrict__ cell_ptr,
+                    const SpCell *__restrict__ cells, int64_t k_per, int l_parts, int n_groups, int group, int nwords, int rows_per_pass,
+                    unsigned long long *cost) {
+    extern __shared__ uint32_t sp_cost_mask[];                            // 2 x nwords
+    __shared__ int total[3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t s0 = int64_t(blockIdx.x % n_groups) * group, k0 = int64_t(blockIdx.x / n_groups / l_parts) * k_per;
+    const int part = blockIdx.x / n_groups % l_parts;
+    int64_t cur = 0, end = 0;                                             // lane sl and sl + 32: of slice s0 + sl
+    if ((lane & 31) < group && s0 + (lane & 31) < slices) {
+        const int64_t na = ptr0[s0 + (lane & 31)], nb = ptr0[s0 + (lane & 31) + 1];
+        auto lower = [&](int64_t lo, int64_t key) {
+            int64_t hi = nb;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (int64_t(idx1[mid]) < key) lo = mid + 1; else hi = mid;
+            }
+            return lo;
+        };
+        cur = lower(na, k0);
+        end = lower(cur, k0 + k_per);
+    }
+    unsigned long long sum = kSpCostPair;
+    for (;;) {
+        const int32_t kk = cur < end ? idx1[cur] : INT32_MAX;
+        int32_t k = kk;
+        for (int d = 16; d; d >>= 1) k = min(k, __shfl_xor(k, d, 32));
+        if (k == INT32_MAX) break;
+        int64_t la = 0, lb = 0;
+        if (kk == k) { la = ptr1[cur]; lb = ptr1[cur + 1]; ++cur; }
+        const int64_t root = w_root_of_k[k];
+        if (root < 0) continue;
+        for (int w = tid; w < 2 * nwords; w += 256) sp_cost_mask[w] = 0u;
+        if (tid < 3) total[tid] = 0;
+        __syncthreads();
+        for (int sl = wave * 8; sl < wave * 8 + 8; ++sl) {
+            const int64_t ea = __shfl(la, sl), eb = __shfl(lb, sl);
+            uint32_t *mask = sp_cost_mask + (sl >> 4) * nwords;
+            for (int64_t e = ea; e < eb; e += 64) {
+                const int j = e + lane < eb ? idx2[e + lane] : -1;
+                const uint32_t bit = j >= 0 ? 1u << (j & 31) : 0u;
+                const int word = j >> 5, word0 = row_first(word);
+                const uint32_t joined = row_or(word == word0 ? bit : 0u);
+                if (bit && ((lane & 15) == 0 || word != word0)) atomicOr(&mask[word], (lane & 15) == 0 ? joined : bit);
+            }
+        }
+        __syncthreads();
+        int n0 = 0, n1 = 0, n = 0;
+        for (int w = tid; w < nwords; w += 256) {
+            const uint32_t m0 = sp_cost_mask[w], m1 = sp_cost_mask[nwords + w];
+            n0 += __popc(m0);
+            n1 += __popc(m1);
+            n += __popc(m0 | m1);
+        }
+        atomicAdd(&total[0], n0);
+        atomicAdd(&total[1], n1);
+        atomicAdd(&total[2], n);
+        __syncthreads();
+        const long long r0 = (total[0] + 7) & ~7, r1 = (total[1] + 7) & ~7, passes = (total[2] + rows_per_pass - 1) / rows_per_pass;
+        const long long n_all = cell_ptr[root + 1] - cell_ptr[root];
+        const long long c0 = cell_ptr[root] + n_all * part / l_parts, c1 = cell_ptr[root] + n_all * (part + 1) / l_parts, halves = (r0 > 0) + (r1 > 0);
+        const long long tiles = c0 < c1 ? (long long)cells[c1 - 1].first + __popc(cells[c1 - 1].mask) - cells[c0].first : 0;
+        sum += (r0 + r1) * (c1 - c0) / 4 + passes * (tiles * 4 * halves + kSpCostPass + (c1 - c0 + 15) / 16 * kSpCostRound);
+        __syncthreads();
+    }
+    if (tid == 0) cost[blockIdx.x] = sum;
 }
 
-__global__ void sp_pair_keys_kernel(int64_t n, const unsigned *__restrict__ cost, uint64_t *keys, uint32_t *ids) {
+__global__ void sp_pair_keys_kernel(int64_t n, const unsigned long long *__restrict__ cost, uint64_t *keys, uint32_t *ids,
+                                    uint8_t *present) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    keys[i] = uint64_t(0xffffffffu - cost[i]);
+    present[i] = cost[i] != kSpCostPair ? 1 : 0;
+    keys[i] = 0xffffffffu - min(cost[i] >> 4, 0xffffffffull);
     ids[i] = uint32_t(i);
+}
+
+// `pairs` in falling order of cost -> lists of them for `workers` workgroups (workgroup w runs on XCD w % 8): runs of eight to
+// the XCD with the least work (by_range: equal ranges of pair numbers instead), there each to the least loaded workgroup.
+// Entry n of `work` is for workgroup n % (workgroups, returned); -1: no more.
+static int deal_pairs(const std::vector<uint32_t> &pairs, const std::vector<unsigned long long> &cost, int workers, bool by_range,
+                       std::vector<int32_t> &work) {
+    constexpr int kXcds = 8;
+    const size_t n = pairs.size();
+    const size_t run = n >= 4 * size_t(std::max(workers, 1)) ? 8 : 1;     // (few pairs: one by one, over all of the chip)
+    workers = std::max(workers, kXcds);
+    using Load = std::pair<unsigned long long, int>;
+    std::vector<std::vector<int32_t>> lists(static_cast<size_t>(workers));
+    std::vector<std::vector<Load>> heaps(kXcds);
+    unsigned long long per_xcd[kXcds] = {};
+    for (int w = 0; w < workers; ++w) heaps[w % kXcds].push_back({0, w});
+    const auto later = std::greater<Load>();
+    for (auto &q : heaps) std::make_heap(q.begin(), q.end(), later);
+    int xcd = 0;
+    for (size_t i = 0; i < n; ++i) {
+        if (by_range) xcd = int(size_t(pairs[i]) * kXcds / cost.size());
+        else if (i % run == 0) xcd = int(std::min_element(per_xcd, per_xcd + kXcds) - per_xcd);
+        const unsigned long long c = cost[pairs[i]];
+        auto &q = heaps[size_t(xcd)];
+        std::pop_heap(q.begin(), q.end(), later);
+        lists[size_t(q.back().second)].push_back(int32_t(pairs[i]));
+        q.back().first += c;
+        std::push_heap(q.begin(), q.end(), later);
+        per_xcd[xcd] += c;
+    }
+    size_t rounds = 1;
+    for (auto &l : lists) rounds = std::max(rounds, l.size());
+    work.assign(rounds * lists.size(), -1);
+    for (size_t w = 0; w < lists.size(); ++w)
+        for (size_t i = 0; i < lists[w].size(); ++i) work[i * lists.size() + w] = lists[w][i];
+    return workers;
 }
 
 static conststn_status build_sp_wg_order(conststn_plan_s *plan) {
     const conststn_csf_s *U = plan->X;
-    const int64_t groups = div_up(U->nodes[0], kSpGroup), n = groups * plan->sp_kc;
-    if (n <= 1 || n >= (int64_t(1) << 31) || U->nodes[1] == 0) return CONSTSTN_OK;
-    DevBuf<unsigned> cost;
+    const int64_t groups = div_up(U->nodes[0], plan->sp_group()), n = groups * plan->sp_kc * plan->sp_l_parts;
+    // (where groups alone are far more than the chip holds, pairs go in their own order)
+    const bool by_cost = n > 1 && n <= (int64_t(1) << 20) && U->nodes[1] > 0;
+    DevBuf<unsigned long long> cost;
     DevBuf<uint64_t> ka, kb;
     DevBuf<uint32_t> ia, ib;
     CST_TRY(cost.alloc(n));
@@ -1148,19 +1254,70 @@ static conststn_status build_sp_wg_order(conststn_plan_s *plan) {
     CST_TRY(kb.alloc(n));
     CST_TRY(ia.alloc(n));
     CST_TRY(ib.alloc(n));
+    CST_TRY(plan->sp_present.alloc(n));
     const dim3 block(256);
-    fill_i32_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(reinterpret_cast<int32_t *>(cost.p), n, 0);
-    sp_pair_cost_kernel<<<dim3(unsigned(div_up(U->nodes[1], 256))), block>>>(
-        U->nodes[1], U->nodes[0], U->ptr[0].p, U->ptr[1].p, U->idx[1].p, plan->sp_k_per, int(groups), cost.p);
-    sp_pair_keys_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(n, cost.p, ka.p, ia.p);
+    if (by_cost) {
+        const int nwords = int(div_up(U->dims[U->mode_order[2]], 32));
+        sp_pair_cost_kernel<<<dim3(unsigned(n)), block, size_t(nwords) * 8>>>(
+            U->nodes[0], U->ptr[0].p, U->ptr[1].p, U->idx[1].p, U->idx[2].p, plan->w_root_of_k.p, plan->w_cell_ptr.p, plan->w_cells.p,
+            plan->sp_k_per, plan->sp_l_parts, int(groups), plan->sp_group(), nwords, kSpUnionRows, cost.p);
+    } else {
+        fill_i64_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(reinterpret_cast<int64_t *>(cost.p), n, 1);
+    }
+    sp_pair_keys_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(n, cost.p, ka.p, ia.p, plan->sp_present.p);
     CST_HIP(hipGetLastError());
     const uint64_t *ks = nullptr;
     const uint32_t *order = nullptr;
     CST_TRY(radix_sort_pairs_u64(ka.p, kb.p, ia.p, ib.p, n, 32, hipStream_t(0), &ks, &order));
-    CST_TRY(plan->sp_wg_order.alloc(size_t(n)));
-    CST_HIP(hipMemcpy(plan->sp_wg_order.p, order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToDevice));
-    CST_HIP(hipDeviceSynchronize());
+    if (!plan->sp_two_waves) {
+        CST_TRY(plan->sp_wg_order.alloc(size_t(n)));
+        CST_HIP(hipMemcpy(plan->sp_wg_order.p, order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToDevice));
+        CST_HIP(hipDeviceSynchronize());
+        return CONSTSTN_OK;
+    }
+    // Lists of pairs for one workgroup per compute unit, each pair to the workgroup with the least work so far, the
+    // heaviest first.  In the hardware's launch order workgroups of unequal length left the compute units idle for
+    // 2.0 of 18.1 ms at 2000 x 2000 x 400.  Pairs of equal cost stand in the order (k chunk, group), and neighbouring
+    // groups read the same W tiles and largely the same rows of V: runs of eight stay on one XCD.
+    std::vector<uint32_t> pairs;
+    std::vector<unsigned long long> costs;
+    std::vector<int32_t> work;
+    try {
+        pairs.resize(size_t(n));
+        costs.resize(size_t(n));
+        CST_HIP(hipMemcpy(pairs.data(), order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToHost));
+        CST_HIP(hipMemcpy(costs.data(), cost.p, size_t(n) * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+        // pairs without work write nothing, unless there is but one result to a row
+        if (plan->sp_kc * plan->sp_l_parts > 1)
+            while (!pairs.empty() && costs[pairs.back()] == kSpCostPair) pairs.pop_back();
+        plan->sp_workers = deal_pairs(pairs, costs, plan->n_cus, plan->opt("sptn3_xcd", 0) == 1, work);
+    } catch (const std::bad_alloc &) {
+        set_error("no host memory for the lists of %lld work pairs", (long long)n);
+        return CONSTSTN_ENOMEM;
+    }
+    CST_TRY(plan->sp_work.alloc(work.size()));
+    CST_HIP(hipMemcpy(plan->sp_work.p, work.data(), work.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     return CONSTSTN_OK;
+}
+
+// First fiber of every slice of U in every chunk of the k range and its k (n = (chunks + 1) x slices; no k for the last).
+__global__ void sp_chunk_fiber_kernel(int64_t slices, int64_t n, int64_t k_per, const int64_t *__restrict__ ptr0,
+                                      const int32_t *__restrict__ idx1, int64_t *out, int32_t *out_k) {
+    const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (x >= n) return;
+    const int64_t s = x % slices, k = x / slices * k_per, last = ptr0[s + 1];
+    int64_t lo = ptr0[s], hi = last;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (int64_t(idx1[mid]) < k) lo = mid + 1; else hi = mid;
+    }
+    out[x] = lo;
+    if (x < n - slices) out_k[x] = lo < last && int64_t(idx1[lo]) < k + k_per ? idx1[lo] : INT32_MAX;
+}
+
+__global__ void sp_slice_of_row_kernel(int64_t slices, const int32_t *__restrict__ idx0, int32_t *slice_of_row) {
+    const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (s < slices) slice_of_row[idx0[s]] = int32_t(s);
 }
 
 __global__ void w_cell_flag_kernel(int64_t n, const uint32_t *__restrict__ mask, int64_t *flag) {
@@ -1234,17 +1391,37 @@ static conststn_status build_w_tiles(conststn_plan_s *plan) {
     CST_TRY(plan->w_cell_ptr.alloc(size_t(roots) + 1));
     w_cell_fill_kernel<<<cgrid, block>>>(cells, LT, plan->w_tile_mask.p, first.p, place.p, n_cells, plan->w_cell_ptr.p, plan->w_cells.p);
     CST_HIP(hipGetLastError());
-    // slices go in groups of 16; the k range is cut into chunks so that the grid fills the chip
-    const int64_t groups = div_up(U->nodes[0], kSpGroup);
-    int64_t want = plan->opt("sptn3_wgs", 8000);
-    int64_t n_kc = std::min<int64_t>(std::max<int64_t>(div_up(want, groups), 1), std::min<int64_t>(K, 64));
+    plan->sp_two_waves = plan->opt("sptn3_waves", 2) == 2 && sptn3_two_waves_fit(int((J + 31) / 32));
+    // slices go in groups of 16 or 32; the k range is cut into chunks so that the grid fills the chip
+    const int64_t groups = div_up(U->nodes[0], plan->sp_group());
+    const int64_t want = plan->opt("sptn3_wgs", 8000);
+    // (more than 64 chunks only where that leaves less than four pairs per compute unit: a chunk costs a partial result)
+    const int64_t most = plan->sp_two_waves ? std::max<int64_t>(64, std::min<int64_t>(128, 4 * int64_t(plan->n_cus) / groups)) : 64;
+    int64_t n_kc = std::min<int64_t>(std::max<int64_t>(div_up(want, groups), 1), std::min<int64_t>(K, most));
     plan->sp_k_per = div_up(K, n_kc);
     plan->sp_kc = int(div_up(K, plan->sp_k_per));
-    if (plan->sp_kc > 1)
-        CST_TRY(plan->partial.alloc(size_t(plan->sp_kc) * size_t(U->nodes[0]) * size_t(M)));
+    // where the pairs are fewer than two per compute unit, each takes half of the blocks of l if that leaves it a round of
+    // sixteen: 7 groups x 60 chunks, 49 blocks, 114 -> 107 us
+    const bool few = plan->sp_two_waves && groups * plan->sp_kc < 2 * int64_t(plan->n_cus) && groups * plan->sp_kc * 2 <= want;
+    plan->sp_l_parts = few && LT >= 32 ? 2 : 1;
+    if (plan->sp_kc * plan->sp_l_parts > 1)
+        CST_TRY(plan->partial.alloc(size_t(plan->sp_kc) * size_t(plan->sp_l_parts) * size_t(U->nodes[0]) * size_t(M)));
+    if (plan->sp_kc * plan->sp_l_parts > 1 && !plan->compact && U->nodes[0] < plan->out_rows) {
+        CST_TRY(plan->sp_slice_of_row.alloc(size_t(plan->out_rows)));
+        fill_i32_kernel<<<dim3(unsigned(div_up(plan->out_rows, 256))), block>>>(plan->sp_slice_of_row.p, plan->out_rows, -1);
+        sp_slice_of_row_kernel<<<dim3(unsigned(div_up(U->nodes[0], 256))), block>>>(U->nodes[0], U->idx[0].p, plan->sp_slice_of_row.p);
+        CST_HIP(hipGetLastError());
+    }
     plan->w_tiled = true;
     CST_TRY(build_sp_wg_order(plan));
-    plan->sp_two_waves = plan->opt("sptn3_waves", 2) == 2 && sptn3_two_waves_fit(int((J + 31) / 32));
+    if (plan->sp_two_waves) {
+        const int64_t n = (int64_t(plan->sp_kc) + 1) * U->nodes[0];
+        CST_TRY(plan->sp_chunk_fiber.alloc(size_t(n)));
+        CST_TRY(plan->sp_chunk_k.alloc(size_t(n)));
+        sp_chunk_fiber_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(U->nodes[0], n, plan->sp_k_per, U->ptr[0].p, U->idx[1].p,
+                                                                      plan->sp_chunk_fiber.p, plan->sp_chunk_k.p);
+        CST_HIP(hipGetLastError());
+    }
     return CONSTSTN_OK;
 }
 

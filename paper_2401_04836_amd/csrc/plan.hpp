@@ -16,6 +16,8 @@ constexpr int kRowLeaves = 16;        // longest run of leaves one MFMA K-row su
 constexpr int kPieceLeaves = 2;       // order-4 path: leaves per piece of a level-2 node
 // three-tensor network, tiled path
 constexpr int kSpGroup = 16;          // root slices of U processed together (one MFMA operand side)
+constexpr int kSpGroupWide = 32;      // ... by the form with two wavefronts per SIMD
+constexpr int kSpUnionRows = 312;     // j that form takes at a time, of the union over the slices
 constexpr int kSpMaxMTiles = 25;      // m tiles whose accumulators a wavefront holds (M <= 400)
 constexpr int kSpMaxJ = 32768;        // extent of the contracted mode j the LDS bit mask covers
 
@@ -132,6 +134,18 @@ constexpr uint32_t kGrpEndsFiber = 1u << 28, kGrpEndsKstep = 1u << 29, kGrpStart
                    kGrpIndexMask = (1u << 26) - 1u;
 // flags of one record: it pads its group, or its second leaf is absent
 constexpr uint32_t kRecEmpty = 1u << 26, kRecOneLeaf = 1u << 27;
+
+#ifdef __HIPCC__
+// the value of a row of sixteen lanes' first lane, and the OR over the row, in every lane of it
+__device__ __forceinline__ int row_first(int x) { return __builtin_amdgcn_update_dpp(x, x, 0x150, 0xf, 0xf, false); }
+__device__ __forceinline__ uint32_t row_or(uint32_t x) {
+    x |= uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x121, 0xf, 0xf, false));   // row_ror: 1, 2, 4, 8
+    x |= uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x122, 0xf, 0xf, false));
+    x |= uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x124, 0xf, 0xf, false));
+    x |= uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x128, 0xf, 0xf, false));
+    return x;
+}
+#endif
 
 // A block of sixteen l under one root of W that holds something: its place, the m tiles present, and the first of
 // them among the dense tiles (those of a root follow one another).
@@ -254,6 +268,7 @@ struct conststn_plan_s {
     cst::DevBuf<int64_t> w_root_of_k;      // [K] root node of W holding index k, or -1
     bool w_tiled = false;                  // W also stored as dense 16 x 16 (l, m) tiles
     bool sp_two_waves = false;             // tiled kernel with two wavefronts per SIMD (m tiles owned by wavefronts)
+    int sp_group() const { return sp_two_waves ? cst::kSpGroupWide : cst::kSpGroup; }
     int64_t n_w_tiles = 0;
     cst::DevBuf<uint32_t> w_tile_mask;     // [roots x ceil(L/16)] m tiles present
     cst::DevBuf<uint32_t> w_tile_first;    // [roots x ceil(L/16)] index of the first of them
@@ -261,8 +276,15 @@ struct conststn_plan_s {
     cst::DevBuf<int32_t> w_cell_ptr;       // [roots + 1] first of them of each root
     cst::DevBuf<double> w_tiles;           // [(tiles + 1) x 256], the last one all zero
     bool sp_xcd_ranges = false;            // contiguous workgroup ranges per XCD
-    cst::DevBuf<int32_t> sp_wg_order;      // [groups x k chunks] pairs by falling number of U leaves, or empty
+    cst::DevBuf<int64_t> sp_chunk_fiber;   // [(k chunks + 1) x slices] first fiber of a slice of U in a k chunk
+    cst::DevBuf<int32_t> sp_chunk_k;       // [k chunks x slices] its k (INT32_MAX: none)
+    cst::DevBuf<int32_t> sp_wg_order;      // [groups x k chunks] pairs by falling cost, or empty
+    cst::DevBuf<uint8_t> sp_present;       // [groups x k chunks] pairs whose partial results are written
+    cst::DevBuf<int32_t> sp_slice_of_row;  // [result rows] slice of U, or -1 (where some rows have none)
+    int sp_workers = 0;                    // workgroups of the form with two wavefronts per SIMD
+    cst::DevBuf<int32_t> sp_work;          // [rounds x workers] their pairs, -1 behind the last of a workgroup
     int sp_kc = 1;                         // chunks of the k range (one workgroup per group and chunk)
+    int sp_l_parts = 1;                    // parts of the blocks of l (with two wavefronts per SIMD)
     int64_t sp_k_per = 0;                  // k values per chunk
 
     // generic executor: one entry per statement, intermediates held whole

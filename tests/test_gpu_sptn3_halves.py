@@ -1,0 +1,53 @@
+"""Three-tensor network on the kernel with two wavefronts per SIMD: numbers of slices on both sides of a half (16) and of a
+group (32), unions of j on both sides of a batch (8), of a group of batches (32) and of a pass (312), rows of the union that only one
+half holds, few pairs over many blocks of l (each pair takes half of them), slices and pairs without work, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2401_04836_amd as cst
+from paper_2401_04836_amd import schedules as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("wgs", [1, 8000])
+@pytest.mark.parametrize("slices,J,shared", [(1, 1, True), (16, 8, True), (17, 33, False), (32, 312, True), (33, 313, False),
+                                             (40, 640, False), (65, 31, True)])
+@pytest.mark.parametrize("L", [40, 600])
+def test_halves_passes_and_parts(slices, J, shared, L, wgs):
+    rng = np.random.default_rng(slices * 1000 + J + L)
+    K, M, rows = 7, 70, slices + 5                        # five rows of the result have no slice
+    row_of = np.sort(rng.permutation(rows)[:slices])
+    per_half = max(1, J // 2)                             # not shared: halves hold different j, a few of them in common
+    u = [[], [], []]
+    for s in range(slices):
+        for k in range(K - 1):                            # no slice holds the last k
+            if k == 2 and s >= 16:
+                continue                                  # here the first half alone
+            js = np.arange(J) if shared else np.unique(np.concatenate([np.arange(per_half) + (s // 16 % 2) * (J - per_half),
+                                                                       rng.integers(0, J, 2)]))
+            js = js[rng.random(js.size) < 0.9] if js.size > 1 else js
+            u[0] += [row_of[s]] * js.size
+            u[1] += list(js)
+            u[2] += [k] * js.size
+    u = [np.array(x, dtype=np.int32) for x in u]
+    wkey = np.unique(rng.integers(0, 5 * L * M, 6 * L))   # nothing in W below the fifth k and on
+    wc = [x.astype(np.int32) for x in np.unravel_index(wkey, (K, L, M))]
+    uv, wv, V = rng.uniform(-1, 1, u[0].size), rng.uniform(-1, 1, wkey.size), rng.uniform(-1, 1, (J, L))
+    print("[case] slices %d J %d shared %s L %d wgs %d nnz %d %d" % (slices, J, shared, L, wgs, uv.size, wv.size), flush=True)
+    up = lambda cs: [torch.from_numpy(x).cuda() for x in cs]
+    U = cst.build_csf(up(u), torch.from_numpy(uv).cuda(), (rows, J, K), [0, 2, 1])
+    W = cst.build_csf(up(wc), torch.from_numpy(wv).cuda(), (K, L, M), [0, 1, 2])
+    v = torch.from_numpy(V).cuda()
+    want = oracle.sptn3(u, uv, (rows, J, K), V, wc, wv, (K, L, M))
+    S_abs = oracle.sptn3_abs(u, uv, (rows, J, K), V, wc, wv, (K, L, M))
+    for flags in (0, cst.OUT_COMPACT):
+        pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], flags=flags, options=dict(sptn3_tiled=2, sptn3_wgs=wgs))
+        assert "two waves" in pl.describe()
+        got = cst.execute(pl, [v]).cpu().numpy().reshape(-1, M)
+        ref, bound = (want[row_of], S_abs[row_of]) if flags else (want, S_abs)
+        assert not np.isnan(got).any() and not got[bound == 0].any()
+        # a sum has at most J K x L products of three factors, in any order: (J + K L + 3) roundings along the longest chain
+        assert oracle.rel_err(got, ref, bound) <= (J + K * L + 3) * 1.1e-16
