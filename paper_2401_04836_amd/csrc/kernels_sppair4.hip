@@ -20,6 +20,12 @@
 //             current one) and one matrix-core pass over the 16 x 16 tiles of the block, whose
 //             accumulators stay in registers; stored elements are written in place.  No atomics on
 //             values; the K are visited in ascending order.
+//
+// Where one tensor stands under both names (the four-index integrals: Ea = Eb = E), V[j,i,n,m] and V[i,j,m,n] are the
+// same sum of the same products, bit for bit: only the pairs with i <= j have a workgroup, which writes its block and the
+// mirror image's.  The plan keeps that one's bit matrix beside its own, and the stored elements ahead of every word.
+// 12 x 12 lattice, 224 M elements: 2.86 -> 1.74 ms.  Of these, switched off in copies: writing the mirror images
+// 0.22 ms, writing at all 0.35; without the passes over K (26 M matrix instructions, 0.72 ms at 27 ns) 0.79, with neither 0.21.
 #include "plan.hpp"
 #include <type_traits>
 
@@ -69,6 +75,8 @@ struct P4Out {
     int32_t *k_alen, *k_blen;               // ... and its length
     int dense;                              // the operands' dense rows are kept
     uint32_t *masks;                        // [pairs x mask_stride]
+    int32_t *pres;                          // ... and the pair's stored elements ahead of every word of it
+    const int32_t *mirror;                  // one tensor under both names: the node of (j,i) for that of (i,j), or null
     int64_t mask_stride;
 };
 
@@ -221,6 +229,13 @@ sppair4_symbolic_kernel(P4Args A, P4Out V, P4SymLds O, int mode, int64_t *rows, 
             V.k_blen[k0 + x] = int32_t(A.b.ptr1[match_b[x] + 1] - b0);
         }
         for (int x = threadIdx.x; x < n_ua * A.W; x += 64 * kP4Waves) V.masks[node * V.mask_stride + x] = rowmask[x];
+        for (int r = threadIdx.x; V.pres && r < n_ua; r += 64 * kP4Waves) {
+            int at = rowleaf[r];
+            for (int w = 0; w < A.W; ++w) {
+                V.pres[node * V.mask_stride + r * A.W + w] = at;
+                at += __popc(rowmask[r * A.W + w]);
+            }
+        }
     }
     if (threadIdx.x == 0) {
         V.idx1[node] = A.b.idx0[rb];
@@ -324,8 +339,16 @@ __global__ void sppair4_cost_key_kernel(P4Args A, P4Out V, uint64_t *keys, uint3
     const int64_t ta = (A.a.u_ptr[ra + 1] - A.a.u_ptr[ra] + 15) / 16, tb = (A.b.u_ptr[rb + 1] - A.b.u_ptr[rb] + 15) / 16;
     const int64_t shared = V.k_ptr ? V.k_ptr[n + 1] - V.k_ptr[n] : 8;
     const uint64_t cost = uint64_t(ta * tb) * uint64_t((shared + 3) / 4) + uint64_t(ta * tb);      // + write-out
-    keys[n] = ~cost & 0xffffffffffull;                    // 40 bits are plenty; ascending sort = falling cost
+    // 40 bits are plenty; ascending sort = falling cost.  (Blocks that their mirror image writes come last.)
+    keys[n] = V.mirror && ra > rb ? 0xffffffffffull : ~cost & 0xffffffffffull;
     pair[n] = uint32_t(n);
+}
+// The node of (j,i) for every node (i,j), and which nodes (i <= j) have a workgroup of their own.
+__global__ void sppair4_mirror_kernel(P4Out V, int64_t roots, const int64_t *__restrict__ node_of, int32_t *mirror, int64_t *own) {
+    const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (n >= V.pairs) return;
+    mirror[n] = int32_t(node_of[int64_t(V.node_b[n]) * roots + V.node_a[n]]);
+    own[n] = V.node_a[n] <= V.node_b[n] ? 1 : 0;
 }
 __global__ void sppair4_order_fill_kernel(int64_t pairs, const uint32_t *__restrict__ sorted, int32_t *wg_pair) {
     const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -347,7 +370,7 @@ __global__ void sppair4_fill_minus1_kernel(int32_t *p, int64_t n) {
 
 // LDS of the numeric kernel
 struct P4NumLds {
-    int match_a, match_b, rowmask, nmask, rowleaf, rowrank, scratch, rowpre, achunk, bchunk, total;
+    int match_a, match_b, rowmask, nmask, rowleaf, rowrank, scratch, rowpre, achunk, bchunk, total, mirmask, mirpre;
 };
 
 // DENSE: the rows of the chunk matrices are copied from the operands' dense rows; otherwise they are
@@ -375,27 +398,46 @@ sppair4_kernel(P4Args A, P4Out V, P4NumLds O, double *__restrict__ out) {
     int n_shared;
     const int64_t *k_first = nullptr;       // kept by the plan: leaf range of every shared K, this wavefront's operand
     const int32_t *k_len = nullptr;
+    // One tensor under both names: V[j,i,n,m] = V[i,j,m,n], so the pairs with i < j write both blocks.
+    int32_t *mirpre = reinterpret_cast<int32_t *>(lds + O.mirpre);
+    uint32_t *mirmask = reinterpret_cast<uint32_t *>(lds + O.mirmask);
+    const bool mirrored = V.mirror && ra != rb;
+    int64_t mirleaf0 = 0;
     if (V.k_ptr) {
         const int64_t kp = V.k_ptr[node];
         n_shared = int(V.k_ptr[node + 1] - kp);
         k_first = (side ? V.k_b : V.k_a) + kp;
         k_len = (side ? V.k_blen : V.k_alen) + kp;
-        for (int x = threadIdx.x; x < n_ua * A.W; x += nthreads) rowmask[x] = V.masks[node * V.mask_stride + x];
-        __syncthreads();
+        const int32_t *pres = V.pres ? V.pres : reinterpret_cast<const int32_t *>(V.masks);   // (not kept: counted below)
+        for (int x = threadIdx.x; x < n_ua * A.W; x += nthreads) {
+            rowmask[x] = V.masks[node * V.mask_stride + x];
+            rowpre[x] = pres[node * V.mask_stride + x];
+        }
+        if (mirrored) {
+            const int64_t other = V.mirror[node];
+            mirleaf0 = V.ptr2[V.ptr1[other]];
+            for (int x = threadIdx.x; x < n_ub * A.W; x += nthreads) {
+                mirmask[x] = V.masks[other * V.mask_stride + x];
+                mirpre[x] = V.pres[other * V.mask_stride + x];
+            }
+        }
     } else {
         n_shared = p4_shared_k<kP4Waves>(A, ra, rb, match_a, match_b, A.max_common, scratch);
         p4_bit_matrix<kP4Waves>(A, match_a, match_b, n_shared, n_ua, rowmask, nmask);
     }
-    p4_row_offsets<kP4Waves>(A, rowmask, n_ua, rowleaf, rowrank);
-    n_shared = __builtin_amdgcn_readfirstlane(n_shared);
-    // position, within the pair's leaves, of the first stored element of every word of the bit matrix
-    for (int r = threadIdx.x; r < n_ua; r += nthreads) {
-        int at = rowleaf[r];
-        for (int w = 0; w < A.W; ++w) {
-            rowpre[r * A.W + w] = at;
-            at += __popc(rowmask[r * A.W + w]);
+    if (!V.pres) {
+        __syncthreads();
+        p4_row_offsets<kP4Waves>(A, rowmask, n_ua, rowleaf, rowrank);
+        // position, within the pair's leaves, of the first stored element of every word of the bit matrix
+        for (int r = threadIdx.x; r < n_ua; r += nthreads) {
+            int at = rowleaf[r];
+            for (int w = 0; w < A.W; ++w) {
+                rowpre[r * A.W + w] = at;
+                at += __popc(rowmask[r * A.W + w]);
+            }
         }
     }
+    n_shared = __builtin_amdgcn_readfirstlane(n_shared);
     __syncthreads();
 
     const int tiles_n = (n_ub + 15) >> 4;
@@ -538,6 +580,16 @@ sppair4_kernel(P4Args A, P4Out V, P4NumLds O, double *__restrict__ out) {
                                 out[leaf0 + rowpre[w] + __popc(word & ((1u << (n & 31)) - 1u))] = acc[x][y][v];
                         }
                     }
+                    if (mirrored && n < n_ub) {                        // row n of the mirror image: m0 .. m0 + 15 lie in one word
+                        const int w = n * A.W + (m0 >> 5);
+                        const uint32_t word = mirmask[w];
+                        double *to = out + mirleaf0 + mirpre[w];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int bit = (m0 & 16) + lk + 4 * v;    // (no bit is set from n_ua on)
+                            if ((word >> bit) & 1u) to[__popc(word & ((1u << bit) - 1u))] = acc[x][y][v];
+                        }
+                    }
                 }
         };
         using std::integral_constant;
@@ -601,6 +653,8 @@ static P4Out p4_out(const conststn_plan_s *plan) {
         o.k_ptr = plan->p4_k_ptr.p; o.k_a = plan->p4_k_a.p; o.k_b = plan->p4_k_b.p;
         o.k_alen = plan->p4_k_alen.p; o.k_blen = plan->p4_k_blen.p;
         o.masks = plan->p4_masks.p;
+        o.pres = plan->p4_pres.p;
+        o.mirror = plan->p4_mirrored ? plan->p4_mirror.p : nullptr;
         o.mask_stride = int64_t(plan->p4_max_ua) * plan->p4_words;
     }
     o.dense = plan->p4_dense ? 1 : 0;
@@ -668,13 +722,19 @@ conststn_status build_sppair4_tables(conststn_plan_s *plan) {
     L.achunk = int(at); at = up16(at + plan->p4_nbuf * 8 * int64_t(kP4Chunk) * plan->p4_mp);
     L.bchunk = int(at); at = up16(at + plan->p4_nbuf * 8 * int64_t(kP4Chunk) * plan->p4_np);
     L.total = int(at);
+    // the bit matrix of the mirror image, where one tensor stands under both names and there is room
+    L.mirmask = int(at); at = up16(at + 4 * int64_t(plan->p4_words) * max_ua);
+    L.mirpre = int(at); at = up16(at + 4 * int64_t(plan->p4_words) * max_ua);
+    const bool mirror = Ea == Eb && at <= 160 * 1024 && plan->opt("sppair4_xcd", 2) == 2;
+    if (mirror) L.total = int(at);
+    at = L.total;
     if (at > 160 * 1024) {
         set_error("the blocks of one (i,j) pair need %lld bytes of LDS (shared K up to %d, %lld x %lld distinct inner indices)",
                   (long long)at, plan->p4_max_common, (long long)max_ua, (long long)max_ub);
         return CONSTSTN_EUNSUPPORTED;
     }
-    const int lay[11] = {L.match_a, L.match_b, L.rowmask, L.nmask, L.rowleaf, L.rowrank, L.scratch, L.rowpre, L.achunk, L.bchunk, L.total};
-    plan->p4_layout.assign(lay, lay + 11);
+    const int lay[13] = {L.match_a, L.match_b, L.rowmask, L.nmask, L.rowleaf, L.rowrank, L.scratch, L.rowpre, L.achunk, L.bchunk, L.mirmask, L.mirpre, L.total};
+    plan->p4_layout.assign(lay, lay + 13);
     const P4SymLds S{L.match_a, L.match_b, L.rowmask, L.nmask, L.rowleaf, L.rowrank, L.scratch, int(sym_bytes)};
     CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sppair4_symbolic_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(sym_bytes)));
     CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sppair4_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, L.total));
@@ -723,6 +783,10 @@ conststn_status build_sppair4_tables(conststn_plan_s *plan) {
         CST_TRY(plan->p4_k_alen.alloc(size_t(total_k)));
         CST_TRY(plan->p4_k_blen.alloc(size_t(total_k)));
         CST_TRY(plan->p4_masks.alloc(size_t(mask_words)));
+        // (the elements ahead of every mask word too, unless they are too large: then every execute counts them)
+        if ((mask_words * 8 + total_k * 24) <= (plan->opt("sppair4_keep_gb", 4) << 30) &&
+            plan->p4_pres.alloc(size_t(mask_words)) != CONSTSTN_OK)
+            plan->p4_pres.release();
         CST_HIP(hipMemcpy(plan->p4_k_ptr.p + pairs, &total_k, sizeof(int64_t), hipMemcpyHostToDevice));
     }
     // Dense rows of the operands (rebuilt from the values by every execute) let the numeric pass copy the
@@ -771,6 +835,19 @@ conststn_status build_sppair4_tables(conststn_plan_s *plan) {
     sppair4_root_fill_kernel<<<p4_grid(pairs + 1), 256, 0, st>>>(A, O, rflag.p, root_of.p);
     CST_HIP(hipGetLastError());
     CST_HIP(hipStreamSynchronize(st));
+    // one tensor under both names: who writes whose block
+    int64_t own_pairs = pairs;
+    if (mirror && plan->p4_pres.p && pairs > 0) {
+        DevBuf<int64_t> own, own_at;
+        CST_TRY(own.alloc(size_t(pairs)));
+        CST_TRY(own_at.alloc(size_t(pairs)));
+        CST_TRY(plan->p4_mirror.alloc(size_t(pairs)));
+        sppair4_mirror_kernel<<<p4_grid(pairs), 256, 0, st>>>(O, Ea->nodes[0], node_of.p, plan->p4_mirror.p, own.p);
+        CST_HIP(hipGetLastError());
+        CST_TRY(exscan(own.p, own_at.p, pairs, &own_pairs));
+        plan->p4_mirrored = true;
+        O = p4_out(plan);
+    }
     // workgroup order of the numeric pass (pairs < 2^31: a pair holds at least one of the nnz < 2^31 leaves)
     plan->p4_n_wg = 0;
     if (pairs > 0 && plan->opt("sppair4_xcd", 2) == 2) {
@@ -786,7 +863,7 @@ conststn_status build_sppair4_tables(conststn_plan_s *plan) {
         const uint64_t *ks = nullptr;
         const uint32_t *ps = nullptr;
         CST_TRY(radix_sort_pairs_u64(ka.p, kb.p, pa.p, pb.p, pairs, 40, st, &ks, &ps));
-        plan->p4_n_wg = pairs;
+        plan->p4_n_wg = own_pairs;
         CST_TRY(plan->p4_wg_pair.alloc(size_t(pairs)));
         sppair4_order_fill_kernel<<<p4_grid(pairs), 256, 0, st>>>(pairs, ps, plan->p4_wg_pair.p);
         CST_HIP(hipGetLastError());
@@ -827,7 +904,7 @@ conststn_status launch_sppair4(const conststn_plan_s *plan, double *out, hipStre
     const P4Out O = p4_out(plan);
     if (O.pairs == 0) return CONSTSTN_OK;
     const std::vector<int> &l = plan->p4_layout;
-    const P4NumLds L{l[0], l[1], l[2], l[3], l[4], l[5], l[6], l[7], l[8], l[9], l[10]};
+    const P4NumLds L{l[0], l[1], l[2], l[3], l[4], l[5], l[6], l[7], l[8], l[9], l[12], l[10], l[11]};
     if (plan->p4_dense) {
         const int64_t n1a = plan->X->nodes[1], n1b = plan->W->nodes[1];
         const int cap_a = (plan->p4_max_ua + 15) / 16 * 16, cap_b = (plan->p4_max_ub + 15) / 16 * 16;

@@ -329,6 +329,9 @@ struct conststn_plan_s {
     cst::DevBuf<int64_t> p4_k_a, p4_k_b;                 // first leaf of each shared K's row in the two operands
     cst::DevBuf<int32_t> p4_k_alen, p4_k_blen;           // and its length
     cst::DevBuf<uint32_t> p4_masks;
+    cst::DevBuf<int32_t> p4_pres;                        // per word of the masks: the pair's stored elements ahead of it
+    bool p4_mirrored = false;                            // one tensor under both names: pairs i < j write (j,i) too
+    cst::DevBuf<int32_t> p4_mirror;                      // node of (j,i) per node (i,j)
     cst::DevBuf<int32_t> p4_wg_pair;                     // workgroup -> (i,j) node of the numeric pass (-1: none)
     int64_t p4_n_wg = 0;
     int p4_nbuf = 2;                                     // chunk buffers per matrix in LDS

@@ -179,3 +179,23 @@ def test_empty_operand():
     dims = (5, 4, 6)
     (ci, cj, cm, cn), vals, _ = _run([np.zeros(0, dtype=np.int64)] * 3, np.zeros(0), dims)
     assert vals.size == 0
+
+
+@pytest.mark.parametrize("n_i,n_m,n_K", [(1, 5, 9), (2, 16, 8), (3, 33, 7), (5, 100, 30), (4, 200, 17)])
+def test_one_tensor_under_both_names_equals_two(n_i, n_m, n_K):
+    """V[j,i,n,m] = V[i,j,m,n] where both names are one handle: the blocks below the diagonal are written by those above.
+    The general form (a second handle of the same tensor) adds the same products in the same order."""
+    dims = (n_K, n_i, n_m)
+    Ec, Ev = _rand_e(5200 + n_m, dims, max(1, int(0.3 * n_K * n_i * n_m)))
+    _say("one tensor under both names: K,i,m = %s" % (dims,))
+    one, v1, _ = _run(Ec, Ev, dims)
+    two, v2, _ = _run(Ec, Ev, dims, Ec, Ev, dims)
+    for a, b in zip(one, two):
+        np.testing.assert_array_equal(a, b)
+    np.testing.assert_array_equal(v1, v2)
+    for opts in ({"sppair4_xcd": 0}, {"sppair4_rows": 2}, {"sppair4_keep": 2}):
+        np.testing.assert_array_equal(_run(Ec, Ev, dims, options=opts)[1], v1)
+    want, S_abs, _ = spsp.pair4(Ec, Ev, dims)
+    G = np.zeros_like(want)
+    G[one] = v1
+    assert oracle.rel_err(G, want, S_abs) <= TOL
