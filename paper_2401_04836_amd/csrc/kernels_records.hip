@@ -37,6 +37,10 @@ namespace {
 constexpr uint32_t kRecFiberEnd = 1u << 30, kRecNodeEnd = 2u << 30, kRecNothing = 3u << 30, kRecSliceEnd = 1u << 29,
                    kRecIndex = (1u << 28) - 1;
 constexpr uint32_t kChunkInside = 1u << 31;           // the chunk begins inside its first slice
+// Chunks of up to so many records take the SHORT instances (the plan gives small tensors chunks of 32): with the fix-up's
+// 16-byte descriptors 14.6 -> 13.7 us at 33 K nonzeros, rank 50; 29.5 -> 27.6 at 384 K, rank 64.  At 512 records the wait at
+// the end is one of 512 steps, and the registers that hold the rows cost a wavefront per SIMD at some ranks.
+constexpr int kRecShort = 64;
 
 typedef double v2f64_u __attribute__((ext_vector_type(2), aligned(8)));
 typedef double v2f64 __attribute__((ext_vector_type(2)));
@@ -70,7 +74,9 @@ __device__ __forceinline__ void each(std::integer_sequence<int, I...>, F &&f) {
     (f(std::integral_constant<int, I>{}), ...);
 }
 
-template <int LPR, int NV, int LEVELS>
+// SHORT: chunks of few records, whose time is the chain of loads from the first to the last: the rows that the chunk leaves
+// open are fetched at its start.
+template <int LPR, int NV, int LEVELS, bool SHORT>
 __global__ void __launch_bounds__(256)
 records_kernel(RecordArgs a) {
     constexpr int U = NV == 1 ? 8 : 4;                 // rows in flight per lane group
@@ -116,6 +122,20 @@ records_kernel(RecordArgs a) {
         ++s;
         row = a.row_of_slice[min(s, a.slices - 1)];
     };
+
+    // what the chunk leaves open behind it, and the rows of that
+    int32_t o1, o2 = -1;
+    v2f64 r1[NV], r2[NV];
+    auto fetch_open = [&]() {
+        o1 = a.open1[c];
+        if (LEVELS == 3) o2 = a.open2[c];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            r1[v] = *reinterpret_cast<const v2f64_u *>(a.f1 + int64_t(max(o1, 0)) * R + col[v]);
+            if (LEVELS == 3) r2[v] = *reinterpret_cast<const v2f64_u *>(a.f2 + int64_t(max(o2, 0)) * R + col[v]);
+        }
+    };
+    if (SHORT) fetch_open();
 
     const int blocks = a.q / LPR;
     uint32_t code_cur = code[gl], code_nxt = code[(blocks > 1 ? LPR : 0) + gl];
@@ -190,23 +210,21 @@ records_kernel(RecordArgs a) {
         val_nxt = val_n2;
     }
     // the chunk may end inside a fiber, a node and a slice: their sums so far count with the rows still to come
-    const int32_t o1 = a.open1[c], o2 = LEVELS == 3 ? a.open2[c] : -1;
+    if (!SHORT) fetch_open();
     if (o1 >= 0) {
-        const double *r1 = a.f1 + int64_t(o1) * R;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                if (LEVELS == 3) u[v][e] = fma(t[v][e], r1[col[v] + e], u[v][e]);
-                else acc[v][e] = fma(t[v][e], r1[col[v] + e], acc[v][e]);
+                if (LEVELS == 3) u[v][e] = fma(t[v][e], r1[v][e], u[v][e]);
+                else acc[v][e] = fma(t[v][e], r1[v][e], acc[v][e]);
             }
     }
     if (LEVELS == 3 && o2 >= 0) {
-        const double *r2 = a.f2 + int64_t(o2) * R;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) acc[v][e] = fma(u[v][e], r2[col[v] + e], acc[v][e]);
+            for (int e = 0; e < 2; ++e) acc[v][e] = fma(u[v][e], r2[v][e], acc[v][e]);
     }
     if (s < a.slices) emit(false);
 }
@@ -218,17 +236,17 @@ records_kernel(RecordArgs a) {
 constexpr int kRecLight = 32, kRecOneBlock = 1024, kRecSegments = 32;
 
 struct RecordFixArgs {
-    int R, q, segments;
+    int R, segments;
     int64_t n_heavy, n_light, n_empty, heavy_blocks, light_blocks;
-    const int32_t *heavy, *light, *empty, *row_of_slice;
-    const int64_t *slice_rec;
+    const RecordShare *heavy, *light;
+    const int32_t *empty;
     const double *partial;
     double *heavy_partial, *out;
 };
 
-// partial row of slice [lo, ...) in chunk c: the second one where the slice begins inside the chunk
-__device__ __forceinline__ int64_t partial_row(int64_t c, int64_t ca, int64_t lo, int q) {
-    return 2 * c + ((c == ca && lo != ca * q) ? 1 : 0);
+// partial row of a slice in its c-th chunk: the second one of the first chunk where the slice begins inside it
+__device__ __forceinline__ int64_t partial_row(const RecordShare &s, int64_t c) {
+    return c == 0 ? s.first : (s.first & ~int64_t(1)) + 2 * c;
 }
 
 template <int W, int THREADS>
@@ -241,26 +259,25 @@ records_fixup_kernel(RecordFixArgs a) {
     int64_t b = blockIdx.x;
     if (b < a.heavy_blocks) {
         const int64_t h = b / a.segments, seg = b % a.segments;
-        const int64_t s = a.heavy[h], lo = a.slice_rec[s], hi = a.slice_rec[s + 1];
-        const int64_t ca = lo / a.q, cb = (hi - 1) / a.q, n = cb - ca + 1;
-        const int64_t c0 = ca + n * seg / a.segments, c1 = ca + n * (seg + 1) / a.segments;
+        const RecordShare s = a.heavy[h];
+        const int64_t n = s.count, c0 = n * seg / a.segments, c1 = n * (seg + 1) / a.segments;
         double sum = 0.0;
         if (mine) {
             int64_t c = c0 + g;
             for (; c + 7 * G < c1; c += 8 * G) {
                 double x[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) x[k] = a.partial[partial_row(c + k * G, ca, lo, a.q) * R + col];
+                for (int k = 0; k < 8; ++k) x[k] = a.partial[partial_row(s, c + k * G) * R + col];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) sum += x[k];
             }
-            for (; c < c1; c += G) sum += a.partial[partial_row(c, ca, lo, a.q) * R + col];
+            for (; c < c1; c += G) sum += a.partial[partial_row(s, c) * R + col];
         }
         red[threadIdx.x] = sum;
         __syncthreads();
         if (g == 0 && mine) {
             for (int gg = 1; gg < G; ++gg) sum += red[gg * W + col];
-            if (a.segments == 1) a.out[int64_t(a.row_of_slice[s]) * R + col] = sum;
+            if (a.segments == 1) a.out[int64_t(s.row) * R + col] = sum;
             else a.heavy_partial[(h * a.segments + seg) * R + col] = sum;
         }
         return;
@@ -269,19 +286,19 @@ records_fixup_kernel(RecordFixArgs a) {
     if (b < a.light_blocks) {
         const int64_t k = b * G + g;
         if (k >= a.n_light || !mine) return;
-        const int64_t s = a.light[k], lo = a.slice_rec[s], hi = a.slice_rec[s + 1];
-        const int64_t ca = lo / a.q, cb = (hi - 1) / a.q;
-        double sum = a.partial[partial_row(ca, ca, lo, a.q) * R + col];
-        int64_t c = ca + 1;
-        for (; c + 3 <= cb; c += 4) {
+        const RecordShare s = a.light[k];
+        double sum = a.partial[partial_row(s, 0) * R + col];
+        const double *x0 = a.partial + (s.first & ~int64_t(1)) * R + col;
+        int64_t c = 1;
+        for (; c + 4 <= s.count; c += 4) {
             double x[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = a.partial[2 * (c + e) * R + col];
+            for (int e = 0; e < 4; ++e) x[e] = x0[2 * (c + e) * R];
 #pragma unroll
             for (int e = 0; e < 4; ++e) sum += x[e];
         }
-        for (; c <= cb; ++c) sum += a.partial[2 * c * R + col];
-        a.out[int64_t(a.row_of_slice[s]) * R + col] = sum;
+        for (; c < s.count; ++c) sum += x0[2 * c * R];
+        a.out[int64_t(s.row) * R + col] = sum;
         return;
     }
     b -= a.light_blocks;
@@ -297,7 +314,7 @@ records_final_kernel(RecordFixArgs a) {
     double sum = 0.0;
 #pragma unroll 8
     for (int seg = 0; seg < kRecSegments; ++seg) sum += a.heavy_partial[(h * kRecSegments + seg) * a.R + col];
-    a.out[int64_t(a.row_of_slice[a.heavy[h]]) * a.R + col] = sum;
+    a.out[int64_t(a.heavy[h].row) * a.R + col] = sum;
 }
 
 // ---- the plan's side ------------------------------------------------------------------------------------
@@ -460,6 +477,15 @@ __global__ void __launch_bounds__(256)
 list_flagged_kernel(int64_t n, const int64_t *__restrict__ flag, const int64_t *__restrict__ pos, int32_t *list) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i < n && flag[i]) list[pos[i]] = int32_t(i);
+}
+// what the fix-up launch needs of the listed slices, in one 16-byte read
+__global__ void __launch_bounds__(256)
+record_shares_kernel(int64_t n, const int32_t *__restrict__ list, const int64_t *__restrict__ slice_rec, const int32_t *__restrict__ row_of_slice,
+                     int64_t q, RecordShare *share) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int64_t s = list[i], lo = slice_rec[s], hi = slice_rec[s + 1], first = lo / q;
+    share[i] = RecordShare{2 * first + (lo != first * q ? 1 : 0), int32_t((hi - 1) / q - first + 1), row_of_slice[s]};
 }
 __global__ void __launch_bounds__(256)
 empty_rows_kernel(int64_t rows, int64_t slices, const int32_t *__restrict__ idx0, int64_t *flag) {
@@ -727,6 +753,11 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     record_shared_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, rs.slice_rec.p, q, 2, flag.p, widest.p);
     CST_HIP(hipGetLastError());
     CST_TRY(list_of_flags(flag, a.slices, rs.heavy, &rs.n_heavy));
+    CST_TRY(rs.heavy_share.alloc(size_t(rs.n_heavy)));
+    CST_TRY(rs.light_share.alloc(size_t(rs.n_light)));
+    record_shares_kernel<<<blocks_for(rs.n_heavy), dim3(256)>>>(rs.n_heavy, rs.heavy.p, rs.slice_rec.p, rs.row_of_slice.p, q, rs.heavy_share.p);
+    record_shares_kernel<<<blocks_for(rs.n_light), dim3(256)>>>(rs.n_light, rs.light.p, rs.slice_rec.p, rs.row_of_slice.p, q, rs.light_share.p);
+    CST_HIP(hipGetLastError());
     int span = 0;
     CST_HIP(hipMemcpy(&span, widest.p, sizeof(int), hipMemcpyDeviceToHost));
     rs.segments = span > kRecOneBlock ? kRecSegments : 1;
@@ -735,15 +766,15 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     return CONSTSTN_OK;
 }
 
-template <int LEVELS>
+template <int LEVELS, bool SHORT>
 static void launch_records_kernel(const RecordArgs &a, hipStream_t stream) {
     const int lanes = a.R <= 16 ? 8 : 16;
     const dim3 grid(unsigned(div_up(a.n_chunks, 256 / lanes))), block(256);
-    if (a.R <= 16) records_kernel<8, 1, LEVELS><<<grid, block, 0, stream>>>(a);
-    else if (a.R <= 32) records_kernel<16, 1, LEVELS><<<grid, block, 0, stream>>>(a);
-    else if (a.R <= 64) records_kernel<16, 2, LEVELS><<<grid, block, 0, stream>>>(a);
-    else if (a.R <= 96) records_kernel<16, 3, LEVELS><<<grid, block, 0, stream>>>(a);
-    else records_kernel<16, 4, LEVELS><<<grid, block, 0, stream>>>(a);
+    if (a.R <= 16) records_kernel<8, 1, LEVELS, SHORT><<<grid, block, 0, stream>>>(a);
+    else if (a.R <= 32) records_kernel<16, 1, LEVELS, SHORT><<<grid, block, 0, stream>>>(a);
+    else if (a.R <= 64) records_kernel<16, 2, LEVELS, SHORT><<<grid, block, 0, stream>>>(a);
+    else if (a.R <= 96) records_kernel<16, 3, LEVELS, SHORT><<<grid, block, 0, stream>>>(a);
+    else records_kernel<16, 4, LEVELS, SHORT><<<grid, block, 0, stream>>>(a);
 }
 
 conststn_status launch_record_stream(const conststn_plan_s *plan, const double *const *dense, double *out, hipStream_t stream) {
@@ -769,22 +800,25 @@ conststn_status launch_record_stream(const conststn_plan_s *plan, const double *
     if (rs.zero_all) CST_TRY(zero_fill(out, plan->out_rows * plan->row_elems, stream));
     if (rs.n_chunks > 0) {
         ProfScope prof(plan, stream);
-        if (rs.levels == 3) launch_records_kernel<3>(a, stream);
-        else launch_records_kernel<2>(a, stream);
+        const bool small = rs.q <= kRecShort;
+        if (rs.levels == 3) {
+            if (small) launch_records_kernel<3, true>(a, stream);
+            else launch_records_kernel<3, false>(a, stream);
+        } else {
+            if (small) launch_records_kernel<2, true>(a, stream);
+            else launch_records_kernel<2, false>(a, stream);
+        }
         CST_HIP(hipGetLastError());
     }
     RecordFixArgs f{};
     f.R = a.R;
-    f.q = a.q;
     f.segments = rs.segments;
     f.n_heavy = rs.n_heavy;
     f.n_light = rs.n_light;
     f.n_empty = rs.n_empty;
-    f.heavy = rs.heavy.p;
-    f.light = rs.light.p;
+    f.heavy = rs.heavy_share.p;
+    f.light = rs.light_share.p;
     f.empty = rs.empty.p;
-    f.row_of_slice = rs.row_of_slice.p;
-    f.slice_rec = rs.slice_rec.p;
     f.partial = rs.partial.p;
     f.heavy_partial = rs.heavy_partial.p;
     f.out = out;
