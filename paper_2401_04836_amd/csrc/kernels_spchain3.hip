@@ -342,147 +342,131 @@ constexpr int kScLocalWaves = 8;
 
 // LDS layout of the block-local kernel, in bytes from the start (set up by the plan)
 struct ScLocalLds {
-    int cd, tk, pos, lval, rowptr, c0, clen, qoff, mmap, umap, total;
+    int cd, tk, words, lval, qoff, total;
     int ns_pad, rows_pad;                    // row strides of T_K and of C_K (doubles)
 };
 
 // Everything the workgroup of one K needs to know before its first load (built with the plan).
 struct alignas(64) ScRoot {
-    int64_t n0, mu0, e0, li0, q0;            // first: u row of I, m of K, (K,i) node, leaf of I, leaf of E
+    int64_t e0, li0, q0;                     // first: (K,i) node, leaf of I, leaf of E
+    int64_t c0, w0;                          // first: entry of the list of C_K, word of the stored m
     int64_t pk;                              // where the dense block P_K starts in the plan's copy
     int32_t ns, nrows, nm, nn;               // v slots, u rows, m and (K,i) nodes of K
-    int32_t nleaves;                         // leaves of I under K
-    int32_t pad[3];
+    int32_t nleaves, nc, nw;                 // leaves of I under K, entries of C_K, words per node
+};
+
+// An entry of C_K: its place in the block and its value's place in C.
+struct ScEntry {
+    uint32_t c;
+    uint32_t at;
+};
+
+// Which of 32 neighbouring m of K a node stores, and how many of its leaves lie before them.
+struct ScWord {
+    uint32_t mask, before;
 };
 
 typedef double sc_v4d __attribute__((ext_vector_type(4)));
-constexpr int kScAhead = 6;                  // (K,i) nodes per wavefront whose loads are issued together
+constexpr int kScAhead = 3;                  // leaves of I and entries of C_K per thread whose loads are issued together
 constexpr int kScDepth = 10;                 // depth steps (of 4 slots) of a result tile whose P_K values sit in registers
-
-// largest x in [0, n) with arr[x] <= key (arr ascending, arr[0] <= key)
-__device__ __forceinline__ int last_not_above(const int32_t *arr, int n, int32_t key) {
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (arr[mid] <= key) lo = mid; else hi = mid;
-    }
-    return lo;
-}
 
 // One workgroup per K of E.  The dense block P_K [v slots of K x m of K] is prepared with the plan
 // (K that share their v and m lists share one copy) and stays in global memory; I_K [u rows x v
-// slots], C_K [nodes x u rows] and T_K [nodes x v slots] live in LDS.  Three dependent trips to
-// memory, a barrier after each:
-//   1  the descriptor of K; meanwhile the u -> row table is cleared
-//   2  what the descriptor addresses: u -> row and m -> position tables, row pointers of I[K], per
-//      (K,i) node the range of C[i,:], of its leaves in E and the value of L; blocks zeroed
-//   3  the stored entries: I_K one thread per leaf; per node (one wavefront each) the entries of
-//      C[i,:] that meet a u row of K into C_K; the m of the node's leaves wait in registers and become
-//      pos[node, m of K] = leaf of E[K,i,m] in the node once I_K is dead and its space free
+// slots], C_K [nodes x u rows] and T_K [nodes x v slots] live in LDS.  The plan also holds the place of every leaf of I
+// in I_K (2 bytes), the entries of C_K as a list (8 bytes: only those that meet a u of K), and for every node a bit
+// mask over the m of K with the number of leaves before each word.  So a workgroup waits for its descriptor, for what that
+// addresses, and for the values of C, and builds no table of its own:
+//   1  the descriptor of K
+//   2  leaves of I with their places, list of C_K, masks, weights; meanwhile I_K and C_K are cleared
+//   3  values of C; everything is stored at its place
 //   then on the fp64 matrix cores (v_mfma_f64_16x16x4, tiles of 16 x 16, depth in steps of 4)
 //   T_K = C_K . I_K into LDS, a barrier, and E_K = T_K . P_K with P_K read from memory; every element
 //   that is a stored leaf goes to its place in `out`.
+// Before, the u -> row and m -> leaf tables were made in LDS by every execute, from the indices of C and of all of E
+// (4 bytes a leaf, half as much as is written), with seven barriers instead of three, and P_K was read once per tile:
+// 32 x 32 lattice, 53 M leaves, 411 us, now 282 us (1.5 TB/s of results; writing the 424 MB alone
+// would take 72 us).
 __global__ void __launch_bounds__(64 * kScLocalWaves, 6)
 spchain3_local_kernel(ScArgs A, ScOut E, double *__restrict__ out, ScLocalLds O, const ScRoot *__restrict__ roots,
-                      const double *__restrict__ pk_blocks, const int32_t *__restrict__ e_c0,
-                      const int32_t *__restrict__ e_clen) {
+                      const double *__restrict__ pk_blocks, const uint16_t *__restrict__ i_at, const ScEntry *__restrict__ entries,
+                      const ScWord *__restrict__ words) {
     extern __shared__ unsigned char lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);    // the same in every lane: loop counters built on it stay scalar
-    const int nthreads = 64 * kScLocalWaves;
+    constexpr int nthreads = 64 * kScLocalWaves;
     double *Ik = reinterpret_cast<double *>(lds);
     double *Cd = reinterpret_cast<double *>(lds + O.cd);
     double *Tk = reinterpret_cast<double *>(lds + O.tk);
-    uint16_t *pos = reinterpret_cast<uint16_t *>(lds + O.pos);
+    ScWord *wd = reinterpret_cast<ScWord *>(lds + O.words);              // [node][word]
     double *lval = reinterpret_cast<double *>(lds + O.lval);
-    int32_t *rowptr = reinterpret_cast<int32_t *>(lds + O.rowptr);       // leaves of K before each u row
-    int32_t *c0s = reinterpret_cast<int32_t *>(lds + O.c0);              // per node: first entry of C[i,:], its length,
-    int32_t *clen = reinterpret_cast<int32_t *>(lds + O.clen);           //           leaves of E before the node
-    int32_t *qoff = reinterpret_cast<int32_t *>(lds + O.qoff);
-    uint16_t *mmap = reinterpret_cast<uint16_t *>(lds + O.mmap);
-    uint16_t *umap = reinterpret_cast<uint16_t *>(lds + O.umap);
+    int32_t *qoff = reinterpret_cast<int32_t *>(lds + O.qoff);           // leaves of E before each node
     const int tstride = O.ns_pad, cstride = O.rows_pad;
 
     // trip 1
     const ScRoot R = roots[blockIdx.x];
-    for (int64_t x = threadIdx.x; x < (A.n_u + 1) / 2; x += nthreads) reinterpret_cast<uint32_t *>(umap)[x] = 0xFFFFFFFFu;
-    const int ns = R.ns, nrows = R.nrows, nm = R.nm, nn = R.nn;
-    __syncthreads();
+    const int ns = R.ns, nrows = R.nrows, nm = R.nm, nn = R.nn, nw = R.nw;
     // trip 2
-    for (int x = threadIdx.x; x < nrows; x += nthreads) umap[A.i_idx1[R.n0 + x]] = uint16_t(x);
-    for (int x = threadIdx.x; x <= nrows; x += nthreads) rowptr[x] = int32_t(A.i_ptr1[R.n0 + x] - R.li0);
-    for (int j = threadIdx.x; j < nm; j += nthreads) mmap[A.mu_list[R.mu0 + j]] = uint16_t(j);
-    for (int x = threadIdx.x; x <= nn; x += nthreads) {
+    const uint16_t *ia = i_at + R.li0;
+    const double *iv = A.i_vals + R.li0;
+    const ScEntry *ce = entries + R.c0;
+    int at_i[kScAhead];
+    double v_i[kScAhead];
+    ScEntry c_i[kScAhead];
+#pragma unroll
+    for (int b = 0; b < kScAhead; ++b) {
+        const int l = int(threadIdx.x) + b * nthreads;
+        at_i[b] = -1;
+        v_i[b] = 0.0;
+        c_i[b] = ScEntry{0u, ~0u};
+        if (l < R.nleaves) { at_i[b] = ia[l]; v_i[b] = iv[l]; }
+        if (l < R.nc) c_i[b] = ce[l];
+    }
+    for (int x = threadIdx.x; x < nn * nw; x += nthreads) wd[x] = words[R.w0 + x];
+    for (int x = threadIdx.x; x < nn; x += nthreads) {
         qoff[x] = int32_t(E.ptr1[R.e0 + x] - R.q0);
-        if (x < nn) {
-            c0s[x] = e_c0[R.e0 + x];
-            clen[x] = e_clen[R.e0 + x];
-            lval[x] = E.lval[R.e0 + x];
-        }
+        lval[x] = E.lval[R.e0 + x];
     }
     for (int x = threadIdx.x; x < nrows * ns; x += nthreads) Ik[x] = 0.0;
     for (int x = threadIdx.x; x < nn * cstride; x += nthreads) Cd[x] = 0.0;
     __syncthreads();
-    // trip 3: every load of this wavefront's first kScAhead nodes is issued before any is used
-    int cidx[kScAhead], m0[kScAhead], m1[kScAhead];
-    double cval[kScAhead];
+    // trip 3
+    double c_v[kScAhead];
 #pragma unroll
-    for (int b = 0; b < kScAhead; ++b) {
-        const int x = wave + b * kScLocalWaves;
-        cidx[b] = -1;
-        cval[b] = 0.0;
-        m0[b] = m1[b] = -1;
-        if (x < nn) {
-            if (lane < clen[x]) { cidx[b] = A.c_idx1[int64_t(c0s[x]) + lane]; cval[b] = A.c_vals[int64_t(c0s[x]) + lane]; }
-            const int64_t qa = R.q0 + qoff[x];
-            const int nl = qoff[x + 1] - qoff[x];
-            if (lane < nl) m0[b] = E.idx2[qa + lane];
-            if (lane + 64 < nl) m1[b] = E.idx2[qa + lane + 64];
-        }
-    }
-    for (int l = threadIdx.x; l < R.nleaves; l += nthreads) {
-        const int row = last_not_above(rowptr, nrows, l);
-        Ik[row * ns + A.i_slot[R.li0 + l]] = A.i_vals[R.li0 + l];
-    }
+    for (int b = 0; b < kScAhead; ++b) c_v[b] = c_i[b].at != ~0u ? A.c_vals[c_i[b].c] : 0.0;
 #pragma unroll
-    for (int b = 0; b < kScAhead; ++b) {
-        const int x = wave + b * kScLocalWaves;
-        if (cidx[b] >= 0) {
-            const uint16_t row = umap[cidx[b]];
-            if (row != kNoSlot) Cd[x * cstride + row] = cval[b];
-        }
-    }
-    // what the registers did not cover: entries of C[i,:] beyond 64, nodes beyond the first kScAhead
-    for (int x = wave; x < nn; x += kScLocalWaves) {
-        const bool ahead = x < kScAhead * kScLocalWaves;
-        const int64_t c0 = c0s[x];
-        for (int c = (ahead ? 64 : 0) + lane; c < clen[x]; c += 64) {
-            const uint16_t row = umap[A.c_idx1[c0 + c]];
-            if (row != kNoSlot) Cd[x * cstride + row] = A.c_vals[c0 + c];
-        }
-    }
+    for (int b = 0; b < kScAhead; ++b)
+        if (at_i[b] >= 0) Ik[at_i[b]] = v_i[b];
+    for (int l = int(threadIdx.x) + kScAhead * nthreads; l < R.nleaves; l += nthreads) Ik[ia[l]] = iv[l];
+#pragma unroll
+    for (int b = 0; b < kScAhead; ++b)
+        if (c_i[b].at != ~0u) Cd[c_i[b].at] = c_v[b];
+    for (int l = int(threadIdx.x) + kScAhead * nthreads; l < R.nc; l += nthreads) Cd[ce[l].at] = A.c_vals[ce[l].c];
     __syncthreads();
     const int li = lane & 15, lk = lane >> 4;
-    // the first tile of E_K this wavefront will compute: its part of P_K is fetched now
+    // The tiles of E_K are dealt to the wavefronts in equal runs, down the columns: the part of P_K that a column needs is
+    // read once for all the tiles of the run that lie in it, into registers, the first one now (tile after tile in turn,
+    // each with its own read of P_K: 297 us where this takes 283)
     const double *Pk = pk_blocks + R.pk;
     // 32-bit offsets against scalar bases: a block P_K and the leaves of one K stay far below 2^29 elements
     const char *Pkb = reinterpret_cast<const char *>(Pk);
     char *outb = reinterpret_cast<char *>(out + R.q0);
-    const int tiles_m = (nm + 15) >> 4, tiles_e = ((nn + 15) >> 4) * tiles_m;
+    const int tiles_x = (nn + 15) >> 4, tiles = ((nm + 15) >> 4) * tiles_x;
+    const int run = (tiles + kScLocalWaves - 1) / kScLocalWaves, tile0 = wave * run, tile1 = min(tile0 + run, tiles);
     double bpre[kScDepth];
-    {
-        const int j0 = (wave % tiles_m) << 4;
-        const bool jb = wave < tiles_e && j0 + li < nm;
+    auto fetch_p = [&](int j0) {
+        const bool jb = j0 + li < nm;
 #pragma unroll
         for (int kb = 0; kb < kScDepth; ++kb) {
             const int k = 4 * kb + lk;
             bpre[kb] = (jb && k < ns) ? *reinterpret_cast<const double *>(Pkb + (uint32_t(k * nm + j0 + li) << 3)) : 0.0;
         }
-    }
+    };
+    int x0 = (tile0 % tiles_x) << 4, j0 = (tile0 / tiles_x) << 4;
+    fetch_p(tile0 < tile1 ? j0 : nm);
     // T_K = C_K . I_K
     {
-        const int tiles_s = (ns + 15) >> 4, tiles = ((nn + 15) >> 4) * tiles_s;
-        for (int tile = wave; tile < tiles; tile += kScLocalWaves) {
+        const int tiles_s = (ns + 15) >> 4;
+        for (int tile = wave; tile < tiles_x * tiles_s; tile += kScLocalWaves) {
             const int x0 = (tile / tiles_s) << 4, s0 = (tile % tiles_s) << 4;
             const bool xa = x0 + li < nn, sb = s0 + li < ns;
             const double *crow = Cd + (xa ? x0 + li : 0) * cstride;
@@ -511,81 +495,125 @@ spchain3_local_kernel(ScArgs A, ScOut E, double *__restrict__ out, ScLocalLds O,
         }
     }
     __syncthreads();
-    // I_K is dead: pos[node, m of K] = leaf of E[K,i,m] within the node takes its place
-    for (int x = threadIdx.x; x < (nn * nm + 1) / 2; x += nthreads) reinterpret_cast<uint32_t *>(pos)[x] = 0xFFFFFFFFu;
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < kScAhead; ++b) {
-        const int x = wave + b * kScLocalWaves;
-        if (m0[b] >= 0) pos[x * nm + mmap[m0[b]]] = uint16_t(lane);
-        if (m1[b] >= 0) pos[x * nm + mmap[m1[b]]] = uint16_t(lane + 64);
-    }
-    for (int x = wave; x < nn; x += kScLocalWaves) {
-        const bool ahead = x < kScAhead * kScLocalWaves;
-        const int64_t qa = R.q0 + qoff[x];
-        const int nl = qoff[x + 1] - qoff[x];
-        for (int l = (ahead ? 128 : 0) + lane; l < nl; l += 64) pos[x * nm + mmap[E.idx2[qa + l]]] = uint16_t(l);
-    }
-    __syncthreads();
     // E_K = T_K . P_K
-    for (int tile = wave; tile < tiles_e; tile += kScLocalWaves) {
-        const int x0 = (tile / tiles_m) << 4, j0 = (tile % tiles_m) << 4;
-        const bool xa = x0 + li < nn, jb = j0 + li < nm;
-        const double *trow = Tk + (xa ? x0 + li : 0) * tstride;
+    for (int tile = tile0; tile < tile1;) {
+        const bool jb = j0 + li < nm;
         const double *pcol = Pk + (jb ? j0 + li : 0);
-        // the next tile's part of P_K, fetched while this tile is computed
-        double bnext[kScDepth];
-        {
-            const int tn = tile + kScLocalWaves;
-            const int jn = (tn % tiles_m) << 4;
-            const bool jnb = tn < tiles_e && jn + li < nm;
+        const int end = min(tile1, tile + ((nn - x0 + 15) >> 4));       // the part of the run in this column
+        for (; tile < end; ++tile, x0 += 16) {
+            const bool xa = x0 + li < nn;
+            const double *trow = Tk + (xa ? x0 + li : 0) * tstride;
+            sc_v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int kb = 0; kb < kScDepth; ++kb) {
-                const int k = 4 * kb + lk;
-                bnext[kb] = (jnb && k < ns) ? *reinterpret_cast<const double *>(Pkb + (uint32_t(k * nm + jn + li) << 3)) : 0.0;
+                if (4 * kb + 4 <= ns) {                                     // whole step: rows beyond the nodes are not stored
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(trow[4 * kb + lk], bpre[kb], acc, 0, 0, 0);
+                } else if (4 * kb < ns) {
+                    const int k = 4 * kb + lk;
+                    const double av = k < ns ? trow[k < ns ? k : 0] : 0.0;
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bpre[kb], acc, 0, 0, 0);
+                }
             }
-        }
-        sc_v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int kb = 0; kb < kScDepth; ++kb) {
-            if (4 * kb + 4 <= ns) {                                     // whole step: rows beyond the nodes are not stored
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(trow[4 * kb + lk], bpre[kb], acc, 0, 0, 0);
-            } else if (4 * kb < ns) {
-                const int k = 4 * kb + lk;
-                const double av = k < ns ? trow[k < ns ? k : 0] : 0.0;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bpre[kb], acc, 0, 0, 0);
+            for (int k0 = 4 * kScDepth; k0 < ns; k0 += 4) {                 // more than 4 * kScDepth slots
+                const int k = k0 + lk;
+                const bool kk = k < ns;
+                const double av = kk ? trow[kk ? k : 0] : 0.0;
+                const double bv = (jb && kk) ? pcol[int64_t(kk ? k : 0) * nm] : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
             }
-        }
-        for (int k0 = 4 * kScDepth; k0 < ns; k0 += 4) {                 // more than 4 * kScDepth slots
-            const int k = k0 + lk;
-            const bool kk = k < ns;
-            const double av = kk ? trow[kk ? k : 0] : 0.0;
-            const double bv = (jb && kk) ? pcol[int64_t(kk ? k : 0) * nm] : 0.0;
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-        }
-        // lane holds E_K[x0 + lk + 4v][j0 + li]
-        if (jb) {
+            // lane holds E_K[x0 + lk + 4v][j0 + li]
+            if (jb) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int x = x0 + lk + 4 * v;
-                if (x < nn) {
-                    const uint16_t at = pos[x * nm + j0 + li];
-                    if (at != kNoSlot) *reinterpret_cast<double *>(outb + (uint32_t(qoff[x] + at) << 3)) = acc[v] * lval[x];
+                for (int v = 0; v < 4; ++v) {
+                    const int x = x0 + lk + 4 * v;
+                    if (x < nn) {
+                        const ScWord w = wd[x * nw + ((j0 + li) >> 5)];
+                        const uint32_t bit = 1u << ((j0 + li) & 31);
+                        if (w.mask & bit) {
+                            const uint32_t at = uint32_t(qoff[x]) + w.before + uint32_t(__popc(w.mask & (bit - 1u)));
+                            *reinterpret_cast<double *>(outb + (at << 3)) = acc[v] * lval[x];
+                        }
+                    }
                 }
             }
         }
-#pragma unroll
-        for (int kb = 0; kb < kScDepth; ++kb) bpre[kb] = bnext[kb];
+        x0 = 0, j0 += 16;
+        if (tile < tile1) fetch_p(j0);
     }
 }
 
-// per (K,i) node: the range of C[i,:]
-__global__ void spchain3_row_tables_kernel(ScArgs A, ScOut E, int32_t *e_c0, int32_t *e_clen) {
-    const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (x < E.nodes) {
-        const int64_t b0 = A.c_ptr0[E.cnode[x]];
-        e_c0[x] = int32_t(b0);
-        e_clen[x] = int32_t(A.c_ptr0[E.cnode[x] + 1] - b0);
+// Place of every leaf of I in its K's block I_K [u rows x v slots]: one workgroup per root of E.
+__global__ void __launch_bounds__(256)
+spchain3_leaf_places_kernel(ScArgs A, ScOut E, uint16_t *i_at) {
+    const int64_t a = E.root_knode[blockIdx.x], n0 = A.i_ptr0[a], nrows = A.i_ptr0[a + 1] - n0;
+    const int64_t ns = A.nu_ptr[a + 1] - A.nu_ptr[a];
+    for (int64_t row = threadIdx.x / 16; row < nrows; row += 16)
+        for (int64_t l = A.i_ptr1[n0 + row] + threadIdx.x % 16; l < A.i_ptr1[n0 + row + 1]; l += 16)
+            i_at[l] = uint16_t(row * ns + A.i_slot[l]);
+}
+
+// The root of a (K,i) node, from the marks of first nodes and their exclusive sum.
+struct ScRootOf {
+    const int64_t *first, *before;
+    __device__ __forceinline__ int64_t operator()(int64_t node) const { return before[node] + first[node] - 1; }
+};
+
+// Per (K,i) node, one wavefront: the entries of C[i,:] that meet a u of K -- their number, or (entries not null)
+// themselves from entry_off[node] on, placed in the block C_K [nodes x cstride].
+__global__ void __launch_bounds__(256)
+spchain3_entries_kernel(ScArgs A, ScOut E, int cstride, ScRootOf root_of, const int64_t *__restrict__ entry_off, int64_t *count, ScEntry *entries) {
+    const int64_t node = int64_t(blockIdx.x) * 4 + threadIdx.x / 64;
+    const int lane = threadIdx.x & 63;
+    if (node >= E.nodes) return;
+    const int64_t r = root_of(node), a = E.knode[node], b = E.cnode[node];
+    const int64_t n0 = A.i_ptr0[a], n1 = A.i_ptr0[a + 1], x = node - E.ptr0[r];
+    int64_t at = entries ? entry_off[node] : 0, found = 0;
+    for (int64_t c = A.c_ptr0[b]; c < A.c_ptr0[b + 1]; c += 64) {
+        const int64_t row = c + lane < A.c_ptr0[b + 1] ? find_in(A.i_idx1, n0, n1, A.c_idx1[c + lane]) : -1;
+        const uint64_t hits = __ballot(row >= 0);
+        if (entries && row >= 0)
+            entries[at + found + __popcll(hits & ((uint64_t(1) << lane) - 1))] = ScEntry{uint32_t(c + lane), uint32_t(x * cstride + (row - n0))};
+        found += __popcll(hits);
+    }
+    if (!entries && lane == 0) count[node] = found;
+}
+
+__device__ __forceinline__ int64_t sc_words(const ScArgs &A, int64_t r) { return (A.mu_ptr[r + 1] - A.mu_ptr[r] + 31) / 32; }
+
+__global__ void spchain3_word_count_kernel(ScArgs A, ScOut E, int64_t *count) {
+    const int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (r < E.roots) count[r] = (E.ptr0[r + 1] - E.ptr0[r]) * sc_words(A, r);
+}
+
+// The words of every (K,i) node, one wavefront each: a lane finds the place of its leaf's m, 64 words at a time are put
+// together in LDS.
+__global__ void __launch_bounds__(256)
+spchain3_words_kernel(ScArgs A, ScOut E, ScRootOf root_of, const int64_t *__restrict__ word_off, ScWord *words) {
+    __shared__ uint32_t masks[4][64];
+    const int64_t node = int64_t(blockIdx.x) * 4 + threadIdx.x / 64;
+    if (node >= E.nodes) return;
+    const int lane = threadIdx.x & 63;
+    uint32_t *mine = masks[threadIdx.x / 64];
+    const int64_t r = root_of(node), nw = sc_words(A, r);
+    const int64_t m0 = A.mu_ptr[r], m1 = A.mu_ptr[r + 1], q0 = E.ptr1[node], q1 = E.ptr1[node + 1];
+    uint32_t before = 0;
+    for (int64_t w0 = 0; w0 < nw; w0 += 64) {
+        mine[lane] = 0u;
+        wave_sync();
+        for (int64_t q = q0 + lane; q < q1; q += 64) {
+            const int64_t j = find_in(A.mu_list, m0, m1, E.idx2[q]) - m0 - 32 * w0;
+            if (j >= 0 && j < 32 * 64) atomicOr(&mine[j >> 5], 1u << (j & 31));
+        }
+        wave_sync();
+        const uint32_t mask = mine[lane];
+        int upto = __popc(mask);
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(upto, d, 64);
+            if (lane >= d) upto += up;
+        }
+        if (w0 + lane < nw) words[word_off[r] + (node - E.ptr0[r]) * nw + w0 + lane] = ScWord{mask, before + uint32_t(upto - __popc(mask))};
+        before += uint32_t(__shfl(upto, 63, 64));
+        wave_sync();
     }
 }
 
@@ -646,21 +674,25 @@ __global__ void spchain3_cost_key_kernel(ScArgs A, ScOut E, uint64_t *keys, uint
 // root order when it is null); flag / block_off: the root that opened r's class of equal lists and its block
 __global__ void spchain3_root_desc_kernel(ScArgs A, ScOut E, const int64_t *__restrict__ flag,
                                           const int64_t *__restrict__ block_off, const uint32_t *__restrict__ order,
-                                          ScRoot *roots) {
+                                          const int64_t *__restrict__ entry_off, int64_t n_entries,
+                                          const int64_t *__restrict__ word_off, ScRoot *roots) {
     const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (p >= E.roots) return;
     const int64_t r = order ? int64_t(order[p]) : p;
     const int64_t a = E.root_knode[r];
     ScRoot R{};
     R.ns = int32_t(A.nu_ptr[a + 1] - A.nu_ptr[a]);
-    R.n0 = A.i_ptr0[a];
-    R.nrows = int32_t(A.i_ptr0[a + 1] - R.n0);
-    R.mu0 = A.mu_ptr[r];
-    R.nm = int32_t(A.mu_ptr[r + 1] - R.mu0);
+    const int64_t n0 = A.i_ptr0[a], e1 = E.ptr0[r + 1];
+    R.nrows = int32_t(A.i_ptr0[a + 1] - n0);
+    R.nm = int32_t(A.mu_ptr[r + 1] - A.mu_ptr[r]);
     R.e0 = E.ptr0[r];
-    R.nn = int32_t(E.ptr0[r + 1] - R.e0);
-    R.li0 = A.i_ptr1[R.n0];
-    R.nleaves = int32_t(A.i_ptr1[R.n0 + R.nrows] - R.li0);
+    R.nn = int32_t(e1 - R.e0);
+    R.li0 = A.i_ptr1[n0];
+    R.nleaves = int32_t(A.i_ptr1[n0 + R.nrows] - R.li0);
+    R.c0 = entry_off[R.e0];
+    R.nc = int32_t((e1 < E.nodes ? entry_off[e1] : n_entries) - R.c0);
+    R.w0 = word_off[r];
+    R.nw = int32_t(sc_words(A, r));
     R.q0 = E.ptr1[R.e0];
     int64_t opener = r;
     while (!flag[opener]) --opener;
@@ -964,30 +996,21 @@ conststn_status build_spchain3_tables(conststn_plan_s *plan) {
             nn_max = std::max(nn_max, h_ep[size_t(r + 1)] - h_ep[size_t(r)]);
         }
         auto up16 = [](int64_t x) { return (x + 15) / 16 * 16; };
-        int64_t posb = 4;                                       // leaf positions, 2 bytes each
-        for (int64_t r = 0; r < roots; ++r)
-            posb = std::max(posb, 2 * (h_ep[size_t(r + 1)] - h_ep[size_t(r)]) * (h_mu[size_t(r + 1)] - h_mu[size_t(r)]) + 4);
         // odd row strides: the 16 rows a tile reads fall in different banks
         const int64_t ns_pad = plan->sc_max_slots | 1, rows_pad = rows_max | 1;
         int64_t at = 0;
-        int64_t o_cd, o_t, o_pos, o_lval, o_rowptr, o_c0, o_clen, o_qoff, o_mmap, o_umap;
-        at = up16(std::max(8 * ik, posb)); o_cd = at;           // I_K, later the leaf positions
+        int64_t o_cd, o_t, o_words, o_lval, o_qoff;
+        at = up16(8 * ik); o_cd = at;
         at = up16(at + 8 * nn_max * rows_pad); o_t = at;
-        at = up16(at + 8 * nn_max * ns_pad); o_pos = 0;
-        o_lval = at;
-        at = up16(at + 8 * nn_max); o_rowptr = at;
-        at = up16(at + 4 * (rows_max + 1)); o_c0 = at;
-        at = up16(at + 4 * nn_max); o_clen = at;
-        at = up16(at + 4 * nn_max); o_qoff = at;
-        at = up16(at + 4 * (nn_max + 1)); o_mmap = at;
-        at = up16(at + 2 * n_m); o_umap = at;
-        at = up16(at + 4 * ((n_u + 1) / 2));
+        at = up16(at + 8 * nn_max * ns_pad); o_words = at;
+        at = up16(at + int64_t(sizeof(ScWord)) * nn_max * ((nm_max + 31) / 32)); o_lval = at;
+        at = up16(at + 8 * nn_max); o_qoff = at;
+        at = up16(at + 4 * nn_max);
         const int64_t bytes = at;
         const int64_t budget = plan->opt("spchain3_local_kb", 78) * 1024;      // two workgroups per compute unit
         const bool offsets_fit = I->nnz < (int64_t(1) << 31) && C->nnz < (int64_t(1) << 31) && nnz < (int64_t(1) << 31);
-        // a node holds each m of its K at most once, so nm_max also bounds the leaves of a node (16-bit positions)
         // (pk < 2^29: the kernel reaches into a block P_K with 32-bit byte offsets)
-        if (rows_max <= 65534 && nm_max <= 65534 && pk < (int64_t(1) << 29) && offsets_fit && bytes <= budget && bytes <= 160 * 1024 &&
+        if (ik <= 65536 && pk < (int64_t(1) << 29) && offsets_fit && bytes <= budget && bytes <= 160 * 1024 &&
             plan->opt("spchain3_form", 1) == 1) {
             ScArgs A2 = make_args(plan);
             // the dense blocks P_K, one per run of K with the same v and m lists
@@ -1000,15 +1023,35 @@ conststn_status build_spchain3_tables(conststn_plan_s *plan) {
             int64_t pk_total = 0;
             CST_TRY(exscan(celems.p, coff.p, roots, &pk_total));
             const int64_t pk_cap = plan->opt("spchain3_pk_gb", 4) << 27;       // doubles
-            if (pk_total <= pk_cap) {
+            // (without memory for the tables the general form takes the plan)
+            auto build_local = [&]() -> conststn_status {
                 CST_TRY(plan->sc_pk_blocks.alloc(size_t(pk_total)));
                 CST_TRY(zero_fill(plan->sc_pk_blocks.p, pk_total, st));
                 spchain3_pk_fill_kernel<<<dim3(unsigned(roots)), 256, 0, st>>>(A2, O, cflag.p, coff.p, plan->sc_pk_blocks.p);
                 CST_HIP(hipGetLastError());
-                CST_TRY(plan->sc_e_c0.alloc(size_t(nodes)));
-                CST_TRY(plan->sc_e_clen.alloc(size_t(nodes)));
                 CST_TRY(plan->sc_roots.alloc(size_t(roots) * sizeof(ScRoot)));
-                spchain3_row_tables_kernel<<<grid_for(nodes), 256, 0, st>>>(A2, O, plan->sc_e_c0.p, plan->sc_e_clen.p);
+                // places of I's leaves, the entries of every C_K and the stored m of every node
+                CST_TRY(plan->sc_i_at.alloc(size_t(I->nnz)));
+                spchain3_leaf_places_kernel<<<dim3(unsigned(roots)), 256, 0, st>>>(A2, O, plan->sc_i_at.p);
+                CST_HIP(hipGetLastError());
+                const ScRootOf root_at{rflag.p, root_of.p};
+                DevBuf<int64_t> count, entry_off, word_off;
+                CST_TRY(count.alloc(size_t(std::max(nodes, roots))));
+                CST_TRY(entry_off.alloc(size_t(nodes)));
+                CST_TRY(word_off.alloc(size_t(roots)));
+                int64_t n_entries = 0, n_words = 0;
+                spchain3_entries_kernel<<<grid_for(nodes, 4), 256, 0, st>>>(A2, O, int(rows_pad), root_at, nullptr, count.p, nullptr);
+                CST_HIP(hipGetLastError());
+                CST_TRY(exscan(count.p, entry_off.p, nodes, &n_entries));
+                CST_TRY(plan->sc_entries.alloc(size_t(n_entries) * sizeof(ScEntry)));
+                ScEntry *entries = reinterpret_cast<ScEntry *>(plan->sc_entries.p);
+                spchain3_entries_kernel<<<grid_for(nodes, 4), 256, 0, st>>>(A2, O, int(rows_pad), root_at, entry_off.p, nullptr, entries);
+                CST_HIP(hipGetLastError());
+                spchain3_word_count_kernel<<<grid_for(roots), 256, 0, st>>>(A2, O, count.p);
+                CST_HIP(hipGetLastError());
+                CST_TRY(exscan(count.p, word_off.p, roots, &n_words));
+                CST_TRY(plan->sc_words.alloc(size_t(n_words) * sizeof(ScWord)));
+                spchain3_words_kernel<<<grid_for(nodes, 4), 256, 0, st>>>(A2, O, root_at, word_off.p, reinterpret_cast<ScWord *>(plan->sc_words.p));
                 CST_HIP(hipGetLastError());
                 DevBuf<uint64_t> ka, kb;
                 DevBuf<uint32_t> ra, rb;
@@ -1023,17 +1066,29 @@ conststn_status build_spchain3_tables(conststn_plan_s *plan) {
                     const uint64_t *ks = nullptr;
                     CST_TRY(radix_sort_pairs_u64(ka.p, kb.p, ra.p, rb.p, roots, 40, st, &ks, &order));
                 }
-                spchain3_root_desc_kernel<<<grid_for(roots), 256, 0, st>>>(A2, O, cflag.p, coff.p, order,
+                spchain3_root_desc_kernel<<<grid_for(roots), 256, 0, st>>>(A2, O, cflag.p, coff.p, order, entry_off.p, n_entries, word_off.p,
                                                                           reinterpret_cast<ScRoot *>(plan->sc_roots.p));
                 CST_HIP(hipGetLastError());
                 CST_HIP(hipStreamSynchronize(st));
                 plan->sc_local = true;
                 plan->sc_local_lds = int(bytes);
                 plan->sc_pk_doubles = pk_total;
-                const int lay[13] = {int(o_cd), int(o_t), int(o_pos), int(o_lval), int(o_rowptr), int(o_c0), int(o_clen),
-                                     int(o_qoff), int(o_mmap), int(o_umap), int(bytes), int(ns_pad), int(rows_pad)};
-                plan->sc_local_layout.assign(lay, lay + 13);
+                const int lay[8] = {int(o_cd), int(o_t), int(o_words), int(o_lval), int(o_qoff), int(bytes), int(ns_pad), int(rows_pad)};
+                plan->sc_local_layout.assign(lay, lay + 8);
                 CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(spchain3_local_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
+                return CONSTSTN_OK;
+            };
+            if (pk_total <= pk_cap) {
+                const conststn_status got = build_local();
+                if (got == CONSTSTN_ENOMEM) {
+                    plan->sc_pk_blocks.release();
+                    plan->sc_i_at.release();
+                    plan->sc_entries.release();
+                    plan->sc_words.release();
+                    plan->sc_roots.release();
+                } else {
+                    CST_TRY(got);
+                }
             }
         }
     }
@@ -1051,10 +1106,10 @@ conststn_status launch_spchain3(const conststn_plan_s *plan, double *out, hipStr
     if (plan->sc_local)
     {
         const std::vector<int> &l = plan->sc_local_layout;
-        const ScLocalLds lay{l[0], l[1], l[2], l[3], l[4], l[5], l[6], l[7], l[8], l[9], l[10], l[11], l[12]};
+        const ScLocalLds lay{l[0], l[1], l[2], l[3], l[4], l[5], l[6], l[7]};
         spchain3_local_kernel<<<dim3(unsigned(O.roots)), 64 * kScLocalWaves, size_t(plan->sc_local_lds), stream>>>(
-            A, O, out, lay, reinterpret_cast<const ScRoot *>(plan->sc_roots.p), plan->sc_pk_blocks.p, plan->sc_e_c0.p,
-            plan->sc_e_clen.p);
+            A, O, out, lay, reinterpret_cast<const ScRoot *>(plan->sc_roots.p), plan->sc_pk_blocks.p, plan->sc_i_at.p,
+            reinterpret_cast<const ScEntry *>(plan->sc_entries.p), reinterpret_cast<const ScWord *>(plan->sc_words.p));
     }
     else
         spchain3_kernel<<<dim3(unsigned(O.roots)), 64 * kScWaves, size_t(plan->sc_lds_bytes), stream>>>(A, O, out, plan->sc_map_bytes);

@@ -320,7 +320,8 @@ struct conststn_plan_s {
     int sc_local_lds = 0;
     cst::DevBuf<double> sc_pk_blocks;                        // dense blocks P_K [v slots x m], one per run of K sharing both lists
     int64_t sc_pk_doubles = 0;
-    cst::DevBuf<int32_t> sc_e_c0, sc_e_clen;                 // per (K,i) node: range of C[i,:]
+    cst::DevBuf<uint16_t> sc_i_at;                           // place of every leaf of I in its K's block
+    cst::DevBuf<unsigned char> sc_entries, sc_words;         // entries of the blocks C_K; per (K,i) node the stored m of K
     cst::DevBuf<unsigned char> sc_roots;                     // per root of the result: the kernel's descriptor
     std::vector<int> sc_local_layout;      // byte offsets of the kernel's LDS arrays
 

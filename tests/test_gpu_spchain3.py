@@ -167,6 +167,26 @@ def test_block_local_with_more_slots_and_entries_than_a_wavefront():
         assert err <= TOL
 
 
+@pytest.mark.parametrize("n_i,n_u,n_m", [(1, 3, 1),        # one node, one m
+                                         (16, 40, 32),     # full tiles, one full word of m, depth as held in registers
+                                         (17, 41, 33),     # one more of each
+                                         (40, 45, 31),     # > 3 x 512 leaves of I and entries of C per K
+                                         (33, 20, 130),    # nine columns of three tiles: runs that start within a column
+                                         (70, 12, 80)])    # five columns of five tiles
+@pytest.mark.parametrize("restricted", [False, True])
+def test_block_local_at_the_edges_of_tiles_words_and_lists(n_i, n_u, n_m, restricted):
+    dims = (5, n_i, n_u, n_m)
+    full = lambda *shape: max(1, int(0.9 * np.prod(shape)))
+    I, C, P, L = _scattered(4110 + n_i, dims, full(5, n_u, n_u), full(n_u, n_i), max(1, n_u * n_m // 8), full(5, n_i))
+    L.vals = torch.randn(L.nnz, generator=torch.Generator().manual_seed(6), dtype=torch.float64)
+    Lx = L if restricted else None
+    Ks = range(dims[0])
+    ref = spsp.chain3(_np(I), _np(C), _np(P), dims, _np(L) if restricted else None, K_values=Ks)
+    for kernel in ("block-local", "general"):
+        coords, vals, _ = _run(I, C, P, Lx, kernel=kernel)
+        assert _compare(coords, vals, ref, dims, Ks) <= TOL
+
+
 def test_empty_result_and_empty_operands():
     dims = (8, 5, 12, 9)
     I, C, P, L = _scattered(4104, dims, 40, 10, 15, 10)
