@@ -178,8 +178,8 @@ scan_tiles_kernel(const unsigned *__restrict__ tile_counts, OFF *__restrict__ ti
 
 // ---- stable LSD radix sort of (key, payload) pairs, 8 or 9 bits per pass ---------------------
 //
-// A workgroup of four wavefronts owns a tile of kSortTile consecutive pairs, wavefront w the w-th
-// quarter of it.  Per pass: (1) every workgroup counts the digits of its tile; (2) scan_tiles_kernel
+// A workgroup of eight wavefronts owns a tile of kSortTile consecutive pairs, wavefront w the w-th
+// eighth of it.  Per pass: (1) every workgroup counts the digits of its tile; (2) scan_tiles_kernel
 // (one block per digit value) turns the counts into the tile's starting offset inside each digit's
 // bucket; (3) every workgroup re-reads its tile, ranks each pair among the pairs of the tile with the
 // same digit that come before it (in a wavefront: 64 pairs at a time, one ballot per bit narrows the set
@@ -191,15 +191,24 @@ scan_tiles_kernel(const unsigned *__restrict__ tile_counts, OFF *__restrict__ ti
 // The first pass of a CSF build reads the coordinates and packs the keys itself (COORDS), and the payload
 // is the value: 8 bytes more per pair and pass than the position, but the values are then not read at random
 // afterwards, a cache line each (emission at 76 M nonzeros: 1.75 -> 0.45 ms, a scatter 0.44 -> 0.55).
-// Bound: memory; a pass moves 40 bytes per pair (32 with positions).  Neighbouring tiles write neighbouring
-// runs (16 or 8 pairs on average) of a bucket, and neighbouring counts: consecutive tiles are given to one
-// XCD, whose L2 puts the parts of a cache line together (in launch order a build takes 0.7 ms longer).
-// Build of 76 M nonzeros, 43 key bits: 7.2 ms with a packing pass, six passes of 8 bits and positions ->
-// 4.55 ms (per pass: counts 0.17, their scan 0.03, scatter 0.55: 4.4 TB/s of the 32 bytes it moves per pair).
+// Bound: memory; a pass moves 40 bytes per pair (32 with positions), and the writes more than their bytes: a run of a
+// bucket that begins and ends inside a line.  So the tiles are as large as two workgroups of a compute unit with four
+// wavefronts per SIMD allow: 12 pairs a lane instead of 16 (118 registers instead of 151), 8 wavefronts, counts of
+// 2 bytes; runs of 12 (9 bits) or 24 pairs on average.  76 M pairs, whole build: 4 wavefronts of 16 pairs, 4096 a tile,
+// 4.57 ms; of 12 pairs 4.75; 8 of 10 pairs 4.25, of 12 4.16, of 14 4.31; 12 of 16 pairs (one workgroup) 4.30.
+// Neighbouring tiles write neighbouring runs and neighbouring counts: consecutive tiles are given to one
+// XCD, whose L2 puts the parts of a cache line together (in launch order a build takes 1.1 ms longer).
+// The counts of a tile are kept in kCountCopies copies, one for every eighth lane: lanes of skewed data that meet at one
+// address wait for each other (counts of a pass 0.17 ms with one copy, 0.147 with eight).
+// Build of 76 M nonzeros, 43 key bits: 7.2 ms with a packing pass, six passes of 8 bits and positions, 4.55 with
+// tiles of 4096 -> 4.15 ms (per pass: counts 0.147, their scan 0.022, scatter 0.50: 4.8 TB/s of the 32 bytes it moves).
 // Work space 33 bytes per pair, 25 with positions: a build that runs out of memory is tried again with those.
-constexpr int kSortItems = 16;
+constexpr int kSortItems = 12;
 constexpr int kSortWave = kSortItems * 64;            // pairs of one wavefront
-constexpr int kSortTile = 4 * kSortWave;
+constexpr int kSortWaves = 8;
+constexpr int kSortThreads = 64 * kSortWaves;
+constexpr int kSortTile = kSortWaves * kSortWave;
+constexpr int kCountCopies = 8;                       // of a digit's count
 
 // key[i] = keys (one word) of the nonzeros min(first + i * step, n - 1), i < COUNT; of fields that begin below bit
 // `below` only.  The level is the outer loop: a lane's loads of one level are in flight together.
@@ -231,60 +240,66 @@ __device__ __forceinline__ bool keys_of(const Levels &lv, int64_t first, int ste
 }
 
 template <int BITS, bool COORDS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kSortThreads)
 radix_count_kernel(int64_t n, const uint64_t *__restrict__ keys, Levels lv, int shift, unsigned *__restrict__ tile_counts,
                    int64_t ntiles) {
     constexpr int kBins = 1 << BITS;
-    __shared__ unsigned hist[kBins];
+    __shared__ unsigned hist[kBins * kCountCopies];
+    unsigned *mine = hist + threadIdx.x % kCountCopies;
     // each XCD takes a contiguous range of tiles, as in the scatter: its L2 puts their counts together
     const int64_t per_xcd = (ntiles + 7) / 8, tile = int64_t(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (tile >= ntiles) return;
-    for (int d = threadIdx.x; d < kBins; d += 256) hist[d] = 0;
+    for (int d = threadIdx.x; d < kBins * kCountCopies; d += kSortThreads) hist[d] = 0;
     __syncthreads();
     const int64_t base = tile * kSortTile;
     const int live = int(n - base < kSortTile ? n - base : int64_t(kSortTile));
     if (COORDS) {
         uint32_t key[kSortItems];                     // (what is out of range is reported by the scatter)
-        keys_of<false>(lv, base + int(threadIdx.x), 256, n, BITS, key);
+        keys_of<false>(lv, base + int(threadIdx.x), kSortThreads, n, BITS, key);
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i)
-            if (i * 256 + int(threadIdx.x) < live) atomicAdd(&hist[key[i] & (kBins - 1)], 1u);
+            if (i * kSortThreads + int(threadIdx.x) < live) atomicAdd(&mine[(key[i] & (kBins - 1)) * kCountCopies], 1u);
     } else {
-        // two keys per load (tiles begin at multiples of 32 KB of a buffer that is aligned to 16 bytes)
+        // two keys per load (tiles begin at multiples of 48 KB of a buffer that is aligned to 16 bytes)
         const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(keys + base);
         ulonglong2 k[kSortItems / 2];
 #pragma unroll
         for (int i = 0; i < kSortItems / 2; ++i) {
-            const int m = i * 256 + int(threadIdx.x);
+            const int m = i * kSortThreads + int(threadIdx.x);
             k[i] = pairs[2 * m < live ? m : 0];       // (an odd last key: the buffers' allocations end on 256 bytes)
         }
 #pragma unroll
         for (int i = 0; i < kSortItems / 2; ++i) {
-            const int m = 2 * (i * 256 + int(threadIdx.x));
-            if (m < live) atomicAdd(&hist[unsigned(k[i].x >> shift) & (kBins - 1)], 1u);
-            if (m + 1 < live) atomicAdd(&hist[unsigned(k[i].y >> shift) & (kBins - 1)], 1u);
+            const int m = 2 * (i * kSortThreads + int(threadIdx.x));
+            if (m < live) atomicAdd(&mine[(unsigned(k[i].x >> shift) & (kBins - 1)) * kCountCopies], 1u);
+            if (m + 1 < live) atomicAdd(&mine[(unsigned(k[i].y >> shift) & (kBins - 1)) * kCountCopies], 1u);
         }
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < kBins; d += 256) tile_counts[int64_t(d) * ntiles + tile] = hist[d];
+    for (int d = threadIdx.x; d < kBins; d += kSortThreads) {
+        unsigned sum = 0;
+#pragma unroll
+        for (int c = 0; c < kCountCopies; ++c) sum += hist[d * kCountCopies + c];
+        tile_counts[int64_t(d) * ntiles + tile] = sum;
+    }
 }
 
 template <int BITS, bool COORDS, typename PAY>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BITS == 9 || sizeof(PAY) == 8 ? 3 : 4)))
+__global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)))
 radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY *__restrict__ pay_in, Levels lv, int *flags,
                      uint64_t *__restrict__ keys_out, PAY *__restrict__ pay_out, int shift,
                      const uint32_t *__restrict__ tile_offsets, const int64_t *__restrict__ totals, int64_t ntiles) {
-    constexpr int kBins = 1 << BITS, kPer = kBins / 256;      // digits of a thread
+    constexpr int kBins = 1 << BITS, kPer = (kBins + kSortThreads - 1) / kSortThreads;      // digits of a thread
     __shared__ uint64_t lkey[kSortTile];                      // the tile's keys by digit, then its positions
-    __shared__ unsigned run[4][kBins];                        // per wavefront: pairs of each digit seen so far, then the place of the next
+    __shared__ uint16_t run[kSortWaves][kBins];                        // per wavefront: pairs of each digit seen so far, then the place of the next
     __shared__ uint32_t gbase[kBins];                         // address of the tile's place p holding digit d: gbase[d] + p (mod 2^32)
-    __shared__ unsigned wsum[2][4];
+    __shared__ unsigned wsum[2][kSortWaves];
     const int wv = threadIdx.x / 64, lane = threadIdx.x % 64;
     // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of tiles
     const int64_t per_xcd = (ntiles + 7) / 8, tile = int64_t(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (tile >= ntiles) return;
     const int64_t base = tile * kSortTile + int64_t(wv) * kSortWave;
-    for (int d = threadIdx.x; d < 4 * kBins; d += 256) (&run[0][0])[d] = 0;
+    for (int d = threadIdx.x; d < kSortWaves * kBins; d += kSortThreads) (&run[0][0])[d] = 0;
     __syncthreads();
     const unsigned long long lt = (1ull << lane) - 1ull;
     uint64_t key[kSortItems];
@@ -317,7 +332,7 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY 
         const unsigned before = unsigned(__popcll(peers & lt));
         rank[i] = run[wv][digit] + before;
         __builtin_amdgcn_wave_barrier();
-        if (before == 0) run[wv][digit] += unsigned(__popcll(peers));      // the lowest peer advances the digit's count
+        if (before == 0) run[wv][digit] += uint16_t(__popcll(peers));      // the lowest peer advances the digit's count
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
@@ -326,8 +341,8 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY 
         // where each wavefront's share begins
         const int d0 = int(threadIdx.x) * kPer;
         unsigned mine = 0, all = 0;
-        for (int x = 0; x < kPer; ++x) {
-            for (int w = 0; w < 4; ++w) mine += run[w][d0 + x];
+        for (int x = 0; x < kPer && d0 + x < kBins; ++x) {
+            for (int w = 0; w < kSortWaves; ++w) mine += run[w][d0 + x];
             all += unsigned(totals[d0 + x]);
         }
         unsigned inc = mine, inc_all = all;
@@ -339,13 +354,13 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY 
         __syncthreads();
         unsigned first = inc - mine, bucket = inc_all - all;
         for (int w = 0; w < wv; ++w) { first += wsum[0][w]; bucket += wsum[1][w]; }
-        for (int x = 0; x < kPer; ++x) {
+        for (int x = 0; x < kPer && d0 + x < kBins; ++x) {
             const int d = d0 + x;
             gbase[d] = bucket + tile_offsets[int64_t(d) * ntiles + tile] - first;
             bucket += unsigned(totals[d]);
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < kSortWaves; ++w) {
                 const unsigned c = run[w][d];
-                run[w][d] = first;
+                run[w][d] = uint16_t(first);
                 first += c;
             }
         }
@@ -362,7 +377,7 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY 
     uint32_t pos[kSortItems];
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        const int p = i * 256 + int(threadIdx.x);
+        const int p = i * kSortThreads + int(threadIdx.x);
         const uint64_t k = lkey[p];
         pos[i] = gbase[unsigned(k >> shift) & (kBins - 1)] + unsigned(p);
         if (p < live_pairs) keys_out[pos[i]] = k;
@@ -374,7 +389,7 @@ radix_scatter_kernel(int64_t n, const uint64_t *__restrict__ keys_in, const PAY 
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        const int p = i * 256 + int(threadIdx.x);
+        const int p = i * kSortThreads + int(threadIdx.x);
         if (p < live_pairs) pay_out[pos[i]] = lpay[p];
     }
 }
@@ -405,9 +420,9 @@ static conststn_status radix_passes(uint64_t *keys_a, uint64_t *keys_b, PAY *pay
     int64_t *totals = reinterpret_cast<int64_t *>(at);
     uint64_t *kin = keys_a, *kout = keys_b;
     PAY *pin = pay_a, *pout = pay_b;
-    const dim3 grid{unsigned(div_up(stiles, 8) * 8)}, block(256);
+    const dim3 grid{unsigned(div_up(stiles, 8) * 8)}, block(kSortThreads);
     const Levels none{};
-    // 9 bits where that saves a pass: 5 instead of 6 at 43 bits, 0.17 ms less at 76 M pairs (a pass of 9 bits costs
+    // 9 bits where that saves a pass: 5 instead of 6 at 43 bits, 4.16 against 4.62 ms at 76 M pairs (a pass of 9 bits costs
     // more than one of 8, so where the number is the same 8 are taken)
     const bool nine = (bits + 8) / 9 < (bits + 7) / 8;
     auto pass = [&](auto digit_bits, auto coords, int shift) {

@@ -1,5 +1,5 @@
-"""CSF builds whose sort takes one to six passes of 8 or 9 bits, at numbers of nonzeros beside the sort's tiles (4096) and
-their rounds over the eight XCDs, without and with duplicates (added in input order), and with a coordinate
+"""CSF builds whose sort takes one to six passes of 8 or 9 bits, at numbers of nonzeros beside the sort's tiles (6144 pairs;
+4096 before) and their rounds over the eight XCDs, without and with duplicates (added in input order), and with a coordinate
 out of range in the last place, bit for bit against the reference build."""
 import numpy as np
 import pytest
@@ -44,6 +44,13 @@ def test_passes_and_tiles(dims, n):
     c[2][n - 1] = dims[2]
     with pytest.raises(Exception, match="below its mode extent"):
         cst.build_csf([torch.from_numpy(x).cuda() for x in c], torch.from_numpy(v).cuda(), dims, order, flags=cst.COALESCE_DUPS)
+
+
+@pytest.mark.parametrize("dims", [DIMS[0], DIMS[3], DIMS[7], DIMS[8], DIMS[9]])
+@pytest.mark.parametrize("n", [767, 769, 6143, 6144, 6145, 8 * 6144, 8 * 6144 + 1, 9 * 6144 - 1])
+def test_wavefronts_and_tiles_of_6144(dims, n):
+    """Beside a wavefront's share (768 pairs) and a tile of the sort; 2 x 1 x 1: every pair of a tile in one or two digits."""
+    test_passes_and_tiles(dims, n)
 
 
 @pytest.mark.parametrize("bad", [-1, 1, 7, 2 ** 31 - 1])
