@@ -10,6 +10,7 @@
 // fibers of W below root k: lanes take the m leaves and add T[l]*W into a per-wavefront copy
 // of Z_i in LDS (no atomics: leaves of one fiber have distinct m).  The copies are added in
 // fixed order at the end, so results are bit-reproducible.
+#include <algorithm>
 #include <type_traits>
 
 #include "plan.hpp"
@@ -945,11 +946,13 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
 
 // Sums the partial results of the k chunks in chunk order; of those marked `present` where the others were not written.
 // Sixteen loads in flight: a chain of single ones took 12 us over 44 chunks, this 4.
-// Row r of the result is that of slice r, or of slice_of_row[r] (-1: none, zeros).
-__global__ void sptn3_fixup_kernel(int64_t rows, int64_t slices, int64_t M, int n_kc, const int32_t *__restrict__ slice_of_row,
-                                   const double *__restrict__ partial, const uint8_t *__restrict__ present, int n_groups,
-                                   double *out) {
-    const int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// Row r of the result is that of slice r, or of slice_of_row[r] (-1: none, zeros).  The launch takes the elements from `first`
+// on: a result of 2^32 of them and more needs several launches, each of which has fewer threads than that.
+constexpr int64_t kSpFixupLaunch = int64_t(1) << 31;
+__global__ void sptn3_fixup_kernel(int64_t first, int64_t rows, int64_t slices, int64_t M, int n_kc,
+                                   const int32_t *__restrict__ slice_of_row, const double *__restrict__ partial,
+                                   const uint8_t *__restrict__ present, int n_groups, double *out) {
+    const int64_t x = first + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (x >= rows * M) return;
     const int64_t row = x / M, m = x - row * M, s = slice_of_row ? slice_of_row[row] : row;
     if (s < 0) {
@@ -1030,10 +1033,13 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     if (a.n_kc > 1) {
         const bool all = plan->compact || a.slices == plan->out_rows;
         const int64_t rows = plan->compact ? a.slices : plan->out_rows;
-        sptn3_fixup_kernel<<<dim3(unsigned((rows * a.M + 255) / 256)), dim3(256), 0, stream>>>(
-            rows, a.slices, a.M, a.n_kc, all ? nullptr : plan->sp_slice_of_row.p, a.partial, owned ? plan->sp_present.p : nullptr,
-            a.n_groups, out);
-        CST_HIP(hipGetLastError());
+        for (int64_t first = 0; first < rows * a.M; first += kSpFixupLaunch) {
+            const int64_t here = std::min(rows * a.M - first, kSpFixupLaunch);
+            sptn3_fixup_kernel<<<dim3(unsigned((here + 255) / 256)), dim3(256), 0, stream>>>(
+                first, rows, a.slices, a.M, a.n_kc, all ? nullptr : plan->sp_slice_of_row.p, a.partial,
+                owned ? plan->sp_present.p : nullptr, a.n_groups, out);
+            CST_HIP(hipGetLastError());
+        }
     }
     return CONSTSTN_OK;
 }

@@ -51,3 +51,38 @@ def test_halves_passes_and_parts(slices, J, shared, L, wgs):
         assert not np.isnan(got).any() and not got[bound == 0].any()
         # a sum has at most J K x L products of three factors, in any order: (J + K L + 3) roundings along the longest chain
         assert oracle.rel_err(got, ref, bound) <= (J + K * L + 3) * 1.1e-16
+
+
+@pytest.mark.parametrize("waves", [2, 1])
+def test_more_elements_than_a_launch_has_threads_for(waves):
+    """A root mode of 10.8 M indices, of which forty hold anything, times 400: 2^32 elements and more, 35 GB.  Every row is
+    written, those without a slice with zeros."""
+    rows, M, J, K, L = (1 << 32) // 400 + 40_000, 400, 9, 5, 40
+    if torch.cuda.mem_get_info()[0] < 8 * rows * M + (4 << 30):
+        pytest.skip("the result does not fit the free device memory")
+    rng = np.random.default_rng(9200)
+    at = np.sort(rng.choice(rows, 40, replace=False))
+    at[-1] = rows - 1
+    ukey = np.unique(rng.integers(0, 40 * J * K, 900))
+    u = [x.astype(np.int32) for x in np.unravel_index(ukey, (40, J, K))]
+    wkey = np.unique(rng.integers(0, K * L * M, 3000))
+    wc = [x.astype(np.int32) for x in np.unravel_index(wkey, (K, L, M))]
+    uv, wv, V = rng.uniform(-1, 1, len(ukey)), rng.uniform(-1, 1, len(wkey)), rng.uniform(-1, 1, (J, L))
+    print("[case] %d rows of %d, waves %d" % (rows, M, waves), flush=True)
+    up = lambda cs: [torch.from_numpy(x).cuda() for x in cs]
+    U = cst.build_csf(up([at[u[0]].astype(np.int32), u[1], u[2]]), torch.from_numpy(uv).cuda(), (rows, J, K), [0, 2, 1])
+    W = cst.build_csf(up(wc), torch.from_numpy(wv).cuda(), (K, L, M), [0, 1, 2])
+    v = torch.from_numpy(V).cuda()
+    want = oracle.sptn3(u, uv, (40, J, K), V, wc, wv, (K, L, M))
+    S_abs = oracle.sptn3_abs(u, uv, (40, J, K), V, wc, wv, (K, L, M))
+    pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], options=dict(sptn3_tiled=2, sptn3_waves=waves))
+    assert "k chunks 1 " not in pl.describe() + " "
+    out = torch.full((rows * M,), 7.0, dtype=torch.float64, device="cuda")
+    cst.execute(pl, [v], out=out)
+    got = out.view(rows, M)[torch.from_numpy(at).cuda()].cpu().numpy()
+    nonzero = sum(int(torch.count_nonzero(part)) for part in out.split(1 << 28))
+    del out
+    torch.cuda.empty_cache()
+    # a sum has at most J K x L products of three factors, in any order: (J + K L + 3) roundings along the longest chain
+    assert oracle.rel_err(got, want, S_abs) <= (J + K * L + 3) * 1.1e-16
+    assert nonzero == np.count_nonzero(want)
