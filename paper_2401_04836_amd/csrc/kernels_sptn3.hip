@@ -492,10 +492,16 @@ constexpr int kOwnWAhead = 4;                                           // ... a
 static_assert(kOwnBlocks * kOwnZ + 2 * kOwnWRing <= kOwnList && kOwnList == 2 * 64, "a wavefront's list of W tiles lies in two registers");
 static_assert(kSpGroupWide == 16 * kOwnHalves && kOwnZ == 7, "slices of a workgroup; accumulators that the consumer tests for");
 
-__host__ __device__ constexpr size_t sptn3_owned_lds(int nwords) {
-    return size_t(kOwnCap * 32 + kOwnBlocks * 2 * 256) * 8 + size_t(nwords) * 16 + size_t(kOwnOffsets) * 4 +
-           size_t(kOwnWaves * kOwnList) * 2 + 256;
+// LDS: Uc, T^t, ranks of the mask words, offsets of V's rows (read 16 bytes at a time), masks, lists, scan
+__host__ __device__ constexpr size_t sptn3_owned_offsets_at(int nwords) {
+    return size_t(kOwnCap * 32 + kOwnBlocks * 2 * 256) * 8 + size_t((nwords + 1) & ~1) * 8;
 }
+__host__ __device__ constexpr size_t sptn3_owned_lds(int nwords) {
+    return sptn3_owned_offsets_at(nwords) + size_t(kOwnOffsets) * 4 + size_t(nwords) * 8 + size_t(kOwnWaves * kOwnList) * 2 + 256;
+}
+static_assert(sptn3_owned_offsets_at(1) % 16 == 0 && sptn3_owned_offsets_at(2) % 16 == 0 && sptn3_owned_lds(1) % 8 == 0,
+              "16-byte reads of the offsets, 8-byte ones of the scan");
+static_assert(sptn3_owned_lds(29696 / 32) <= 160 * 1024, "J up to 29 696");
 
 // orders LDS between the wavefronts of a workgroup without waiting for loads from memory in flight
 __device__ __forceinline__ void sp_lds_barrier() {
@@ -515,7 +521,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     double *Uc = reinterpret_cast<double *>(smem);                        // kOwnCap x 16 columns x 2 halves
     double *Tx = Uc + kOwnCap * 32;                                       // kOwnBlocks x 2 halves x 256
     uint64_t *wpre = reinterpret_cast<uint64_t *>(Tx + kOwnBlocks * 2 * 256);  // nwords: ranks, 21 bits a category
-    uint32_t *jl = reinterpret_cast<uint32_t *>(wpre + a.nwords);         // kOwnOffsets: byte offsets of V's rows
+    uint32_t *jl = reinterpret_cast<uint32_t *>(smem + sptn3_owned_offsets_at(a.nwords));  // kOwnOffsets: byte offsets of V's rows
     uint32_t *mask = jl + kOwnOffsets;                                    // 2 x nwords
     uint16_t *lists = reinterpret_cast<uint16_t *>(mask + 2 * a.nwords);  // kOwnWaves x kOwnList
     uint64_t *scan = reinterpret_cast<uint64_t *>(smem + sptn3_owned_lds(a.nwords) - 64);  // kOwnWaves

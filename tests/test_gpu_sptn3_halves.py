@@ -1,6 +1,6 @@
 """Three-tensor network on the kernel with two wavefronts per SIMD: numbers of slices on both sides of a half (16) and of a
-group (32), unions of j on both sides of a batch (8), of a group of batches (32) and of a pass (312), rows of the union that only one
-half holds, few pairs over many blocks of l (each pair takes half of them), slices and pairs without work, against the oracle."""
+group (32), unions of j on both sides of a batch (8), of a group of batches (32) and of a pass (312), odd and even numbers of mask
+words (J = 31, 70, 2000; 33, 640), rows of the union that only one half holds, few pairs over many blocks of l (each pair takes half of them), slices and pairs without work, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("wgs", [1, 8000])
 @pytest.mark.parametrize("slices,J,shared", [(1, 1, True), (16, 8, True), (17, 33, False), (32, 312, True), (33, 313, False),
-                                             (40, 640, False), (65, 31, True)])
+                                             (40, 640, False), (65, 31, True), (20, 70, False), (18, 2000, False)])
 @pytest.mark.parametrize("L", [40, 600])
 def test_halves_passes_and_parts(slices, J, shared, L, wgs):
     rng = np.random.default_rng(slices * 1000 + J + L)
