@@ -233,7 +233,7 @@ records_kernel(RecordArgs a) {
 //
 // One launch: first the slices of many chunks (kRecLight and more; a workgroup, or kRecSegments of them, per
 // slice), then those of a few (W threads each), then the rows of empty slices, which are zero.
-constexpr int kRecLight = 32, kRecOneBlock = 1024, kRecSegments = 32;
+constexpr int kRecOneBlock = 1024, kRecSegments = 32;
 
 struct RecordFixArgs {
     int R, segments;
@@ -458,11 +458,6 @@ record_spent_ends_kernel(int64_t n_chunks, int64_t q, int64_t n_rec, uint32_t *c
     }
 }
 
-// 0: inside one chunk; 1: shared by a few chunks; 2: by many
-__device__ __forceinline__ int share_of(const int64_t *slice_rec, int64_t s, int64_t q) {
-    const int64_t span = (slice_rec[s + 1] - 1) / q - slice_rec[s] / q;
-    return span == 0 ? 0 : (span < kRecLight ? 1 : 2);
-}
 __global__ void __launch_bounds__(256)
 record_shared_kernel(int64_t slices, const int64_t *__restrict__ slice_rec, int64_t q, int kind, int64_t *flag, int *widest) {
     const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -484,8 +479,7 @@ record_shares_kernel(int64_t n, const int32_t *__restrict__ list, const int64_t 
                      int64_t q, RecordShare *share) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i >= n) return;
-    const int64_t s = list[i], lo = slice_rec[s], hi = slice_rec[s + 1], first = lo / q;
-    share[i] = RecordShare{2 * first + (lo != first * q ? 1 : 0), int32_t((hi - 1) / q - first + 1), row_of_slice[s]};
+    share[i] = record_share(slice_rec, list[i], q, row_of_slice[list[i]]);
 }
 __global__ void __launch_bounds__(256)
 empty_rows_kernel(int64_t rows, int64_t slices, const int32_t *__restrict__ idx0, int64_t *flag) {
@@ -520,12 +514,13 @@ conststn_status list_of_flags(DevBuf<int64_t> &flag, int64_t n, DevBuf<int32_t> 
 }
 
 // Every record and its value recomputed from the level arrays, every chunk's slice and open rows, the row of every
-// slice, and the lists of rows that the fix-up launch works through against what they must name.
+// slice, and what the fix-up launch works through (the shares of its slices and the empty rows) against what it must be.
 struct RecordCheck {
     RecordFill a;
     int64_t q, n_chunks, out_rows, n_light, n_heavy, n_empty;
     const uint32_t *chunk_slice;
-    const int32_t *open1, *open2, *row_of_slice, *light, *heavy, *empty, *idx0;
+    const int32_t *open1, *open2, *row_of_slice, *empty, *idx0;
+    const RecordShare *light, *heavy;
     int compact;
     unsigned bad_code, bad_chunk, bad_list;
 };
@@ -577,8 +572,10 @@ check_records_kernel(RecordCheck c, int64_t threads, unsigned *flags) {
             if (t == a.slices ? a.slice_rec[t] != a.n_rec : (a.slice_rec[t] < 0 || a.slice_rec[t + 1] <= a.slice_rec[t])) bad |= c.bad_chunk;
             else if (t < a.slices) {
                 if (c.row_of_slice[t] != (c.compact ? int32_t(t) : c.idx0[t]) || c.row_of_slice[t] >= c.out_rows) bad |= c.bad_chunk;
-                const int share = share_of(a.slice_rec, t, q);
-                if (listed(c.light, c.n_light, t) != (share == 1) || listed(c.heavy, c.n_heavy, t) != (share == 2)) bad |= c.bad_list;
+                const int kind = share_of(a.slice_rec, t, q);
+                if (kind && !share_listed(kind == 1 ? c.light : c.heavy, kind == 1 ? c.n_light : c.n_heavy,
+                                          record_share(a.slice_rec, t, q, c.row_of_slice[t])))
+                    bad |= c.bad_list;
             }
         }
         if (t < c.n_chunks) {
@@ -596,10 +593,8 @@ check_records_kernel(RecordCheck c, int64_t threads, unsigned *flags) {
             if (c.open1[t] != o1 || (c.open2 && c.open2[t] != o2)) bad |= c.bad_chunk;
         }
         // the lists ascend (so that the searches above find what is there) and hold nothing else
-        if (t < c.n_light && (t > 0 && c.light[t - 1] >= c.light[t])) bad |= c.bad_list;
-        if (t < c.n_heavy && (t > 0 && c.heavy[t - 1] >= c.heavy[t])) bad |= c.bad_list;
-        if (t < c.n_light && (c.light[t] < 0 || c.light[t] >= a.slices)) bad |= c.bad_list;
-        if (t < c.n_heavy && (c.heavy[t] < 0 || c.heavy[t] >= a.slices)) bad |= c.bad_list;
+        if (t < c.n_light && !share_entry_right(c.light, t, 1, a.slice_rec, a.slices, a.n_rec, q, c.row_of_slice)) bad |= c.bad_list;
+        if (t < c.n_heavy && !share_entry_right(c.heavy, t, 2, a.slice_rec, a.slices, a.n_rec, q, c.row_of_slice)) bad |= c.bad_list;
         if (t < c.n_empty && (c.empty[t] < 0 || c.empty[t] >= c.out_rows || (t > 0 && c.empty[t - 1] >= c.empty[t]) ||
                               listed(c.idx0, a.slices, c.empty[t])))
             bad |= c.bad_list;
@@ -652,8 +647,8 @@ conststn_status check_record_stream(const conststn_plan_s *plan, unsigned bad_co
     c.open1 = rs.open1.p;
     c.open2 = rs.open2.p;
     c.row_of_slice = rs.row_of_slice.p;
-    c.light = rs.light.p;
-    c.heavy = rs.heavy.p;
+    c.light = rs.light_share.p;
+    c.heavy = rs.heavy_share.p;
     c.empty = rs.empty.p;
     c.idx0 = X->idx[0].p;
     c.compact = plan->compact ? 1 : 0;
@@ -744,19 +739,20 @@ conststn_status build_record_stream(conststn_plan_s *plan) {
     CST_HIP(hipGetLastError());
     DevBuf<int64_t> flag;
     DevBuf<int> widest;
+    DevBuf<int32_t> light, heavy;                                     // the slices themselves
     CST_TRY(flag.alloc(size_t(a.slices)));
     CST_TRY(widest.alloc(1));
     CST_HIP(hipMemset(widest.p, 0, sizeof(int)));
     record_shared_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, rs.slice_rec.p, q, 1, flag.p, widest.p);
     CST_HIP(hipGetLastError());
-    CST_TRY(list_of_flags(flag, a.slices, rs.light, &rs.n_light));
+    CST_TRY(list_of_flags(flag, a.slices, light, &rs.n_light));
     record_shared_kernel<<<blocks_for(a.slices), dim3(256)>>>(a.slices, rs.slice_rec.p, q, 2, flag.p, widest.p);
     CST_HIP(hipGetLastError());
-    CST_TRY(list_of_flags(flag, a.slices, rs.heavy, &rs.n_heavy));
+    CST_TRY(list_of_flags(flag, a.slices, heavy, &rs.n_heavy));
     CST_TRY(rs.heavy_share.alloc(size_t(rs.n_heavy)));
     CST_TRY(rs.light_share.alloc(size_t(rs.n_light)));
-    record_shares_kernel<<<blocks_for(rs.n_heavy), dim3(256)>>>(rs.n_heavy, rs.heavy.p, rs.slice_rec.p, rs.row_of_slice.p, q, rs.heavy_share.p);
-    record_shares_kernel<<<blocks_for(rs.n_light), dim3(256)>>>(rs.n_light, rs.light.p, rs.slice_rec.p, rs.row_of_slice.p, q, rs.light_share.p);
+    record_shares_kernel<<<blocks_for(rs.n_heavy), dim3(256)>>>(rs.n_heavy, heavy.p, rs.slice_rec.p, rs.row_of_slice.p, q, rs.heavy_share.p);
+    record_shares_kernel<<<blocks_for(rs.n_light), dim3(256)>>>(rs.n_light, light.p, rs.slice_rec.p, rs.row_of_slice.p, q, rs.light_share.p);
     CST_HIP(hipGetLastError());
     int span = 0;
     CST_HIP(hipMemcpy(&span, widest.p, sizeof(int), hipMemcpyDeviceToHost));

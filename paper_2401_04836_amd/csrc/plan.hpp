@@ -6,6 +6,7 @@
 #include <memory>
 
 #include "common.hpp"
+#include "record_shares.hpp"
 #include "schedule.hpp"
 
 namespace cst {
@@ -175,12 +176,6 @@ struct MttkrpPart {
 };
 
 // MTTKRP of order 3 or 4 as one stream of records, each of which reads one factor row (kernels_records.hip)
-// A slice of the record stream that several chunks share.
-struct alignas(16) RecordShare {
-    int64_t first;                         // 2 x its first chunk, + 1 where it begins inside that
-    int32_t count, row;                    // number of its chunks; row of the result
-};
-
 struct RecordStream {
     int levels = 0;                        // kinds of record: 2 (leaf, end of fiber) or 3 (and end of the node above)
     int64_t n_rec = 0, q = 0, n_chunks = 0, slices = 0;
@@ -192,8 +187,8 @@ struct RecordStream {
     DevBuf<int32_t> open1, open2;          // [n_chunks] factor row of the fiber / node the chunk leaves open, or -1
     DevBuf<double> partial;                // [n_chunks x 2 x R]
     DevBuf<double> zeros;                  // [R] the row of a record that adds nothing
-    DevBuf<RecordShare> heavy_share, light_share;   // what the fix-up launch needs of them
-    DevBuf<int32_t> heavy, light, empty;   // slices shared by many / by a few chunks; result rows without nonzeros
+    DevBuf<RecordShare> heavy_share, light_share;   // slices shared by many / by a few chunks
+    DevBuf<int32_t> empty;                 // result rows without nonzeros
     int64_t n_heavy = 0, n_light = 0, n_empty = 0;
     bool zero_all = false;                 // too many empty rows for a list: the whole result is cleared first
     int segments = 1;                      // workgroups that share a heavy slice

@@ -1,6 +1,6 @@
-"""Host sanitizers (no GPU): the CPU oracle and the schedule front end (parser, legality rules, lowering,
-search) are compiled with -fsanitize=address,undefined together with small drivers under tests/sanitize/
-and run; any report from a sanitizer fails the test."""
+"""Host sanitizers (no GPU): the CPU oracle, the schedule front end (parser, legality rules, lowering, search), the block
+cache and the check of the record stream's shares are compiled with -fsanitize=address,undefined together with small drivers
+under tests/sanitize/ and run; any report from a sanitizer fails the test."""
 import os
 import shutil
 import subprocess
@@ -53,3 +53,11 @@ def test_block_cache_over_a_small_device(tmp_path, sanitize):
            "-lpthread", "-o", exe]
     subprocess.check_call(cmd)
     assert "san_memory: ok" in _run(exe)
+
+
+def test_check_of_the_record_streams_shares(tmp_path):
+    exe = str(tmp_path / "san_records")
+    cmd = ["g++", "-O1", "-g", "-std=c++17", "-fno-omit-frame-pointer", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-static-libasan", "-I" + CSRC, os.path.join(SAN, "san_records.cpp"), "-o", exe]
+    subprocess.check_call(cmd)
+    assert "san_records: ok" in _run(exe)
