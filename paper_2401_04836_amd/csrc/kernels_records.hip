@@ -244,11 +244,8 @@ struct RecordFixArgs {
     double *heavy_partial, *out;
 };
 
-// partial row of a slice in its c-th chunk: the second one of the first chunk where the slice begins inside it
-__device__ __forceinline__ int64_t partial_row(const RecordShare &s, int64_t c) {
-    return c == 0 ? s.first : (s.first & ~int64_t(1)) + 2 * c;
-}
-
+// Partial rows of a slice: `first` in its first chunk (the second one there where the slice begins inside the chunk), the
+// first one of every chunk behind that.
 template <int W, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 records_fixup_kernel(RecordFixArgs a) {
@@ -263,15 +260,24 @@ records_fixup_kernel(RecordFixArgs a) {
         const int64_t n = s.count, c0 = n * seg / a.segments, c1 = n * (seg + 1) / a.segments;
         double sum = 0.0;
         if (mine) {
+            // (one address that moves on: the choice of the first chunk's row inside the loop cost 0.5 us of 16 over 900 chunks)
             int64_t c = c0 + g;
-            for (; c + 7 * G < c1; c += 8 * G) {
+            const int64_t step = 2 * int64_t(G) * R;
+            const double *p = a.partial + (s.first & ~int64_t(1)) * R + col + 2 * c * R;
+            int64_t begins = c == 0 ? (s.first & 1) * R : 0;
+            for (; c + 7 * G < c1; c += 8 * G, p += 8 * step) {
                 double x[8];
+                x[0] = p[begins];
+                begins = 0;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) x[k] = a.partial[partial_row(s, c + k * G) * R + col];
+                for (int k = 1; k < 8; ++k) x[k] = p[k * step];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) sum += x[k];
             }
-            for (; c < c1; c += G) sum += a.partial[partial_row(s, c) * R + col];
+            for (; c < c1; c += G, p += step) {
+                sum += p[begins];
+                begins = 0;
+            }
         }
         red[threadIdx.x] = sum;
         __syncthreads();
@@ -287,7 +293,7 @@ records_fixup_kernel(RecordFixArgs a) {
         const int64_t k = b * G + g;
         if (k >= a.n_light || !mine) return;
         const RecordShare s = a.light[k];
-        double sum = a.partial[partial_row(s, 0) * R + col];
+        double sum = a.partial[s.first * R + col];
         const double *x0 = a.partial + (s.first & ~int64_t(1)) * R + col;
         int64_t c = 1;
         for (; c + 4 <= s.count; c += 4) {
