@@ -191,7 +191,8 @@ conststn_status conststn_plan(const char *schedule, const int *fusion, int n_ope
  * ttmc3_rowsplit (by size = rows per work item of the matrix-core kernels),
  * ttmc4_mfma (1), ttmc4_split (256), ttmc4_ksplit (by size), sptn3_tiled (1; 0 = baseline kernel, 2 = tiled kernel
  * also where W fills its 16 x 16 tiles to less than a sixteenth),
- * sptn3_waves (2), sptn3_wgs (8000), sptn3_xcd (0), spchain3_form (1; 2 = general numeric pass),
+ * sptn3_waves (2), sptn3_slices (0 = 16 or 32 root slices to a workgroup by the cost of both; 16, 32),
+ * sptn3_wgs (8000), sptn3_xcd (0), spchain3_form (1; 2 = general numeric pass),
  * spchain3_local_kb (78), spchain3_pk_gb (4), sppair4_keep (1), sppair4_keep_gb (4), sppair4_rows (1),
  * spchain3_order (1 = workgroups take the roots of the result by falling cost, 0 = in root order),
  * sppair4_rows_gb (8), sppair4_buffers (2), sppair4_xcd (2 = workgroups take the pairs by falling cost,

@@ -492,7 +492,8 @@ static const PlanOptionRange kPlanOptions[] = {
     {"ttmc3_split", 1, int64_t(1) << 40, {}},                             {"ttmc3_rowsplit", 1, int64_t(1) << 40, {}},
     {"ttmc4_mfma", 0, 1, {}},          {"ttmc4_split", 1, int64_t(1) << 40, {}},
     {"ttmc4_ksplit", 1, int64_t(1) << 40, {}},
-    {"sptn3_tiled", 0, 2, {}},         {"sptn3_waves", 1, 2, {}},         {"sptn3_wgs", 1, int64_t(1) << 24, {}},
+    {"sptn3_tiled", 0, 2, {}},         {"sptn3_waves", 1, 2, {}},         {"sptn3_slices", 1, 0, {0, 16, 32, 32, 32}},
+    {"sptn3_wgs", 1, int64_t(1) << 24, {}},
     {"sptn3_xcd", 0, 1, {}},
     {"spchain3_form", 1, 2, {}},       {"spchain3_order", 0, 1, {}},      {"spchain3_local_kb", 1, 160, {}},
     {"spchain3_pk_gb", 0, 4096, {}},
@@ -657,8 +658,8 @@ static conststn_status make_plan(const char *schedule, const int *fusion, int n_
     if (plan->family == FAM_SPTN3) {
         char b[96];
         if (plan->w_tiled)
-            snprintf(b, sizeof(b), " kernel=tiled %s k chunks %d w tiles %lld", plan->sp_two_waves ? "two waves per SIMD" : "one wave per SIMD",
-                     plan->sp_kc, (long long)plan->n_w_tiles);
+            snprintf(b, sizeof(b), " kernel=tiled %s k chunks %d w tiles %lld slices %d", plan->sp_two_waves ? "two waves per SIMD" : "one wave per SIMD",
+                     plan->sp_kc, (long long)plan->n_w_tiles, plan->sp_group());
         else
             snprintf(b, sizeof(b), " kernel=baseline");
         plan->description += b;

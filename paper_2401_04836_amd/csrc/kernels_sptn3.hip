@@ -12,6 +12,7 @@
 // fixed order at the end, so results are bit-reproducible.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "plan.hpp"
 
@@ -456,52 +457,56 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 // ---- tiled kernel with two wavefronts per SIMD ------------------------------------------------
 // The kernel above reads one operand from memory and one from LDS for every matrix instruction, and its 200
 // accumulator registers leave room for one wavefront per SIMD.  Here a workgroup of eight wavefronts takes 32 slices
-// (two *halves* of sixteen) and only the blocks of sixteen l below which W holds anything under the k at hand (a list
-// made with the plan; T is read nowhere else).  Sixteen blocks make a *round*:
+// (two *halves* of sixteen; H = 1: one) and only the blocks of sixteen l below which W holds anything under the k at hand (a
+// list made with the plan; T is read nowhere else).  Sixteen blocks make a *round*:
 //   producer: wavefront w computes T^t of the blocks w and w + 8 for both halves, so that four operands (two
 //     8-byte pieces of V's rows, one 16-byte read of Uc) feed four matrix instructions.  The union rows stand in the
 //     order (first half only, both, second half only): a batch of eight rows that a half does not hold costs that
 //     half nothing, so 32 slices never take more matrix instructions than twice 16 would.
 //   consumer: split by m.  Wavefront w owns half w % 2 and the m tiles x = (w / 2) mod 4, + 4, + 8, ... (seven
-//     accumulator tiles, kept in registers across all k of the workgroup).  The two wavefronts of a SIMD own tiles of
-//     one parity: a block of W spans two or three neighbouring tiles, which so spread over the SIMDs.  The T^t of a
-//     round go through LDS; W's tiles come straight from memory, four ahead, the first four of them before the
-//     producer starts.  A wavefront finds its tiles of a round by a prefix sum over the blocks' masks.
+//     accumulator tiles, kept in registers across all k of the workgroup); with one half the tiles w mod 8, + 8, ... (four).
+//     The two wavefronts of a SIMD own tiles of one parity: a block of W spans two or three neighbouring tiles, which so
+//     spread over the SIMDs.  The T^t of a round go through LDS; W's tiles come straight from memory, eight ahead, the first
+//     four of them before the producer starts.  A wavefront finds its tiles of a round by a prefix sum over the blocks' masks.
 // Two barriers a round, around the writes of T^t: a wavefront with few tiles goes on to the next round's producer.
 // V's loads run three batches ahead across rounds; a round is padded to whole groups of four batches, whose empty
 // batches load and do nothing.
-// 2000 x 2000 x 400 in blocks of 100 x 100 x 20 (356 M matrix instructions, 9.7 ms at the 28 ns one takes): 23.2 -> 15.6 ms.
+// 2000 x 2000 x 400 in blocks of 100 x 100 x 20 (356 M matrix instructions, 9.7 ms at the 28 ns one takes): 23.4 -> 15.8 ms.
 // The form before took 16 slices at a time: one 8-byte piece of V and one of Uc for every instruction, 363 M of them.
-// Of a workgroup's time the producer takes 40 % (8.4 us a round of 9.1 us of matrix instructions: it is bound by
-// them), the consumer 26 %, waiting at the two barriers 18 %, finding W's tiles 4 %, everything between two k 12 %
-// (16 us of latencies).  V's addresses made one cache line change nothing.
+// Of a workgroup's time the producer takes 40 %, the consumer 26 %, waiting at the two barriers 18 %, finding W's tiles 4 %,
+// everything between two k 12 % (16 us of latencies).
+// H = 1 is for networks that leave compute units with a pair or less: half the matrix instructions of a pair follow one
+// another, and two lane rows fetch a slice's leaves.  Where the line lies stands with the plan's choice (choose_cut).
 constexpr int kOwnWaves = 8;
-constexpr int kOwnHalves = 2;
 constexpr int kOwnCap = kSpUnionRows;                                   // union rows of Uc per pass (78 KB)
-constexpr int kOwnHeld = 24;                                            // leaves per lane kept between mask and scatter
+constexpr int kOwnHeld = 24;                                            // leaves per lane and half kept between mask and scatter
 constexpr int kOwnRows = 8;                                             // union rows of a batch (two K-steps)
 constexpr int kOwnRing = 4;                                             // batches of a group = stages of V's ring
 constexpr int kOwnBlocks = 2 * kOwnWaves;                               // blocks of l in a round
 constexpr int kOwnChunk = 8;                                            // rounds whose blocks a wavefront holds (128 blocks)
-constexpr int kOwnClasses = 4;                                          // m tile mod 4 -> pair of wavefronts
-constexpr int kOwnZ = (kSpMaxMTiles + kOwnClasses - 1) / kOwnClasses;   // accumulator tiles per wavefront
+// with H halves: m tile mod 8 / H -> H wavefronts, and accumulator tiles per wavefront
+constexpr int own_classes(int h) { return kOwnWaves / h; }
+constexpr int own_z(int h) { return (kSpMaxMTiles + own_classes(h) - 1) / own_classes(h); }
+constexpr int kOwnNoZ = 7;                                              // the accumulator of a place behind a list: none
 constexpr int kOwnList = 128;                                           // places for a wavefront's W tiles of a round
 constexpr int kOwnOffsets = (kOwnCap + kOwnRows * kOwnRing - 1) / (kOwnRows * kOwnRing) * (kOwnRows * kOwnRing);
 constexpr int kOwnWRing = 8;                                            // W tiles in flight in the consumer ...
 constexpr int kOwnWAhead = 4;                                           // ... and beside the producer
-static_assert(kOwnBlocks * kOwnZ + 2 * kOwnWRing <= kOwnList && kOwnList == 2 * 64, "a wavefront's list of W tiles lies in two registers");
-static_assert(kSpGroupWide == 16 * kOwnHalves && kOwnZ == 7, "slices of a workgroup; accumulators that the consumer tests for");
+static_assert(kOwnBlocks * own_z(2) + 2 * kOwnWRing <= kOwnList && kOwnList == 2 * 64, "a wavefront's list of W tiles lies in two registers");
+static_assert(kSpGroupWide == 32 && own_z(2) == 7 && own_z(1) == 4, "slices of a workgroup; accumulators that the consumer tests for");
 
 // LDS: Uc, T^t, ranks of the mask words, offsets of V's rows (read 16 bytes at a time), masks, lists, scan
-__host__ __device__ constexpr size_t sptn3_owned_offsets_at(int nwords) {
-    return size_t(kOwnCap * 32 + kOwnBlocks * 2 * 256) * 8 + size_t((nwords + 1) & ~1) * 8;
+__host__ __device__ constexpr size_t sptn3_owned_offsets_at(int nwords, int h) {
+    return size_t(kOwnCap * 16 + kOwnBlocks * 256) * size_t(h) * 8 + size_t((nwords + 1) & ~1) * 8;
 }
-__host__ __device__ constexpr size_t sptn3_owned_lds(int nwords) {
-    return sptn3_owned_offsets_at(nwords) + size_t(kOwnOffsets) * 4 + size_t(nwords) * 8 + size_t(kOwnWaves * kOwnList) * 2 + 256;
+__host__ __device__ constexpr size_t sptn3_owned_lds(int nwords, int h) {
+    return sptn3_owned_offsets_at(nwords, h) + size_t(kOwnOffsets) * 4 + size_t((nwords + 1) & ~1) * 4 * size_t(h) +
+           size_t(kOwnWaves * kOwnList) * 2 + 256;
 }
-static_assert(sptn3_owned_offsets_at(1) % 16 == 0 && sptn3_owned_offsets_at(2) % 16 == 0 && sptn3_owned_lds(1) % 8 == 0,
+static_assert(sptn3_owned_offsets_at(1, 1) % 16 == 0 && sptn3_owned_offsets_at(2, 1) % 16 == 0 && sptn3_owned_offsets_at(1, 2) % 16 == 0 &&
+              sptn3_owned_offsets_at(2, 2) % 16 == 0 && sptn3_owned_lds(1, 1) % 8 == 0 && sptn3_owned_lds(1, 2) % 8 == 0,
               "16-byte reads of the offsets, 8-byte ones of the scan");
-static_assert(sptn3_owned_lds(29696 / 32) <= 160 * 1024, "J up to 29 696");
+static_assert(sptn3_owned_lds(29696 / 32, 2) <= 160 * 1024, "J up to 29 696");
 
 // orders LDS between the wavefronts of a workgroup without waiting for loads from memory in flight
 __device__ __forceinline__ void sp_lds_barrier() {
@@ -510,21 +515,31 @@ __device__ __forceinline__ void sp_lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+template <int... I, typename F>
+__device__ __forceinline__ void sp_each(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
 __device__ inline uint64_t shfl_up_u64(uint64_t x, int d) {
     const uint32_t lo = __shfl_up(uint32_t(x), d), hi = __shfl_up(uint32_t(x >> 32), d);
     return uint64_t(hi) << 32 | lo;
 }
 
+template <int H>
 __global__ void __launch_bounds__(64 * kOwnWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 sptn3_owned_kernel(Sptn3TileArgs a) {
+    constexpr int kClasses = own_classes(H), kZ = own_z(H), kSlices = 16 * H;
+    constexpr int kLeafLanes = 64 * kOwnWaves / kSlices;                  // lanes of a slice between two k: one lane row, or two
+    using Col = typename std::conditional<H == 2, v2d, double>::type;     // what one row of Uc holds under a column
+    using lds_col = __attribute__((address_space(3))) Col;
     extern __shared__ __align__(16) unsigned char smem[];
-    double *Uc = reinterpret_cast<double *>(smem);                        // kOwnCap x 16 columns x 2 halves
-    double *Tx = Uc + kOwnCap * 32;                                       // kOwnBlocks x 2 halves x 256
-    uint64_t *wpre = reinterpret_cast<uint64_t *>(Tx + kOwnBlocks * 2 * 256);  // nwords: ranks, 21 bits a category
-    uint32_t *jl = reinterpret_cast<uint32_t *>(smem + sptn3_owned_offsets_at(a.nwords));  // kOwnOffsets: byte offsets of V's rows
-    uint32_t *mask = jl + kOwnOffsets;                                    // 2 x nwords
-    uint16_t *lists = reinterpret_cast<uint16_t *>(mask + 2 * a.nwords);  // kOwnWaves x kOwnList
-    uint64_t *scan = reinterpret_cast<uint64_t *>(smem + sptn3_owned_lds(a.nwords) - 64);  // kOwnWaves
+    double *Uc = reinterpret_cast<double *>(smem);                        // kOwnCap x 16 columns x H halves
+    double *Tx = Uc + kOwnCap * 16 * H;                                   // kOwnBlocks x H halves x 256
+    uint64_t *wpre = reinterpret_cast<uint64_t *>(Tx + kOwnBlocks * H * 256);  // nwords: ranks, 21 bits a category
+    uint32_t *jl = reinterpret_cast<uint32_t *>(smem + sptn3_owned_offsets_at(a.nwords, H));  // kOwnOffsets: byte offsets of V's rows
+    uint32_t *mask = jl + kOwnOffsets;                                    // H x nwords
+    uint16_t *lists = reinterpret_cast<uint16_t *>(mask + H * ((a.nwords + 1) & ~1));  // kOwnWaves x kOwnList
+    uint64_t *scan = reinterpret_cast<uint64_t *>(smem + sptn3_owned_lds(a.nwords, H) - 64);  // kOwnWaves
 
     const int tid = threadIdx.x, lane = tid & 63, slot = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -533,12 +548,12 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     const char *Vbytes = reinterpret_cast<const char *>(a.V);
     const uint32_t lane16 = uint32_t(lane) * 16u;
     const int nwords = a.nwords;
-    const lds_v2d *UcV = (const lds_v2d *)(Uc);
+    const lds_col *UcV = (const lds_col *)(Uc);
     const lds_v2d *TxV = (const lds_v2d *)(Tx);
-    const int my_half = wave & 1, my_class = wave >> 1;
+    const int my_half = wave & (H - 1), my_class = wave / H;
     uint32_t own = 0u;                                                    // m tiles of this wavefront
 #pragma unroll
-    for (int x = 0; x < kOwnZ; ++x) own |= 1u << (my_class + kOwnClasses * x);
+    for (int x = 0; x < kZ; ++x) own |= my_class + kClasses * x < 32 ? 1u << (my_class + kClasses * x) : 0u;
     uint16_t *list = lists + wave * kOwnList;
 
     // A workgroup per compute unit, with a list of (k chunk, part of l, group) triples made by the plan.
@@ -546,19 +561,17 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     const int logical = __builtin_amdgcn_readfirstlane(a.work[item]);
     if (logical < 0) break;
     const int group = logical % a.n_groups, kc = logical / a.n_groups, chunk = kc / a.l_parts, part = kc % a.l_parts;
-    const int64_t s0 = int64_t(group) * kSpGroupWide;
+    const int64_t s0 = int64_t(group) * kSlices;
     // lane sl (and sl + 32) holds the cursor of slice s0 + sl, its place in the k chunk, and the k there
     int64_t cur = 0, end = 0;
     int32_t kk = INT32_MAX;
-    if (s0 + (lane & 31) < a.slices) {
+    if ((lane & 31) < kSlices && s0 + (lane & 31) < a.slices) {
         const int64_t at = int64_t(chunk) * a.slices + s0 + (lane & 31);
         cur = a.chunk_fiber[at];
         end = a.chunk_fiber[at + a.slices];
         kk = a.chunk_k[at];
     }
-    v4d accZ[kOwnZ];
-#pragma unroll
-    for (int x = 0; x < kOwnZ; ++x) accZ[x] = v4d{0.0, 0.0, 0.0, 0.0};
+    v4d accZ[kZ] = {};                                                    // (indexed by constants only, see the end)
 
     // Walk over the k that any of the slices holds.  What a k needs from the tables is fetched while the one before it
     // is prepared: its fibers' leaves, its root in W, and (kk) the k that follows in every slice.
@@ -588,36 +601,38 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
         const int n_all = __builtin_amdgcn_readfirstlane(a.wcell_ptr[cell_row + 1]) - cell_all;
         const int cell0 = cell_all + n_all * part / a.l_parts;
         const int cells = cell_all + n_all * (part + 1) / a.l_parts - cell0;
-        // one lane row per slice: slice 4*wave + slot, of half wave / 4
-        const int irow = 4 * wave + slot;
+        // one lane row per slice: slice 4*wave + slot, of half wave / 4; with one half two, 16 leaves in turn
+        const int irow = (4 * wave + slot) & (kSlices - 1);
         const int64_t ea = __shfl(la, irow), eb = known ? __shfl(lb, irow) : ea;
-        uint32_t *my_mask = mask + (wave >> 2) * nwords;
-        double *my_col = Uc + (irow & 15) * 2 + (wave >> 2);
+        const int64_t e0 = ea + c + (H == 1 ? 16 * (wave >> 2) : 0);
+        uint32_t *my_mask = mask + (H == 2 ? wave >> 2 : 0) * nwords;
+        double *my_col = Uc + (irow & 15) * H + (H == 2 ? wave >> 2 : 0);
         // the first leaves of a lane stay in registers for the scatter below
-        int32_t jheld[kOwnHeld];
-        double vheld[kOwnHeld];
+        constexpr int kHeld = kOwnHeld * H / 2;
+        int32_t jheld[kHeld];
+        double vheld[kHeld];
 #pragma unroll
-        for (int h = 0; h < kOwnHeld; ++h) {
-            const int64_t e = ea + c + 16 * h;
+        for (int h = 0; h < kHeld; ++h) {
+            const int64_t e = e0 + kLeafLanes * h;
             jheld[h] = e < eb ? a.uidx2[e] : -1;
             vheld[h] = e < eb ? a.uvals[e] : 0.0;
         }
         sp_lds_barrier();                                                 // LDS of the previous k is free
-        for (int w = tid; w < 2 * nwords; w += 64 * kOwnWaves) mask[w] = 0u;
-        for (int x = tid; x < min(kOwnCap, 32 * nwords) * 16; x += 64 * kOwnWaves) reinterpret_cast<v2d *>(Uc)[x] = v2d{0.0, 0.0};
+        for (int w = tid; w < H * nwords; w += 64 * kOwnWaves) mask[w] = 0u;
+        for (int x = tid; x < min(kOwnCap, 32 * nwords) * 8 * H; x += 64 * kOwnWaves) reinterpret_cast<v2d *>(Uc)[x] = v2d{0.0, 0.0};
         for (int x = tid; x < kOwnOffsets; x += 64 * kOwnWaves) jl[x] = 0u;
         sp_lds_barrier();
         // (neighbouring leaves tend to share a word, on which the lanes' atomics would queue: the bits of the lanes of a
         // row with the word of its first lane are joined first)
 #pragma unroll
-        for (int h = 0; h < kOwnHeld; ++h) {
+        for (int h = 0; h < kHeld; ++h) {
             const int word = jheld[h] >> 5;                               // (-1: no leaf)
             const uint32_t bit = jheld[h] >= 0 ? 1u << (jheld[h] & 31) : 0u;
             const int word0 = row_first(word);
             const uint32_t joined = row_or(word == word0 ? bit : 0u);
             if (bit && (c == 0 || word != word0)) atomicOr(&my_mask[word], c == 0 ? joined : bit);
         }
-        for (int64_t e = ea + c + 16 * kOwnHeld; e < eb; e += 16) {
+        for (int64_t e = e0 + kLeafLanes * kHeld; e < eb; e += kLeafLanes) {
             const int32_t j = a.uidx2[e];
             atomicOr(&my_mask[j >> 5], 1u << (j & 31));
         }
@@ -631,7 +646,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
             const int w = 2 * tid + q;
             cnt[q] = 0;
             if (w < nwords) {
-                const uint32_t m0 = mask[w], m1 = mask[nwords + w];
+                const uint32_t m0 = mask[w], m1 = H == 2 ? mask[nwords + w] : 0u;
                 cnt[q] = uint64_t(__popc(m0 & ~m1)) | uint64_t(__popc(m0 & m1)) << 21 | uint64_t(__popc(m1 & ~m0)) << 42;
             }
             mine += cnt[q];
@@ -667,7 +682,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
         // (r / 4) % 2, lane row r % 4).  The first pass takes the leaves held in registers and finds both cleared.
         auto prepare = [&](int p0, int np, auto first) {
             if (!decltype(first)::value) {
-                for (int x = tid; x < kOwnCap * 16; x += 64 * kOwnWaves) reinterpret_cast<v2d *>(Uc)[x] = v2d{0.0, 0.0};
+                for (int x = tid; x < kOwnCap * 8 * H; x += 64 * kOwnWaves) reinterpret_cast<v2d *>(Uc)[x] = v2d{0.0, 0.0};
                 for (int x = tid; x < kOwnOffsets; x += 64 * kOwnWaves) jl[x] = 0u;
                 sp_lds_barrier();
             }
@@ -679,7 +694,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
             };
             for (int x = tid; x < 8 * nwords; x += 64 * kOwnWaves) {      // four bits of a mask word each
                 const int w = x >> 3;
-                const uint32_t m0 = mask[w], m1 = mask[nwords + w];
+                const uint32_t m0 = mask[w], m1 = H == 2 ? mask[nwords + w] : 0u;
                 const uint64_t pre = wpre[w];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
@@ -691,15 +706,15 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                 }
             }
             auto place = [&](int32_t j, double v) {
-                const int r = place_of(1u << (j & 31), mask[j >> 5], mask[nwords + (j >> 5)], wpre[j >> 5]);
-                if (r >= 0 && r < np) my_col[r * 32] = v;
+                const int r = place_of(1u << (j & 31), mask[j >> 5], H == 2 ? mask[nwords + (j >> 5)] : 0u, wpre[j >> 5]);
+                if (r >= 0 && r < np) my_col[r * kSlices] = v;
             };
             if (decltype(first)::value) {
 #pragma unroll
-                for (int h = 0; h < kOwnHeld; ++h)
+                for (int h = 0; h < kHeld; ++h)
                     if (jheld[h] >= 0) place(jheld[h], vheld[h]);
             }
-            for (int64_t e = ea + c + (decltype(first)::value ? 16 * kOwnHeld : 0); e < eb; e += 16)
+            for (int64_t e = e0 + (decltype(first)::value ? kLeafLanes * kHeld : 0); e < eb; e += kLeafLanes)
                 place(a.uidx2[e], a.uvals[e]);
             sp_lds_barrier();
         };
@@ -733,7 +748,11 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                     }
                 };
                 double V[kOwnRing][2][2];                                 // [batch of the group][K-step][block]
-                v2d U[2][2];                                              // [parity of the batch][K-step] halves
+                Col U[2][2];                                              // [parity of the batch][K-step] halves
+                auto half = [](const Col &u, int h) -> double {
+                    if constexpr (H == 2) return u[h];
+                    else return u;
+                };
                 uint4 J[2];                                               // V offsets of the group's eight K-steps
                 auto offset = [&](int i) -> uint32_t {
                     const uint4 &q = J[i >> 2];
@@ -751,7 +770,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                         for (int d = 0; d < 2; ++d)
                             v[ks][d] = *reinterpret_cast<const double *>(Vbytes + (offset(2 * u + ks) + col[d]));
                 };
-                auto read_u = [&](v2d (&u)[2], int b) {                   // (batches behind the last row read T^t: unused)
+                auto read_u = [&](Col (&u)[2], int b) {                   // (batches behind the last row read T^t: unused)
                     u[0] = UcV[b * 128 + lane];
                     u[1] = UcV[b * 128 + 64 + lane];
                 };
@@ -777,17 +796,17 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                         if (c >= d) upto += up;
                     }
                     // (nothing to do where the half holds no slice with this k)
-                    const bool idle = my_half ? n_union == n_one : end0 == 0;
+                    const bool idle = H == 2 && (my_half ? n_union == n_one : end0 == 0);
                     const int n_tiles = idle ? 0 : __builtin_amdgcn_readlane(upto, kOwnBlocks - 1);
                     int at = upto - __popc(todo);
                     while (todo) {
                         const int b = __builtin_ctz(todo);
                         todo &= todo - 1u;
                         list[at++] = uint16_t((bf - first + __popc(bm & ((1u << b) - 1u))) | uint32_t(c) << 9 |
-                                              uint32_t(b >> 2) << 13);
+                                              uint32_t(b / kClasses) << 13);
                     }
                     // (behind the list's end: the round's first tile, added to nothing)
-                    if (lane < 2 * kOwnWRing) list[n_tiles + lane] = uint16_t(kOwnZ << 13);
+                    if (lane < 2 * kOwnWRing) list[n_tiles + lane] = uint16_t(kOwnNoZ << 13);
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     const uint32_t code0 = list[lane], code1 = list[64 + lane];
                     const char *round_tiles = reinterpret_cast<const char *>(a.wtiles + int64_t(first) * 256);
@@ -803,11 +822,11 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                     for (int u = 0; u < kOwnWAhead; ++u) fetch(u, code0, u);
 
                     // ---- producer ----
-                    v4d T[2][2];                                          // [block][half]
+                    v4d T[2][H];                                          // [block][half]
 #pragma unroll
                     for (int d = 0; d < 2; ++d)
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) T[d][h] = v4d{0.0, 0.0, 0.0, 0.0};
+                        for (int h = 0; h < H; ++h) T[d][h] = v4d{0.0, 0.0, 0.0, 0.0};
                     // (simple tests without alternatives: an if / else around matrix instructions makes the compiler copy
                     // the accumulators where the paths meet)
                     const bool two = here - r * kOwnBlocks > kOwnWaves + wave, some = here - r * kOwnBlocks > wave;
@@ -830,19 +849,21 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
 #pragma unroll
                             for (int d = 0; d < 2; ++d) {
                                 if (row < stop0[d]) {
-                                    T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][0][d], U[u & 1][0].x, T[d][0], 0, 0, 0);
-                                    T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][1][d], U[u & 1][1].x, T[d][0], 0, 0, 0);
+                                    T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][0][d], half(U[u & 1][0], 0), T[d][0], 0, 0, 0);
+                                    T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][1][d], half(U[u & 1][1], 0), T[d][0], 0, 0, 0);
                                 }
-                                if (row1 < stop1[d]) {
-                                    T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][0][d], U[u & 1][0].y, T[d][1], 0, 0, 0);
-                                    T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][1][d], U[u & 1][1].y, T[d][1], 0, 0, 0);
+                                if constexpr (H == 2) {
+                                    if (row1 < stop1[d]) {
+                                        T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][0][d], half(U[u & 1][0], 1), T[d][1], 0, 0, 0);
+                                        T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][1][d], half(U[u & 1][1], 1), T[d][1], 0, 0, 0);
+                                    }
                                 }
                             }
                         }
                     };
                     // the groups whose rows both halves hold, then those with tests
                     int g = 0;
-                    if (n_one <= p0) {
+                    if (H == 1 || n_one <= p0) {
                         const int whole = min(min(row_end0, np) / (kOwnRows * kOwnRing), n_groups - 1);
                         for (; g < whole; ++g) {
 #pragma unroll
@@ -859,8 +880,9 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                                 for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
                                     for (int d = 0; d < 2; ++d) {
-                                        T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][ks][d], U[u & 1][ks].x, T[d][0], 0, 0, 0);
-                                        T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][ks][d], U[u & 1][ks].y, T[d][1], 0, 0, 0);
+                                        T[d][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][ks][d], half(U[u & 1][ks], 0), T[d][0], 0, 0, 0);
+                                        if constexpr (H == 2)
+                                            T[d][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[u][ks][d], half(U[u & 1][ks], 1), T[d][1], 0, 0, 0);
                                     }
                             }
                         }
@@ -874,8 +896,8 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
 #pragma unroll
                     for (int d = 0; d < 2; ++d)
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            double *tp = Tx + ((d * kOwnWaves + wave) * 2 + h) * 256 + lane * 2;
+                        for (int h = 0; h < H; ++h) {
+                            double *tp = Tx + ((d * kOwnWaves + wave) * H + h) * 256 + lane * 2;
                             *reinterpret_cast<v2d *>(tp) = v2d{T[d][h].x, T[d][h].y};
                             *reinterpret_cast<v2d *>(tp + 128) = v2d{T[d][h].z, T[d][h].w};
                         }
@@ -887,7 +909,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                     // ---- consumer: T^t of the next tile is read while a tile is multiplied ----
                     v2d Tr[2][2];
                     auto read_t = [&](v2d (&t)[2], uint32_t code) {
-                        const lds_v2d *tp = TxV + (code >> 9 & 15u) * 256 + my_half * 128 + lane;
+                        const lds_v2d *tp = TxV + ((code >> 9 & 15u) * H + my_half) * 128 + lane;
                         t[0] = tp[0];
                         t[1] = tp[64];
                     };
@@ -907,16 +929,18 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
                                 z = __builtin_amdgcn_mfma_f64_16x16x4f64(W[u][1].x, Tr[u & 1][1].x, z, 0, 0, 0);
                                 z = __builtin_amdgcn_mfma_f64_16x16x4f64(W[u][1].y, Tr[u & 1][1].y, z, 0, 0, 0);
                             };
-                            if (hot & 0x0fu) {
+                            if (H == 1 || hot & 0x0fu) {
                                 if (hot & 0x01u) add(accZ[0]);
                                 if (hot & 0x02u) add(accZ[1]);
                                 if (hot & 0x04u) add(accZ[2]);
                                 if (hot & 0x08u) add(accZ[3]);
                             }
-                            if (hot & 0x70u) {
-                                if (hot & 0x10u) add(accZ[4]);
-                                if (hot & 0x20u) add(accZ[5]);
-                                if (hot & 0x40u) add(accZ[6]);
+                            if constexpr (H == 2) {
+                                if (hot & 0x70u) {
+                                    if (hot & 0x10u) add(accZ[4]);
+                                    if (hot & 0x20u) add(accZ[5]);
+                                    if (hot & 0x40u) add(accZ[6]);
+                                }
                             }
                             fetch(u, codes, e0 + u + kOwnWRing);
                         }
@@ -937,15 +961,17 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     if (s < a.slices) {
         const int64_t row = a.compact ? s : int64_t(a.uidx0[s]);
         double *dst = a.n_kc == 1 ? a.out + row * M : a.partial + (int64_t(kc) * a.slices + s) * M;
-#pragma unroll
-        for (int x = 0; x < kOwnZ; ++x) {
-            const int mt = my_class + kOwnClasses * x;
+        // (a loop over the tiles, though unrolled later, makes the compiler hold four of them as one vector of 32 registers,
+        // which it copies whole at every test of the consumer)
+        sp_each(std::make_integer_sequence<int, kZ>{}, [&](auto X) {
+            constexpr int x = decltype(X)::value;
+            const int mt = my_class + kClasses * x;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * mt + slot + 4 * v;
                 if (mt < a.MT && m < M) dst[m] = accZ[x][v];
             }
-        }
+        });
     }
     }
 }
@@ -957,7 +983,7 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
 constexpr int64_t kSpFixupLaunch = int64_t(1) << 31;
 __global__ void sptn3_fixup_kernel(int64_t first, int64_t rows, int64_t slices, int64_t M, int n_kc,
                                    const int32_t *__restrict__ slice_of_row, const double *__restrict__ partial,
-                                   const uint8_t *__restrict__ present, int n_groups, double *out) {
+                                   const uint8_t *__restrict__ present, int n_groups, int group_shift, double *out) {
     const int64_t x = first + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (x >= rows * M) return;
     const int64_t row = x / M, m = x - row * M, s = slice_of_row ? slice_of_row[row] : row;
@@ -971,7 +997,7 @@ __global__ void sptn3_fixup_kernel(int64_t first, int64_t rows, int64_t slices, 
         bool has[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u)
-            has[u] = kc + u < n_kc && (!present || present[int64_t(min(kc + u, n_kc - 1)) * n_groups + s / kSpGroupWide]);
+            has[u] = kc + u < n_kc && (!present || present[int64_t(min(kc + u, n_kc - 1)) * n_groups + (s >> group_shift)]);
 #pragma unroll
         for (int u = 0; u < 16; ++u) v[u] = partial[(int64_t(min(kc + u, n_kc - 1)) * slices + s) * M + m];
 #pragma unroll
@@ -980,7 +1006,7 @@ __global__ void sptn3_fixup_kernel(int64_t first, int64_t rows, int64_t slices, 
     out[x] = z;
 }
 
-bool sptn3_two_waves_fit(int nwords) { return sptn3_owned_lds(nwords) <= 160 * 1024; }
+bool sptn3_two_waves_fit(int nwords) { return sptn3_owned_lds(nwords, 2) <= 160 * 1024; }
 
 static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const double *const *dense, double *out,
                                           hipStream_t stream) {
@@ -1027,12 +1053,13 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
         CST_TRY(zero_fill(out, plan->out_rows * plan->row_elems, stream));
     if (a.slices == 0) return CONSTSTN_OK;
     // two wavefronts per SIMD (m tiles owned by wavefronts) when the plan chose it, else one (l tiles owned)
-    const size_t lds_owned = sptn3_owned_lds(a.nwords);
+    const size_t lds_owned = sptn3_owned_lds(a.nwords, plan->sp_halves);
     const bool owned = plan->sp_two_waves;
     {
         ProfScope prof(plan, stream);
         const unsigned n_wg = unsigned(a.n_groups) * unsigned(a.n_kc);
-        if (owned) sptn3_owned_kernel<<<dim3(unsigned(plan->sp_workers)), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
+        if (owned && plan->sp_halves == 1) sptn3_owned_kernel<1><<<dim3(unsigned(plan->sp_workers)), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
+        else if (owned) sptn3_owned_kernel<2><<<dim3(unsigned(plan->sp_workers)), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
         else sptn3_tiled_kernel<<<dim3((n_wg + 7) / 8 * 8), dim3(256), lds_bytes, stream>>>(a);
     }
     CST_HIP(hipGetLastError());
@@ -1043,7 +1070,7 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
             const int64_t here = std::min(rows * a.M - first, kSpFixupLaunch);
             sptn3_fixup_kernel<<<dim3(unsigned((here + 255) / 256)), dim3(256), 0, stream>>>(
                 first, rows, a.slices, a.M, a.n_kc, all ? nullptr : plan->sp_slice_of_row.p, a.partial,
-                owned ? plan->sp_present.p : nullptr, a.n_groups, out);
+                owned ? plan->sp_present.p : nullptr, a.n_groups, plan->sp_group() == kSpGroupWide ? 5 : 4, out);
             CST_HIP(hipGetLastError());
         }
     }
@@ -1055,7 +1082,9 @@ conststn_status prepare_sptn3_launch(conststn_plan_s *plan) {
     plan->sp_xcd_ranges = plan->opt("sptn3_xcd", 0) == 1;
     CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sptn3_tiled_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-    CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sptn3_owned_kernel),
+    CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sptn3_owned_kernel<1>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    CST_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(sptn3_owned_kernel<2>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     return CONSTSTN_OK;
 }

@@ -1121,16 +1121,21 @@ __global__ void w_first_u32_kernel(int64_t n, const int64_t *__restrict__ first,
     if (x < n) out[x] = uint32_t(first[x]);
 }
 
-// Cost of a (k chunk, group of slices) pair in matrix instructions, one workgroup per pair: the tiled kernels take the
-// pairs in falling order of it.  Per k: the producer's rows of the union of each half's j (rounded to batches of eight)
-// x blocks of l / 4, the consumer's W tiles x 4 per half and pass over the union, and what a pass and its rounds of
-// sixteen blocks cost beside them (20 us and 4 us of a workgroup at 2000 x 2000 x 400, which has four SIMDs); per pair 5 us.
-constexpr int kSpCostPair = 700, kSpCostPass = 3000, kSpCostRound = 600;
+// Cost of a (k chunk, group of slices) pair in ns of its workgroup, one workgroup per pair: the tiled kernels take the
+// pairs in falling order of it.  Per k: matrix instructions of the producer (rows of the union of each half's j, rounded to
+// batches of eight, x blocks of l / 4) and of the consumer (W tiles x 4 per half and pass over the union), and what a pass and
+// its rounds of sixteen blocks take beside them; per pair what its start and end take.
+struct SpCost { int pair, pass, round, producer, consumer; };
+// One wavefront per SIMD; two with one half of slices; two with two halves.  The last as measured at 2000 x 2000 x 400.  Those
+// of one half so that the longest lists of both compare as their times do, over 46 networks from 44 x 280 x 56 (14 us) to
+// 1500 x 1780 x 180 (3 ms).
+constexpr SpCost kSpCost[3] = {{4900, 21000, 4200, 7, 7}, {3000, 11500, 2400, 9, 9}, {4900, 21000, 4200, 7, 7}};
+constexpr int kSpFixupNs = 4000, kSpFixupPartNs = 120;    // the pass that adds the partial results, and each part of a row
 __global__ void __launch_bounds__(256)
 sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int64_t *__restrict__ ptr1, const int32_t *__restrict__ idx1,
                     const int32_t *__restrict__ idx2, const int64_t *__restrict__ w_root_of_k, const int32_t *__restrict__ cell_ptr,
                     const SpCell *__restrict__ cells, int64_t k_per, int l_parts, int n_groups, int group, int nwords, int rows_per_pass,
-                    unsigned long long *cost) {
+                    SpCost ns, unsigned long long *cost) {
     extern __shared__ uint32_t sp_cost_mask[];                            // 2 x nwords
     __shared__ int total[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1150,7 +1155,7 @@ sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int6
         cur = lower(na, k0);
         end = lower(cur, k0 + k_per);
     }
-    unsigned long long sum = kSpCostPair;
+    unsigned long long sum = ns.pair;
     for (;;) {
         const int32_t kk = cur < end ? idx1[cur] : INT32_MAX;
         int32_t k = kk;
@@ -1190,17 +1195,15 @@ sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int6
         const long long n_all = cell_ptr[root + 1] - cell_ptr[root];
         const long long c0 = cell_ptr[root] + n_all * part / l_parts, c1 = cell_ptr[root] + n_all * (part + 1) / l_parts, halves = (r0 > 0) + (r1 > 0);
         const long long tiles = c0 < c1 ? (long long)cells[c1 - 1].first + __popc(cells[c1 - 1].mask) - cells[c0].first : 0;
-        sum += (r0 + r1) * (c1 - c0) / 4 + passes * (tiles * 4 * halves + kSpCostPass + (c1 - c0 + 15) / 16 * kSpCostRound);
+        sum += (r0 + r1) * (c1 - c0) / 4 * ns.producer + passes * (tiles * 4 * halves * ns.consumer + ns.pass + (c1 - c0 + 15) / 16 * ns.round);
         __syncthreads();
     }
     if (tid == 0) cost[blockIdx.x] = sum;
 }
 
-__global__ void sp_pair_keys_kernel(int64_t n, const unsigned long long *__restrict__ cost, uint64_t *keys, uint32_t *ids,
-                                    uint8_t *present) {
+__global__ void sp_pair_keys_kernel(int64_t n, const unsigned long long *__restrict__ cost, uint64_t *keys, uint32_t *ids) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    present[i] = cost[i] != kSpCostPair ? 1 : 0;
     keys[i] = 0xffffffffu - min(cost[i] >> 4, 0xffffffffull);
     ids[i] = uint32_t(i);
 }
@@ -1241,11 +1244,51 @@ static int deal_pairs(const std::vector<uint32_t> &pairs, const std::vector<unsi
     return workers;
 }
 
-static conststn_status build_sp_wg_order(conststn_plan_s *plan) {
-    const conststn_csf_s *U = plan->X;
-    const int64_t groups = div_up(U->nodes[0], plan->sp_group()), n = groups * plan->sp_kc * plan->sp_l_parts;
+// A way to cut the network: groups of slices, chunks of the k range, parts of the blocks of l, and what the plan makes of it.
+struct SpCut {
+    int halves = 0;                        // of sixteen slices in a group, with two wavefronts per SIMD; 0: one wavefront
+    int64_t groups = 0, k_per = 0;
+    int kc = 1, l_parts = 1;
+    // with two wavefronts per SIMD
+    std::vector<int32_t> work;             // see deal_pairs
+    int workers = 0;
+    std::vector<uint8_t> present;          // pairs whose partial results are written
+    int64_t n_present = 0;
+    unsigned long long time = 0;           // ns of the longest list and of the fix-up pass
+
+    int slices() const { return std::max(halves, 1) * kSpGroup; }
+    int parts() const { return kc * l_parts; }
+    int64_t pairs() const { return groups * parts(); }
     // (where groups alone are far more than the chip holds, pairs go in their own order)
-    const bool by_cost = n > 1 && n <= (int64_t(1) << 20) && U->nodes[1] > 0;
+    bool by_cost() const { return pairs() > 1 && pairs() <= (int64_t(1) << 20); }
+};
+
+static SpCut cut_network(const conststn_plan_s *plan, int64_t K, int64_t LT, int halves) {
+    SpCut cut;
+    cut.halves = halves;
+    cut.groups = div_up(plan->X->nodes[0], cut.slices());
+    const int64_t want = plan->opt("sptn3_wgs", 8000);
+    // (more than 64 chunks only where that leaves less than four pairs per compute unit: a chunk costs a partial result)
+    const int64_t most = halves ? std::max<int64_t>(64, std::min<int64_t>(128, 4 * int64_t(plan->n_cus) / cut.groups)) : 64;
+    const int64_t n_kc = std::min<int64_t>(std::max<int64_t>(div_up(want, cut.groups), 1), std::min<int64_t>(K, most));
+    cut.k_per = div_up(K, n_kc);
+    cut.kc = int(div_up(K, cut.k_per));
+    // where the pairs are fewer than two per compute unit, each takes half of the blocks of l if that leaves it a round of
+    // sixteen: 7 groups x 60 chunks, 49 blocks, 114 -> 107 us
+    const bool few = halves && cut.groups * cut.kc < 2 * int64_t(plan->n_cus) && cut.groups * cut.kc * 2 <= want;
+    cut.l_parts = few && LT >= 32 ? 2 : 1;
+    return cut;
+}
+
+// The pairs of a cut in falling order of cost (`order`), and with two wavefronts per SIMD their lists: one workgroup per
+// compute unit, each pair to the workgroup with the least work so far, the heaviest first.  In the hardware's launch order
+// workgroups of unequal length left the compute units idle for 2.0 of 18.1 ms at 2000 x 2000 x 400.  Pairs of equal cost stand
+// in the order (k chunk, group), and neighbouring groups read the same W tiles and largely the same rows of V: runs of eight
+// stay on one XCD.
+static conststn_status order_pairs(const conststn_plan_s *plan, SpCut &cut, DevBuf<int32_t> &order_out) {
+    const conststn_csf_s *U = plan->X;
+    const int64_t n = cut.pairs();
+    const SpCost ns = kSpCost[cut.halves];
     DevBuf<unsigned long long> cost;
     DevBuf<uint64_t> ka, kb;
     DevBuf<uint32_t> ia, ib;
@@ -1254,49 +1297,64 @@ static conststn_status build_sp_wg_order(conststn_plan_s *plan) {
     CST_TRY(kb.alloc(n));
     CST_TRY(ia.alloc(n));
     CST_TRY(ib.alloc(n));
-    CST_TRY(plan->sp_present.alloc(n));
     const dim3 block(256);
-    if (by_cost) {
+    if (cut.by_cost()) {
         const int nwords = int(div_up(U->dims[U->mode_order[2]], 32));
         sp_pair_cost_kernel<<<dim3(unsigned(n)), block, size_t(nwords) * 8>>>(
             U->nodes[0], U->ptr[0].p, U->ptr[1].p, U->idx[1].p, U->idx[2].p, plan->w_root_of_k.p, plan->w_cell_ptr.p, plan->w_cells.p,
-            plan->sp_k_per, plan->sp_l_parts, int(groups), plan->sp_group(), nwords, kSpUnionRows, cost.p);
+            cut.k_per, cut.l_parts, int(cut.groups), cut.slices(), nwords, kSpUnionRows, ns, cost.p);
     } else {
         fill_i64_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(reinterpret_cast<int64_t *>(cost.p), n, 1);
     }
-    sp_pair_keys_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(n, cost.p, ka.p, ia.p, plan->sp_present.p);
+    sp_pair_keys_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(n, cost.p, ka.p, ia.p);
     CST_HIP(hipGetLastError());
     const uint64_t *ks = nullptr;
     const uint32_t *order = nullptr;
     CST_TRY(radix_sort_pairs_u64(ka.p, kb.p, ia.p, ib.p, n, 32, hipStream_t(0), &ks, &order));
-    if (!plan->sp_two_waves) {
-        CST_TRY(plan->sp_wg_order.alloc(size_t(n)));
-        CST_HIP(hipMemcpy(plan->sp_wg_order.p, order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToDevice));
+    if (!cut.halves) {
+        CST_TRY(order_out.alloc(size_t(n)));
+        CST_HIP(hipMemcpy(order_out.p, order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToDevice));
         CST_HIP(hipDeviceSynchronize());
         return CONSTSTN_OK;
     }
-    // Lists of pairs for one workgroup per compute unit, each pair to the workgroup with the least work so far, the
-    // heaviest first.  In the hardware's launch order workgroups of unequal length left the compute units idle for
-    // 2.0 of 18.1 ms at 2000 x 2000 x 400.  Pairs of equal cost stand in the order (k chunk, group), and neighbouring
-    // groups read the same W tiles and largely the same rows of V: runs of eight stay on one XCD.
-    std::vector<uint32_t> pairs;
-    std::vector<unsigned long long> costs;
-    std::vector<int32_t> work;
     try {
-        pairs.resize(size_t(n));
-        costs.resize(size_t(n));
+        std::vector<uint32_t> pairs(static_cast<size_t>(n));
+        std::vector<unsigned long long> costs(static_cast<size_t>(n));
         CST_HIP(hipMemcpy(pairs.data(), order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToHost));
         CST_HIP(hipMemcpy(costs.data(), cost.p, size_t(n) * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+        cut.present.resize(size_t(n));
+        cut.n_present = 0;
+        for (size_t i = 0; i < size_t(n); ++i) cut.n_present += cut.present[i] = costs[i] != (unsigned long long)ns.pair;
         // pairs without work write nothing, unless there is but one result to a row
-        if (plan->sp_kc * plan->sp_l_parts > 1)
-            while (!pairs.empty() && costs[pairs.back()] == kSpCostPair) pairs.pop_back();
-        plan->sp_workers = deal_pairs(pairs, costs, plan->n_cus, plan->opt("sptn3_xcd", 0) == 1, work);
+        if (cut.parts() > 1)
+            while (!pairs.empty() && !cut.present[pairs.back()]) pairs.pop_back();
+        cut.workers = deal_pairs(pairs, costs, plan->n_cus, plan->opt("sptn3_xcd", 0) == 1, cut.work);
+        std::vector<unsigned long long> load(size_t(cut.workers), 0);
+        for (size_t i = 0; i < cut.work.size(); ++i)
+            if (cut.work[i] >= 0) load[i % size_t(cut.workers)] += costs[size_t(cut.work[i])];
+        cut.time = *std::max_element(load.begin(), load.end()) +
+                   (cut.parts() > 1 ? kSpFixupNs + (unsigned long long)cut.parts() * kSpFixupPartNs : 0);
     } catch (const std::bad_alloc &) {
         set_error("no host memory for the lists of %lld work pairs", (long long)n);
         return CONSTSTN_ENOMEM;
     }
-    CST_TRY(plan->sp_work.alloc(work.size()));
-    CST_HIP(hipMemcpy(plan->sp_work.p, work.data(), work.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    return CONSTSTN_OK;
+}
+
+// With two wavefronts per SIMD: 32 slices to a workgroup, or 16.  32 read V and W half as often and wait half as often between
+// two k; 16 make twice the pairs, of each of which half the matrix instructions follow one another.  Where a compute unit has
+// one pair of 32 at most, that is the time: 116 x 200 x 12 takes 23.6 us with 32 and 16.8 with 16, 26 such networks 1.02 to
+// 1.41 times as long.  From eight pairs on 32 are faster (2000 x 2000 x 400: 15.8 ms against 17.9).  Between, both are dealt
+// and the one with the shorter time by the costs is taken: of 92 networks, 0.77 to 1.37 of one another, 1 % above the better
+// one on the mean and 7 % at most.
+static conststn_status choose_cut(const conststn_plan_s *plan, int64_t K, int64_t LT, SpCut &cut, DevBuf<int32_t> &order) {
+    const int64_t told = plan->opt("sptn3_slices", 0);
+    cut = cut_network(plan, K, LT, !plan->sp_two_waves ? 0 : told == kSpGroup ? 1 : 2);
+    CST_TRY(order_pairs(plan, cut, order));
+    if (!plan->sp_two_waves || told || !cut.by_cost() || cut.n_present >= 8 * int64_t(plan->n_cus)) return CONSTSTN_OK;
+    SpCut narrow = cut_network(plan, K, LT, 1);
+    CST_TRY(order_pairs(plan, narrow, order));
+    if (narrow.time < cut.time) cut = std::move(narrow);
     return CONSTSTN_OK;
 }
 
@@ -1393,17 +1451,12 @@ static conststn_status build_w_tiles(conststn_plan_s *plan) {
     CST_HIP(hipGetLastError());
     plan->sp_two_waves = plan->opt("sptn3_waves", 2) == 2 && sptn3_two_waves_fit(int((J + 31) / 32));
     // slices go in groups of 16 or 32; the k range is cut into chunks so that the grid fills the chip
-    const int64_t groups = div_up(U->nodes[0], plan->sp_group());
-    const int64_t want = plan->opt("sptn3_wgs", 8000);
-    // (more than 64 chunks only where that leaves less than four pairs per compute unit: a chunk costs a partial result)
-    const int64_t most = plan->sp_two_waves ? std::max<int64_t>(64, std::min<int64_t>(128, 4 * int64_t(plan->n_cus) / groups)) : 64;
-    int64_t n_kc = std::min<int64_t>(std::max<int64_t>(div_up(want, groups), 1), std::min<int64_t>(K, most));
-    plan->sp_k_per = div_up(K, n_kc);
-    plan->sp_kc = int(div_up(K, plan->sp_k_per));
-    // where the pairs are fewer than two per compute unit, each takes half of the blocks of l if that leaves it a round of
-    // sixteen: 7 groups x 60 chunks, 49 blocks, 114 -> 107 us
-    const bool few = plan->sp_two_waves && groups * plan->sp_kc < 2 * int64_t(plan->n_cus) && groups * plan->sp_kc * 2 <= want;
-    plan->sp_l_parts = few && LT >= 32 ? 2 : 1;
+    SpCut cut;
+    CST_TRY(choose_cut(plan, K, LT, cut, plan->sp_wg_order));
+    if (cut.halves) plan->sp_halves = cut.halves;
+    plan->sp_k_per = cut.k_per;
+    plan->sp_kc = cut.kc;
+    plan->sp_l_parts = cut.l_parts;
     if (plan->sp_kc * plan->sp_l_parts > 1)
         CST_TRY(plan->partial.alloc(size_t(plan->sp_kc) * size_t(plan->sp_l_parts) * size_t(U->nodes[0]) * size_t(M)));
     if (plan->sp_kc * plan->sp_l_parts > 1 && !plan->compact && U->nodes[0] < plan->out_rows) {
@@ -1413,8 +1466,12 @@ static conststn_status build_w_tiles(conststn_plan_s *plan) {
         CST_HIP(hipGetLastError());
     }
     plan->w_tiled = true;
-    CST_TRY(build_sp_wg_order(plan));
     if (plan->sp_two_waves) {
+        plan->sp_workers = cut.workers;
+        CST_TRY(plan->sp_work.alloc(cut.work.size()));
+        CST_HIP(hipMemcpy(plan->sp_work.p, cut.work.data(), cut.work.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        CST_TRY(plan->sp_present.alloc(cut.present.size()));
+        CST_HIP(hipMemcpy(plan->sp_present.p, cut.present.data(), cut.present.size(), hipMemcpyHostToDevice));
         const int64_t n = (int64_t(plan->sp_kc) + 1) * U->nodes[0];
         CST_TRY(plan->sp_chunk_fiber.alloc(size_t(n)));
         CST_TRY(plan->sp_chunk_k.alloc(size_t(n)));

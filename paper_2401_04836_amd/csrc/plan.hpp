@@ -270,7 +270,8 @@ struct conststn_plan_s {
     cst::DevBuf<int64_t> w_root_of_k;      // [K] root node of W holding index k, or -1
     bool w_tiled = false;                  // W also stored as dense 16 x 16 (l, m) tiles
     bool sp_two_waves = false;             // tiled kernel with two wavefronts per SIMD (m tiles owned by wavefronts)
-    int sp_group() const { return sp_two_waves ? cst::kSpGroupWide : cst::kSpGroup; }
+    int sp_halves = 2;                     // of sixteen slices that a workgroup of it takes
+    int sp_group() const { return sp_two_waves ? sp_halves * cst::kSpGroup : cst::kSpGroup; }
     int64_t n_w_tiles = 0;
     cst::DevBuf<uint32_t> w_tile_mask;     // [roots x ceil(L/16)] m tiles present
     cst::DevBuf<uint32_t> w_tile_first;    // [roots x ceil(L/16)] index of the first of them

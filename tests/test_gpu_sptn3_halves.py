@@ -1,4 +1,4 @@
-"""Three-tensor network on the kernel with two wavefronts per SIMD: numbers of slices on both sides of a half (16) and of a
+"""Three-tensor network on the kernel with two wavefronts per SIMD, in groups of 32 slices and of 16: numbers of slices on both sides of a half (16) and of a
 group (32), unions of j on both sides of a batch (8), of a group of batches (32) and of a pass (312), odd and even numbers of mask
 words (J = 31, 70, 2000; 33, 640), rows of the union that only one half holds, few pairs over many blocks of l (each pair takes half of them), slices and pairs without work, against the oracle."""
 import numpy as np
@@ -43,9 +43,9 @@ def test_halves_passes_and_parts(slices, J, shared, L, wgs):
     v = torch.from_numpy(V).cuda()
     want = oracle.sptn3(u, uv, (rows, J, K), V, wc, wv, (K, L, M))
     S_abs = oracle.sptn3_abs(u, uv, (rows, J, K), V, wc, wv, (K, L, M))
-    for flags in (0, cst.OUT_COMPACT):
-        pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], flags=flags, options=dict(sptn3_tiled=2, sptn3_wgs=wgs))
-        assert "two waves" in pl.describe()
+    for flags, cut in ((0, 32), (cst.OUT_COMPACT, 32), (0, 16), (cst.OUT_COMPACT, 16)):
+        pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], flags=flags, options=dict(sptn3_tiled=2, sptn3_wgs=wgs, sptn3_slices=cut))
+        assert "two waves" in pl.describe() and "slices %d" % cut in pl.describe()
         got = cst.execute(pl, [v]).cpu().numpy().reshape(-1, M)
         ref, bound = (want[row_of], S_abs[row_of]) if flags else (want, S_abs)
         assert not np.isnan(got).any() and not got[bound == 0].any()
@@ -53,8 +53,8 @@ def test_halves_passes_and_parts(slices, J, shared, L, wgs):
         assert oracle.rel_err(got, ref, bound) <= (J + K * L + 3) * 1.1e-16
 
 
-@pytest.mark.parametrize("waves", [2, 1])
-def test_more_elements_than_a_launch_has_threads_for(waves):
+@pytest.mark.parametrize("cut,waves", [(32, 2), (16, 2), (0, 1)])
+def test_more_elements_than_a_launch_has_threads_for(cut, waves):
     """A root mode of 10.8 M indices, of which forty hold anything, times 400: 2^32 elements and more, 35 GB.  Every row is
     written, those without a slice with zeros."""
     rows, M, J, K, L = (1 << 32) // 400 + 40_000, 400, 9, 5, 40
@@ -68,14 +68,14 @@ def test_more_elements_than_a_launch_has_threads_for(waves):
     wkey = np.unique(rng.integers(0, K * L * M, 3000))
     wc = [x.astype(np.int32) for x in np.unravel_index(wkey, (K, L, M))]
     uv, wv, V = rng.uniform(-1, 1, len(ukey)), rng.uniform(-1, 1, len(wkey)), rng.uniform(-1, 1, (J, L))
-    print("[case] %d rows of %d, waves %d" % (rows, M, waves), flush=True)
+    print("[case] %d rows of %d, waves %d, slices %d" % (rows, M, waves, cut), flush=True)
     up = lambda cs: [torch.from_numpy(x).cuda() for x in cs]
     U = cst.build_csf(up([at[u[0]].astype(np.int32), u[1], u[2]]), torch.from_numpy(uv).cuda(), (rows, J, K), [0, 2, 1])
     W = cst.build_csf(up(wc), torch.from_numpy(wv).cuda(), (K, L, M), [0, 1, 2])
     v = torch.from_numpy(V).cuda()
     want = oracle.sptn3(u, uv, (40, J, K), V, wc, wv, (K, L, M))
     S_abs = oracle.sptn3_abs(u, uv, (40, J, K), V, wc, wv, (K, L, M))
-    pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], options=dict(sptn3_tiled=2, sptn3_waves=waves))
+    pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], options=dict(sptn3_tiled=2, sptn3_waves=waves, sptn3_slices=cut))
     assert "k chunks 1 " not in pl.describe() + " "
     out = torch.full((rows * M,), 7.0, dtype=torch.float64, device="cuda")
     cst.execute(pl, [v], out=out)
@@ -86,3 +86,27 @@ def test_more_elements_than_a_launch_has_threads_for(waves):
     # a sum has at most J K x L products of three factors, in any order: (J + K L + 3) roundings along the longest chain
     assert oracle.rel_err(got, want, S_abs) <= (J + K * L + 3) * 1.1e-16
     assert nonzero == np.count_nonzero(want)
+
+
+@pytest.mark.parametrize("slices,J,K,cut", [(20, 60, 6, 16), (4096, 8, 64, 32)])
+def test_slices_of_a_group_follow_the_pairs_of_the_chip(slices, J, K, cut):
+    """Groups of 16 where a compute unit has one pair or none, of 32 where it has many; both forms give the same sums."""
+    rng = np.random.default_rng(slices)
+    L, M = 64, 48
+    u = [x.ravel().astype(np.int32) for x in np.meshgrid(np.arange(slices), np.arange(J), np.arange(K), indexing="ij")]
+    wc = [x.ravel().astype(np.int32) for x in np.meshgrid(np.arange(K), np.arange(L), np.arange(M), indexing="ij")]
+    uv, wv, V = rng.uniform(-1, 1, u[0].size), rng.uniform(-1, 1, wc[0].size), rng.uniform(-1, 1, (J, L))
+    print("[case] %d slices, J %d, K %d" % (slices, J, K), flush=True)
+    up = lambda cs: [torch.from_numpy(x).cuda() for x in cs]
+    U = cst.build_csf(up(u), torch.from_numpy(uv).cuda(), (slices, J, K), [0, 2, 1])
+    W = cst.build_csf(up(wc), torch.from_numpy(wv).cuda(), (K, L, M), [0, 1, 2])
+    v = torch.from_numpy(V).cuda()
+    want = np.tensordot(np.tensordot(uv.reshape(slices, J, K), V, (1, 0)), wv.reshape(K, L, M), ((1, 2), (0, 1)))
+    a, b, c = (np.abs(x) for x in (uv.reshape(slices, J, K), V, wv.reshape(K, L, M)))
+    S_abs = np.tensordot(np.tensordot(a, b, (1, 0)), c, ((1, 2), (0, 1)))
+    for told in (0, 16, 32):
+        pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)], options=dict(sptn3_slices=told))
+        assert "slices %d" % (told or cut) in pl.describe()
+        got = cst.execute(pl, [v]).cpu().numpy().reshape(slices, M)
+        # (J + K L + 3) roundings along the longest chain, on both sides
+        assert oracle.rel_err(got, want, S_abs) <= 2 * (J + K * L + 3) * 1.1e-16
