@@ -13,6 +13,7 @@
 #include <cstdlib>
 #include <functional>
 #include <new>
+#include <numeric>
 #include <utility>
 #include <vector>
 
@@ -1280,51 +1281,62 @@ static SpCut cut_network(const conststn_plan_s *plan, int64_t K, int64_t LT, int
     return cut;
 }
 
-// The pairs of a cut in falling order of cost (`order`), and with two wavefronts per SIMD their lists: one workgroup per
-// compute unit, each pair to the workgroup with the least work so far, the heaviest first.  In the hardware's launch order
-// workgroups of unequal length left the compute units idle for 2.0 of 18.1 ms at 2000 x 2000 x 400.  Pairs of equal cost stand
-// in the order (k chunk, group), and neighbouring groups read the same W tiles and largely the same rows of V: runs of eight
-// stay on one XCD.
-static conststn_status order_pairs(const conststn_plan_s *plan, SpCut &cut, DevBuf<int32_t> &order_out) {
+// Costs of the pairs of a cut, on the device.
+static conststn_status launch_pair_costs(const conststn_plan_s *plan, const SpCut &cut, unsigned long long *cost) {
     const conststn_csf_s *U = plan->X;
     const int64_t n = cut.pairs();
-    const SpCost ns = kSpCost[cut.halves];
-    DevBuf<unsigned long long> cost;
-    DevBuf<uint64_t> ka, kb;
-    DevBuf<uint32_t> ia, ib;
-    CST_TRY(cost.alloc(n));
-    CST_TRY(ka.alloc(n));
-    CST_TRY(kb.alloc(n));
-    CST_TRY(ia.alloc(n));
-    CST_TRY(ib.alloc(n));
-    const dim3 block(256);
     if (cut.by_cost()) {
         const int nwords = int(div_up(U->dims[U->mode_order[2]], 32));
-        sp_pair_cost_kernel<<<dim3(unsigned(n)), block, size_t(nwords) * 8>>>(
+        sp_pair_cost_kernel<<<dim3(unsigned(n)), dim3(256), size_t(nwords) * 8>>>(
             U->nodes[0], U->ptr[0].p, U->ptr[1].p, U->idx[1].p, U->idx[2].p, plan->w_root_of_k.p, plan->w_cell_ptr.p, plan->w_cells.p,
-            cut.k_per, cut.l_parts, int(cut.groups), cut.slices(), nwords, kSpUnionRows, ns, cost.p);
+            cut.k_per, cut.l_parts, int(cut.groups), cut.slices(), nwords, kSpUnionRows, kSpCost[cut.halves], cost);
     } else {
-        fill_i64_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(reinterpret_cast<int64_t *>(cost.p), n, 1);
+        fill_i64_kernel<<<dim3(unsigned(div_up(n, 256))), dim3(256)>>>(reinterpret_cast<int64_t *>(cost), n, 1);
     }
-    sp_pair_keys_kernel<<<dim3(unsigned(div_up(n, 256))), block>>>(n, cost.p, ka.p, ia.p);
+    CST_HIP(hipGetLastError());
+    return CONSTSTN_OK;
+}
+
+// Numbers of the n pairs in falling order of cost, pairs of equal cost in the order (k chunk, group); sorted on the device.
+static conststn_status sort_pairs(int64_t n, const unsigned long long *cost, void *out, hipMemcpyKind kind) {
+    DevBuf<uint64_t> ka, kb;
+    DevBuf<uint32_t> ia, ib;
+    CST_TRY(ka.alloc(size_t(n)));
+    CST_TRY(kb.alloc(size_t(n)));
+    CST_TRY(ia.alloc(size_t(n)));
+    CST_TRY(ib.alloc(size_t(n)));
+    sp_pair_keys_kernel<<<dim3(unsigned(div_up(n, 256))), dim3(256)>>>(n, cost, ka.p, ia.p);
     CST_HIP(hipGetLastError());
     const uint64_t *ks = nullptr;
     const uint32_t *order = nullptr;
     CST_TRY(radix_sort_pairs_u64(ka.p, kb.p, ia.p, ib.p, n, 32, hipStream_t(0), &ks, &order));
-    if (!cut.halves) {
-        CST_TRY(order_out.alloc(size_t(n)));
-        CST_HIP(hipMemcpy(order_out.p, order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToDevice));
-        CST_HIP(hipDeviceSynchronize());
-        return CONSTSTN_OK;
-    }
+    CST_HIP(hipMemcpy(out, order, size_t(n) * sizeof(uint32_t), kind));
+    CST_HIP(hipDeviceSynchronize());
+    return CONSTSTN_OK;
+}
+
+// The lists of a cut's pairs with two wavefronts per SIMD: one workgroup per compute unit, each pair to the workgroup with the
+// least work so far, the heaviest first.  In the hardware's launch order workgroups of unequal length left the compute units
+// idle for 2.0 of 18.1 ms at 2000 x 2000 x 400.  Neighbouring groups read the same W tiles and largely the same rows of V:
+// runs of eight stay on one XCD.
+// Up to kSpHostSort pairs are sorted on the host, which has the costs anyway: 5 us for 500, 180 for 4096, where the device's
+// sort with its launches, copy and waits takes 200 (a plan of 700 x 420 x 170 in 1254 and 2508 pairs: 0.77 ms against 0.97).
+constexpr int64_t kSpHostSort = 4096;
+static conststn_status deal_cut(const conststn_plan_s *plan, SpCut &cut, const unsigned long long *cost, const unsigned long long *host_cost) {
+    const int64_t n = cut.pairs();
     try {
+        const std::vector<unsigned long long> costs(host_cost, host_cost + n);
         std::vector<uint32_t> pairs(static_cast<size_t>(n));
-        std::vector<unsigned long long> costs(static_cast<size_t>(n));
-        CST_HIP(hipMemcpy(pairs.data(), order, size_t(n) * sizeof(uint32_t), hipMemcpyDeviceToHost));
-        CST_HIP(hipMemcpy(costs.data(), cost.p, size_t(n) * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+        if (n <= kSpHostSort) {
+            std::iota(pairs.begin(), pairs.end(), 0u);
+            std::stable_sort(pairs.begin(), pairs.end(), [&](uint32_t a, uint32_t b) { return costs[a] >> 4 > costs[b] >> 4; });
+        } else {
+            CST_TRY(sort_pairs(n, cost, pairs.data(), hipMemcpyDeviceToHost));
+        }
+        const unsigned long long none = (unsigned long long)kSpCost[cut.halves].pair;
         cut.present.resize(size_t(n));
         cut.n_present = 0;
-        for (size_t i = 0; i < size_t(n); ++i) cut.n_present += cut.present[i] = costs[i] != (unsigned long long)ns.pair;
+        for (size_t i = 0; i < size_t(n); ++i) cut.n_present += cut.present[i] = costs[i] != none;
         // pairs without work write nothing, unless there is but one result to a row
         if (cut.parts() > 1)
             while (!pairs.empty() && !cut.present[pairs.back()]) pairs.pop_back();
@@ -1348,12 +1360,36 @@ static conststn_status order_pairs(const conststn_plan_s *plan, SpCut &cut, DevB
 // and the one with the shorter time by the costs is taken: of 92 networks, 0.77 to 1.37 of one another, 1 % above the better
 // one on the mean and 7 % at most.
 static conststn_status choose_cut(const conststn_plan_s *plan, int64_t K, int64_t LT, SpCut &cut, DevBuf<int32_t> &order) {
-    const int64_t told = plan->opt("sptn3_slices", 0);
+    const int64_t told = plan->opt("sptn3_slices", 0), many = 8 * int64_t(plan->n_cus);
     cut = cut_network(plan, K, LT, !plan->sp_two_waves ? 0 : told == kSpGroup ? 1 : 2);
-    CST_TRY(order_pairs(plan, cut, order));
-    if (!plan->sp_two_waves || told || !cut.by_cost() || cut.n_present >= 8 * int64_t(plan->n_cus)) return CONSTSTN_OK;
     SpCut narrow = cut_network(plan, K, LT, 1);
-    CST_TRY(order_pairs(plan, narrow, order));
+    const bool both = plan->sp_two_waves && !told && cut.by_cost() && narrow.by_cost();
+    const int64_t n = cut.pairs(), n_narrow = both ? narrow.pairs() : 0;
+    DevBuf<unsigned long long> cost;
+    CST_TRY(cost.alloc(size_t(n + n_narrow)));
+    CST_TRY(launch_pair_costs(plan, cut, cost.p));
+    if (!plan->sp_two_waves) {
+        CST_TRY(order.alloc(size_t(n)));
+        return sort_pairs(n, cost.p, order.p, hipMemcpyDeviceToDevice);
+    }
+    std::vector<unsigned long long> host;
+    try {
+        host.resize(size_t(n + n_narrow));
+    } catch (const std::bad_alloc &) {
+        set_error("no host memory for the costs of %lld work pairs", (long long)(n + n_narrow));
+        return CONSTSTN_ENOMEM;
+    }
+    // (one copy for both where the first is sure to have too few pairs)
+    const bool together = both && n < many;
+    if (together) CST_TRY(launch_pair_costs(plan, narrow, cost.p + n));
+    CST_HIP(hipMemcpy(host.data(), cost.p, size_t(n + (together ? n_narrow : 0)) * sizeof(host[0]), hipMemcpyDeviceToHost));
+    CST_TRY(deal_cut(plan, cut, cost.p, host.data()));
+    if (!both || cut.n_present >= many) return CONSTSTN_OK;
+    if (!together) {
+        CST_TRY(launch_pair_costs(plan, narrow, cost.p + n));
+        CST_HIP(hipMemcpy(host.data() + n, cost.p + n, size_t(n_narrow) * sizeof(host[0]), hipMemcpyDeviceToHost));
+    }
+    CST_TRY(deal_cut(plan, narrow, cost.p + n, host.data() + n));
     if (narrow.time < cut.time) cut = std::move(narrow);
     return CONSTSTN_OK;
 }
