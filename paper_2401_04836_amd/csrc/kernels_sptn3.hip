@@ -125,8 +125,7 @@ struct Sptn3TileArgs {
     int compact, xcd_ranges;
     const int64_t *chunk_fiber;            // [(k chunks + 1) x slices] first fiber of a slice in a k chunk
     const int32_t *chunk_k;                // ... and the k there
-    const int32_t *work;                   // pairs of the workgroups with two wavefronts per SIMD, entry n for workgroup
-    int64_t work_end;                      // n % workgroups; -1: no more
+    const int32_t *work;                   // pairs of the workgroups with two wavefronts per SIMD (-1: none), from the launch's first on
     const int32_t *wg_order;               // workgroup -> (k chunk, group) pair, heaviest pairs first (or null)
 };
 
@@ -471,13 +470,14 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 // Two barriers a round, around the writes of T^t: a wavefront with few tiles goes on to the next round's producer.
 // V's loads run three batches ahead across rounds; a round is padded to whole groups of four batches, whose empty
 // batches load and do nothing.
-// 2000 x 2000 x 400 in blocks of 100 x 100 x 20 (356 M matrix instructions, 9.7 ms at the 28 ns one takes): 23.4 -> 15.8 ms.
+// 2000 x 2000 x 400 in blocks of 100 x 100 x 20 (356 M matrix instructions, 9.7 ms at the 28 ns one takes): 23.4 -> 15.4 ms.
 // The form before took 16 slices at a time: one 8-byte piece of V and one of Uc for every instruction, 363 M of them.
 // Of a workgroup's time the producer takes 40 %, the consumer 26 %, waiting at the two barriers 18 %, finding W's tiles 4 %,
 // everything between two k 12 % (16 us of latencies).
 // H = 1 is for networks that leave compute units with a pair or less: half the matrix instructions of a pair follow one
 // another, and two lane rows fetch a slice's leaves.  Where the line lies stands with the plan's choice (choose_cut).
 constexpr int kOwnWaves = 8;
+constexpr int64_t kOwnLaunch = int64_t(1) << 22;                        // workgroups of a launch
 constexpr int kOwnCap = kSpUnionRows;                                   // union rows of Uc per pass (78 KB)
 constexpr int kOwnHeld = 24;                                            // leaves per lane and half kept between mask and scatter
 constexpr int kOwnRows = 8;                                             // union rows of a batch (two K-steps)
@@ -556,10 +556,9 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
     for (int x = 0; x < kZ; ++x) own |= my_class + kClasses * x < 32 ? 1u << (my_class + kClasses * x) : 0u;
     uint16_t *list = lists + wave * kOwnList;
 
-    // A workgroup per compute unit, with a list of (k chunk, part of l, group) triples made by the plan.
-    for (int64_t item = blockIdx.x; item < a.work_end; item += gridDim.x) {
-    const int logical = __builtin_amdgcn_readfirstlane(a.work[item]);
-    if (logical < 0) break;
+    // A workgroup per (k chunk, part of l, group) triple
+    const int logical = __builtin_amdgcn_readfirstlane(a.work[blockIdx.x]);
+    if (logical < 0) return;
     const int group = logical % a.n_groups, kc = logical / a.n_groups, chunk = kc / a.l_parts, part = kc % a.l_parts;
     const int64_t s0 = int64_t(group) * kSlices;
     // lane sl (and sl + 32) holds the cursor of slice s0 + sl, its place in the k chunk, and the k there
@@ -973,7 +972,6 @@ sptn3_owned_kernel(Sptn3TileArgs a) {
             }
         });
     }
-    }
 }
 
 // Sums the partial results of the k chunks in chunk order; of those marked `present` where the others were not written.
@@ -1011,6 +1009,7 @@ bool sptn3_two_waves_fit(int nwords) { return sptn3_owned_lds(nwords, 2) <= 160 
 static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const double *const *dense, double *out,
                                           hipStream_t stream) {
     const conststn_csf_s *U = plan->X, *W = plan->W;
+    const bool owned = plan->sp_two_waves;
     Sptn3TileArgs a{};
     a.slices = U->nodes[0];
     a.L = W->dims[W->mode_order[1]];
@@ -1042,8 +1041,7 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     a.compact = plan->compact ? 1 : 0;
     a.chunk_fiber = plan->sp_chunk_fiber.p;
     a.chunk_k = plan->sp_chunk_k.p;
-    a.work = plan->sp_work.p;
-    a.work_end = int64_t(plan->sp_work.n);
+    const int64_t n_work = owned ? int64_t(plan->sp_work.n) : 0;
     a.wg_order = plan->sp_xcd_ranges ? nullptr : plan->sp_wg_order.p;
     a.xcd_ranges = plan->sp_xcd_ranges ? 1 : 0;      // measured: halves the HBM fetch, 4 % slower
     const size_t lds_bytes = size_t(kCap) * 16 * 8 + size_t(4 * kStage) * 256 * 8 + size_t(a.MT) * 256 * 8 +
@@ -1054,13 +1052,17 @@ static conststn_status launch_sptn3_tiled(const conststn_plan_s *plan, const dou
     if (a.slices == 0) return CONSTSTN_OK;
     // two wavefronts per SIMD (m tiles owned by wavefronts) when the plan chose it, else one (l tiles owned)
     const size_t lds_owned = sptn3_owned_lds(a.nwords, plan->sp_halves);
-    const bool owned = plan->sp_two_waves;
     {
         ProfScope prof(plan, stream);
         const unsigned n_wg = unsigned(a.n_groups) * unsigned(a.n_kc);
-        if (owned && plan->sp_halves == 1) sptn3_owned_kernel<1><<<dim3(unsigned(plan->sp_workers)), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
-        else if (owned) sptn3_owned_kernel<2><<<dim3(unsigned(plan->sp_workers)), dim3(64 * kOwnWaves), lds_owned, stream>>>(a);
-        else sptn3_tiled_kernel<<<dim3((n_wg + 7) / 8 * 8), dim3(256), lds_bytes, stream>>>(a);
+        // (a launch has fewer than 2^32 threads)
+        for (int64_t first = 0; first < n_work; first += kOwnLaunch) {
+            const dim3 grid(unsigned(std::min(n_work - first, kOwnLaunch))), block(64 * kOwnWaves);
+            a.work = plan->sp_work.p + first;
+            if (plan->sp_halves == 1) sptn3_owned_kernel<1><<<grid, block, lds_owned, stream>>>(a);
+            else sptn3_owned_kernel<2><<<grid, block, lds_owned, stream>>>(a);
+        }
+        if (!owned) sptn3_tiled_kernel<<<dim3((n_wg + 7) / 8 * 8), dim3(256), lds_bytes, stream>>>(a);
     }
     CST_HIP(hipGetLastError());
     if (a.n_kc > 1) {

@@ -1128,8 +1128,8 @@ __global__ void w_first_u32_kernel(int64_t n, const int64_t *__restrict__ first,
 // its rounds of sixteen blocks take beside them; per pair what its start and end take.
 struct SpCost { int pair, pass, round, producer, consumer; };
 // One wavefront per SIMD; two with one half of slices; two with two halves.  The last as measured at 2000 x 2000 x 400.  Those
-// of one half so that the longest lists of both compare as their times do, over 46 networks from 44 x 280 x 56 (14 us) to
-// 1500 x 1780 x 180 (3 ms).
+// of one half so that the times by the costs of both compare as the measured ones do, over 46 networks from 44 x 280 x 56
+// (14 us) to 1500 x 1780 x 180 (3 ms).
 constexpr SpCost kSpCost[3] = {{4900, 21000, 4200, 7, 7}, {3000, 11500, 2400, 9, 9}, {4900, 21000, 4200, 7, 7}};
 constexpr int kSpFixupNs = 4000, kSpFixupPartNs = 120;    // the pass that adds the partial results, and each part of a row
 __global__ void __launch_bounds__(256)
@@ -1209,40 +1209,37 @@ __global__ void sp_pair_keys_kernel(int64_t n, const unsigned long long *__restr
     ids[i] = uint32_t(i);
 }
 
-// `pairs` in falling order of cost -> lists of them for `workers` workgroups (workgroup w runs on XCD w % 8): runs of eight to
-// the XCD with the least work (by_range: equal ranges of pair numbers instead), there each to the least loaded workgroup.
-// Entry n of `work` is for workgroup n % (workgroups, returned); -1: no more.
-static int deal_pairs(const std::vector<uint32_t> &pairs, const std::vector<unsigned long long> &cost, int workers, bool by_range,
-                       std::vector<int32_t> &work) {
+// `pairs` in falling order of cost -> the pair of every workgroup (-1: none; workgroup b runs on XCD b % 8): runs of eight to
+// the XCD with the least work (by_range: equal ranges of pair numbers instead), there in falling order.  Returns the time by
+// the costs when the last pair ends, each begun by the compute unit that is free first.
+static unsigned long long deal_pairs(const std::vector<uint32_t> &pairs, const std::vector<unsigned long long> &cost, int n_cus,
+                                     bool by_range, std::vector<int32_t> &work) {
     constexpr int kXcds = 8;
-    const size_t n = pairs.size();
-    const size_t run = n >= 4 * size_t(std::max(workers, 1)) ? 8 : 1;     // (few pairs: one by one, over all of the chip)
-    workers = std::max(workers, kXcds);
-    using Load = std::pair<unsigned long long, int>;
-    std::vector<std::vector<int32_t>> lists(static_cast<size_t>(workers));
-    std::vector<std::vector<Load>> heaps(kXcds);
-    unsigned long long per_xcd[kXcds] = {};
-    for (int w = 0; w < workers; ++w) heaps[w % kXcds].push_back({0, w});
-    const auto later = std::greater<Load>();
-    for (auto &q : heaps) std::make_heap(q.begin(), q.end(), later);
+    const size_t n = pairs.size(), units = size_t(std::max(n_cus / kXcds, 1));
+    const size_t run = n >= 4 * kXcds * units ? 8 : 1;                    // (few pairs: one by one, over all of the chip)
+    std::vector<std::vector<int32_t>> queues(kXcds);
+    std::vector<std::vector<unsigned long long>> ends(kXcds, std::vector<unsigned long long>(units, 0));
+    unsigned long long per_xcd[kXcds] = {}, last = 0;
+    const auto later = std::greater<unsigned long long>();
     int xcd = 0;
     for (size_t i = 0; i < n; ++i) {
         if (by_range) xcd = int(size_t(pairs[i]) * kXcds / cost.size());
         else if (i % run == 0) xcd = int(std::min_element(per_xcd, per_xcd + kXcds) - per_xcd);
         const unsigned long long c = cost[pairs[i]];
-        auto &q = heaps[size_t(xcd)];
-        std::pop_heap(q.begin(), q.end(), later);
-        lists[size_t(q.back().second)].push_back(int32_t(pairs[i]));
-        q.back().first += c;
-        std::push_heap(q.begin(), q.end(), later);
+        queues[size_t(xcd)].push_back(int32_t(pairs[i]));
         per_xcd[xcd] += c;
+        auto &q = ends[size_t(xcd)];
+        std::pop_heap(q.begin(), q.end(), later);
+        q.back() += c;
+        last = std::max(last, q.back());
+        std::push_heap(q.begin(), q.end(), later);
     }
-    size_t rounds = 1;
-    for (auto &l : lists) rounds = std::max(rounds, l.size());
-    work.assign(rounds * lists.size(), -1);
-    for (size_t w = 0; w < lists.size(); ++w)
-        for (size_t i = 0; i < lists[w].size(); ++i) work[i * lists.size() + w] = lists[w][i];
-    return workers;
+    size_t longest = 1;
+    for (auto &q : queues) longest = std::max(longest, q.size());
+    work.assign(longest * kXcds, -1);
+    for (size_t x = 0; x < kXcds; ++x)
+        for (size_t i = 0; i < queues[x].size(); ++i) work[i * kXcds + x] = queues[x][i];
+    return last;
 }
 
 // A way to cut the network: groups of slices, chunks of the k range, parts of the blocks of l, and what the plan makes of it.
@@ -1252,10 +1249,9 @@ struct SpCut {
     int kc = 1, l_parts = 1;
     // with two wavefronts per SIMD
     std::vector<int32_t> work;             // see deal_pairs
-    int workers = 0;
     std::vector<uint8_t> present;          // pairs whose partial results are written
     int64_t n_present = 0;
-    unsigned long long time = 0;           // ns of the longest list and of the fix-up pass
+    unsigned long long time = 0;           // ns by the costs, with the fix-up pass
 
     int slices() const { return std::max(halves, 1) * kSpGroup; }
     int parts() const { return kc * l_parts; }
@@ -1315,10 +1311,10 @@ static conststn_status sort_pairs(int64_t n, const unsigned long long *cost, voi
     return CONSTSTN_OK;
 }
 
-// The lists of a cut's pairs with two wavefronts per SIMD: one workgroup per compute unit, each pair to the workgroup with the
-// least work so far, the heaviest first.  In the hardware's launch order workgroups of unequal length left the compute units
-// idle for 2.0 of 18.1 ms at 2000 x 2000 x 400.  Neighbouring groups read the same W tiles and largely the same rows of V:
-// runs of eight stay on one XCD.
+// The workgroups' pairs with two wavefronts per SIMD, in falling order of cost.  Neighbouring groups read the same W tiles and
+// largely the same rows of V: runs of eight stay on one XCD.  The hardware gives the next pair to the compute unit that is
+// free.  One workgroup per compute unit with a list of pairs dealt beforehand took 15.9 instead of 15.4 ms at
+// 2000 x 2000 x 400 (costs are not exact), and 32 where another stream held one compute unit: its list began last.
 // Up to kSpHostSort pairs are sorted on the host, which has the costs anyway: 5 us for 500, 180 for 4096, where the device's
 // sort with its launches, copy and waits takes 200 (a plan of 700 x 420 x 170 in 1254 and 2508 pairs: 0.77 ms against 0.97).
 constexpr int64_t kSpHostSort = 4096;
@@ -1340,14 +1336,10 @@ static conststn_status deal_cut(const conststn_plan_s *plan, SpCut &cut, const u
         // pairs without work write nothing, unless there is but one result to a row
         if (cut.parts() > 1)
             while (!pairs.empty() && !cut.present[pairs.back()]) pairs.pop_back();
-        cut.workers = deal_pairs(pairs, costs, plan->n_cus, plan->opt("sptn3_xcd", 0) == 1, cut.work);
-        std::vector<unsigned long long> load(size_t(cut.workers), 0);
-        for (size_t i = 0; i < cut.work.size(); ++i)
-            if (cut.work[i] >= 0) load[i % size_t(cut.workers)] += costs[size_t(cut.work[i])];
-        cut.time = *std::max_element(load.begin(), load.end()) +
+        cut.time = deal_pairs(pairs, costs, plan->n_cus, plan->opt("sptn3_xcd", 0) == 1, cut.work) +
                    (cut.parts() > 1 ? kSpFixupNs + (unsigned long long)cut.parts() * kSpFixupPartNs : 0);
     } catch (const std::bad_alloc &) {
-        set_error("no host memory for the lists of %lld work pairs", (long long)n);
+        set_error("no host memory for the order of %lld work pairs", (long long)n);
         return CONSTSTN_ENOMEM;
     }
     return CONSTSTN_OK;
@@ -1503,7 +1495,6 @@ static conststn_status build_w_tiles(conststn_plan_s *plan) {
     }
     plan->w_tiled = true;
     if (plan->sp_two_waves) {
-        plan->sp_workers = cut.workers;
         CST_TRY(plan->sp_work.alloc(cut.work.size()));
         CST_HIP(hipMemcpy(plan->sp_work.p, cut.work.data(), cut.work.size() * sizeof(int32_t), hipMemcpyHostToDevice));
         CST_TRY(plan->sp_present.alloc(cut.present.size()));

@@ -284,8 +284,7 @@ struct conststn_plan_s {
     cst::DevBuf<int32_t> sp_wg_order;      // [groups x k chunks] pairs by falling cost, or empty
     cst::DevBuf<uint8_t> sp_present;       // [groups x k chunks] pairs whose partial results are written
     cst::DevBuf<int32_t> sp_slice_of_row;  // [result rows] slice of U, or -1 (where some rows have none)
-    int sp_workers = 0;                    // workgroups of the form with two wavefronts per SIMD
-    cst::DevBuf<int32_t> sp_work;          // [rounds x workers] their pairs, -1 behind the last of a workgroup
+    cst::DevBuf<int32_t> sp_work;          // pairs of the workgroups of the form with two wavefronts per SIMD, or -1
     int sp_kc = 1;                         // chunks of the k range (one workgroup per group and chunk)
     int sp_l_parts = 1;                    // parts of the blocks of l (with two wavefronts per SIMD)
     int64_t sp_k_per = 0;                  // k values per chunk

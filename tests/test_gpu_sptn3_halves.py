@@ -110,3 +110,52 @@ def test_slices_of_a_group_follow_the_pairs_of_the_chip(slices, J, K, cut):
         got = cst.execute(pl, [v]).cpu().numpy().reshape(slices, M)
         # (J + K L + 3) roundings along the longest chain, on both sides
         assert oracle.rel_err(got, want, S_abs) <= 2 * (J + K * L + 3) * 1.1e-16
+
+
+def test_a_compute_unit_that_another_stream_holds():
+    """Several pairs per compute unit, one of which another stream holds for many times the network's time: its share goes to
+    the others (an eighth more for each of them here), it does not wait for a second round of the whole."""
+    rng = np.random.default_rng(9300)
+    slices, J, K, L, M = 1024, 64, 64, 512, 64
+    u = [x.ravel().astype(np.int32) for x in np.meshgrid(np.arange(slices), np.arange(J), np.arange(K), indexing="ij")]
+    wc = [x.ravel().astype(np.int32) for x in np.meshgrid(np.arange(K), np.arange(L), np.arange(M), indexing="ij")]
+    up = lambda x: torch.from_numpy(x).cuda()
+    U = cst.build_csf([up(x) for x in u], up(rng.uniform(-1, 1, u[0].size)), (slices, J, K), [0, 2, 1])
+    W = cst.build_csf([up(x) for x in wc], up(rng.uniform(-1, 1, wc[0].size)), (K, L, M), [0, 1, 2])
+    v = up(rng.uniform(-1, 1, (J, L)))
+    pl = cst.plan(S.SPTN3, [("U", U), ("V", v), ("W", W)])
+    out = torch.empty(slices * M, dtype=torch.float64, device="cuda")
+    side, event = torch.cuda.Stream(), lambda: torch.cuda.Event(enable_timing=True)
+
+    def best_ms(f):
+        times = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            a, b = event(), event()
+            f(a, b)
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    def network(a, b):
+        a.record()
+        cst.execute(pl, [v], out=out)
+        b.record()
+
+    def sleep(a, b):
+        a.record()
+        torch.cuda._sleep(1_000_000)
+        b.record()
+
+    def held(a, b):
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(cycles)
+            begun.record()
+        network(a, b)
+
+    begun = event()
+    alone, per_cycle = best_ms(network), best_ms(sleep) / 1_000_000
+    cycles = int(20 * alone / per_cycle)                       # one workgroup of one wavefront, 20 times as long
+    beside = best_ms(held)
+    print("[case] alone %.3f ms, beside a held compute unit %.3f ms" % (alone, beside), flush=True)
+    assert beside < 1.5 * alone
