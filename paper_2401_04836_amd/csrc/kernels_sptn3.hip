@@ -472,8 +472,10 @@ sptn3_tiled_kernel(Sptn3TileArgs a) {
 // batches load and do nothing.
 // 2000 x 2000 x 400 in blocks of 100 x 100 x 20 (356 M matrix instructions, 9.7 ms at the 28 ns one takes): 23.4 -> 15.4 ms.
 // The form before took 16 slices at a time: one 8-byte piece of V and one of Uc for every instruction, 363 M of them.
-// Of a workgroup's time the producer takes 40 %, the consumer 26 %, waiting at the two barriers 18 %, finding W's tiles 4 %,
-// everything between two k 12 % (16 us of latencies).
+// Of a workgroup's time (taken at 15.8 ms, before the kernel did without lists of pairs) the producer has 40 %, the consumer
+// 26 %, waiting at the two barriers 18 %, finding W's tiles 4 %, everything between two k 12 % (16 us of latencies).  With all
+// of W's tiles read from one place (a switched-off copy) it takes 14.6 ms: their way from past the L2 costs 0.8; V's rows
+// read from one cache line change nothing.
 // H = 1 is for networks that leave compute units with a pair or less: half the matrix instructions of a pair follow one
 // another, and two lane rows fetch a slice's leaves.  Where the line lies stands with the plan's choice (choose_cut).
 constexpr int kOwnWaves = 8;
