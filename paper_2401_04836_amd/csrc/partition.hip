@@ -1122,21 +1122,21 @@ __global__ void w_first_u32_kernel(int64_t n, const int64_t *__restrict__ first,
     if (x < n) out[x] = uint32_t(first[x]);
 }
 
-// Cost of a (k chunk, group of slices) pair in ns of its workgroup, one workgroup per pair: the tiled kernels take the
+// Cost of a (k chunk, group of slices) pair in tenths of a ns of its workgroup, one workgroup per pair: the tiled kernels take the
 // pairs in falling order of it.  Per k: matrix instructions of the producer (rows of the union of each half's j, rounded to
 // batches of eight, x blocks of l / 4) and of the consumer (W tiles x 4 per half and pass over the union), and what a pass and
 // its rounds of sixteen blocks take beside them; per pair what its start and end take.
 struct SpCost { int pair, pass, round, producer, consumer; };
-// One wavefront per SIMD; two with one half of slices; two with two halves.  The last as measured at 2000 x 2000 x 400.  Those
-// of one half so that the times by the costs of both compare as the measured ones do, over 46 networks from 44 x 280 x 56
-// (14 us) to 1500 x 1780 x 180 (3 ms).
-constexpr SpCost kSpCost[3] = {{4900, 21000, 4200, 7, 7}, {3000, 11500, 2400, 9, 9}, {4900, 21000, 4200, 7, 7}};
-constexpr int kSpFixupNs = 4000, kSpFixupPartNs = 120;    // the pass that adds the partial results, and each part of a row
+// One wavefront per SIMD; two with one half of slices; two with two halves.  The last two fitted together, so that the times by the
+// costs, and above all their ratio, are as measured over 200 networks with blocks from 15 us to 5 ms (the ratio to 4 % on the mean;
+// 10 % with figures for two halves from the phases of 2000 x 2000 x 400 alone).
+constexpr SpCost kSpCost[3] = {{49000, 210000, 42000, 70, 70}, {34000, 46000, 23000, 114, 91}, {21000, 92000, 20000, 116, 105}};
+constexpr int kSpFixup = 40000, kSpFixupPart = 1200;      // the pass that adds the partial results, and each part of a row
 __global__ void __launch_bounds__(256)
 sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int64_t *__restrict__ ptr1, const int32_t *__restrict__ idx1,
                     const int32_t *__restrict__ idx2, const int64_t *__restrict__ w_root_of_k, const int32_t *__restrict__ cell_ptr,
                     const SpCell *__restrict__ cells, int64_t k_per, int l_parts, int n_groups, int group, int nwords, int rows_per_pass,
-                    SpCost ns, unsigned long long *cost) {
+                    SpCost unit, unsigned long long *cost) {
     extern __shared__ uint32_t sp_cost_mask[];                            // 2 x nwords
     __shared__ int total[3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1156,7 +1156,7 @@ sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int6
         cur = lower(na, k0);
         end = lower(cur, k0 + k_per);
     }
-    unsigned long long sum = ns.pair;
+    unsigned long long sum = unit.pair;
     for (;;) {
         const int32_t kk = cur < end ? idx1[cur] : INT32_MAX;
         int32_t k = kk;
@@ -1196,7 +1196,7 @@ sp_pair_cost_kernel(int64_t slices, const int64_t *__restrict__ ptr0, const int6
         const long long n_all = cell_ptr[root + 1] - cell_ptr[root];
         const long long c0 = cell_ptr[root] + n_all * part / l_parts, c1 = cell_ptr[root] + n_all * (part + 1) / l_parts, halves = (r0 > 0) + (r1 > 0);
         const long long tiles = c0 < c1 ? (long long)cells[c1 - 1].first + __popc(cells[c1 - 1].mask) - cells[c0].first : 0;
-        sum += (r0 + r1) * (c1 - c0) / 4 * ns.producer + passes * (tiles * 4 * halves * ns.consumer + ns.pass + (c1 - c0 + 15) / 16 * ns.round);
+        sum += (r0 + r1) * (c1 - c0) / 4 * unit.producer + passes * (tiles * 4 * halves * unit.consumer + unit.pass + (c1 - c0 + 15) / 16 * unit.round);
         __syncthreads();
     }
     if (tid == 0) cost[blockIdx.x] = sum;
@@ -1251,7 +1251,7 @@ struct SpCut {
     std::vector<int32_t> work;             // see deal_pairs
     std::vector<uint8_t> present;          // pairs whose partial results are written
     int64_t n_present = 0;
-    unsigned long long time = 0;           // ns by the costs, with the fix-up pass
+    unsigned long long time = 0;           // tenths of a ns by the costs, with the fix-up pass
 
     int slices() const { return std::max(halves, 1) * kSpGroup; }
     int parts() const { return kc * l_parts; }
@@ -1337,7 +1337,7 @@ static conststn_status deal_cut(const conststn_plan_s *plan, SpCut &cut, const u
         if (cut.parts() > 1)
             while (!pairs.empty() && !cut.present[pairs.back()]) pairs.pop_back();
         cut.time = deal_pairs(pairs, costs, plan->n_cus, plan->opt("sptn3_xcd", 0) == 1, cut.work) +
-                   (cut.parts() > 1 ? kSpFixupNs + (unsigned long long)cut.parts() * kSpFixupPartNs : 0);
+                   (cut.parts() > 1 ? kSpFixup + (unsigned long long)cut.parts() * kSpFixupPart : 0);
     } catch (const std::bad_alloc &) {
         set_error("no host memory for the order of %lld work pairs", (long long)n);
         return CONSTSTN_ENOMEM;
@@ -1347,10 +1347,9 @@ static conststn_status deal_cut(const conststn_plan_s *plan, SpCut &cut, const u
 
 // With two wavefronts per SIMD: 32 slices to a workgroup, or 16.  32 read V and W half as often and wait half as often between
 // two k; 16 make twice the pairs, of each of which half the matrix instructions follow one another.  Where a compute unit has
-// one pair of 32 at most, that is the time: 116 x 200 x 12 takes 23.6 us with 32 and 16.8 with 16, 26 such networks 1.02 to
-// 1.41 times as long.  From eight pairs on 32 are faster (2000 x 2000 x 400: 15.8 ms against 17.9).  Between, both are dealt
-// and the one with the shorter time by the costs is taken: of 92 networks, 0.77 to 1.37 of one another, 1 % above the better
-// one on the mean and 7 % at most.
+// one pair of 32 at most, that is the time: 116 x 200 x 12 takes 20.3 us with 32 and 16.1 with 16, such networks 1.1 to 1.25 times
+// as long.  From eight pairs on 32 are faster (2000 x 2000 x 400: 15.4 ms against 17.4).  Between, both are dealt and the one with
+// the shorter time by the costs is taken: of 180 networks, 0.73 to 1.34 of one another, 0.3 % above the better one on the mean and 5 % at most.
 static conststn_status choose_cut(const conststn_plan_s *plan, int64_t K, int64_t LT, SpCut &cut, DevBuf<int32_t> &order) {
     const int64_t told = plan->opt("sptn3_slices", 0), many = 8 * int64_t(plan->n_cus);
     cut = cut_network(plan, K, LT, !plan->sp_two_waves ? 0 : told == kSpGroup ? 1 : 2);
