@@ -1,5 +1,7 @@
 """conststn_execute_static (partial row blocks in the library's static device array, nothing allocated by
 the call) against conststn_execute, on two calls in a row, the second with a smaller input."""
+import gc
+
 import pytest
 import torch
 
@@ -86,6 +88,7 @@ def test_memory_of_destroyed_objects_is_given_back_on_demand():
     print("[case] build, destroy, release", flush=True)
     alive = cst.build_csf(coords, vals, (n, n, n), [0, 1, 2])
     torch.cuda.synchronize()
+    gc.collect()             # handles of other tests, in the cycle of a caught exception: collected in between they give memory back too
     cst.release_memory()
     before = torch.cuda.mem_get_info()[0]
     cst.build_csf(coords, vals, (n, n, n), [1, 2, 0]).destroy()
